@@ -666,11 +666,16 @@ __device__ __forceinline__ void stage_priority(int stage, int wave, int waves) {
 // memory operations outstanding" means the copies of the stage about to be used
 // have landed.  Vector-memory operations the compiler issues itself only add to
 // the outstanding count, which makes the wait longer, never shorter.
-template <class Net, int WAVES, int NBUF, int CPS>
+// L1S: the layer-1 tiles lie in front of the chunk blocks in the space of one more and come first as a stage of
+// their own.
+template <class Net, int WAVES, int NBUF, int CPS, bool L1S = false>
 struct WeightStream {
   // a stage = CPS consecutive chunk blocks of one network
   static_assert(Net::NUC % CPS == 0, "stages must not straddle networks");
-  static constexpr int STAGES_PER_NET = Net::NUC / CPS;
+  static_assert(!L1S || (CPS == 1 && Net::L1_TILES <= Net::CHUNK_TILES), "layer 1 as a stage of one chunk block");
+  static constexpr int CHUNK_STAGES = Net::NUC / CPS;  // of one layer
+  static constexpr int L1_STAGES = L1S ? 1 : 0;
+  static constexpr int STAGES_PER_NET = CHUNK_STAGES + L1_STAGES;
   static constexpr int STAGES_PER_STEP = 2 * STAGES_PER_NET;
   static constexpr int STAGE_TILES = CPS * Net::CHUNK_TILES;
   static constexpr int PER_WAVE = (STAGE_TILES + WAVES - 1) / WAVES;  // copies per wave and stage
@@ -712,6 +717,12 @@ struct WeightStream {
   __device__ __forceinline__ void issue(int s, int buf) const {
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) issue_part(s, buf, i);
+  }
+  // this wave's copies for stage s dealt out over `n` calls, i = 0 .. n-1
+  __device__ __forceinline__ void spread(int s, int buf, int i, int n) const {
+#pragma unroll
+    for (int k = 0; k < PER_WAVE; ++k)
+      if (k * n / PER_WAVE == i) issue_part(s, buf, k);
   }
   // wait until the oldest stage in flight has landed, then for every wave of the workgroup
   __device__ __forceinline__ void wait_oldest() const {

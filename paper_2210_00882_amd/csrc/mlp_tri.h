@@ -1,0 +1,349 @@
+// fp32 policy / value networks on the bf16 matrix pipe, one wave per 32 rows.
+//
+// The fp32 MFMA runs at a sixteenth of the bf16 one's rate, and with it these networks spend three quarters of
+// their time on the matrix pipe.  So every fp32 operand is taken apart into three bf16 pieces,
+//     x = x0 + x1 + x2,   x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)   (round to nearest even),
+// which is exact (3 x 8 significant bits hold the 24 of an fp32 value; the two differences are exact in fp32), and a
+// product becomes six bf16 MFMAs into one fp32 accumulator,
+//     w x = w2 x0 + w1 x0 + w1 x1 + w0 x0 + w0 x1 + w0 x2.
+// The three products left out are below 2^-24 of w x (|x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|), i.e. below the rounding
+// of the fp32 product they stand in for, and 16 inputs enter the accumulator per rounding instead of two.  Six bf16
+// MFMAs of 16 inputs take 192 cycles where eight fp32 ones take 512.
+//
+// Everything else is as in mlp.h: layers transposed, a layer's accumulators are the next layer's B operand (the
+// bf16 "chained" input map), weights as A-operand tiles in LDS (packed.h: a k tile is three 1 KiB pieces), the tanh
+// of a chunk beside the MFMAs of the next one.  The interleaving is spelled out: a wave issues in order and
+// an MFMA keeps the pipe for 32 cycles, so between two MFMAs there is room for about seven vector instructions, and
+// the work on the chunk before is cut into steps of two to ten instructions that are dealt out over those gaps
+// (fp32 networks of 256 units run one wave per SIMD: nothing else would fill them).
+#pragma once
+#include "mlp.h"
+
+namespace msrl {
+
+// one B operand: 8 values of a row as three bf16 pieces
+struct Tri {
+  u32x4 p[3];
+};
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {  // round to nearest even, a in the low half
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ float bf16_low(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_high(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// the pieces of values a, b as pair `i` of an operand
+__device__ __forceinline__ void tri_pair(float a, float b, Tri& o, int i) {
+  const uint32_t p0 = bf16_pair(a, b);
+  a -= bf16_low(p0);
+  b -= bf16_high(p0);
+  const uint32_t p1 = bf16_pair(a, b);
+  o.p[0][i] = p0;
+  o.p[1][i] = p1;
+  o.p[2][i] = bf16_pair(a - bf16_low(p1), b - bf16_high(p1));
+}
+__device__ __forceinline__ Tri tri_operand(const f32x8& f) {
+  Tri o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) tri_pair(f[2 * i], f[2 * i + 1], o, i);
+  return o;
+}
+__device__ __forceinline__ f32x16 mma_piece(const u32x4& w, const u32x4& x, f32x16 c) {
+  return mma(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c);
+}
+// piece of the weight / of the operand in MFMA m of a k tile; the pieces of the weight are used up in the order 2, 1, 0
+constexpr int TRI_W[6] = {2, 1, 1, 0, 0, 0}, TRI_X[6] = {0, 0, 1, 0, 1, 2};
+
+// What is done with the accumulators of the chunk before beside the MFMAs of a chunk: nothing, tanh and split
+// into operands of the next layer, tanh and the output layer on the VALU, tanh and split and the output layer of a
+// Gaussian policy on the MFMA.
+enum : int { TRI_NONE = 0, TRI_SPLIT = 1, TRI_OUT = 2, TRI_GAUSS = 3 };
+
+// ... as a list of steps, two accumulator registers at a time
+template <int MODE>
+struct TriWork {
+  static constexpr int PER_PAIR = MODE == TRI_NONE ? 0 : MODE == TRI_OUT ? 5 : 8;
+  static constexpr int STEPS = 8 * PER_PAIR;
+  f32x16 prev;        // pre-activations (times 2 log2(e), see fast_tanh_prescaled)
+  float t[16];        // tanh chain, then remainders of the split
+  Tri op[2];          // TRI_SPLIT / TRI_GAUSS: the chunk's 32 units as operands
+  const float* w3h;   // TRI_OUT: this half-wave's output weights of the chunk (MlpTri::out_weights)
+  f32x4 wg[8];
+  template <int NOUT>
+  __device__ __forceinline__ void step(int i, f32x16& out) {
+    constexpr int P = PER_PAIR > 0 ? PER_PAIR : 1;
+    const int r = 2 * (i / P), s = i % P, o = r / 8, w = r % 8 / 2;
+    switch (s) {
+      case 0:
+        t[r] = __builtin_amdgcn_exp2f(prev[r]);
+        t[r + 1] = __builtin_amdgcn_exp2f(prev[r + 1]);
+        if constexpr (MODE == TRI_OUT) {
+          if (r % 4 == 0) {
+#pragma unroll
+            for (int k = 0; k < NOUT; ++k) wg[k] = *(const f32x4*)(w3h + (r / 4) * 64 + k * 4);
+          }
+        }
+        break;
+      case 1:
+        t[r] += 1.0f;
+        t[r + 1] += 1.0f;
+        break;
+      case 2:
+        t[r] = __builtin_amdgcn_rcpf(t[r]);
+        t[r + 1] = __builtin_amdgcn_rcpf(t[r + 1]);
+        break;
+      case 3:
+        t[r] = 1.0f - 2.0f * t[r];
+        t[r + 1] = 1.0f - 2.0f * t[r + 1];
+        break;
+      case 4:
+        if constexpr (MODE == TRI_OUT) {
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) out[k] = __builtin_fmaf(t[r], wg[k][r % 4], out[k]);
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) out[k] = __builtin_fmaf(t[r + 1], wg[k][r % 4 + 1], out[k]);
+        } else {
+          op[o].p[0][w] = bf16_pair(t[r], t[r + 1]);
+        }
+        break;
+      case 5:
+        t[r] -= bf16_low(op[o].p[0][w]);
+        t[r + 1] -= bf16_high(op[o].p[0][w]);
+        break;
+      case 6:
+        op[o].p[1][w] = bf16_pair(t[r], t[r + 1]);
+        break;
+      default:
+        op[o].p[2][w] = bf16_pair(t[r] - bf16_low(op[o].p[1][w]), t[r + 1] - bf16_high(op[o].p[1][w]));
+    }
+  }
+};
+
+// GAUSS: the policy's output layer is that of a Gaussian policy (2 K <= 16 outputs, OUT_GAUSS), multiplied by the
+// MFMA; otherwise both output layers have at most 8 outputs and run on the VALU.
+template <int H, int KT1, bool GAUSS = false>
+struct MlpTri {
+  typedef Tri Op;
+  static constexpr int PT = 1, PC = 2;                // operands per k tile; made from one 32-unit accumulator
+  static constexpr int NUC = H / 32, KT2 = H / 16;
+  // sizes in 1 KiB tiles (packed.h): layer 1; a chunk block = layer-2 tiles, bias tile, output layer of chunk c-1, of chunk c
+  static constexpr int L1_TILES = NUC * KT1 * 3;
+  static constexpr int L3T = GAUSS ? 4 : 1;
+  static constexpr int BIAS = 3 * KT2, L3_PREV = BIAS + 1, L3_OWN = L3_PREV + L3T;
+  static constexpr int CHUNK_TILES = 3 * KT2 + 1 + 2 * L3T;
+  static constexpr int G = 2;  // LDS reads run two k tiles (twelve MFMAs) ahead of the MFMAs
+
+  template <uint32_t OUTS>
+  static constexpr bool on_mfma() { return __builtin_popcount(OUTS) > 8; }
+  // this half-wave's output weights in the L3 tile `at` of the chunk block at `tiles` (this lane's slot of tile 0):
+  // weight of unit 8 i + 4 h + j, output o at float i * 64 + h * 32 + o * 4 + j
+  __device__ static __forceinline__ const float* out_weights(const u32x4* tiles, int at, int h) {
+    return (const float*)(tiles + at * 64 - lane_id()) + 32 * h;
+  }
+  __device__ static __forceinline__ int lane_id() {
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  }
+
+  // the operand that meets a bias tile: the three pieces of a bias lie at k slots 0, 1, 2 of h = 0
+  __device__ static __forceinline__ u32x4 ones(int h) {
+    const u32x4 v = {h == 0 ? 0x3F803F80u : 0u, h == 0 ? 0x00003F80u : 0u, 0u, 0u};
+    return v;
+  }
+
+  // One chunk of NT k tiles: acc <- W b, the steps of wk dealt out over the gaps behind the MFMAs.  Tile `k` of the
+  // stream of TOTAL tiles that this chunk belongs to lies (k / NT) STRIDE + 3 (k % NT) KiB behind `tiles`; `first` is
+  // the chunk's first, whose pieces are in the ring with the G - 1 tiles behind it.  LEAD steps come before the
+  // first MFMA (they cover the latency of the first LDS reads).  tick(kt) once per tile.
+  template <int NT, int TOTAL, int STRIDE, int MODE, int NOUT, class Tick>
+  __device__ static __forceinline__ void chunk(const u32x4* tiles, int first, u32x4 (&ring)[G][3], const Tri* b,
+                                               f32x16& acc, TriWork<MODE>& wk, f32x16& out, int lead, Tick&& tick) {
+    constexpr int GAPS = 6 * NT, STEPS = TriWork<MODE>::STEPS;
+    acc = zero16();
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i)
+      if (i < lead) wk.template step<NOUT>(i, out);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kt = 0; kt < NT; ++kt) {
+#pragma unroll
+      for (int m = 0; m < 6; ++m) {
+        const int k = first + kt, g = 6 * kt + m, w = TRI_W[m];
+        acc = mma_piece(ring[k % G][w], b[kt].p[TRI_X[m]], acc);
+        if ((m == 5 || TRI_W[m + 1 < 6 ? m + 1 : 5] != w) && k + G < TOTAL)
+          ring[k % G][w] = tiles[(((k + G) / NT) * STRIDE + 3 * ((k + G) % NT) + w) * 64];
+        if (m == 5) tick(kt);
+        __builtin_amdgcn_sched_barrier(0);
+        const int left = STEPS - lead;
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i)
+          if (i >= lead + g * left / GAPS && i < lead + (g + 1) * left / GAPS) wk.template step<NOUT>(i, out);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  template <int NT, int TOTAL, int STRIDE>
+  __device__ static __forceinline__ void fill_ring(const u32x4* tiles, u32x4 (&ring)[G][3]) {
+#pragma unroll
+    for (int k = 0; k < G && k < TOTAL; ++k)
+#pragma unroll
+      for (int w = 2; w >= 0; --w) ring[k][w] = tiles[((k / NT) * STRIDE + 3 * (k % NT) + w) * 64];
+  }
+  // the steps with no MFMAs to hide behind (behind a layer's last chunk)
+  template <int MODE, int NOUT>
+  __device__ static __forceinline__ void drain(TriWork<MODE>& wk, f32x16& out) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)  // (a group of four registers shares its output weights)
+#pragma unroll
+      for (int s = 0; s < TriWork<MODE>::PER_PAIR; ++s)
+#pragma unroll
+        for (int q = 2 * g; q < 2 * g + 2; ++q) wk.template step<NOUT>(q * TriWork<MODE>::PER_PAIR + s, out);
+  }
+
+  // Layer 1.  tiles: this lane's slot of tile 0 in LDS; x holds the observation with the constant 1 at input in_dim
+  // (its bias).  tick(i), i = 0 .. NUC * KT1 - 1, once per k tile.
+  template <class Tick>
+  __device__ static __forceinline__ void layer1(const u32x4* tiles, const Op (&x)[1][KT1], Op (&h1)[1][KT2], Tick&& tick) {
+    u32x4 ring[G][3];
+    fill_ring<KT1, NUC * KT1, 3 * KT1>(tiles, ring);
+    f32x16 acc, none;
+    TriWork<TRI_NONE> w0;
+    chunk<KT1, NUC * KT1, 3 * KT1, TRI_NONE, 0>(tiles, 0, ring, x[0], acc, w0, none, 0, tick);
+    TriWork<TRI_SPLIT> wk;
+#pragma unroll
+    for (int uc = 1; uc <= NUC; ++uc) {
+      wk.prev = acc;
+      if (uc < NUC)
+        chunk<KT1, NUC * KT1, 3 * KT1, TRI_SPLIT, 0>(tiles, uc * KT1, ring, x[0], acc, wk, none, 0,
+                                                     [&](int kt) { tick(uc * KT1 + kt); });
+      else
+        drain<TRI_SPLIT, 0>(wk, none);
+      h1[0][2 * uc - 2] = wk.op[0];
+      h1[0][2 * uc - 1] = wk.op[1];
+    }
+  }
+  __device__ static __forceinline__ void layer1(const u32x4* tiles, const Op (&x)[1][KT1], Op (&h1)[1][KT2]) {
+    layer1(tiles, x, h1, [](int) {});
+  }
+
+  // start value of the output accumulators: the bias (MFMA), or zero (VALU: the bias comes in out_finish)
+  template <uint32_t OUTS>
+  __device__ static __forceinline__ f32x16 out_init(const float* lds_bias, int h) {
+    if constexpr (on_mfma<OUTS>()) return bias_init(lds_bias, h);
+    else return zero16();
+  }
+  // output layer of a Gaussian policy: tile 0 of a k tile has the leading pieces of the weights in output rows 0 .. 15
+  // and the middle ones in rows 16 .. 31, tile 1 the last pieces in rows 0 .. 15; out_finish adds the two row ranges
+  __device__ static __forceinline__ void gauss_out(const u32x4* tiles, int at, const Tri (&h2)[2], f32x16& out) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const u32x4 hm = tiles[(at + 2 * i) * 64], lo = tiles[(at + 2 * i + 1) * 64];
+      out = mma_piece(lo, h2[i].p[0], out);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) out = mma_piece(hm, h2[i].p[m], out);
+    }
+  }
+  // behind the last chunk: the outputs in accumulator layout (register r of lane (n, h): output 8 (r / 4) + 4 h + r % 4)
+  template <uint32_t OUTS>
+  __device__ static __forceinline__ void out_finish(f32x16 (&out)[1], const float* lds_bias, int h) {
+    f32x16 res;
+    if constexpr (on_mfma<OUTS>()) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) res[r] = r < 8 ? out[0][r] + out[0][r + 8] : 0.0f;
+    } else {
+      // partial sums of the two lanes of a row, and the bias
+      float tot[8];
+#pragma unroll
+      for (int o = 0; o < 8; ++o) tot[o] = (OUTS >> o) & 1u ? out[0][o] + __shfl_xor(out[0][o], 32) + lds_bias[o] : 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) res[r] = r < 4 ? (h ? tot[r + 4] : tot[r]) : 0.0f;
+    }
+    out[0] = res;
+  }
+
+  // The CPS chunk blocks of a stage (consecutive in the LDS buffer) as one stream of tiles.  On entry `acc` holds the
+  // pre-activations of the chunk before (PIPE0), which get tanh and feed the output layer meanwhile.
+  // nout: outputs in use (a constant where the caller's loop over the networks is unrolled).  tick(c, kt) once per k tile.
+  template <bool PIPE0, int CPS, uint32_t OUTS, class Tick>
+  __device__ static __forceinline__ void layer2_chunks(const u32x4* tiles, const Op (&h1)[1][KT2], f32x16 (&acc)[1],
+                                                       f32x16 (&out)[1], int h, int nout, Tick&& tick) {
+    constexpr int MODE = on_mfma<OUTS>() ? TRI_GAUSS : TRI_OUT;
+    u32x4 ring[G][3];
+    fill_ring<KT2, CPS * KT2, CHUNK_TILES>(tiles, ring);
+    f32x16 none;
+    const u32x4 one = ones(h);
+#pragma unroll
+    for (int c = 0; c < CPS; ++c) {
+      auto tk = [&](int kt) { tick(c, kt); };
+      if (PIPE0 || c > 0) {
+        TriWork<MODE> wk;
+        wk.prev = acc[0];
+        if constexpr (MODE == TRI_OUT) wk.w3h = out_weights(tiles, c * CHUNK_TILES + L3_PREV, h);
+        // (two pairs' chains ahead of the first MFMA of a stage: they cover the latency of its first LDS reads)
+        const int lead = c == 0 ? 2 * TriWork<MODE>::PER_PAIR : 0;
+        constexpr int ALL = __builtin_popcount(OUTS);
+        if (ALL > 1 && nout == 1)
+          chunk<KT2, CPS * KT2, CHUNK_TILES, MODE, 1>(tiles, c * KT2, ring, h1[0], acc[0], wk, out[0], lead, tk);
+        else
+          chunk<KT2, CPS * KT2, CHUNK_TILES, MODE, (MODE == TRI_OUT ? ALL : 0)>(tiles, c * KT2, ring, h1[0], acc[0], wk,
+                                                                                out[0], lead, tk);
+        if constexpr (MODE == TRI_GAUSS) gauss_out(tiles, c * CHUNK_TILES + L3_PREV, wk.op, out[0]);
+      } else {
+        TriWork<TRI_NONE> w0;
+        chunk<KT2, CPS * KT2, CHUNK_TILES, TRI_NONE, 0>(tiles, c * KT2, ring, h1[0], acc[0], w0, none, 0, tk);
+      }
+      acc[0] = mma_piece(tiles[(c * CHUNK_TILES + BIAS) * 64], one, acc[0]);
+    }
+  }
+  template <bool PIPE, uint32_t OUTS, class Tick>
+  __device__ static __forceinline__ void layer2_chunk(const u32x4* tiles, const Op (&h1)[1][KT2], f32x16 (&acc)[1],
+                                                      f32x16 (&out)[1], int h, int nout, Tick&& tick) {
+    layer2_chunks<PIPE, 1, OUTS>(tiles, h1, acc, out, h, nout, [&](int, int kt) { tick(kt); });
+  }
+  // behind the last chunk block (tiles: that block): its tanh and share of the output layer
+  template <uint32_t OUTS>
+  __device__ static __forceinline__ void layer2_drain(const u32x4* tiles, const f32x16 (&acc)[1], f32x16 (&out)[1], int h,
+                                                      int nout) {
+    constexpr int MODE = on_mfma<OUTS>() ? TRI_GAUSS : TRI_OUT;
+    TriWork<MODE> wk;
+    wk.prev = acc[0];
+    if constexpr (MODE == TRI_OUT) wk.w3h = out_weights(tiles, L3_OWN, h);
+    constexpr int ALL = __builtin_popcount(OUTS);
+    if (ALL > 1 && nout == 1)
+      drain<MODE, 1>(wk, out[0]);
+    else
+      drain<MODE, (MODE == TRI_OUT ? ALL : 0)>(wk, out[0]);
+    if constexpr (MODE == TRI_GAUSS) gauss_out(tiles, L3_OWN, wk.op, out[0]);
+  }
+
+  // A chunk block of a hidden layer that is not the last one: acc <- pre-activations of the chunk; if PIPE, those of
+  // the chunk before, in `acc` on entry, are returned activated as operands in hprev.
+  template <bool PIPE, class Tick>
+  __device__ static __forceinline__ void hidden_chunk(const u32x4* tiles, const Op (&hin)[1][KT2], f32x16 (&acc)[1],
+                                                      Op (&hprev)[1][PC], int h, Tick&& tick) {
+    u32x4 ring[G][3];
+    fill_ring<KT2, KT2, CHUNK_TILES>(tiles, ring);
+    f32x16 none;
+    if constexpr (PIPE) {
+      TriWork<TRI_SPLIT> wk;
+      wk.prev = acc[0];
+      chunk<KT2, KT2, CHUNK_TILES, TRI_SPLIT, 0>(tiles, 0, ring, hin[0], acc[0], wk, none, 2 * wk.PER_PAIR, tick);
+      hprev[0][0] = wk.op[0];
+      hprev[0][1] = wk.op[1];
+    } else {
+      TriWork<TRI_NONE> w0;
+      chunk<KT2, KT2, CHUNK_TILES, TRI_NONE, 0>(tiles, 0, ring, hin[0], acc[0], w0, none, 0, tick);
+    }
+    acc[0] = mma_piece(tiles[BIAS * 64], ones(h), acc[0]);
+  }
+  __device__ static __forceinline__ void hidden_drain(const f32x16 (&acc)[1], Op (&hlast)[1][PC]) {
+    TriWork<TRI_SPLIT> wk;
+    f32x16 none;
+    wk.prev = acc[0];
+    drain<TRI_SPLIT, 0>(wk, none);
+    hlast[0][0] = wk.op[0];
+    hlast[0][1] = wk.op[1];
+  }
+};
+
+}  // namespace msrl

@@ -167,7 +167,7 @@ PackJob weight_job(const void* src, void* dst, bool bf16, int n_in, int n_out, i
                    int in_map, int out_map, int gauss_k) {
   PackJob j;
   memset(&j, 0, sizeof(j));
-  j.src = src; j.dst = dst; j.src_bf16 = bf16; j.is_bias = 0;
+  j.src = src; j.dst = dst; j.src_bf16 = bf16; j.kind = PACK_TILES;
   j.n_in = n_in; j.n_out = n_out; j.src_out_major = 0;
   j.nuc = nuc; j.kt = kt; j.in_map = in_map; j.out_map = out_map; j.gauss_k = gauss_k;
   j.group = kt; j.chunk_stride = kt; j.slot_base = 0;  // plain (uc major, kt minor) order
@@ -178,9 +178,21 @@ PackJob weight_job(const void* src, void* dst, bool bf16, int n_in, int n_out, i
 PackJob bias_job(const void* src, void* dst, bool bf16, int n_out, int nuc, int out_map, int gauss_k) {
   PackJob j;
   memset(&j, 0, sizeof(j));
-  j.src = src; j.dst = dst; j.src_bf16 = bf16; j.is_bias = 1;
+  j.src = src; j.dst = dst; j.src_bf16 = bf16; j.kind = PACK_BIAS;
   j.n_out = n_out; j.nuc = nuc; j.out_map = out_map; j.gauss_k = gauss_k;
   return j;
+}
+
+// what the tiles of the policy's (and a per-agent critic's) packed image hold: fp32 networks run on the bf16 matrix
+// pipe in three pieces, but for the pursuit env, whose four networks would not fit the LDS in that form
+int image_format(const msrl_env_cfg& env, const msrl_policy_cfg& p) {
+  return p.dtype == MSRL_BF16 ? FMT_BF16 : env.kind == MSRL_ENV_TAG ? FMT_F32 : FMT_TRI;
+}
+
+// inputs of layer 1 that one agent's row takes in the joint observation's layer-1 tiles (as the centralised critic's
+// kernel counts them), and those tiles
+int joint_tiles(int in_used, bool bf16) {
+  return bf16 ? tiles_for_inputs(in_used + 1, FMT_BF16) : octet_tiles(in_used + 1);
 }
 
 // Enqueue the re-ordering of the caller's parameter buffer into st->packed.
@@ -188,20 +200,26 @@ int pack_params(msrl_state* st, const void* params, hipStream_t stream) {
   const msrl_policy_cfg& p = st->pol;
   const bool bf16 = p.dtype == MSRL_BF16;
   const size_t esz = bf16 ? 2 : 4;
-  const int in_map1 = st->env.kind == MSRL_ENV_LINGAUSS ? IN_CHAIN : (bf16 ? IN_LINEAR16 : IN_PAIRS);
+  const int fmt = image_format(st->env, p);
+  const bool gauss = p.dist == MSRL_DIAG_GAUSSIAN;
   PackJobs jobs;
   jobs.n = 0;
   const uint8_t* src = (const uint8_t*)params;
   for (int net = 0; net < 2 * roles_of(p); ++net) {  // per role: policy, value
     const int out = net % 2 == 0 ? p.out_dim : 1;
-    const int out_map = (net % 2 == 0 && p.dist == MSRL_DIAG_GAUSSIAN) ? OUT_GAUSS : OUT_NATURAL;
+    const int out_map = (net % 2 == 0 && gauss) ? OUT_GAUSS : OUT_NATURAL;
     const int gk = p.out_dim / 2;
-    // a centralised critic has a layout of its own (more layer-1 tiles) behind the policy network
+    // a centralised critic has a layout (and for fp32 networks a format) of its own behind the policy network
     const bool joint = st->central && net == 1;
     const NetLayout& L = joint ? st->critic_layout : st->layout;
+    const bool tri = fmt == FMT_TRI && !joint;
+    const int in_map1 = st->env.kind == MSRL_ENV_LINGAUSS ? IN_CHAIN
+                        : fmt == FMT_F32                  ? IN_PAIRS
+                        : joint && !bf16                  ? IN_OCTETS
+                                                          : IN_LINEAR16;
     const int in_rows = net % 2 == 1 ? value_in_of(p) : p.in_dim;
     // joint observation: per agent a block of whole layer-1 tiles, the row's non-zero prefix at its start
-    const int block = tiles_for_inputs(st->in_used + 1, bf16) * (bf16 ? 16 : 8);
+    const int block = tiles_for_inputs(st->in_used + 1, FMT_BF16) * 16;
     const int in_used = joint ? st->env.num_agents * block : st->in_used;
     uint8_t* dst = st->packed + (size_t)net * st->layout.bytes;
     const int layers = layers_of(p);
@@ -213,10 +231,10 @@ int pack_params(msrl_state* st, const void* params, hipStream_t stream) {
     const uint8_t* b2 = W2 + hh;
     const uint8_t* W3 = b2 + hb;
     const uint8_t* b3 = W3 + (size_t)p.hidden * out * esz;
-    // only the inputs that can be non-zero are packed (a prefix of the rows of W1)
-    PackJob j1 = weight_job(W1, dst + L.w1, bf16, in_used, p.hidden, L.nuc, L.kt1, in_map1, OUT_NATURAL, 0);
     // fp32 hidden layers are stored times 2 log2(e): the kernels' tanh then starts at the exp2 (dev_common.h)
     const float hidden_scale = bf16 ? 1.0f : TANH_PRESCALE;
+    // only the inputs that can be non-zero are packed (a prefix of the rows of W1)
+    PackJob j1 = weight_job(W1, dst + L.w1, bf16, in_used, p.hidden, L.nuc, L.kt1, in_map1, OUT_NATURAL, 0);
     j1.scale = hidden_scale;
     j1.bias = b1;  // the bias is the input after them; the kernels feed 1 there
     j1.bias_index = joint ? st->in_used : in_used;  // (joint: in the padding of the first agent's block)
@@ -224,39 +242,55 @@ int pack_params(msrl_state* st, const void* params, hipStream_t stream) {
       j1.in_block = block;
       j1.in_block_used = st->in_used;
       j1.in_block_stride = p.in_dim;
+      j1.in_block_tiles = joint_tiles(st->in_used, bf16);
+    }
+    if (tri) {
+      j1.kind = PACK_TRI;
+      j1.tri_k = L.kt1;
+      j1.chunk_stride = 3 * L.kt1;
     }
     jobs.job[jobs.n++] = j1;
-    // chunk blocks of the hidden layers before the last one: kt2 tiles of the chunk and its bias tile
+    // chunk block of a hidden layer: the chunk's kt2 tiles and its bias tile
+    auto chunk_job = [&](const uint8_t* W, const uint8_t* b, uint8_t* at) {
+      PackJob j = weight_job(W, at, bf16, p.hidden, p.hidden, L.nuc, L.kt2 + 1, IN_CHAIN, OUT_NATURAL, 0);
+      j.scale = hidden_scale;
+      j.bias = b;
+      j.bias_index = p.hidden;
+      j.chunk_stride = L.chunk_tiles;
+      if (tri) {
+        j.kind = PACK_TRI;
+        j.tri_k = L.kt2;
+      }
+      jobs.job[jobs.n++] = j;
+    };
     for (int l = 0; l < layers - 2; ++l) {
       const uint8_t* Wl = Wmid + (size_t)l * (hh + hb);
-      PackJob jm = weight_job(Wl, dst + L.chunks + (size_t)l * L.nuc * L.chunk_bytes, bf16, p.hidden, p.hidden, L.nuc,
-                              L.kt2 + 1, IN_CHAIN, OUT_NATURAL, 0);
-      jm.scale = hidden_scale;
-      jm.bias = Wl + hh;
-      jm.bias_index = p.hidden;
-      jm.chunk_stride = L.chunk_tiles;
-      jobs.job[jobs.n++] = jm;
+      chunk_job(Wl, Wl + hh, dst + L.chunks + (size_t)l * L.nuc * L.chunk_bytes);
     }
-    // chunk block uc of the last hidden layer: kt2 tiles of chunk uc, its bias tile, the tpc layer-3
-    // tiles fed by chunk uc-1, the tpc layer-3 tiles fed by chunk uc
+    // chunk block uc of the last hidden layer: kt2 tiles of chunk uc, its bias tile, the layer-3 part fed by
+    // chunk uc-1, the layer-3 part fed by chunk uc
     uint8_t* last = dst + L.chunks + (size_t)(layers - 2) * L.nuc * L.chunk_bytes;
-    PackJob j2 = weight_job(W2, last, bf16, p.hidden, p.hidden, L.nuc, L.kt2 + 1, IN_CHAIN, OUT_NATURAL, 0);
-    j2.scale = hidden_scale;
-    j2.bias = b2;
-    j2.bias_index = p.hidden;
-    j2.chunk_stride = L.chunk_tiles;
-    jobs.job[jobs.n++] = j2;
-    PackJob j3 = weight_job(W3, last, bf16, p.hidden, out, 1, L.kt2, IN_CHAIN, out_map, gk);
-    j3.group = L.tpc;
-    j3.chunk_stride = L.chunk_tiles;
-    j3.slot_base = L.kt2 + 1 + L.tpc;  // own chunk's copy
-    jobs.job[jobs.n++] = j3;
-    if (L.nuc > 1) {
-      PackJob j3b = j3;               // copy for the following chunk's stage: tiles of chunks 0 .. nuc-2
-      j3b.dst = last + L.chunk_bytes;
-      j3b.kt = L.kt2 - L.tpc;
-      j3b.slot_base = L.kt2 + 1;
-      jobs.job[jobs.n++] = j3b;
+    chunk_job(W2, b2, last);
+    if (tri) {
+      PackJob j3 = weight_job(W3, last, bf16, p.hidden, out, L.nuc, out_map == OUT_GAUSS ? L.tpc : 1, IN_CHAIN, out_map, gk);
+      j3.kind = out_map == OUT_GAUSS ? PACK_OUT_GAUSS : PACK_OUT_VALU;
+      j3.chunk_stride = L.chunk_tiles;
+      j3.slot_prev = 3 * L.kt2 + 1;
+      j3.slot_base = j3.slot_prev + L.tpc;
+      jobs.job[jobs.n++] = j3;
+    } else {
+      PackJob j3 = weight_job(W3, last, bf16, p.hidden, out, 1, L.kt2, IN_CHAIN, out_map, gk);
+      j3.group = L.tpc;
+      j3.chunk_stride = L.chunk_tiles;
+      j3.slot_base = L.kt2 + 1 + L.tpc;  // own chunk's copy
+      jobs.job[jobs.n++] = j3;
+      if (L.nuc > 1) {
+        PackJob j3b = j3;               // copy for the following chunk's stage: tiles of chunks 0 .. nuc-2
+        j3b.dst = last + L.chunk_bytes;
+        j3b.kt = L.kt2 - L.tpc;
+        j3b.slot_base = L.kt2 + 1;
+        jobs.job[jobs.n++] = j3b;
+      }
     }
     jobs.job[jobs.n++] = bias_job(b3, dst + L.b3, bf16, out, 1, out_map, gk);
     src = b3 + (size_t)out * esz;
@@ -505,12 +539,13 @@ int configure_state(msrl_state* st, const char* who, const msrl_env_cfg* env, co
   // The particle observation ends in 2 (N - 1) slots that are always zero: layer 1 skips them.
   st->in_used = env->kind == MSRL_ENV_PARTICLE ? 4 * env->num_agents + 2 : policy->in_dim;
   const int n_nets = 2 * roles_of(*policy);
-  st->layout = net_layout(st->in_used, policy->hidden, policy->dtype == MSRL_BF16, layers_of(*policy));
+  st->layout = net_layout(st->in_used, policy->hidden, image_format(*env, *policy), layers_of(*policy),
+                          policy->dist == MSRL_DIAG_GAUSSIAN);
   st->central = central_of(*policy);
   // (joint observation: num_agents blocks of whole layer-1 tiles, see pack_params)
   {
     const bool bf16 = policy->dtype == MSRL_BF16;
-    st->critic_layout = net_layout(env->num_agents * tiles_for_inputs(st->in_used + 1, bf16) * (bf16 ? 16 : 8) - 1,
+    st->critic_layout = net_layout(env->num_agents * joint_tiles(st->in_used, bf16) * (bf16 ? 16 : 8) - 1,
                                    policy->hidden, bf16);
   }
   // (behind a centralised critic's image: the memory its kernel's tile fetches may read past the end)
@@ -613,7 +648,7 @@ int msrl_rollout_init(const msrl_env_cfg* env, const msrl_policy_cfg* policy, ui
   INIT_TRY(hipMemset(st->packed, 0, packed_bytes));
   if (env->kind == MSRL_ENV_LINGAUSS) {
     const int D = env->obs_dim, K = env->act_dim;
-    const int ktA = tiles_for_inputs(D + 1, false), ktB = tiles_for_inputs(K, false);  // as the kernel counts them
+    const int ktA = tiles_for_inputs(D + 1, FMT_F32), ktB = tiles_for_inputs(K, FMT_F32);  // as the kernel counts them
     INIT_TRY(hipMalloc((void**)&st->dyn_src, ((size_t)D * D + (size_t)D * K) * sizeof(float)));
     INIT_TRY(hipMalloc((void**)&st->dyn, (size_t)(ktA + ktB) * 1024));
     INIT_TRY(hipMemcpy(st->dyn_src, env->A, (size_t)D * D * sizeof(float), hipMemcpyHostToDevice));

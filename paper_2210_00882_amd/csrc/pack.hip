@@ -6,12 +6,16 @@
 
 namespace msrl {
 
-__device__ __forceinline__ int in_index(int map, bool bf16, int kt, int h, int e) {
-  switch (map) {
+__device__ __forceinline__ int in_index(const PackJob& j, bool octet, int kt, int h, int e) {
+  switch (j.in_map) {
+    case IN_OCTETS: {
+      const int k = kt % j.in_block_tiles;
+      return kt / j.in_block_tiles * j.in_block + 16 * (k >> 1) + 8 * h + 4 * (k & 1) + e;
+    }
     case IN_LINEAR16: return 16 * kt + 8 * h + e;
     case IN_PAIRS: return 8 * kt + 2 * e + h;
     default:
-      return bf16 ? 32 * (kt >> 1) + 16 * (kt & 1) + 8 * (e >> 2) + 4 * h + (e & 3)
+      return octet ? 32 * (kt >> 1) + 16 * (kt & 1) + 8 * (e >> 2) + 4 * h + (e & 3)
                   : 32 * (kt >> 2) + 8 * (kt & 3) + 4 * h + e;
   }
 }
@@ -34,11 +38,40 @@ __device__ __forceinline__ float load_src(const void* src, int bf16, int idx) {
   return ((const float*)src)[idx];
 }
 
+// bf16 pieces of a value (mlp_tri.h)
+__device__ __forceinline__ void three_pieces(float v, uint32_t (&p)[3]) {
+  for (int k = 0; k < 3; ++k) {
+    const __bf16 b = (__bf16)v;  // round to nearest even
+    p[k] = __builtin_bit_cast(uint16_t, b);
+    v -= (float)b;
+  }
+}
+
+// the NE source values (times the job's scale) of lane (m, h) in k tile kt of chunk uc
+template <int NE>
+__device__ __forceinline__ void tile_values(const PackJob& j, int uc, int kt, int m, int h, float (&v)[NE]) {
+  const int o = out_index(j.out_map, j.gauss_k, 32 * uc + m, j.n_out);
+  for (int e = 0; e < NE; ++e) {
+    const int i = in_index(j, NE == 8, kt, h, e);
+    v[e] = 0.0f;
+    bool weight = i < j.n_in;
+    int li = i;
+    if (j.in_block > 0) {
+      weight = weight && i % j.in_block < j.in_block_used;
+      li = (i / j.in_block) * j.in_block_stride + i % j.in_block;
+    }
+    if (o >= 0 && weight)
+      v[e] = load_src(j.src, j.src_bf16, j.src_out_major ? o * j.n_in + li : li * j.n_out + o) * j.scale;
+    else if (o >= 0 && j.bias && i == j.bias_index)
+      v[e] = load_src(j.bias, j.src_bf16, o) * j.scale;
+  }
+}
+
 // grid: (blocks over work items, job); one thread per (tile, lane) or per bias slot.
 __global__ void pack_kernel(PackJobs jobs) {
   const PackJob& j = jobs.job[blockIdx.y];
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j.is_bias) {
+  if (j.kind == PACK_BIAS) {
     if (tid >= 32 * j.nuc) return;
     const int o = out_index(j.out_map, j.gauss_k, tid, j.n_out);
     ((float*)j.dst)[tid] = o >= 0 ? load_src(j.src, j.src_bf16, o) : 0.0f;
@@ -48,34 +81,66 @@ __global__ void pack_kernel(PackJobs jobs) {
   if (tid >= n_tiles * 64) return;
   const int tile = tid >> 6, lane = tid & 63;
   const int uc = tile / j.kt, kt = tile % j.kt;
-  const int dst_slot = ((uc + kt / j.group) * j.chunk_stride + j.slot_base + kt % j.group) * 64 + lane;
   const int m = lane & 31, h = lane >> 5;
-  const int o = out_index(j.out_map, j.gauss_k, 32 * uc + m, j.n_out);
-  const bool bf16 = j.src_bf16 != 0;
-  const int ne = bf16 ? 8 : 4;
-  float v[8];
-  for (int e = 0; e < ne; ++e) {
-    const int i = in_index(j.in_map, bf16, kt, h, e);
-    v[e] = 0.0f;
-    bool weight = i < j.n_in;
-    int li = i;
-    if (j.in_block > 0) {
-      weight = weight && i % j.in_block < j.in_block_used;
-      li = (i / j.in_block) * j.in_block_stride + i % j.in_block;
+  if (j.kind == PACK_TRI) {
+    uint4* dst = (uint4*)j.dst + ((size_t)uc * j.chunk_stride + j.slot_base + 3 * kt) * 64 + lane;
+    if (kt == j.tri_k) {  // bias tile
+      const int o = out_index(j.out_map, j.gauss_k, 32 * uc + m, j.n_out);
+      uint32_t p[3] = {0, 0, 0};
+      if (h == 0 && o >= 0) three_pieces(load_src(j.bias, j.src_bf16, o) * j.scale, p);
+      *dst = make_uint4(p[0] | p[1] << 16, p[2], 0, 0);
+      return;
     }
-    if (o >= 0 && weight)
-      v[e] = load_src(j.src, j.src_bf16, j.src_out_major ? o * j.n_in + li : li * j.n_out + o);
-    else if (o >= 0 && j.bias && i == j.bias_index)
-      v[e] = load_src(j.bias, j.src_bf16, o);
+    float v[8];
+    tile_values(j, uc, kt, m, h, v);
+    uint32_t w[3][4];
+    for (int q = 0; q < 4; ++q) {
+      uint32_t a[3], b[3];
+      three_pieces(v[2 * q], a);
+      three_pieces(v[2 * q + 1], b);
+      for (int k = 0; k < 3; ++k) w[k][q] = a[k] | b[k] << 16;
+    }
+    for (int k = 0; k < 3; ++k) dst[k * 64] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+    return;
   }
-  if (bf16) {
-    // values are bfloat16-representable already: keep the top 16 bits
+  if (j.kind == PACK_OUT_VALU || j.kind == PACK_OUT_GAUSS) {
+    uint4 w;
+    if (j.kind == PACK_OUT_VALU) {  // floats 4 lane .. 4 lane + 3 of the block
+      const int i = lane >> 4, hh = (lane >> 3) & 1, o = lane & 7;
+      float v[4];
+      for (int e = 0; e < 4; ++e)
+        v[e] = o < j.n_out ? load_src(j.src, j.src_bf16, (32 * uc + 8 * i + 4 * hh + e) * j.n_out + o) : 0.0f;
+      w = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+    } else {  // tile 2 i + q: k tile i, pieces 0 | 1 (q = 0) or 2 | - (q = 1) in output rows 0 .. 15 | 16 .. 31
+      const int i = kt >> 1, q = kt & 1, piece = 2 * q + (m >> 4);
+      const int o = out_index(j.out_map, j.gauss_k, m & 15, j.n_out);
+      uint32_t r[8];
+      for (int e = 0; e < 8; ++e) {
+        uint32_t p[3] = {0, 0, 0};
+        const int u = 32 * uc + 16 * i + 8 * (e >> 2) + 4 * h + (e & 3);
+        if (o >= 0) three_pieces(load_src(j.src, j.src_bf16, u * j.n_out + o), p);
+        r[e] = piece == 0 ? p[0] : piece == 1 ? p[1] : piece == 2 ? p[2] : 0u;
+      }
+      w = make_uint4(r[0] | r[1] << 16, r[2] | r[3] << 16, r[4] | r[5] << 16, r[6] | r[7] << 16);
+    }
+    uint4* dst = (uint4*)j.dst + lane;
+    dst[((size_t)uc * j.chunk_stride + j.slot_base + kt) * 64] = w;
+    if (uc + 1 < j.nuc) dst[((size_t)(uc + 1) * j.chunk_stride + j.slot_prev + kt) * 64] = w;
+    return;
+  }
+  const int dst_slot = ((uc + kt / j.group) * j.chunk_stride + j.slot_base + kt % j.group) * 64 + lane;
+  if (j.src_bf16) {
+    float v[8];
+    tile_values(j, uc, kt, m, h, v);
+    // values are bfloat16-representable already (their scale is 1): keep the top 16 bits
     uint32_t w[4];
     for (int p = 0; p < 4; ++p)
       w[p] = (__float_as_uint(v[2 * p]) >> 16) | (__float_as_uint(v[2 * p + 1]) & 0xFFFF0000u);
     ((uint4*)j.dst)[dst_slot] = make_uint4(w[0], w[1], w[2], w[3]);
   } else {
-    ((float4*)j.dst)[dst_slot] = make_float4(v[0] * j.scale, v[1] * j.scale, v[2] * j.scale, v[3] * j.scale);
+    float v[4];
+    tile_values(j, uc, kt, m, h, v);
+    ((float4*)j.dst)[dst_slot] = make_float4(v[0], v[1], v[2], v[3]);
   }
 }
 
@@ -84,7 +149,7 @@ hipError_t launch_pack(const PackJobs& jobs, hipStream_t stream) {
   int max_items = 0;
   for (int k = 0; k < jobs.n; ++k) {
     const PackJob& j = jobs.job[k];
-    const int items = j.is_bias ? 32 * j.nuc : j.nuc * j.kt * 64;
+    const int items = j.kind == PACK_BIAS ? 32 * j.nuc : j.nuc * j.kt * 64;
     if (items > max_items) max_items = items;
   }
   dim3 grid((max_items + 255) / 256, jobs.n);

@@ -19,7 +19,12 @@
 //   chained f32  : 32*(kt/4) + 8*(kt%4) + 4*h + j
 //   linear  bf16 : 16*kt + 8*h + s                  (particle observation, layer 1)
 //   pairs   f32  : 8*kt + 2*j + h                   (particle observation, layer 1)
+//   octets f32  : 16*(k/2) + 8*h + 4*(k%2) + j, k the tile's index within its block of inputs
+//                 (joint observation of a centralised critic in fp32, one block per agent)
 // Inputs or outputs beyond the real sizes hold zeros.
+//
+// fp32 networks on the bf16 matrix pipe ("tri", mlp_tri.h): a k tile has 16 inputs in the bf16 maps and is three
+// consecutive 1 KiB tiles, the three bf16 pieces of its weights.
 //
 // Biases of layers 1 and 2 ride along as one more input: input index n_in holds
 // the bias, and the kernels feed the constant 1 at that index.  (A bias read
@@ -36,6 +41,10 @@
 //   [b3: 32 floats in physical output order]
 // With more than two hidden layers, every further hidden layer contributes nuc chunk blocks of the
 // same size in front of those of the last hidden layer (layer order), with the layer-3 slots unused.
+// tri images: the layer-3 part of a chunk is one 1 KiB block of fp32 weights for up to 8 outputs (float
+//     i * 64 + h * 32 + o * 4 + j = weight of unit 8 i + 4 h + j of the chunk, output o), or for Gaussian policies four
+//     tiles (see MlpTri::gauss_out); with 256 units the layer-1 tiles fill the place of one more chunk block in front
+//     of the others and are streamed like one.
 // The kernels keep the layer-1 tiles resident in LDS and stream the chunk blocks
 // through an LDS window, one block per stage; they activate chunk uc-1 while the
 // MFMAs of chunk uc run, which is why a block carries the layer-3 tiles of the
@@ -46,15 +55,16 @@
 
 namespace msrl {
 
-enum InMap : int { IN_CHAIN = 0, IN_LINEAR16 = 1, IN_PAIRS = 2 };
+enum Fmt : int { FMT_F32 = 0, FMT_BF16 = 1, FMT_TRI = 2 };  // what the tiles of an image hold
+enum InMap : int { IN_CHAIN = 0, IN_LINEAR16 = 1, IN_PAIRS = 2, IN_OCTETS = 3 };
 // physical output row m of a layer-3 tile -> logical output
 //   OUT_NATURAL : m
 //   OUT_GAUSS   : m < 8 -> mean m;  8 <= m < 16 -> log-std (m - 8)   (act_dim <= 8)
 enum OutMap : int { OUT_NATURAL = 0, OUT_GAUSS = 1 };
 
 struct NetLayout {
-  int kt1, kt2, nuc, tpc;  // tiles per chunk in layer 1 / layer 2; chunks of 32 units; layer-3 tiles per chunk
-  int chunk_tiles;         // tiles of one chunk block
+  int kt1, kt2, nuc, tpc;  // k tiles per chunk in layer 1 / layer 2; chunks of 32 units; layer-3 tiles per chunk
+  int chunk_tiles;         // 1 KiB tiles of one chunk block
   int layers;              // hidden layers (>= 2); chunk blocks: (layers - 1) * nuc
   size_t w1;               // byte offset of the layer-1 tiles
   size_t chunks;           // byte offset of chunk block 0
@@ -63,26 +73,42 @@ struct NetLayout {
   size_t bytes;            // size of one packed network, a multiple of 1 KiB
 };
 
-__host__ __device__ inline int tiles_for_inputs(int n_in, bool bf16) {
-  return bf16 ? (n_in + 15) / 16 : (n_in + 7) / 8;
+__host__ __device__ inline int tiles_for_inputs(int n_in, int fmt) {
+  return fmt == FMT_F32 ? (n_in + 7) / 8 : (n_in + 15) / 16;
 }
+// fp32 tiles that `n_in` inputs take in the octets map: a block of 16 inputs is two tiles, of which the second one
+// holds inputs 4 .. 7 and 12 .. 15
+__host__ __device__ constexpr int octet_tiles(int n_in) {
+  return 2 * (n_in / 16) + (n_in % 16 == 0 ? 0 : n_in % 16 <= 4 ? 1 : 2);
+}
+// tri images: the layer-1 tiles come through the LDS window like a chunk block (256 units: they would not fit the LDS
+// beside it)
+__host__ __device__ constexpr bool tri_streams_layer1(int hidden) { return hidden >= 256; }
 
 // in_used: number of leading inputs of layer 1 that are packed (the rest are known to be zero)
-__host__ __device__ inline NetLayout net_layout(int in_used, int hidden, bool bf16, int layers = 2) {
+// gauss: tri images only, the layer-3 part is that of a Gaussian policy
+__host__ __device__ inline NetLayout net_layout(int in_used, int hidden, int fmt, int layers = 2, bool gauss = false) {
   NetLayout L;
-  L.kt1 = tiles_for_inputs(in_used + 1, bf16);
-  L.kt2 = tiles_for_inputs(hidden, bf16);
+  const int pieces = fmt == FMT_TRI ? 3 : 1;
+  L.kt1 = tiles_for_inputs(in_used + 1, fmt);
+  L.kt2 = tiles_for_inputs(hidden, fmt);
   L.nuc = hidden / 32;
-  L.tpc = L.kt2 / L.nuc;
-  L.chunk_tiles = L.kt2 + 1 + 2 * L.tpc;
+  L.tpc = fmt == FMT_TRI ? (gauss ? 4 : 1) : L.kt2 / L.nuc;
+  L.chunk_tiles = pieces * L.kt2 + 1 + 2 * L.tpc;
   L.layers = layers;
   L.w1 = 0;
-  L.chunks = L.w1 + (size_t)L.nuc * L.kt1 * 1024;
   L.chunk_bytes = (size_t)L.chunk_tiles * 1024;
+  L.chunks = fmt == FMT_TRI && tri_streams_layer1(hidden) ? L.chunk_bytes : L.w1 + (size_t)L.nuc * L.kt1 * pieces * 1024;
   L.b3 = L.chunks + (size_t)(layers - 1) * L.nuc * L.chunk_bytes;
   L.bytes = (L.b3 + 32 * 4 + 1023) / 1024 * 1024;
   return L;
 }
+
+// PACK_TILES: native tiles of the source type; PACK_BIAS: n_out values through the output map into 32 * nuc floats;
+// PACK_TRI: k tiles of three pieces (the last one, index tri_k, is the bias tile where kt = tri_k + 1); PACK_OUT_VALU,
+// PACK_OUT_GAUSS: layer-3 part of a chunk of a tri image, once at slot_base of the chunk's block and once at slot_prev
+// of the block behind it
+enum PackKind : int { PACK_TILES = 0, PACK_BIAS = 1, PACK_TRI = 2, PACK_OUT_VALU = 3, PACK_OUT_GAUSS = 4 };
 
 // One matrix (or bias vector) to re-order.
 struct PackJob {
@@ -90,7 +116,7 @@ struct PackJob {
   const void* bias;   // device, or null: values served at input index bias_index
   void* dst;          // device
   int src_bf16;       // source element type (dst tiles have the same type; bias vectors become f32)
-  int is_bias;        // 1: copy n_out values through the output map into 32*nuc floats
+  int kind;           // PackKind
   int n_in, n_out;    // logical sizes
   int bias_index;     // input index that reads bias[out] (only if bias != null)
   int src_out_major;  // 0: src[in * n_out + out] (network weights); 1: src[out * n_in + in]
@@ -100,12 +126,14 @@ struct PackJob {
   // layers 1, 2: group = kt (tiles of a chunk are consecutive); layer 3: group = tiles
   // per chunk block, so its tiles follow the layer-2 tiles of the chunk they consume.
   int group, chunk_stride, slot_base;
+  int tri_k, slot_prev;
   int in_map, out_map, gauss_k;
   // in_block > 0: the packed inputs come in blocks of in_block; input i reads source input
   // (i / in_block) * in_block_stride + i % in_block if i % in_block < in_block_used and is zero otherwise
   // (the joint observation of a centralised critic: per agent, the non-zero prefix of its row padded to
   // whole tiles; the bias sits in the padding of the first block, at bias_index)
-  int in_block, in_block_used, in_block_stride;
+  // (IN_OCTETS: a block is in_block_tiles tiles)
+  int in_block, in_block_used, in_block_stride, in_block_tiles;
   // fp32 images: factor on the weights and on the bias riding with them (1, or TANH_PRESCALE for the layers
   // that end in tanh); bf16 images are not scaled (the product would not be a bfloat16 value)
   float scale;

@@ -23,8 +23,11 @@
 // scalars (value, action, logp, reward, done) of all waves are collected in LDS
 // and written by one wave per array, after a barrier of the following step.
 #pragma once
+#include <type_traits>
+
 #include "dev_common.h"
 #include "mlp.h"
+#include "mlp_tri.h"
 #include "packed.h"
 
 namespace msrl {
@@ -55,7 +58,7 @@ struct RolloutArgs {
 
 // Copies the layer-1 tiles and the output biases of both packed networks into LDS (once per kernel).
 __device__ __forceinline__ void load_resident(u32x4* l1, float* b3, const uint8_t* packed,
-                                              const NetLayout& ly, int l1_tiles) {
+                                              const NetLayout& ly, int l1_tiles) {  // (0: only the biases)
   for (int net = 0; net < 2; ++net) {
     const u32x4* src = (const u32x4*)(packed + (size_t)net * ly.bytes + ly.w1);
     for (int i = threadIdx.x; i < l1_tiles * 64; i += blockDim.x) l1[net * l1_tiles * 64 + i] = src[i];
@@ -147,18 +150,15 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   // padding of the layout), so layer 1 contracts over NZ inputs plus the constant 1 that carries
   // the bias, which sits at input index NZ.
   constexpr int NZ = 4 * N + 2;
-  constexpr int KT1 = BF16 ? (NZ + 1 + 15) / 16 : (NZ + 1 + 7) / 8;
+  constexpr int KT1 = (NZ + 1 + 15) / 16;
   constexpr bool ACT = PHASE == PHASE_ACT || PHASE == PHASE_ACT_DEEP || PHASE == PHASE_ACT_CENTRAL;
   constexpr bool CENTRAL = PHASE == PHASE_CENTRAL || PHASE == PHASE_ACT_CENTRAL;
   // chunk blocks per stage (fewer barriers when they fit; the centralised critic needs the LDS)
   constexpr int CPS = BF16 && H >= 64 && !CENTRAL ? 2 : 1;
-  // (fp32 operand mm of layer 1 is the input pair 2 mm + h: the NZ + 1 inputs end in MFMA L1_LAST of the last tile)
-  constexpr int L1_LAST = BF16 ? 0 : (NZ + 1 - 8 * (KT1 - 1) + 1) / 2;
-  // fp32 networks of 256 units run one wave per SIMD (four per workgroup): their layer-1 outputs live in the
-  // accumulation registers that would otherwise lie idle, which leaves room for the output layer on the VALU
-  // (the full rollout and the actor fragment alike: they must agree bit for bit)
-  constexpr bool H1_ACC = !BF16 && H >= 256 && WAVES == 4 && (PHASE == PHASE_ALL || PHASE == PHASE_ACT);
-  typedef Mlp<H, BF16, NB, KT1, L1_LAST, H1_ACC> Net;
+  // fp32 networks run on the bf16 matrix pipe (mlp_tri.h)
+  typedef std::conditional_t<BF16, Mlp<H, true, 1, KT1>, MlpTri<H, KT1>> Net;
+  constexpr bool L1S = !BF16 && tri_streams_layer1(H);  // the layer-1 tiles come through the window
+  typedef Mlp<H, BF16, 1, KT1> Critic;  // the centralised critic's layers 2 and 3: native tiles for both types
   // PHASE_SPLIT: waves [0, RW) evaluate the policy network of row blocks 0 .. RW-1, waves [RW, 2 RW) the value
   // network of the same row blocks (role 1); every stage of both networks is resident in LDS
   constexpr bool SPLIT = PHASE == PHASE_SPLIT;
@@ -166,15 +166,19 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   constexpr int RW = SPLIT ? WAVES / 2 : WAVES;  // row blocks of a workgroup
   // LDS window: the stage in use and the one being copied; PHASE_SPLIT: all stages of a step
   constexpr int NBUF = SPLIT ? 2 * Net::NUC / CPS : 2;
-  typedef WeightStream<Net, WAVES, NBUF, CPS> Stream;
+  static_assert(!SPLIT || !L1S, "two waves per row block: layer 1 is resident");
+  typedef WeightStream<Net, WAVES, NBUF, CPS, L1S> Stream;
   typedef typename Net::Op Op;
+  typedef typename Critic::Op COp;
   static_assert(EPW >= 1, "a wave must hold at least one env");
   constexpr bool DEEP = PHASE == PHASE_DEEP || PHASE == PHASE_ACT_DEEP;
   constexpr bool FULL = (PHASE == PHASE_ALL || PHASE == PHASE_CLOCKS || DEEP || CENTRAL || SPLIT) && !ACT;
   static_assert(!CENTRAL || WAVES == Net::NUC, "centralised critic: one wave per 32-unit chunk");
-  // The joint observation is laid out as one block of KT1 tiles per agent, the agent's row exactly as the
-  // policy's layer 1 takes it (its constant 1 at input NZ included: agent 0's carries the critic's bias).
-  constexpr int KT1C = N * KT1;
+  // The joint observation is laid out as one block of JT tiles per agent, the agent's row as the policy's layer 1
+  // takes it (its constant 1 at input NZ included: agent 0's carries the critic's bias); fp32: four values of
+  // every octet per tile, the octets map of packed.h.
+  constexpr int JT = BF16 ? KT1 : octet_tiles(NZ + 1);
+  constexpr int KT1C = N * JT;
   constexpr int JCOLS = WAVES * EPW;            // envs of a workgroup = columns of the critic's tile
   static_assert(!CENTRAL || JCOLS <= 32, "the envs of a workgroup are the columns of one tile");
   constexpr bool HAS_NETS = PHASE != PHASE_ENV && PHASE != PHASE_STEP;     // the variant runs the networks
@@ -189,7 +193,7 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   // layer-1 tiles and the window, fp32 ones the more, so their staging areas are smaller).
   constexpr bool TIGHT = SPLIT && H >= 128;  // (all weights resident: little LDS left)
   constexpr int STG_ALL = (!BF16 && H >= 256) || TIGHT ? 2048 : 4608;
-  constexpr int STG_SOME = H >= 256 ? (BF16 ? 2560 : 2048) : (TIGHT ? 2048 : 3072);
+  constexpr int STG_SOME = H >= 256 ? (BF16 ? 2560 : 2048) : (TIGHT ? 2048 : !BF16 && H >= 128 ? 2560 : 3072);
   constexpr int SE = EPW * N * D * 4 <= STG_ALL ? EPW : (STG_SOME / (N * D * 4) >= 1 ? STG_SOME / (N * D * 4) : 1);
   constexpr int SR = SE * N;
   constexpr int PASSES = (EPW + SE - 1) / SE;
@@ -198,13 +202,14 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
 
   // (the variants without networks hold no weights, so that as many of their workgroups fit a CU
   // as their registers allow)
-  constexpr int L1_SLOTS = HAS_NETS ? Net::L1_TILES * 64 : 1;
+  constexpr int L1_SLOTS = HAS_NETS && !L1S ? Net::L1_TILES * 64 : 1;
   constexpr int W_SLOTS = HAS_NETS ? NBUF * Stream::BUF_SLOTS : 1;
   __shared__ __attribute__((aligned(16))) u32x4 s_l1[CENTRAL ? 1 : 2][L1_SLOTS];  // resident layer-1 tiles
   // centralised critic: joint observations as B-operand tiles, the layer outputs as tiles, partial values
   __shared__ __attribute__((aligned(16))) u32x4 s_j[CENTRAL ? KT1C * 64 : 1];
-  __shared__ __attribute__((aligned(16))) u32x4 s_hc[CENTRAL ? Net::KT2 * 64 : 1];
-  __shared__ __attribute__((aligned(16))) u32x4 s_w3c[CENTRAL ? WAVES * Net::TPC * 64 : 1];  // its output-layer tiles
+  __shared__ __attribute__((aligned(16))) u32x4 s_hc[CENTRAL ? Critic::KT2 * 64 : 1];
+  // its output layer: the tiles of the chunks (bf16), or the weights of its one output (fp32)
+  __shared__ __attribute__((aligned(16))) u32x4 s_w3c[CENTRAL ? (BF16 ? WAVES * Critic::TPC * 64 : H / 4) : 1];
   __shared__ float s_vpart[CENTRAL ? WAVES : 1][32];
   __shared__ __attribute__((aligned(16))) u32x4 s_w[W_SLOTS];       // chunk-block window
   __shared__ __attribute__((aligned(16))) float s_b3[2][32];
@@ -214,7 +219,7 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   // workgroup and written one array per wave after the next barrier: WAVES * VR consecutive rows
   // per store instead of VR, so that all but the edge cache lines are written whole.
   constexpr int WGR = PHASE == PHASE_MLP ? 1 : RW * VR;
-  constexpr int PF = D < (BF16 ? 16 : 8) * KT1 ? D : (BF16 ? 16 : 8) * KT1;  // features every write fills
+  constexpr int PF = D < 16 * KT1 ? D : 16 * KT1;  // features every write fills
   constexpr bool PART_IN_STG = PF >= 32 && SR >= 2 && STORES_OBS && H >= 256;
   __shared__ float s_part[WAVES][PART_IN_STG ? 1 : 2 * ROWS];
   // (PHASE_SPLIT: two copies, used in turn by the steps, since the step has no barrier between the
@@ -237,16 +242,16 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   const bool rew_writer = !SPLIT || role == 1;
   const int n = lane & 31, h = lane >> 5;
   const int layers = DEEP ? a.layers : 2;
-  const NetLayout ly = net_layout(NZ, H, BF16, layers);
+  const NetLayout ly = net_layout(NZ, H, BF16 ? FMT_BF16 : FMT_TRI, layers);
   Stream ws;
   ws.lds = s_w;
   ws.packed = a.packed;
   ws.net_bytes = ly.bytes;
-  ws.chunks_off = ly.chunks;
+  ws.chunks_off = L1S ? ly.w1 : ly.chunks;
   ws.chunk_bytes = ly.chunk_bytes;
   ws.wave = wave;
   ws.lane = lane;
-  if constexpr (DEEP) ws.stages_per_net = (layers - 1) * Stream::STAGES_PER_NET;
+  if constexpr (DEEP) ws.stages_per_net = (layers - 1) * Stream::CHUNK_STAGES + Stream::L1_STAGES;
   // the critic's image (PHASE_CENTRAL): KT1C layer-1 tiles of 16 (bf16) or 8 (fp32) inputs
   const NetLayout lyc = net_layout(KT1C * (BF16 ? 16 : 8) - 1, H, BF16);
   if constexpr (HAS_NETS) {
@@ -260,14 +265,21 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
         s_b3[0][threadIdx.x] = *(const float*)(a.packed + ly.b3 + threadIdx.x * 4);
         s_b3[1][threadIdx.x] = *(const float*)(a.critic + lyc.b3 + threadIdx.x * 4);
       }
+      if constexpr (BF16) {
 #pragma unroll
-      for (int i = 0; i < Net::TPC; ++i)  // every wave keeps the output-layer tiles of its own chunk
-        s_w3c[(wave * Net::TPC + i) * 64 + lane] =
-            ((const u32x4*)(a.critic + lyc.chunks + ((size_t)wave * Net::CHUNK_TILES + Net::L3_OWN + i) * 1024))[lane];
+        for (int i = 0; i < Critic::TPC; ++i)  // every wave keeps the output-layer tiles of its own chunk
+          s_w3c[(wave * Critic::TPC + i) * 64 + lane] =
+              ((const u32x4*)(a.critic + lyc.chunks + ((size_t)wave * Critic::CHUNK_TILES + Critic::L3_OWN + i) * 1024))[lane];
+      } else {
+        // weights of output 0: slots 0 and 32 of the chunk's tile i hold units 8 i + 4 h .. + 3
+        if (lane < 8)
+          s_w3c[wave * 8 + lane] = ((const u32x4*)(a.critic + lyc.chunks +
+              ((size_t)wave * Critic::CHUNK_TILES + Critic::L3_OWN + lane / 2) * 1024))[32 * (lane % 2)];
+      }
       // joint observations: columns without an env stay zero
       for (int i = threadIdx.x; i < KT1C * 64 * 4; i += blockDim.x) ((uint32_t*)s_j)[i] = 0u;
     } else {
-      load_resident(&s_l1[0][0], &s_b3[0][0], a.packed, ly, Net::L1_TILES);
+      load_resident(&s_l1[0][0], &s_b3[0][0], a.packed, ly, L1S ? 0 : Net::L1_TILES);
     }
   }
   // features the lanes never write (>= the layer-1 tile range) stay zero for the whole kernel
@@ -390,7 +402,7 @@ next_row_block:
   // The last step's layers 2 and 3 run behind the loop.
   constexpr int SPN = Stream::STAGES_PER_NET;
   static_assert(!CENTRAL || SPN >= 2, "the critic rides on the policy stages");
-  constexpr int L2T = Net::KT2 + 1;  // layer-2 tiles of a chunk, the bias tile included
+  constexpr int L2T = Critic::KT2 + 1;  // layer-2 tiles of a chunk, the bias tile included
   constexpr int S2_ = (SPN * L2T + (L2T + KT1C) / 2) / (L2T + KT1C);  // stages in proportion to the tiles
   constexpr int S2 = S2_ < 1 ? 1 : (S2_ > SPN - 1 ? SPN - 1 : S2_);
   constexpr int S1 = SPN - S2;
@@ -402,7 +414,7 @@ next_row_block:
   static_assert(!CENTRAL || (S2 * RING - L2T <= CRITIC_FETCH_PAD_TILES && S1 * RING - KT1C <= CRITIC_FETCH_PAD_TILES),
                 "fetch range");
   const uint8_t* t1 = a.critic + (size_t)wave * KT1C * 1024;
-  const uint8_t* t2 = a.critic + lyc.chunks + (size_t)wave * Net::CHUNK_TILES * 1024;
+  const uint8_t* t2 = a.critic + lyc.chunks + (size_t)wave * Critic::CHUNK_TILES * 1024;
   const uint32_t lane16 = (uint32_t)lane * 16u;
   // Fetch of tiles [0, CNT) behind a base address into dst[0 .. CNT).  Left alone, the compiler
   // computes 64-bit vector addresses and keeps them in registers.  So the lane offset and the scalar
@@ -428,7 +440,7 @@ next_row_block:
   u32x4 cring[RING];
   // layer-2 tile kt of the chunk times the layer-1 outputs in s_hc (the bias tile times the constant 1)
   // (a tile of B operands in LDS is 16 bytes per lane for both types: one bf16 operand or the four fp32 ones)
-  auto lds_operands = [&](const u32x4& raw, Op (&b)[Net::PT]) {
+  auto lds_operands = [&](const u32x4& raw, COp (&b)[Critic::PT]) {
     if constexpr (BF16) {
       b[0] = __builtin_bit_cast(bf16x8, raw);
     } else {
@@ -438,8 +450,8 @@ next_row_block:
     }
   };
   auto critic_l2_tile = [&](const u32x4& w, int kt, f32x16& c) {
-    if (kt < Net::KT2) {
-      Op b[Net::PT];
+    if (kt < Critic::KT2) {
+      COp b[Critic::PT];
       lds_operands(s_hc[kt * 64 + lane], b);
       mma_tile<BF16>(w, b, c);
     } else {
@@ -449,29 +461,41 @@ next_row_block:
   // tanh of the chunk's layer-2 sums and the output layer: the chunk's share of the value of column lane % 32
   auto critic_l3 = [&](const f32x16& c) {
     float tt[16];
-    Op h2c[Net::PC];
     tanh_range<!BF16>(c, tt, 0, 16, false);
-    to_operands<BF16>(tt, h2c);
-    f32x16 ov = zero16();
+    if constexpr (BF16) {
+      COp h2c[Critic::PC];
+      to_operands<BF16>(tt, h2c);
+      f32x16 ov = zero16();
 #pragma unroll
-    for (int i = 0; i < Net::TPC; ++i) mma_tile<BF16>(s_w3c[(wave * Net::TPC + i) * 64 + lane], &h2c[i * Net::PT], ov);
-    if (h == 0) s_vpart[wave][n] = ov[0];  // output 0: register 0 of the h = 0 lanes
+      for (int i = 0; i < Critic::TPC; ++i) mma_tile<BF16>(s_w3c[(wave * Critic::TPC + i) * 64 + lane], &h2c[i * Critic::PT], ov);
+      if (h == 0) s_vpart[wave][n] = ov[0];  // output 0: register 0 of the h = 0 lanes
+    } else {
+      float part = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 w = __builtin_bit_cast(f32x4, s_w3c[wave * 8 + 2 * i + h]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part = __builtin_fmaf(tt[4 * i + k], w[k], part);
+      }
+      part += __shfl_xor(part, 32);
+      if (h == 0) s_vpart[wave][n] = part;
+    }
   };
   // tanh of the chunk's layer-1 sums; outputs (as the next layer's operand tiles) to s_hc
   auto critic_l1_publish = [&](const f32x16& c) {
     float tt[16];
-    Op hc[Net::PC];
+    COp hc[Critic::PC];
     tanh_range<!BF16>(c, tt, 0, 16, false);
     to_operands<BF16>(tt, hc);
     // the chunk's 32 units are TPC tiles of the next layer's contraction
 #pragma unroll
-    for (int i = 0; i < Net::TPC; ++i) {
+    for (int i = 0; i < Critic::TPC; ++i) {
       u32x4 raw;
       if constexpr (BF16)
         raw = __builtin_bit_cast(u32x4, hc[i]);
       else
         raw = __builtin_bit_cast(u32x4, f32x4{hc[4 * i], hc[4 * i + 1], hc[4 * i + 2], hc[4 * i + 3]});
-      s_hc[(Net::TPC * wave + i) * 64 + lane] = raw;
+      s_hc[(Critic::TPC * wave + i) * 64 + lane] = raw;
     }
   };
   // value of the rows' envs from the shares in s_vpart
@@ -511,7 +535,7 @@ next_row_block:
         ws.wait_oldest();
       }
     };
-    if constexpr (CENTRAL || DEEP) {
+    if constexpr (CENTRAL || DEEP || (!BF16 && H == 128)) {
       // The compiler moves every address and constant that does not change over the steps in front of
       // the loop; with the registers of these variants on top they no longer fit and would be reloaded from
       // scratch memory step by step.  Hiding the lane's indices from it once per step keeps that
@@ -553,9 +577,8 @@ next_row_block:
         if (gp == 0) o = v[q];
         return o;
       };
-      // pairs this lane contributes to the stored row: bf16 tiles hold 4 consecutive pairs per lane,
-      // f32 tiles hold pair mm on both half-waves, of which half-wave mm % 2 stores it
-      constexpr int NP = BF16 ? 4 * KT1 : 2 * KT1;
+      // pairs this lane contributes to the stored row: four consecutive ones of every layer-1 tile
+      constexpr int NP = 4 * KT1;
       float2 pr[NP];
       // PHASE_ACT takes the pair from the caller's row instead (zero beyond the row and for idle rows)
       auto pair_in = [&](int gp) -> float2 {
@@ -572,30 +595,12 @@ next_row_block:
         for (int i = 0; i < NP; ++i) pr[i] = make_float2(0.0f, 0.0f);
 #pragma unroll
         for (int i = 0; i < KT1 * Net::PT; ++i) x[q][i] = Op{};
-      } else if constexpr (BF16) {
-#pragma unroll
-        for (int i = 0; i < NP; ++i) pr[i] = pair_in(8 * (i / 4) + 4 * h + i % 4);
       } else {
 #pragma unroll
-        for (int mm = 0; mm < KT1 * 4; ++mm) {
-          const float2 o = pair_in(mm);
-          if ((mm & 1) == 0) pr[mm / 2] = o;
-          if ((mm & 1) == 1 && h == 1) pr[mm / 2] = o;
-          x[q][mm] = h ? o.y : o.x;
-          if (2 * mm == NZ) x[q][mm] = h ? 0.0f : 1.0f;  // input NZ carries the bias
-        }
-        if constexpr (CENTRAL) {
-          // the same operands, four to a tile, are the agent's block of column (env) `col` of the joint observation
-          if (valid[q]) {
-            u32x4* dst = s_j + (ag[q] * KT1) * 64 + h * 32 + wave * EPW + base[q] / N;
-#pragma unroll
-            for (int kt = 0; kt < KT1; ++kt)
-              dst[kt * 64] = __builtin_bit_cast(u32x4, f32x4{x[q][4 * kt], x[q][4 * kt + 1], x[q][4 * kt + 2], x[q][4 * kt + 3]});
-          }
-        }
+        for (int i = 0; i < NP; ++i) pr[i] = pair_in(8 * (i / 4) + 4 * h + i % 4);
       }
       // feature index of pr[i]
-      auto feat = [&](int i) { return BF16 ? 16 * (i / 4) + 8 * h + 2 * (i % 4) : 4 * i + 2 * h; };
+      auto feat = [&](int i) { return 16 * (i / 4) + 8 * h + 2 * (i % 4); };
       if (STORES_OBS && build) {
 #pragma unroll
         for (int ps = 0; ps < PASSES; ++ps) {
@@ -603,7 +608,7 @@ next_row_block:
           const int lr = row[q] - r0;
           if (valid[q] && lr >= 0 && lr < SR) {
             float* dst = stg + lr * D;
-            if constexpr (BF16 && D % 4 == 0) {
+            if constexpr (D % 4 == 0) {
 #pragma unroll
               for (int i = 0; i < NP; i += 2)
                 if (feat(i) + 4 <= D)
@@ -630,24 +635,32 @@ next_row_block:
           wave_lds_sync();
         }
       }
-      if constexpr (BF16) {
 #pragma unroll
-        for (int kt = 0; kt < KT1; ++kt) {
-          f32x8 f;
+      for (int kt = 0; kt < KT1; ++kt) {
+        f32x8 f;
 #pragma unroll
-          for (int pi = 0; pi < 4; ++pi) {
-            f[2 * pi] = pr[4 * kt + pi].x;
-            f[2 * pi + 1] = pr[4 * kt + pi].y;
-          }
-          if (NZ / 16 == kt && (NZ % 16) / 8 == h) f[NZ % 8] = 1.0f;  // input NZ carries the bias
-          x[q][kt] = __builtin_convertvector(f, bf16x8);
+        for (int pi = 0; pi < 4; ++pi) {
+          f[2 * pi] = pr[4 * kt + pi].x;
+          f[2 * pi + 1] = pr[4 * kt + pi].y;
         }
+        if (NZ / 16 == kt && (NZ % 16) / 8 == h) f[NZ % 8] = 1.0f;  // input NZ carries the bias
+        if constexpr (BF16)
+          x[q][kt] = __builtin_convertvector(f, bf16x8);
+        else
+          x[q][kt] = tri_operand(f);
         if constexpr (CENTRAL) {
-          // the same operands are the agent's block of column (env) `col` of the joint observation
+          // the same operands (fp32: the values, four to a tile) are the agent's block of column (env) `col` of the
+          // joint observation
           if (valid[q]) {
-            u32x4* dst = s_j + (ag[q] * KT1) * 64 + h * 32 + wave * EPW + base[q] / N;
+            u32x4* dst = s_j + (ag[q] * JT) * 64 + h * 32 + wave * EPW + base[q] / N;
+            if constexpr (BF16) {
+              dst[kt * 64] = __builtin_bit_cast(u32x4, x[q][kt]);
+            } else {
 #pragma unroll
-            for (int kt = 0; kt < KT1; ++kt) dst[kt * 64] = __builtin_bit_cast(u32x4, x[q][kt]);
+              for (int i = 0; i < 2; ++i)
+                if (2 * kt + i < JT)
+                  dst[(2 * kt + i) * 64] = __builtin_bit_cast(u32x4, f32x4{f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]});
+            }
           }
         }
       }
@@ -670,20 +683,28 @@ next_row_block:
             ws.wait_oldest();
             if (t > 0) flush(t - 1, 0x1f);
           }
-          Net::layer1(&s_l1[net][0] + lane, x, h1);
           int sn = 0;  // stage within the network
           auto prefetch_target = [&](int& next, int& nbuf) {
             next = net * spn + sn + Stream::AHEAD;
             if (next >= 2 * spn) next -= 2 * spn;
             nbuf = (gs + Stream::AHEAD) % NBUF;
           };
+          if constexpr (L1S) {
+            int next, nbuf;
+            prefetch_target(next, nbuf);
+            Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });
+            ++gs;
+            ++sn;
+          } else {
+            Net::layer1(&s_l1[net][0] + lane, x, h1);
+          }
           f32x16 acc[NB];
           // hidden layers 2 .. layers-1: h1 <- tanh(W h1 + b), one 32-unit chunk per block
 #pragma unroll 1
           for (int layer = 2; layer < layers; ++layer) {
             Op hb[NB][Net::KT2 * Net::PT];
 #pragma unroll 1
-            for (int sc = 0; sc < Stream::STAGES_PER_NET; ++sc) {
+            for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
               if (sn != 0) ws.wait_oldest();
               int next, nbuf;
               prefetch_target(next, nbuf);
@@ -691,11 +712,7 @@ next_row_block:
 #pragma unroll
               for (int c = 0; c < CPS; ++c) {
                 const u32x4* tiles = ws.tiles(gs % NBUF, c);
-                auto tick = [&](int kt) {
-#pragma unroll
-                  for (int i = 0; i < Stream::PER_WAVE; ++i)
-                    if (i * (CPS * Net::KT2) / Stream::PER_WAVE == c * Net::KT2 + kt) ws.issue_part(next, nbuf, i);
-                };
+                auto tick = [&](int kt) { ws.spread(next, nbuf, c * Net::KT2 + kt, CPS * Net::KT2); };
                 if (c == 0 && sc == 0)
                   Net::template hidden_chunk<false>(tiles, h1, acc, hn[c], h, tick);
                 else
@@ -703,7 +720,7 @@ next_row_block:
               }
               // file the finished chunks (register indices are compile-time constants inside each branch)
 #pragma unroll
-              for (int k = 0; k < Stream::STAGES_PER_NET; ++k)
+              for (int k = 0; k < Stream::CHUNK_STAGES; ++k)
                 if (sc == k) {
 #pragma unroll
                   for (int c = 0; c < CPS; ++c) {
@@ -739,23 +756,19 @@ next_row_block:
             for (int q = 0; q < NB; ++q) out[q] = b;
           }
 #pragma unroll 1
-          for (int sc = 0; sc < Stream::STAGES_PER_NET; ++sc) {
+          for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
             if (sn != 0) ws.wait_oldest();
             int next, nbuf;
             prefetch_target(next, nbuf);
 #pragma unroll
             for (int c = 0; c < CPS; ++c) {
               const u32x4* tiles = ws.tiles(gs % NBUF, c);
-              auto tick = [&](int kt) {
-#pragma unroll
-                for (int i = 0; i < Stream::PER_WAVE; ++i)
-                  if (i * (CPS * Net::KT2) / Stream::PER_WAVE == c * Net::KT2 + kt) ws.issue_part(next, nbuf, i);
-              };
+              auto tick = [&](int kt) { ws.spread(next, nbuf, c * Net::KT2 + kt, CPS * Net::KT2); };
               if (c == 0 && sc == 0)
                 Net::template layer2_chunk<false, OUTS>(tiles, h1, acc, out, h, 16, tick);
               else
                 Net::template layer2_chunk<true, OUTS>(tiles, h1, acc, out, h, 16, tick);
-              if (c == CPS - 1 && sc == Stream::STAGES_PER_NET - 1)
+              if (c == CPS - 1 && sc == Stream::CHUNK_STAGES - 1)
                 Net::template layer2_drain<OUTS>(tiles, acc, out, h, 16);
             }
             ++gs;
@@ -821,7 +834,7 @@ next_row_block:
             for (int i = 0; i < RING; ++i) {
               const int kt = (sc - S2) * RING + i;
               if (kt < KT1C) {
-                Op b[Net::PT];
+                COp b[Critic::PT];
                 lds_operands(s_j[kt * 64 + lane], b);
                 mma_tile<BF16>(cring[i], b, cacc);
               }
@@ -837,11 +850,7 @@ next_row_block:
           if (next >= SPN) next -= SPN;
           const int nbuf = (gs + Stream::AHEAD) % NBUF;
           const u32x4* tiles = ws.tiles(gs % NBUF, 0);
-          auto tick = [&](int kt) {
-#pragma unroll
-            for (int i = 0; i < Stream::PER_WAVE; ++i)
-              if (i * Net::KT2 / Stream::PER_WAVE == kt) ws.issue_part(next, nbuf, i);
-          };
+          auto tick = [&](int kt) { ws.spread(next, nbuf, kt, Net::KT2); };
           if (sc == 0)
             Net::template layer2_chunk<false, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
           else
@@ -871,7 +880,17 @@ next_row_block:
             // that fits a single stage has none, so the order is made explicit here.
             if constexpr (Stream::STAGES_PER_NET == 1) __syncthreads();
           }
-          Net::layer1(&s_l1[net][0] + lane, x, h1);
+          auto stage_ahead = [&](int s) {  // AHEAD stages behind stage s of this network, cyclic over the step
+            const int next = net * Stream::STAGES_PER_NET + s + Stream::AHEAD;
+            return next >= Stream::STAGES_PER_STEP ? next - Stream::STAGES_PER_STEP : next;
+          };
+          if constexpr (L1S) {
+            const int next = stage_ahead(0), nbuf = (gs + Stream::AHEAD) % NBUF;
+            Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });
+            ++gs;
+          } else {
+            Net::layer1(&s_l1[net][0] + lane, x, h1);
+          }
           stamp(net == 0 ? CLK_P_L1 : CLK_V_L1);
           f32x16 acc[NB];
           const int nout = net == 0 ? 5 : 1;  // (a constant once the loop over the networks is unrolled)
@@ -881,24 +900,21 @@ next_row_block:
             for (int q = 0; q < NB; ++q) out[q] = b;
           }
   #pragma unroll 1
-          for (int sc = 0; sc < Stream::STAGES_PER_NET; ++sc) {
-            if (sc != 0) stage_wait();
-            int next = net * Stream::STAGES_PER_NET + sc + Stream::AHEAD;  // AHEAD stages ahead, cyclic over the step
-            if (next >= Stream::STAGES_PER_STEP) next -= Stream::STAGES_PER_STEP;
+          for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
+            if (L1S || sc != 0) stage_wait();
+            const int next = stage_ahead(sc + Stream::L1_STAGES);
             const int nbuf = (gs + Stream::AHEAD) % NBUF;
             {
               // the copies of the stage AHEAD stages later, spread over this stage's tile loops
               auto tick = [&](int c, int kt) {
-  #pragma unroll
-                for (int i = 0; i < Stream::PER_WAVE; ++i)
-                  if (i * (CPS * Net::KT2) / Stream::PER_WAVE == c * Net::KT2 + kt) ws.issue_part(next, nbuf, i);
+                ws.spread(next, nbuf, c * Net::KT2 + kt, CPS * Net::KT2);
                 if (kt == 0 && c == 0) stage_priority(sc, wave, WAVES);  // (1 % of the call at the benchmark's shape)
               };
               if (sc == 0)
                 Net::template layer2_chunks<false, CPS, OUTS>(ws.tiles(gs % NBUF, 0), h1, acc, out, h, nout, tick);
               else
                 Net::template layer2_chunks<true, CPS, OUTS>(ws.tiles(gs % NBUF, 0), h1, acc, out, h, nout, tick);
-              if (sc == Stream::STAGES_PER_NET - 1)
+              if (sc == Stream::CHUNK_STAGES - 1)
                 Net::template layer2_drain<OUTS>(ws.tiles(gs % NBUF, CPS - 1), acc, out, h, nout);
             }
             ++gs;
@@ -1099,18 +1115,16 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
   constexpr bool HAS_NETS = PHASE != PHASE_STEP;
   constexpr bool DEEP = PHASE == PHASE_DEEP || PHASE == PHASE_ACT_DEEP;
   constexpr bool ACT = PHASE == PHASE_ACT || PHASE == PHASE_ACT_DEEP;
-  constexpr int KT1 = (D + 1 + 7) / 8;  // + the constant-1 input that carries the bias
-  constexpr int NR = 4 * KT1;           // state registers per lane
+  constexpr int KTS = (D + 1 + 7) / 8;  // fp32 tiles of the state (the constant-1 input that carries the bias included)
+  constexpr int NR = 4 * KTS;           // state registers per lane
+  constexpr int KT1 = (D + 1 + 15) / 16;
   constexpr int NBUF = 2, CPS = 1;
-  // (the state sits in accumulator layout: MFMA j of a layer-1 tile multiplies inputs 8 kt + j and 8 kt + 4 + j,
-  // so the D + 1 inputs, the constant 1 included, reach MFMA min(4, inputs in the last tile) of the last tile)
-  constexpr int L1_REST = D + 1 - 8 * (KT1 - 1);
-  // (one wave per SIMD: the layer-1 outputs live in accumulation registers, 151 vector registers instead of 256)
-  typedef Mlp<H, false, 1, KT1, L1_REST < 4 ? L1_REST : 4, true> Net;
-  typedef WeightStream<Net, WAVES, NBUF, CPS> Stream;
+  typedef MlpTri<H, KT1, true> Net;     // (mlp_tri.h)
+  constexpr bool L1S = tri_streams_layer1(H);
+  typedef WeightStream<Net, WAVES, NBUF, CPS, L1S> Stream;
   static_assert(D <= 31 && K <= 8, "one MFMA chunk of state (plus the constant input), one tile of action");
 
-  __shared__ __attribute__((aligned(16))) u32x4 s_l1[2][HAS_NETS ? Net::L1_TILES * 64 : 1];
+  __shared__ __attribute__((aligned(16))) u32x4 s_l1[2][HAS_NETS && !L1S ? Net::L1_TILES * 64 : 1];
   __shared__ __attribute__((aligned(16))) u32x4 s_w[HAS_NETS ? NBUF * Stream::BUF_SLOTS : 1];
   __shared__ __attribute__((aligned(16))) float s_b3[2][32];
 
@@ -1118,20 +1132,20 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: lives in a scalar register
   const int n = lane & 31, h = lane >> 5;
   const int layers = DEEP ? a.layers : 2;
-  const NetLayout ly = net_layout(D, H, false, layers);
+  const NetLayout ly = net_layout(D, H, FMT_TRI, layers, true);
   Stream ws;
   ws.lds = s_w;
   ws.packed = a.packed;
   ws.net_bytes = ly.bytes;
-  ws.chunks_off = ly.chunks;
+  ws.chunks_off = L1S ? ly.w1 : ly.chunks;
   ws.chunk_bytes = ly.chunk_bytes;
   ws.wave = wave;
   ws.lane = lane;
-  if constexpr (DEEP) ws.stages_per_net = (layers - 1) * Stream::STAGES_PER_NET;
+  if constexpr (DEEP) ws.stages_per_net = (layers - 1) * Stream::CHUNK_STAGES + Stream::L1_STAGES;
   if constexpr (HAS_NETS) {
 #pragma unroll
     for (int s = 0; s < Stream::AHEAD; ++s) ws.issue(s, s);
-    load_resident(&s_l1[0][0], &s_b3[0][0], a.packed, ly, Net::L1_TILES);
+    load_resident(&s_l1[0][0], &s_b3[0][0], a.packed, ly, L1S ? 0 : Net::L1_TILES);
   }
   __syncthreads();
 
@@ -1141,10 +1155,10 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
   const bool valid = env0 + n < blk_end;
   const uint32_t env = (uint32_t)(valid ? env0 + n : blk0);
   // the dynamics tiles are read once per step by every wave: they stay in registers
-  u32x4 dynA[KT1], dynB;
+  u32x4 dynA[KTS], dynB;
 #pragma unroll
-  for (int kt = 0; kt < KT1; ++kt) dynA[kt] = ((const u32x4*)a.dyn)[kt * 64 + lane];
-  dynB = ((const u32x4*)a.dyn)[KT1 * 64 + lane];
+  for (int kt = 0; kt < KTS; ++kt) dynA[kt] = ((const u32x4*)a.dyn)[kt * 64 + lane];
+  dynB = ((const u32x4*)a.dyn)[KTS * 64 + lane];
   int gs = 0;
 
   float s[1][NR];
@@ -1174,44 +1188,53 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
     if constexpr (!HAS_NETS) {
       out_p[0] = out_v[0] = zero16();
     } else {
-      float h1[1][Net::KT2 * Net::PT];
-      float x[1][NR];  // the state with the constant 1 at input D
+      Tri h1[1][Net::KT2];
+      Tri x[1][KT1];  // the state with the constant 1 at input D
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int u = 8 * (r >> 2) + 4 * h + (r & 3);
-        x[0][r] = u == D ? 1.0f : s[0][r];
+      for (int kt = 0; kt < KT1; ++kt) {
+        f32x8 f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int r = 8 * kt + e, u = 8 * (r >> 2) + 4 * h + (r & 3);
+          f[e] = u == D ? 1.0f : r < NR ? s[0][r < NR ? r : 0] : 0.0f;
+        }
+        x[0][kt] = tri_operand(f);
       }
 #pragma unroll
       for (int net = 0; net < 2; ++net) {
         f32x16(&out)[1] = net == 0 ? out_p : out_v;
-        Net::layer1(&s_l1[net][0] + lane, x, h1);
         f32x16 acc[1];
         const int spn = ws.stages_per_net;
         int sn = 0;  // stage within the network
+        if constexpr (L1S) {
+          ws.wait_oldest();
+          const int next = net * spn + Stream::AHEAD, nbuf = (gs + Stream::AHEAD) % NBUF;
+          Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });
+          ++gs;
+          ++sn;
+        } else {
+          Net::layer1(&s_l1[net][0] + lane, x, h1);
+        }
         if constexpr (DEEP) {
           // hidden layers 2 .. layers-1 (see the particle kernel): h1 <- tanh(W h1 + b)
 #pragma unroll 1
           for (int layer = 2; layer < layers; ++layer) {
-            float hb[1][Net::KT2 * Net::PT];
+            Tri hb[1][Net::KT2];
 #pragma unroll 1
-            for (int sc = 0; sc < Stream::STAGES_PER_NET; ++sc) {
+            for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
               ws.wait_oldest();
               int next = net * spn + sn + Stream::AHEAD;
               if (next >= 2 * spn) next -= 2 * spn;
               const int nbuf = (gs + Stream::AHEAD) % NBUF;
-              float hn[1][Net::PC];
+              Tri hn[1][Net::PC];
               const u32x4* tiles = ws.tiles(gs % NBUF, 0);
-              auto tick = [&](int kt) {
-#pragma unroll
-                for (int i = 0; i < Stream::PER_WAVE; ++i)
-                  if (i * Net::KT2 / Stream::PER_WAVE == kt) ws.issue_part(next, nbuf, i);
-              };
+              auto tick = [&](int kt) { ws.spread(next, nbuf, kt, Net::KT2); };
               if (sc == 0)
                 Net::template hidden_chunk<false>(tiles, h1, acc, hn, h, tick);
               else
                 Net::template hidden_chunk<true>(tiles, h1, acc, hn, h, tick);
 #pragma unroll
-              for (int k = 1; k < Stream::STAGES_PER_NET; ++k)
+              for (int k = 1; k < Stream::CHUNK_STAGES; ++k)
                 if (sc == k) {
 #pragma unroll
                   for (int j = 0; j < Net::PC; ++j) hb[0][(k - 1) * Net::PC + j] = hn[0][j];
@@ -1220,13 +1243,13 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
               ++sn;
             }
             {
-              float hl[1][Net::PC];
+              Tri hl[1][Net::PC];
               Net::hidden_drain(acc, hl);
 #pragma unroll
               for (int j = 0; j < Net::PC; ++j) hb[0][(Net::NUC - 1) * Net::PC + j] = hl[0][j];
             }
 #pragma unroll
-            for (int j = 0; j < Net::KT2 * Net::PT; ++j) h1[0][j] = hb[0][j];
+            for (int j = 0; j < Net::KT2; ++j) h1[0][j] = hb[0][j];
           }
         }
         // Output layer: the policy's 2 K outputs on the MFMA (all 16 bits), the one value on the VALU (`net` is a
@@ -1235,7 +1258,7 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
         constexpr uint32_t OUTS_P = 0xFFFFu, OUTS_V = 0x1u;
         out[0] = net == 0 ? Net::template out_init<OUTS_P>(s_b3[net], h) : Net::template out_init<OUTS_V>(s_b3[net], h);
 #pragma unroll 1
-        for (int sc = 0; sc < Stream::STAGES_PER_NET; ++sc) {
+        for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
           ws.wait_oldest();
           int next = net * spn + sn + Stream::AHEAD;  // AHEAD stages ahead, cyclic over the step
           if (next >= 2 * spn) next -= 2 * spn;
@@ -1245,12 +1268,8 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
           for (int c = 0; c < CPS; ++c) {
             const u32x4* tiles = ws.tiles(gs % NBUF, c);
             // the copies of the stage AHEAD stages later, spread over this stage's tile loops
-            auto tick = [&](int kt) {
-#pragma unroll
-              for (int i = 0; i < Stream::PER_WAVE; ++i)
-                if (i * (CPS * Net::KT2) / Stream::PER_WAVE == c * Net::KT2 + kt) ws.issue_part(next, nbuf, i);
-            };
-            const bool first = c == 0 && sc == 0, last = c == CPS - 1 && sc == Stream::STAGES_PER_NET - 1;
+            auto tick = [&](int kt) { ws.spread(next, nbuf, c * Net::KT2 + kt, CPS * Net::KT2); };
+            const bool first = c == 0 && sc == 0, last = c == CPS - 1 && sc == Stream::CHUNK_STAGES - 1;
             if (net == 0) {
               if (first)
                 Net::template layer2_chunk<false, OUTS_P>(tiles, h1, acc, out, h, 16, tick);
@@ -1319,10 +1338,10 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-    for (int kt = 0; kt < KT1; ++kt) mma_tile<false>(dynA[kt], &s[0][4 * kt], acc);
+    for (int kt = 0; kt < KTS; ++kt) mma_tile<false>(dynA[kt], &s[0][4 * kt], acc);
     mma_tile<false>(dynB, act, acc);
 #pragma unroll
-    for (int b = 0; b < KT1; ++b) {
+    for (int b = 0; b < KTS; ++b) {
       float e[4];  // reset draw (stream 1, new episode) or step noise (stream 2, step counter)
       normals4(a.seed_lo, a.seed_hi, env, 0, done ? episode + 1 : g32, done ? 1u : 2u,
                (uint32_t)(2 * b + h), e);
