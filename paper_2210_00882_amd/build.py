@@ -21,13 +21,13 @@ FLAGS = [
 ] + os.environ.get("MSRL_EXTRA_FLAGS", "").split()
 
 
-# Flags for single translation units (by file-name prefix).  The lin-Gauss kernel's tile loops (32 tiles of a
-# 256-unit fp32 layer with the output layer's arithmetic between them) are longer than the compiler's limit for
-# loops it unrolls on request; not unrolled, the register arrays they index end up in scratch memory.
-PER_FILE = {
-    "inst_l17_": ["-mllvm", "-pragma-unroll-threshold=200000"],
-    "inst_family_h256_f32_": ["-mllvm", "-pragma-unroll-threshold=200000"],
-}
+# Flags for single translation units (by file-name prefix): the fp32 kernels of 256 units, one wave per SIMD.  Their tile
+# loops (96 MFMAs per chunk with the activation work between them) are longer than the compiler's limit for loops it
+# unrolls on request; not unrolled, the register arrays they index end up in scratch memory.  MFMA results stay in
+# vector registers: the accumulation registers hold the layer-1 outputs, and a result there would be copied over
+# before its tanh.
+_F32_256 = ["-mllvm", "-pragma-unroll-threshold=200000", "-mllvm", "-amdgpu-mfma-vgpr-form"]
+PER_FILE = {"inst_l17_": _F32_256, "inst_family_h256_f32_": _F32_256}
 
 
 def _compile(src: str) -> str:

@@ -45,13 +45,34 @@ __device__ __forceinline__ Words4 draw(uint32_t seed_lo, uint32_t seed_hi, uint3
 // u in [0,1) from the top 24 bits: exact in fp32.
 __device__ __forceinline__ float u01(uint32_t w) { return (float)(w >> 8) * 5.9604644775390625e-08f; }
 
+// sin and cos of 2 pi u for u in [0, 1): the quarter turn nearest to u is taken off exactly, what is left is at most
+// an eighth of a turn either way and goes through the Taylor series in quarter turns (first term left out below 2e-9).
+// A third of sincosf's instructions, and without the rounding of the product 2 pi u.
+__device__ __forceinline__ void sincos_turns(float u, float& s, float& c) {
+  const float t = 4.0f * u, q = __builtin_rintf(t), r = t - q, r2 = r * r;
+  float ps = 1.6044118e-4f, pc = -2.5202042e-5f;
+  ps = __builtin_fmaf(ps, r2, -4.6817541e-3f);
+  pc = __builtin_fmaf(pc, r2, 9.1926027e-4f);
+  ps = __builtin_fmaf(ps, r2, 7.9692626e-2f);
+  pc = __builtin_fmaf(pc, r2, -2.0863481e-2f);
+  ps = __builtin_fmaf(ps, r2, -6.4596410e-1f);
+  pc = __builtin_fmaf(pc, r2, 2.5366951e-1f);
+  ps = __builtin_fmaf(ps, r2, 1.5707963f) * r;
+  pc = __builtin_fmaf(pc, r2, -1.2337006f);
+  pc = __builtin_fmaf(pc, r2, 1.0f);
+  const uint32_t k = (uint32_t)(int)q;  // quarter turns, 0 .. 4
+  const float ss = k & 1u ? pc : ps, cc = k & 1u ? ps : pc;
+  s = __uint_as_float(__float_as_uint(ss) ^ ((k & 2u) << 30));
+  c = __uint_as_float(__float_as_uint(cc) ^ (((k + 1u) & 2u) << 30));
+}
+
 // Box-Muller pair; the radius uses a uniform in (0,1].
 __device__ __forceinline__ void normal_pair(uint32_t w0, uint32_t w1, float& e0, float& e1) {
   const float u1 = (float)((w0 >> 8) + 1u) * 5.9604644775390625e-08f;
   const float u2 = (float)(w1 >> 8) * 5.9604644775390625e-08f;
   const float r = sqrtf(-2.0f * logf(u1));
   float s, c;
-  sincosf(6.283185307179586f * u2, &s, &c);
+  sincos_turns(u2, s, c);
   e0 = r * c;
   e1 = r * s;
 }

@@ -388,10 +388,7 @@ void ppo_rows_kernel(RowsArgs a) {
   const int64_t groups = (a.n_tiles + WAVES - 1) / WAVES;
   // copies of stage `next` into buffer `nbuf`, spread over the tile loops of the current stage
   auto spread = [&](int next, int nbuf, int c, int kt) {
-    if constexpr (RESIDENT) return;
-#pragma unroll
-    for (int i = 0; i < Stream::PER_WAVE; ++i)
-      if (i * (CPS * KT2) / Stream::PER_WAVE == c * KT2 + kt) ws.issue_part(next, nbuf, i);
+    if constexpr (!RESIDENT) ws.spread(next, nbuf, c * KT2 + kt, CPS * KT2);
   };
   // ONCHIP: chunk c of dL/dz1 (operand form) times the observation operands -> W1's gradient tiles
   auto dz1_product = [&](int c, const Op (&dz)[2]) {

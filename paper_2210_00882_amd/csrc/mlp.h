@@ -11,6 +11,8 @@
 // at zero.  Layer 3 is accumulated as the layer-2 chunks complete, so h2 is
 // consumed as soon as it is produced.
 #pragma once
+#include <utility>
+
 #include "dev_common.h"
 #include "packed.h"
 
@@ -688,42 +690,49 @@ struct WeightStream {
   int wave, lane;
   int stages_per_net = STAGES_PER_NET;  // more with more than two hidden layers (set by the kernel)
 
-  // copy number i (0 .. PER_WAVE-1) of this wave for stage s (0 .. 2 stages_per_net - 1) into buffer `buf`
-  __device__ __forceinline__ void issue_part(int s, int buf, int i) const {
+  // copy number I (0 .. PER_WAVE-1) of this wave for stage s (0 .. 2 stages_per_net - 1) into buffer `buf`
+  template <int I>
+  __device__ __forceinline__ void issue_part(int s, int buf) const {
     const int net = s >= stages_per_net ? 1 : 0;
     const uint8_t* src = packed + (size_t)net * net_bytes + chunks_off +
                          (size_t)(s - net * stages_per_net) * CPS * chunk_bytes;
     typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-    const uint32_t base = (uint32_t)(uintptr_t)(lds_u32x4*)(lds + buf * BUF_SLOTS);
-    // a wave with no tile left copies tile 0 once more (same bytes to the same place), so that
-    // every wave issues exactly PER_WAVE copies per stage
-    int t = wave + i * WAVES;
-    t = t < STAGE_TILES ? t : 0;
-    // Scalar base address + per-lane byte offset: no vector registers are tied up by addresses
-    // (`wave` must be wave-uniform; the kernels read it with readfirstlane).  The address is copied
-    // by a scalar instruction inside the asm block: that is the one wait state the hardware wants
-    // between the write of M0 and the copy instruction, and it makes the address register
-    // scalar-written whatever produced the operand (a memory instruction may not read a scalar
-    // register a vector instruction wrote less than 5 cycles earlier, and the compiler cannot
-    // see into the block to keep that distance).
-    const uint64_t sbase = (uint64_t)(uintptr_t)(src + (size_t)t * 1024);
-    const uint32_t m0 = base + (uint32_t)t * 1024u;
-    uint64_t tmp;
-    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
-                 : "=&s"(tmp)
-                 : "v"(lane * 16), "s"(sbase), "s"(m0)
-                 : "memory", "m0");
-  }
-  __device__ __forceinline__ void issue(int s, int buf) const {
-#pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i) issue_part(s, buf, i);
+    // Tile wave + I WAVES of the stage: a scalar base address and the lane's byte offset, the same for all copies of a
+    // stage (`wave` must be wave-uniform; the kernels read it with readfirstlane).  What tells the copies apart is added
+    // by scalar instructions inside the block, into VCC, so that no registers are tied up by addresses.  They are also
+    // the wait state the hardware wants between the write of M0 and the copy instruction, and they make the
+    // address scalar-written whatever produced the operands (a memory instruction may not read a scalar register a
+    // vector instruction wrote less than 5 cycles earlier, and the compiler cannot see into the block to keep that
+    // distance).
+    const uint64_t sbase = (uint64_t)(uintptr_t)(src + (size_t)wave * 1024);
+    const uint32_t m0 = (uint32_t)(uintptr_t)(lds_u32x4*)(lds + buf * BUF_SLOTS) + (uint32_t)wave * 1024u;
+    constexpr uint32_t AHEAD_BYTES = (uint32_t)I * WAVES * 1024u;
+    if constexpr ((I + 1) * WAVES <= STAGE_TILES) {
+      asm volatile("s_add_u32 m0, %3, %4\n\ts_add_u32 vcc_lo, %1, %4\n\ts_addc_u32 vcc_hi, %2, 0\n\t"
+                   "global_load_lds_dwordx4 %0, vcc"
+                   :
+                   : "v"(lane * 16), "s"((uint32_t)sbase), "s"((uint32_t)(sbase >> 32)), "s"(m0), "n"(AHEAD_BYTES)
+                   : "memory", "vcc", "scc");
+    } else {
+      // a wave with no tile left copies its first one again (same bytes to the same place), so that every wave issues
+      // exactly PER_WAVE copies per stage
+      const uint32_t ahead = wave + I * WAVES < STAGE_TILES ? AHEAD_BYTES : 0u;
+      asm volatile("s_add_u32 m0, %3, %4\n\ts_add_u32 vcc_lo, %1, %4\n\ts_addc_u32 vcc_hi, %2, 0\n\t"
+                   "global_load_lds_dwordx4 %0, vcc"
+                   :
+                   : "v"(lane * 16), "s"((uint32_t)sbase), "s"((uint32_t)(sbase >> 32)), "s"(m0), "s"(ahead)
+                   : "memory", "vcc", "scc");
+    }
   }
   // this wave's copies for stage s dealt out over `n` calls, i = 0 .. n-1
-  __device__ __forceinline__ void spread(int s, int buf, int i, int n) const {
-#pragma unroll
-    for (int k = 0; k < PER_WAVE; ++k)
-      if (k * n / PER_WAVE == i) issue_part(s, buf, k);
+  template <int... I>
+  __device__ __forceinline__ void spread(int s, int buf, int i, int n, std::integer_sequence<int, I...>) const {
+    ((I * n / PER_WAVE == i ? issue_part<I>(s, buf) : void()), ...);
   }
+  __device__ __forceinline__ void spread(int s, int buf, int i, int n) const {
+    spread(s, buf, i, n, std::make_integer_sequence<int, PER_WAVE>{});
+  }
+  __device__ __forceinline__ void issue(int s, int buf) const { spread(s, buf, 0, 1); }
   // wait until the oldest stage in flight has landed, then for every wave of the workgroup
   __device__ __forceinline__ void wait_oldest() const {
     static_assert((NBUF - 2) * PER_WAVE <= 15, "the hand-written wait encodes the count in 4 bits");

@@ -30,18 +30,30 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {  // round to n
   const f32x2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-__device__ __forceinline__ float bf16_low(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16_high(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+// v minus the low / high half of a bf16 pair: one dot product with (-1, 0) or (0, -1), exact here like the
+// subtraction it stands for (the difference of a value and its rounding has no more bits than the value).  The
+// constants are hidden from the compiler, which would turn the first into the inline constant -1.0, a value of
+// the high half.
+__device__ __forceinline__ float minus_low(float v, uint32_t w) {
+  uint32_t c = 0x0000BF80u;
+  asm("" : "+s"(c));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, c), v, false);
+}
+__device__ __forceinline__ float minus_high(float v, uint32_t w) {
+  uint32_t c = 0xBF800000u;
+  asm("" : "+s"(c));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, c), v, false);
+}
 
 // the pieces of values a, b as pair `i` of an operand
 __device__ __forceinline__ void tri_pair(float a, float b, Tri& o, int i) {
   const uint32_t p0 = bf16_pair(a, b);
-  a -= bf16_low(p0);
-  b -= bf16_high(p0);
+  a = minus_low(a, p0);
+  b = minus_high(b, p0);
   const uint32_t p1 = bf16_pair(a, b);
   o.p[0][i] = p0;
   o.p[1][i] = p1;
-  o.p[2][i] = bf16_pair(a - bf16_low(p1), b - bf16_high(p1));
+  o.p[2][i] = bf16_pair(minus_low(a, p1), minus_high(b, p1));
 }
 __device__ __forceinline__ Tri tri_operand(const f32x8& f) {
   Tri o;
@@ -53,6 +65,8 @@ __device__ __forceinline__ f32x16 mma_piece(const u32x4& w, const u32x4& x, f32x
   return mma(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c);
 }
 // piece of the weight / of the operand in MFMA m of a k tile; the pieces of the weight are used up in the order 2, 1, 0
+// (two accumulators in turn, one for the three smallest products, were measured: 2 to 6 % slower, the chain of
+// dependent MFMAs is no bound)
 constexpr int TRI_W[6] = {2, 1, 1, 0, 0, 0}, TRI_X[6] = {0, 0, 1, 0, 1, 2};
 
 // What is done with the accumulators of the chunk before beside the MFMAs of a chunk: nothing, tanh and split
@@ -108,14 +122,14 @@ struct TriWork {
         }
         break;
       case 5:
-        t[r] -= bf16_low(op[o].p[0][w]);
-        t[r + 1] -= bf16_high(op[o].p[0][w]);
+        t[r] = minus_low(t[r], op[o].p[0][w]);
+        t[r + 1] = minus_high(t[r + 1], op[o].p[0][w]);
         break;
       case 6:
         op[o].p[1][w] = bf16_pair(t[r], t[r + 1]);
         break;
       default:
-        op[o].p[2][w] = bf16_pair(t[r] - bf16_low(op[o].p[1][w]), t[r + 1] - bf16_high(op[o].p[1][w]));
+        op[o].p[2][w] = bf16_pair(minus_low(t[r], op[o].p[1][w]), minus_high(t[r + 1], op[o].p[1][w]));
     }
   }
 };
@@ -153,11 +167,13 @@ struct MlpTri {
 
   // One chunk of NT k tiles: acc <- W b, the steps of wk dealt out over the gaps behind the MFMAs.  Tile `k` of the
   // stream of TOTAL tiles that this chunk belongs to lies (k / NT) STRIDE + 3 (k % NT) KiB behind `tiles`; `first` is
-  // the chunk's first, whose pieces are in the ring with the G - 1 tiles behind it.  LEAD steps come before the
-  // first MFMA (they cover the latency of the first LDS reads).  tick(kt) once per tile.
-  template <int NT, int TOTAL, int STRIDE, int MODE, int NOUT, class Tick>
+  // the chunk's first, whose pieces are in the ring with the G - 1 tiles behind it.  `lead` steps come before the
+  // first MFMA (they cover the latency of the first LDS reads).  extra[]: the 1 KiB tiles at `xt`, fetched during the
+  // last two k tiles for what follows the chunk.  tick(kt) once per tile.
+  template <int NT, int TOTAL, int STRIDE, int MODE, int NOUT, int NX, class Tick>
   __device__ static __forceinline__ void chunk(const u32x4* tiles, int first, u32x4 (&ring)[G][3], const Tri* b,
-                                               f32x16& acc, TriWork<MODE>& wk, f32x16& out, int lead, Tick&& tick) {
+                                               f32x16& acc, TriWork<MODE>& wk, f32x16& out, int lead, const u32x4* xt,
+                                               u32x4 (&extra)[NX], Tick&& tick) {
     constexpr int GAPS = 6 * NT, STEPS = TriWork<MODE>::STEPS;
     acc = zero16();
 #pragma unroll
@@ -172,6 +188,9 @@ struct MlpTri {
         acc = mma_piece(ring[k % G][w], b[kt].p[TRI_X[m]], acc);
         if ((m == 5 || TRI_W[m + 1 < 6 ? m + 1 : 5] != w) && k + G < TOTAL)
           ring[k % G][w] = tiles[(((k + G) / NT) * STRIDE + 3 * ((k + G) % NT) + w) * 64];
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+          if (xt && g == GAPS - 12 + 2 * i) extra[i] = xt[i * 64];
         if (m == 5) tick(kt);
         __builtin_amdgcn_sched_barrier(0);
         const int left = STEPS - lead;
@@ -207,15 +226,16 @@ struct MlpTri {
     u32x4 ring[G][3];
     fill_ring<KT1, NUC * KT1, 3 * KT1>(tiles, ring);
     f32x16 acc, none;
+    u32x4 no_tiles[1];
     TriWork<TRI_NONE> w0;
-    chunk<KT1, NUC * KT1, 3 * KT1, TRI_NONE, 0>(tiles, 0, ring, x[0], acc, w0, none, 0, tick);
+    chunk<KT1, NUC * KT1, 3 * KT1, TRI_NONE, 0>(tiles, 0, ring, x[0], acc, w0, none, 0, nullptr, no_tiles, tick);
     TriWork<TRI_SPLIT> wk;
 #pragma unroll
     for (int uc = 1; uc <= NUC; ++uc) {
       wk.prev = acc;
       if (uc < NUC)
-        chunk<KT1, NUC * KT1, 3 * KT1, TRI_SPLIT, 0>(tiles, uc * KT1, ring, x[0], acc, wk, none, 0,
-                                                     [&](int kt) { tick(uc * KT1 + kt); });
+        chunk<KT1, NUC * KT1, 3 * KT1, TRI_SPLIT, 0>(tiles, uc * KT1, ring, x[0], acc, wk, none, 0, nullptr,
+                                                     no_tiles, [&](int kt) { tick(uc * KT1 + kt); });
       else
         drain<TRI_SPLIT, 0>(wk, none);
       h1[0][2 * uc - 2] = wk.op[0];
@@ -232,15 +252,15 @@ struct MlpTri {
     if constexpr (on_mfma<OUTS>()) return bias_init(lds_bias, h);
     else return zero16();
   }
-  // output layer of a Gaussian policy: tile 0 of a k tile has the leading pieces of the weights in output rows 0 .. 15
-  // and the middle ones in rows 16 .. 31, tile 1 the last pieces in rows 0 .. 15; out_finish adds the two row ranges
-  __device__ static __forceinline__ void gauss_out(const u32x4* tiles, int at, const Tri (&h2)[2], f32x16& out) {
+  // output layer of a Gaussian policy (w: its tiles): tile 0 of a k tile has the leading pieces of the weights in
+  // output rows 0 .. 15 and the middle ones in rows 16 .. 31, tile 1 the last pieces in rows 0 .. 15; out_finish adds
+  // the two row ranges
+  __device__ static __forceinline__ void gauss_out(const u32x4* w, const Tri (&h2)[2], f32x16& out) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const u32x4 hm = tiles[(at + 2 * i) * 64], lo = tiles[(at + 2 * i + 1) * 64];
-      out = mma_piece(lo, h2[i].p[0], out);
+      out = mma_piece(w[2 * i + 1], h2[i].p[0], out);
 #pragma unroll
-      for (int m = 0; m < 3; ++m) out = mma_piece(hm, h2[i].p[m], out);
+      for (int m = 0; m < 3; ++m) out = mma_piece(w[2 * i], h2[i].p[m], out);
     }
   }
   // behind the last chunk: the outputs in accumulator layout (register r of lane (n, h): output 8 (r / 4) + 4 h + r % 4)
@@ -275,6 +295,7 @@ struct MlpTri {
 #pragma unroll
     for (int c = 0; c < CPS; ++c) {
       auto tk = [&](int kt) { tick(c, kt); };
+      const u32x4* xt = tiles + (c * CHUNK_TILES + BIAS) * 64;  // bias tile, then the output layer of the chunk before
       if (PIPE0 || c > 0) {
         TriWork<MODE> wk;
         wk.prev = acc[0];
@@ -282,17 +303,20 @@ struct MlpTri {
         // (two pairs' chains ahead of the first MFMA of a stage: they cover the latency of its first LDS reads)
         const int lead = c == 0 ? 2 * TriWork<MODE>::PER_PAIR : 0;
         constexpr int ALL = __builtin_popcount(OUTS);
+        u32x4 extra[MODE == TRI_GAUSS ? 5 : 1];
         if (ALL > 1 && nout == 1)
-          chunk<KT2, CPS * KT2, CHUNK_TILES, MODE, 1>(tiles, c * KT2, ring, h1[0], acc[0], wk, out[0], lead, tk);
+          chunk<KT2, CPS * KT2, CHUNK_TILES, MODE, 1>(tiles, c * KT2, ring, h1[0], acc[0], wk, out[0], lead, xt, extra, tk);
         else
           chunk<KT2, CPS * KT2, CHUNK_TILES, MODE, (MODE == TRI_OUT ? ALL : 0)>(tiles, c * KT2, ring, h1[0], acc[0], wk,
-                                                                                out[0], lead, tk);
-        if constexpr (MODE == TRI_GAUSS) gauss_out(tiles, c * CHUNK_TILES + L3_PREV, wk.op, out[0]);
+                                                                                out[0], lead, xt, extra, tk);
+        acc[0] = mma_piece(extra[0], one, acc[0]);
+        if constexpr (MODE == TRI_GAUSS) gauss_out(extra + 1, wk.op, out[0]);
       } else {
         TriWork<TRI_NONE> w0;
-        chunk<KT2, CPS * KT2, CHUNK_TILES, TRI_NONE, 0>(tiles, c * KT2, ring, h1[0], acc[0], w0, none, 0, tk);
+        u32x4 extra[1];
+        chunk<KT2, CPS * KT2, CHUNK_TILES, TRI_NONE, 0>(tiles, c * KT2, ring, h1[0], acc[0], w0, none, 0, xt, extra, tk);
+        acc[0] = mma_piece(extra[0], one, acc[0]);
       }
-      acc[0] = mma_piece(tiles[(c * CHUNK_TILES + BIAS) * 64], one, acc[0]);
     }
   }
   template <bool PIPE, uint32_t OUTS, class Tick>
@@ -307,13 +331,19 @@ struct MlpTri {
     constexpr int MODE = on_mfma<OUTS>() ? TRI_GAUSS : TRI_OUT;
     TriWork<MODE> wk;
     wk.prev = acc[0];
-    if constexpr (MODE == TRI_OUT) wk.w3h = out_weights(tiles, L3_OWN, h);
+    u32x4 w3[L3T];
+    if constexpr (MODE == TRI_OUT) {
+      wk.w3h = out_weights(tiles, L3_OWN, h);
+    } else {
+#pragma unroll
+      for (int i = 0; i < L3T; ++i) w3[i] = tiles[(L3_OWN + i) * 64];
+    }
     constexpr int ALL = __builtin_popcount(OUTS);
     if (ALL > 1 && nout == 1)
       drain<MODE, 1>(wk, out[0]);
     else
       drain<MODE, (MODE == TRI_OUT ? ALL : 0)>(wk, out[0]);
-    if constexpr (MODE == TRI_GAUSS) gauss_out(tiles, L3_OWN, wk.op, out[0]);
+    if constexpr (MODE == TRI_GAUSS) gauss_out(w3, wk.op, out[0]);
   }
 
   // A chunk block of a hidden layer that is not the last one: acc <- pre-activations of the chunk; if PIPE, those of
@@ -324,17 +354,19 @@ struct MlpTri {
     u32x4 ring[G][3];
     fill_ring<KT2, KT2, CHUNK_TILES>(tiles, ring);
     f32x16 none;
+    u32x4 bias[1];
+    const u32x4* xt = tiles + BIAS * 64;
     if constexpr (PIPE) {
       TriWork<TRI_SPLIT> wk;
       wk.prev = acc[0];
-      chunk<KT2, KT2, CHUNK_TILES, TRI_SPLIT, 0>(tiles, 0, ring, hin[0], acc[0], wk, none, 2 * wk.PER_PAIR, tick);
+      chunk<KT2, KT2, CHUNK_TILES, TRI_SPLIT, 0>(tiles, 0, ring, hin[0], acc[0], wk, none, 2 * wk.PER_PAIR, xt, bias, tick);
       hprev[0][0] = wk.op[0];
       hprev[0][1] = wk.op[1];
     } else {
       TriWork<TRI_NONE> w0;
-      chunk<KT2, KT2, CHUNK_TILES, TRI_NONE, 0>(tiles, 0, ring, hin[0], acc[0], w0, none, 0, tick);
+      chunk<KT2, KT2, CHUNK_TILES, TRI_NONE, 0>(tiles, 0, ring, hin[0], acc[0], w0, none, 0, xt, bias, tick);
     }
-    acc[0] = mma_piece(tiles[BIAS * 64], ones(h), acc[0]);
+    acc[0] = mma_piece(bias[0], ones(h), acc[0]);
   }
   __device__ static __forceinline__ void hidden_drain(const f32x16 (&acc)[1], Op (&hlast)[1][PC]) {
     TriWork<TRI_SPLIT> wk;

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   const bool writer = role == 0;
   const bool obs_writer = !SPLIT || role == 1;
   const bool rew_writer = !SPLIT || role == 1;
-  const int n = lane & 31, h = lane >> 5;
+  int n = lane & 31, h = lane >> 5;
   const int layers = DEEP ? a.layers : 2;
   const NetLayout ly = net_layout(NZ, H, BF16 ? FMT_BF16 : FMT_TRI, layers);
   Stream ws;
@@ -539,9 +539,9 @@ next_row_block:
       // The compiler moves every address and constant that does not change over the steps in front of
       // the loop; with the registers of these variants on top they no longer fit and would be reloaded from
       // scratch memory step by step.  Hiding the lane's indices from it once per step keeps that
-      // arithmetic (a few dozen integer operations) inside the step.  (n, h and the wave's
-      // scalars stay where they are.)
+      // arithmetic (a few dozen integer operations) inside the step.
       asm volatile("" : "+v"(ag[0]), "+v"(base[0]), "+v"(row[0]), "+v"(env[0]), "+v"(lane));
+      if constexpr (BF16) asm volatile("" : "+v"(n), "+v"(h), "+v"(tau[0]), "+v"(episode[0]), "+v"(g32[0]));
     }
     if constexpr (!HAS_NETS) {  // (no stage barriers in these variants)
       __syncthreads();
@@ -1173,7 +1173,11 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
   int tau = (int)(g64 % a.ep);
   uint32_t episode = (uint32_t)(g64 / a.ep);
 
+  uint32_t seed_lo = a.seed_lo, seed_hi = a.seed_hi;
   for (int t = 0; t <= a.T; ++t) {
+    // (hidden from the compiler once per step, so that the generator's twenty round keys are not moved in front of the
+    // loop, where they would not fit the scalar registers)
+    asm volatile("" : "+s"(seed_lo), "+s"(seed_hi));
     const size_t o = (size_t)t * a.M + env;
     // PHASE_STEP writes one observation, that of the last state, to row block 0
     if (valid && !ACT && (PHASE != PHASE_STEP || t == a.T)) {
@@ -1297,7 +1301,7 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
 
     // action dims 4h + c: mean in register c, log-std in register 4 + c
     float eps[4], act[4], lp = 0.0f, cost = 0.0f;
-    normals4(a.seed_lo, a.seed_hi, env, 0, g32, 0, (uint32_t)h, eps);
+    normals4(seed_lo, seed_hi, env, 0, g32, 0, (uint32_t)h, eps);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int d = 4 * h + c;
@@ -1342,9 +1346,11 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
     mma_tile<false>(dynB, act, acc);
 #pragma unroll
     for (int b = 0; b < KTS; ++b) {
-      float e[4];  // reset draw (stream 1, new episode) or step noise (stream 2, step counter)
-      normals4(a.seed_lo, a.seed_hi, env, 0, done ? episode + 1 : g32, done ? 1u : 2u,
-               (uint32_t)(2 * b + h), e);
+      // reset draw (stream 1, new episode) or step noise (stream 2, step counter); a pair that reaches no unit is not made
+      float e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      const Words4 w = draw(seed_lo, seed_hi, env, 0, done ? episode + 1 : g32, done ? 1u : 2u, (uint32_t)(2 * b + h));
+      if (8 * b < D) normal_pair(w.w[0], w.w[1], e[0], e[1]);
+      if (8 * b + 2 < D) normal_pair(w.w[2], w.w[3], e[2], e[3]);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int u = 8 * b + 4 * h + c;
