@@ -1,5 +1,6 @@
 // Re-orders network parameters (and the linear-Gaussian dynamics matrices) into
 // MFMA operand tiles; see packed.h for the layout.
+#include "dev_common.h"
 #include "packed.h"
 
 #include <hip/hip_runtime.h>
@@ -38,8 +39,9 @@ __device__ __forceinline__ float load_src(const void* src, int bf16, int idx) {
   return ((const float*)src)[idx];
 }
 
-// bf16 pieces of a value (mlp_tri.h)
+// bf16 pieces of a value (mlp_tri.h); an infinite weight takes part as the largest bf16 value
 __device__ __forceinline__ void three_pieces(float v, uint32_t (&p)[3]) {
+  v = bf16_range(v);
   for (int k = 0; k < 3; ++k) {
     const __bf16 b = (__bf16)v;  // round to nearest even
     p[k] = __builtin_bit_cast(uint16_t, b);

@@ -278,6 +278,35 @@ def test_act_on_caller_chosen_rows_against_the_oracle(which):
         np.testing.assert_array_equal(g1, g)      # acting does not advance the state
 
 
+@pytest.mark.parametrize("hidden,gauss", [(64, False), (128, False), (256, False), (256, True)])
+def test_infinite_and_nan_observations_in_fp32(hidden, gauss):
+    # an infinite input saturates the first layer's units, as in fp32 arithmetic; a NaN spreads within its row only
+    import torch
+    cfg = synth.lingauss("inf", 8, 17, 6, 256, 4, 1000) if gauss else synth.particle("inf", 4, 3, hidden, 4, 25, synth.F32)
+    _, _, params, dyn = oracle_setup(cfg)
+    rng = np.random.default_rng(3)
+    rows = rng.uniform(-1, 1, (cfg.M, cfg.obs_dim)).astype(np.float32)
+    rows[0, 0], rows[1, 3], rows[2, 1], rows[3, 2] = np.inf, -np.inf, np.nan, 3.4e38
+    with GpuRollout(cfg, params.astype(np.float32), 11, dyn=dyn) as gpu:
+        B = gpu.B
+        a = torch.empty((cfg.M, cfg.act_dim) if gauss else (cfg.M,), dtype=torch.float32 if gauss else torch.int32, device="cuda")
+        lp, v = torch.empty(cfg.M, device="cuda"), torch.empty(cfg.M, device="cuda")
+        B.msrl_act(gpu.state, gpu.params, torch.from_numpy(rows).cuda(), a, lp, v)
+        torch.cuda.synchronize()
+        v = v.cpu().numpy()
+    if not gauss and cfg.num_agents > 1:
+        rows[:, -2 * (cfg.num_agents - 1):] = 0.0     # the silent slots are not read
+    at = params.size - sum(i * o + o for i, o in ((cfg.obs_dim, cfg.hidden), (cfg.hidden, cfg.hidden), (cfg.hidden, 1)))
+    x = rows.astype(np.float64)
+    for k, (i, o) in enumerate(((cfg.obs_dim, cfg.hidden), (cfg.hidden, cfg.hidden), (cfg.hidden, 1))):
+        x = x @ params[at:at + i * o].reshape(i, o) + params[at + i * o:at + i * o + o]
+        at += i * o + o
+        x = np.tanh(x) if k < 2 else x
+    assert np.isnan(v[2]) and np.isnan(x[2])
+    keep = np.arange(cfg.M) != 2
+    assert_close(v[keep], x[keep, 0], TOL_F32, "values")
+
+
 @pytest.mark.parametrize("which", sorted(ACT_CASES))
 def test_observe_against_the_oracle(which):
     """msrl_observe == the oracle's observation of the state msrl_state_get returns, at the initial
