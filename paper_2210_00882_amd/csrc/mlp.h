@@ -670,7 +670,11 @@ __device__ __forceinline__ void stage_priority(int stage, int wave, int waves) {
 // the outstanding count, which makes the wait longer, never shorter.
 // L1S: the layer-1 tiles lie in front of the chunk blocks in the space of one more and come first as a stage of
 // their own.
-template <class Net, int WAVES, int NBUF, int CPS, bool L1S = false>
+// ADDR_IN_VCC: where the copies' addresses are formed.  In VCC they take no scalar registers from the kernel (the fp32
+// kernels spilled up to 132 of them), but no lane mask can live across a copy.  The particle env's bf16 kernels, short of
+// vector registers, are better off with a register pair per copy: the deep one of 256 units spills 51 vector registers
+// instead of 81, 8191 envs x 10 agents with six hidden layers 9.6 instead of 9.85 ms.
+template <class Net, int WAVES, int NBUF, int CPS, bool L1S = false, bool ADDR_IN_VCC = true>
 struct WeightStream {
   // a stage = CPS consecutive chunk blocks of one network
   static_assert(Net::NUC % CPS == 0, "stages must not straddle networks");
@@ -704,6 +708,18 @@ struct WeightStream {
     // address scalar-written whatever produced the operands (a memory instruction may not read a scalar register a
     // vector instruction wrote less than 5 cycles earlier, and the compiler cannot see into the block to keep that
     // distance).
+    if constexpr (!ADDR_IN_VCC) {
+      int t = wave + I * WAVES;
+      t = t < STAGE_TILES ? t : 0;  // (no tile left: tile 0 once more, see below)
+      const uint64_t from = (uint64_t)(uintptr_t)(src + (size_t)t * 1024);
+      const uint32_t to = (uint32_t)(uintptr_t)(lds_u32x4*)(lds + buf * BUF_SLOTS) + (uint32_t)t * 1024u;
+      uint64_t tmp;
+      asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                   : "=&s"(tmp)
+                   : "v"(lane * 16), "s"(from), "s"(to)
+                   : "memory", "m0");
+      return;
+    }
     const uint64_t sbase = (uint64_t)(uintptr_t)(src + (size_t)wave * 1024);
     const uint32_t m0 = (uint32_t)(uintptr_t)(lds_u32x4*)(lds + buf * BUF_SLOTS) + (uint32_t)wave * 1024u;
     constexpr uint32_t AHEAD_BYTES = (uint32_t)I * WAVES * 1024u;

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   // LDS window: the stage in use and the one being copied; PHASE_SPLIT: all stages of a step
   constexpr int NBUF = SPLIT ? 2 * Net::NUC / CPS : 2;
   static_assert(!SPLIT || !L1S, "two waves per row block: layer 1 is resident");
-  typedef WeightStream<Net, WAVES, NBUF, CPS, L1S> Stream;
+  typedef WeightStream<Net, WAVES, NBUF, CPS, L1S, !BF16> Stream;
   typedef typename Net::Op Op;
   typedef typename Critic::Op COp;
   static_assert(EPW >= 1, "a wave must hold at least one env");
@@ -541,7 +541,8 @@ next_row_block:
       // scratch memory step by step.  Hiding the lane's indices from it once per step keeps that
       // arithmetic (a few dozen integer operations) inside the step.
       asm volatile("" : "+v"(ag[0]), "+v"(base[0]), "+v"(row[0]), "+v"(env[0]), "+v"(lane));
-      if constexpr (BF16) asm volatile("" : "+v"(n), "+v"(h), "+v"(tau[0]), "+v"(episode[0]), "+v"(g32[0]));
+      // (the deep kernel of 256 units spills 82 registers instead of 51 with these too)
+      if constexpr (BF16 && CENTRAL) asm volatile("" : "+v"(n), "+v"(h), "+v"(tau[0]), "+v"(episode[0]), "+v"(g32[0]));
     }
     if constexpr (!HAS_NETS) {  // (no stage barriers in these variants)
       __syncthreads();
