@@ -275,10 +275,12 @@ int msrl_rollout_gae(msrl_state* st, const void* params, int32_t T,
  *     consecutive msrl_rollout_gae calls do.  (An initial state can come from msrl_state_get of a
  *     state made at set-up time, or from the caller's own draws.)
  *   - The re-ordered parameter image, which msrl_rollout_init would allocate, lives in a static
- *     device array of the library of MSRL_STATIC_SCRATCH_BYTES per GPU (held until the process
- *     ends).  A configuration whose image is larger (e.g. 256-unit networks with more than three
- *     hidden layers) is refused with MSRL_EUNSUPPORTED, as is MSRL_ENV_LINGAUSS (its dynamics
- *     matrices are HOST pointers and would need a device copy).
+ *     device array of the library (1.25 MiB per GPU, held until the process ends).  A configuration
+ *     whose image, counted with the weights in the networks' own type, is larger than
+ *     MSRL_STATIC_SCRATCH_BYTES (e.g. 256-unit bf16 networks with more than three hidden layers) is
+ *     refused with MSRL_EUNSUPPORTED, as is MSRL_ENV_LINGAUSS (its dynamics matrices are HOST
+ *     pointers and would need a device copy).  (fp32 networks are kept in a form up to an eighth larger
+ *     than that count, which the array has room for.)
  *   - The first call on a device looks the array's address up (hipGetSymbolAddress); make that
  *     call outside a graph capture.
  *   - Every call on a GPU uses that GPU's one array: two such calls that overlap in time on one

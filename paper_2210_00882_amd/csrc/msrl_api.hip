@@ -560,7 +560,11 @@ int configure_state(msrl_state* st, const char* who, const msrl_env_cfg* env, co
 // msrl_rollout_gae_static keeps the packed parameter image (the buffer msrl_rollout_init would
 // allocate) in this array.  Every GPU holds its own copy at its own address; in host code the name
 // below is only a handle for hipGetSymbolAddress, never a device address.
-static __device__ __align__(256) uint8_t scratch[MSRL_STATIC_SCRATCH_BYTES];
+// What a configuration may take is counted in the networks' own type (own_type_bytes), so that it does not depend on the
+// form the kernels read; the largest image within that limit, fp32 networks of 128 units and six hidden layers, takes
+// 1,132,544 bytes in three bf16 pieces.
+constexpr size_t STATIC_ARRAY_BYTES = (size_t)MSRL_STATIC_SCRATCH_BYTES / 4 * 5;
+static __device__ __align__(256) uint8_t scratch[STATIC_ARRAY_BYTES];
 
 namespace {
 
@@ -584,6 +588,14 @@ int scratch_of_current_device(uint8_t** out) {
   }
   *out = g_scratch_ptr[dev];
   return MSRL_OK;
+}
+
+// bytes of a state's packed image if every tile held weights of the networks' own type
+size_t own_type_bytes(const msrl_state& st, size_t packed_bytes) {
+  if (image_format(st.env, st.pol) != FMT_TRI) return packed_bytes;
+  const size_t nets = st.central ? 1 : 2;  // (a centralised critic is in its own type)
+  return packed_bytes - nets * st.layout.bytes +
+         nets * net_layout(st.in_used, st.pol.hidden, FMT_F32, layers_of(st.pol)).bytes;
 }
 
 // p[0 .. n) <- 0 in 16-byte pieces (a kernel rather than a memset node: the call may be captured into a graph)
@@ -734,10 +746,11 @@ int msrl_rollout_gae_static(const msrl_env_cfg* env, const msrl_policy_cfg* poli
   size_t packed_bytes = 0;
   int rc = configure_state(&st, "msrl_rollout_gae_static", env, policy, seed, &packed_bytes);
   if (rc != MSRL_OK) return rc;
-  if (packed_bytes > (size_t)MSRL_STATIC_SCRATCH_BYTES)
+  const size_t counted = own_type_bytes(st, packed_bytes);
+  if (counted > (size_t)MSRL_STATIC_SCRATCH_BYTES || packed_bytes > STATIC_ARRAY_BYTES)
     return fail(MSRL_EUNSUPPORTED, "msrl_rollout_gae_static: the packed parameters of this configuration take %zu "
                                    "bytes, the static scratch array holds %zu; use msrl_rollout_init + msrl_rollout_gae",
-                packed_bytes, (size_t)MSRL_STATIC_SCRATCH_BYTES);
+                counted, (size_t)MSRL_STATIC_SCRATCH_BYTES);
   rc = check_traj(&st, out, true);
   if (rc != MSRL_OK) return rc;
   uint8_t* sp = nullptr;

@@ -60,6 +60,24 @@ def test_static_entry_point_matches_the_allocating_one():
     run_both(synth.CONFIGS[5].with_(num_envs=70, episode_len=4), 41, 6, calls=1)
 
 
+def test_static_entry_point_at_its_limit():
+    # The limit (1 MiB) counts weights in the networks' own type, whatever form the kernels read: six fp32 hidden layers of
+    # 128 units fit with three agents (1,042,432 bytes) and not with four (1,050,624), four bf16 ones of 256 do not.
+    import torch
+    from paper_2210_00882_amd import binding as B
+    deep = synth.particle("deep", 70, 3, 128, 5, 4, synth.F32, 60).with_(hidden_layers=6)
+    run_both(deep, 45, 5, calls=1)
+    for cfg in (synth.particle("deep4", 8, 4, 128, 5, 4, synth.F32, 61).with_(hidden_layers=6),
+                synth.particle("wide4", 8, 3, 256, 5, 4, synth.BF16, 62).with_(hidden_layers=4)):
+        e, _keep = B.make_env_cfg(cfg)
+        es = torch.zeros((cfg.num_envs, cfg.env_state_size), dtype=torch.float32, device="cuda")
+        g = torch.zeros(cfg.num_envs, dtype=torch.int64, device="cuda")
+        with pytest.raises(B.MsrlError) as ei:
+            B.msrl_rollout_gae_static(e, B.make_policy_cfg(cfg), 1, es, g, B.upload_params(cfg, synth.make_params(cfg)), 3,
+                                      0.99, 0.95, B.alloc_traj(cfg, 3, logits=False, gae=True))
+        assert ei.value.code == B.MSRL_EUNSUPPORTED and "static scratch" in str(ei.value)
+
+
 def test_static_entry_point_refusals():
     import torch
     from paper_2210_00882_amd import binding as B
