@@ -728,7 +728,7 @@ struct WeightStream {
                    "global_load_lds_dwordx4 %0, vcc"
                    :
                    : "v"(lane * 16), "s"((uint32_t)sbase), "s"((uint32_t)(sbase >> 32)), "s"(m0), "n"(AHEAD_BYTES)
-                   : "memory", "vcc", "scc");
+                   : "memory", "m0", "vcc", "scc");
     } else {
       // a wave with no tile left copies its first one again (same bytes to the same place), so that every wave issues
       // exactly PER_WAVE copies per stage
@@ -737,7 +737,7 @@ struct WeightStream {
                    "global_load_lds_dwordx4 %0, vcc"
                    :
                    : "v"(lane * 16), "s"((uint32_t)sbase), "s"((uint32_t)(sbase >> 32)), "s"(m0), "s"(ahead)
-                   : "memory", "vcc", "scc");
+                   : "memory", "m0", "vcc", "scc");
     }
   }
   // this wave's copies for stage s dealt out over `n` calls, i = 0 .. n-1

@@ -83,3 +83,21 @@ def test_null_and_size_checks():
     assert lib.msrl_state_get(None, None, None) == B.MSRL_EINVAL
     assert lib.msrl_rollout_shape(None, None, None, None) == B.MSRL_EINVAL
     lib.msrl_rollout_destroy(None)
+
+
+def test_inline_asm_names_the_special_registers_it_writes():
+    # (an unnamed write lets the compiler keep a value of its own in the register across the block)
+    import glob
+    n = 0
+    for path in glob.glob(os.path.join(ROOT, "paper_2210_00882_amd", "csrc", "*.h*")):
+        for block in re.findall(r"\basm(?: volatile)?\s*\((.*?)\)\s*;", open(path).read(), re.S):
+            text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', block.split(":")[0]))
+            clobbers = re.findall(r'"(\w+)"', block.rsplit(":", 1)[1]) if ":" in block else []
+            for ins in text.split("\\n\\t"):
+                m = re.match(r"s_\w+ (m0|vcc)(?:_lo|_hi)?,", ins)
+                if m:
+                    n += 1
+                    assert m.group(1) in clobbers, (path, ins)
+                if re.match(r"s_addc?_u32", ins):
+                    assert "scc" in clobbers, (path, ins)
+    assert n >= 7
