@@ -13,12 +13,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// v within the range of bf16: infinities and what would round to one become the largest bf16 value, a NaN stays one
-__device__ __forceinline__ float bf16_range(float v) {
-  constexpr float MOST = 0x1.FEp127f;
-  return __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, -MOST), MOST);
-}
-
 // ---------------------------------------------------------------- Philox4x32-10
 // Counter (env, entity, time, stream<<16 | block), key = 64-bit seed
 // (Salmon et al., SC'11).  Streams: 0 action noise, 1 reset draws, 2 env noise.

@@ -1,7 +1,7 @@
 // Re-orders network parameters (and the linear-Gaussian dynamics matrices) into
 // MFMA operand tiles; see packed.h for the layout.
-#include "dev_common.h"
 #include "packed.h"
+#include "tri.h"
 
 #include <hip/hip_runtime.h>
 
@@ -37,16 +37,6 @@ __device__ __forceinline__ float load_src(const void* src, int bf16, int idx) {
     return __uint_as_float(b);
   }
   return ((const float*)src)[idx];
-}
-
-// bf16 pieces of a value (mlp_tri.h); an infinite weight takes part as the largest bf16 value
-__device__ __forceinline__ void three_pieces(float v, uint32_t (&p)[3]) {
-  v = bf16_range(v);
-  for (int k = 0; k < 3; ++k) {
-    const __bf16 b = (__bf16)v;  // round to nearest even
-    p[k] = __builtin_bit_cast(uint16_t, b);
-    v -= (float)b;
-  }
 }
 
 // the NE source values (times the job's scale) of lane (m, h) in k tile kt of chunk uc
@@ -88,21 +78,18 @@ __global__ void pack_kernel(PackJobs jobs) {
     uint4* dst = (uint4*)j.dst + ((size_t)uc * j.chunk_stride + j.slot_base + 3 * kt) * 64 + lane;
     if (kt == j.tri_k) {  // bias tile
       const int o = out_index(j.out_map, j.gauss_k, 32 * uc + m, j.n_out);
-      uint32_t p[3] = {0, 0, 0};
-      if (h == 0 && o >= 0) three_pieces(load_src(j.bias, j.src_bf16, o) * j.scale, p);
-      *dst = make_uint4(p[0] | p[1] << 16, p[2], 0, 0);
+      const float b[1] = {h == 0 && o >= 0 ? load_src(j.bias, j.src_bf16, o) * j.scale : 0.0f};
+      uint32_t p[1][3];
+      weight_pieces(b, p);
+      *dst = make_uint4(p[0][0] | p[0][1] << 16, p[0][2], 0, 0);
       return;
     }
     float v[8];
     tile_values(j, uc, kt, m, h, v);
-    uint32_t w[3][4];
-    for (int q = 0; q < 4; ++q) {
-      uint32_t a[3], b[3];
-      three_pieces(v[2 * q], a);
-      three_pieces(v[2 * q + 1], b);
-      for (int k = 0; k < 3; ++k) w[k][q] = a[k] | b[k] << 16;
-    }
-    for (int k = 0; k < 3; ++k) dst[k * 64] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+    uint32_t p[8][3];
+    weight_pieces(v, p);
+    for (int k = 0; k < 3; ++k)
+      dst[k * 64] = make_uint4(p[0][k] | p[1][k] << 16, p[2][k] | p[3][k] << 16, p[4][k] | p[5][k] << 16, p[6][k] | p[7][k] << 16);
     return;
   }
   if (j.kind == PACK_OUT_VALU || j.kind == PACK_OUT_GAUSS) {
@@ -116,13 +103,14 @@ __global__ void pack_kernel(PackJobs jobs) {
     } else {  // tile 2 i + q: k tile i, pieces 0 | 1 (q = 0) or 2 | - (q = 1) in output rows 0 .. 15 | 16 .. 31
       const int i = kt >> 1, q = kt & 1, piece = 2 * q + (m >> 4);
       const int o = out_index(j.out_map, j.gauss_k, m & 15, j.n_out);
-      uint32_t r[8];
+      float v[8];
       for (int e = 0; e < 8; ++e) {
-        uint32_t p[3] = {0, 0, 0};
         const int u = 32 * uc + 16 * i + 8 * (e >> 2) + 4 * h + (e & 3);
-        if (o >= 0) three_pieces(load_src(j.src, j.src_bf16, u * j.n_out + o), p);
-        r[e] = piece == 0 ? p[0] : piece == 1 ? p[1] : piece == 2 ? p[2] : 0u;
+        v[e] = o >= 0 ? load_src(j.src, j.src_bf16, u * j.n_out + o) : 0.0f;
       }
+      uint32_t p[8][3], r[8];
+      weight_pieces(v, p);
+      for (int e = 0; e < 8; ++e) r[e] = piece == 0 ? p[e][0] : piece == 1 ? p[e][1] : piece == 2 ? p[e][2] : 0u;
       w = make_uint4(r[0] | r[1] << 16, r[2] | r[3] << 16, r[4] | r[5] << 16, r[6] | r[7] << 16);
     }
     uint4* dst = (uint4*)j.dst + lane;

@@ -636,31 +636,33 @@ next_row_block:
           wave_lds_sync();
         }
       }
+      f32x8 f[KT1];
 #pragma unroll
       for (int kt = 0; kt < KT1; ++kt) {
-        f32x8 f;
 #pragma unroll
         for (int pi = 0; pi < 4; ++pi) {
-          f[2 * pi] = pr[4 * kt + pi].x;
-          f[2 * pi + 1] = pr[4 * kt + pi].y;
+          f[kt][2 * pi] = pr[4 * kt + pi].x;
+          f[kt][2 * pi + 1] = pr[4 * kt + pi].y;
         }
-        if (NZ / 16 == kt && (NZ % 16) / 8 == h) f[NZ % 8] = 1.0f;  // input NZ carries the bias
-        if constexpr (BF16)
-          x[q][kt] = __builtin_convertvector(f, bf16x8);
-        else
-          x[q][kt] = tri_operand(f);
-        if constexpr (CENTRAL) {
-          // the same operands (fp32: the values, four to a tile) are the agent's block of column (env) `col` of the
-          // joint observation
-          if (valid[q]) {
-            u32x4* dst = s_j + (ag[q] * JT) * 64 + h * 32 + wave * EPW + base[q] / N;
+        if (NZ / 16 == kt && (NZ % 16) / 8 == h) f[kt][NZ % 8] = 1.0f;  // input NZ carries the bias
+        if constexpr (BF16) x[q][kt] = __builtin_convertvector(f[kt], bf16x8);
+      }
+      if constexpr (!BF16 && HAS_NETS) tri_operands(f, x[q]);
+      if constexpr (CENTRAL) {
+        // the same operands (fp32: the values, four to a tile) are the agent's block of column (env) `col` of the
+        // joint observation
+        if (valid[q]) {
+          u32x4* dst = s_j + (ag[q] * JT) * 64 + h * 32 + wave * EPW + base[q] / N;
+#pragma unroll
+          for (int kt = 0; kt < KT1; ++kt) {
             if constexpr (BF16) {
               dst[kt * 64] = __builtin_bit_cast(u32x4, x[q][kt]);
             } else {
 #pragma unroll
               for (int i = 0; i < 2; ++i)
                 if (2 * kt + i < JT)
-                  dst[(2 * kt + i) * 64] = __builtin_bit_cast(u32x4, f32x4{f[4 * i], f[4 * i + 1], f[4 * i + 2], f[4 * i + 3]});
+                  dst[(2 * kt + i) * 64] =
+                      __builtin_bit_cast(u32x4, f32x4{f[kt][4 * i], f[kt][4 * i + 1], f[kt][4 * i + 2], f[kt][4 * i + 3]});
             }
           }
         }
@@ -1195,16 +1197,15 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
     } else {
       Tri h1[1][Net::KT2];
       Tri x[1][KT1];  // the state with the constant 1 at input D
+      f32x8 f[KT1];
 #pragma unroll
-      for (int kt = 0; kt < KT1; ++kt) {
-        f32x8 f;
+      for (int kt = 0; kt < KT1; ++kt)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int r = 8 * kt + e, u = 8 * (r >> 2) + 4 * h + (r & 3);
-          f[e] = u == D ? 1.0f : r < NR ? s[0][r < NR ? r : 0] : 0.0f;
+          f[kt][e] = u == D ? 1.0f : r < NR ? s[0][r < NR ? r : 0] : 0.0f;
         }
-        x[0][kt] = tri_operand(f);
-      }
+      tri_operands(f, x[0]);
 #pragma unroll
       for (int net = 0; net < 2; ++net) {
         f32x16(&out)[1] = net == 0 ? out_p : out_v;

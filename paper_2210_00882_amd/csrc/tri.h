@@ -7,8 +7,18 @@
 // product becomes six bf16 MFMAs into one fp32 accumulator,
 //     w x = w2 x0 + w1 x0 + w1 x1 + w0 x0 + w0 x1 + w0 x2.
 // The three products left out are below 2^-24 of w x (|x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|), i.e. below the rounding
-// of the fp32 product they stand in for, and 16 inputs enter the accumulator per rounding instead of two.  Six bf16
-// MFMAs of 16 inputs take 192 cycles where eight fp32 ones take 512.
+// of the fp32 product they stand in for, and 16 inputs enter the accumulator in six roundings instead of eight.  Six
+// bf16 MFMAs of 16 inputs take 192 cycles where eight fp32 ones take 512.
+//
+// Infinities and what overflows behave as in fp32 arithmetic (0 * inf and inf - inf are NaN, a NaN spreads in its row):
+//   - x2 meets w0 only and w2 meets x0 only, so an infinite value is kept as ("outermost") (+-1, 0, +-inf): each of its
+//     products has one infinite term, of the right sign, or NaN where the other factor is 0;
+//   - a rounded piece can have the other sign than its value, and where w x0 overflows, so can w1 x0, the other way
+//     round.  Pieces by truncation have the value's sign.  Weights of 8 and more and inputs of 65536 and more are
+//     truncated: then no sum of up to 48 products of the other sign reaches the range's end (|w1| <= 2^-6 below 8,
+//     |x1| <= 2^7 below 65536).  Still three pieces, still exact;
+//   - that holds for weights below 2^100.  A finite weight beyond takes part like an infinite one, with the eight
+//     leading bits of its value (no network that still computes anything has one).
 #pragma once
 #include "dev_common.h"
 
@@ -50,13 +60,81 @@ __device__ __forceinline__ void tri_pair(float a, float b, Tri& o, int i) {
   o.p[1][i] = p1;
   o.p[2][i] = bf16_pair(minus_low(a, p1), minus_high(b, p1));
 }
-// the network's input (observations): an infinity has no pieces (its remainder would be NaN) and takes part as the
-// largest bf16 value, which saturates the same units; a NaN stays one
-__device__ __forceinline__ Tri tri_operand(const f32x8& f) {
-  Tri o;
+// the pieces of one value: rounded, truncated, "outermost" (see above)
+__device__ __forceinline__ void rounded_pieces(float v, uint32_t (&p)[3]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) tri_pair(bf16_range(f[2 * i]), bf16_range(f[2 * i + 1]), o, i);
-  return o;
+  for (int k = 0; k < 3; ++k) {
+    const __bf16 b = (__bf16)v;
+    p[k] = __builtin_bit_cast(uint16_t, b);
+    v -= (float)b;
+  }
+}
+__device__ __forceinline__ void truncated_pieces(float v, uint32_t (&p)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    p[k] = __float_as_uint(v) >> 16;
+    v -= __uint_as_float(p[k] << 16);
+  }
+}
+__device__ __forceinline__ void outermost_pieces(float v, uint32_t (&p)[3]) {
+  p[0] = __float_as_uint(__builtin_copysignf(1.0f, v)) >> 16;
+  p[1] = 0;
+  p[2] = __float_as_uint(v) >> 16;
+}
+// m <- max(m, |a|, |b|)  (as fmaxf the compiler puts two more instructions in front, for signalling NaNs)
+__device__ __forceinline__ void max_magnitude(float& m, float a, float b) {
+  asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+}
+
+// pieces of N weights (a NaN compares false and is rounded: NaN pieces).  Called by whole waves.
+constexpr float TRI_LARGE_WEIGHT = 8.0f, TRI_OUTERMOST_WEIGHT = 0x1.0p100f;
+template <int N>
+__device__ __forceinline__ void weight_pieces(const float (&w)[N], uint32_t (&p)[N][3]) {
+  float most = 0.0f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    rounded_pieces(w[e], p[e]);
+    max_magnitude(most, w[e], w[e]);
+  }
+  if (__builtin_expect(!__any(most >= TRI_LARGE_WEIGHT), 1)) return;
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const float a = __builtin_fabsf(w[e]);
+    if (a >= TRI_OUTERMOST_WEIGHT) outermost_pieces(w[e], p[e]);
+    else if (a >= TRI_LARGE_WEIGHT) truncated_pieces(w[e], p[e]);
+  }
+}
+
+// A row's network input (observation, 8 values per operand): a value's pieces depend on that value only.  The ordinary
+// path runs first and is replaced where the wave holds a large value (one test per step and wave).
+constexpr float TRI_LARGE_INPUT = 65536.0f;
+template <int N>
+__device__ __forceinline__ void tri_operands(const f32x8 (&f)[N], Tri (&x)[N]) {
+  float most = 0.0f;
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      max_magnitude(most, f[k][2 * i], f[k][2 * i + 1]);
+      tri_pair(f[k][2 * i], f[k][2 * i + 1], x[k], i);
+    }
+  if (__builtin_expect(__any(most >= TRI_LARGE_INPUT), 0)) {
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float v = f[k][e], a = __builtin_fabsf(v);
+        uint32_t r[3], t[3], o[3];
+        rounded_pieces(v, r);
+        truncated_pieces(v, t);
+        outermost_pieces(v, o);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const uint32_t p = a == __builtin_inff() ? o[i] : a >= TRI_LARGE_INPUT ? t[i] : r[i];
+          x[k].p[i][e / 2] = e % 2 ? (x[k].p[i][e / 2] & 0xFFFFu) | p << 16 : p;
+        }
+      }
+  }
 }
 __device__ __forceinline__ f32x16 mma_piece(const u32x4& w, const u32x4& x, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);

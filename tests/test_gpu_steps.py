@@ -307,6 +307,95 @@ def test_infinite_and_nan_observations_in_fp32(hidden, gauss):
     assert_close(v[keep], x[keep, 0], TOL_F32, "values")
 
 
+def ieee_net(params, dims, at, x):
+    """A network in float64 with the products written out: infinities and NaN as IEEE arithmetic has them."""
+    with np.errstate(all="ignore"):
+        for k, (i, o) in enumerate(zip(dims[:-1], dims[1:])):
+            w = params[at:at + i * o].reshape(i, o)
+            y = np.empty((x.shape[0], o))
+            for r in range(x.shape[0]):
+                y[r] = (x[r][:, None] * w).sum(0)
+            x = y + params[at + i * o:at + i * o + o]
+            at += i * o + o
+            x = np.tanh(x) if k < len(dims) - 2 else x
+    return x, at
+
+
+@pytest.mark.parametrize("where", ["inputs", "hidden weight", "opposed hidden weights", "hidden bias", "first layer",
+                                   "output layer"])
+@pytest.mark.parametrize("hidden,gauss,layers", [(64, False, 2), (128, False, 2), (128, False, 3), (256, False, 2),
+                                                 (256, True, 2), (256, True, 3)])
+def test_infinities_behave_as_in_fp32_arithmetic(hidden, gauss, layers, where):
+    # products with an infinity, infinities that meet, and values whose products overflow: finite, infinite and NaN where
+    # IEEE arithmetic has them
+    import torch
+    cfg = synth.lingauss("inf", 64, 17, 6, 256, 4, 1000) if gauss else synth.particle("inf", 16, 4, hidden, 4, 25, synth.F32)
+    cfg = cfg.with_(hidden_layers=layers)
+    _, _, params, dyn = oracle_setup(cfg)
+    params = params.astype(np.float32)
+    D, H = cfg.obs_dim, cfg.hidden
+    dims = [D] + [H] * layers
+    value_at = params.size - sum(i * o + o for i, o in zip(dims, dims[1:] + [1]))
+    rng = np.random.default_rng(3)
+    rows = rng.uniform(-1, 1, (cfg.M, D)).astype(np.float32)
+    if not gauss:
+        rows[:, -2 * (cfg.num_agents - 1):] = 0.0     # the silent slots are not read
+    for at in (0, value_at):                          # both networks
+        w1, w2 = params[at:at + D * H].reshape(D, H), params[at + D * H + H:at + D * H + H + H * H].reshape(H, H)
+        if where == "inputs":
+            w1[2] = np.sign(w1[2]) * np.geomspace(1.0, 3e6, H)  # (times any huge input: saturated, never NaN)
+            w1[5, 7] = 0.0
+        elif where == "hidden weight":
+            w2[3, 4] = np.inf
+        elif where == "opposed hidden weights":       # NaN in the rows whose two units agree in sign
+            w2[3, 4], w2[5, 4] = np.inf, -np.inf
+        elif where == "hidden bias":
+            params[at + D * H + H + H * H + 1] = -np.inf
+        elif where == "first layer":
+            w1[0, 1], w1[1, 2], w1[3, 3] = -np.inf, 1e38, np.inf
+        else:
+            n = 1 if at else cfg.out_dim
+            end = params.size if at else value_at
+            w3 = params[end - n - H * n:end - n].reshape(H, n)
+            w3[7, 0] = np.inf
+            if not at:
+                w3[9, 3] = -np.inf
+    if where == "inputs":
+        rows[:, 2] = 0.0
+        rows[0, 0], rows[1, 3], rows[2, 1] = np.inf, -np.inf, np.nan
+        for k, v in enumerate((3.4e38, -3.3895e38, 1e38, -7e4, 65536.0, 1e20, np.inf, -np.inf)):
+            rows[3 + k, 2] = v
+        rows[11, 0], rows[11, 1] = np.inf, np.inf     # meet with both signs
+        rows[12, 5] = np.inf                          # times a weight of 0
+        rows[13, 0], rows[13, 2] = -np.inf, np.nan
+    if where == "first layer":
+        rows[0, 0], rows[1, 0], rows[2, 3] = 0.0, np.inf, -np.inf   # inf * 0, inf * inf
+    with GpuRollout(cfg, params, 11, dyn=dyn) as gpu:
+        B = gpu.B
+        a = torch.empty((cfg.M, cfg.act_dim) if gauss else (cfg.M,), dtype=torch.float32 if gauss else torch.int32, device="cuda")
+        lp, v = torch.empty(cfg.M, device="cuda"), torch.empty(cfg.M, device="cuda")
+        lg = torch.empty((cfg.M, cfg.out_dim), device="cuda")
+        B.msrl_act(gpu.state, gpu.params, torch.from_numpy(rows).cuda(), a, lp, v, lg)
+        torch.cuda.synchronize()
+        got = np.concatenate([lg.cpu().numpy(), v.cpu().numpy()[:, None]], 1).astype(np.float64)
+    x = rows.astype(np.float64)
+    if not gauss:
+        x[:, -2 * (cfg.num_agents - 1):] = 0.0
+    pol, at = ieee_net(params.astype(np.float64), dims + [cfg.out_dim], 0, x)
+    val, end = ieee_net(params.astype(np.float64), dims + [1], value_at, x)
+    assert at == value_at and end == params.size
+    want = np.concatenate([pol, val], 1)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want), err_msg="NaN")
+    inf = np.isinf(want)
+    np.testing.assert_array_equal(np.isinf(got), inf, err_msg="infinite")
+    np.testing.assert_array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)
+    assert fin.any()
+    if where in ("opposed hidden weights", "inputs"):
+        assert np.isnan(want).any(1).any() and not np.isnan(want).any(1).all()
+    assert_close(got[fin], want[fin], TOL_F32, "finite outputs")
+
+
 @pytest.mark.parametrize("which", sorted(ACT_CASES))
 def test_observe_against_the_oracle(which):
     """msrl_observe == the oracle's observation of the state msrl_state_get returns, at the initial
