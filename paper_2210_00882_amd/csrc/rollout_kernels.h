@@ -181,6 +181,13 @@ __global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArg
   constexpr int KT1C = N * JT;
   constexpr int JCOLS = WAVES * EPW;            // envs of a workgroup = columns of the critic's tile
   static_assert(!CENTRAL || JCOLS <= 32, "the envs of a workgroup are the columns of one tile");
+  // fp32 kernels that spill (eight waves of 128 units, the deep one of 256): the observation lives through the policy
+  // network as fp32 values, 8 registers per operand instead of the 12 of its pieces, and each network takes it apart
+  // for itself.  128 units: 0.95 (rollouts) and 0.90 (actor) of the time over 1 to 10 agents; 8 agents at 8192 envs: 8
+  // steps 350 -> 325 us, the actor 54 -> 35.5.  Deep 256: 0.99.  Kernels that don't spill lose 1 to 2.5 % and keep the
+  // pieces.
+  constexpr bool SPLIT_PER_NET = !BF16 && !SPLIT && !CENTRAL &&
+                                 ((H == 128 && WAVES == 8) || (H == 256 && PHASE == PHASE_DEEP));
   constexpr bool HAS_NETS = PHASE != PHASE_ENV && PHASE != PHASE_STEP;     // the variant runs the networks
   constexpr bool STORES_OBS = PHASE != PHASE_MLP && !ACT;                  // ... stores observation rows
   static_assert(NB == 1, "the observation staging below assumes one 32-row block per wave");
@@ -563,6 +570,7 @@ next_row_block:
     }
     // ---------------- observation rows: build, store (through the staging area), convert to MFMA operands
     Op x[NB][KT1 * Net::PT];
+    f32x8 f[KT1];
     {
       constexpr int q = 0;
       auto pair_value = [&](int gp) -> float2 {
@@ -636,7 +644,6 @@ next_row_block:
           wave_lds_sync();
         }
       }
-      f32x8 f[KT1];
 #pragma unroll
       for (int kt = 0; kt < KT1; ++kt) {
 #pragma unroll
@@ -647,7 +654,7 @@ next_row_block:
         if (NZ / 16 == kt && (NZ % 16) / 8 == h) f[kt][NZ % 8] = 1.0f;  // input NZ carries the bias
         if constexpr (BF16) x[q][kt] = __builtin_convertvector(f[kt], bf16x8);
       }
-      if constexpr (!BF16 && HAS_NETS) tri_operands(f, x[q]);
+      if constexpr (!BF16 && HAS_NETS && !SPLIT_PER_NET) tri_operands(f, x[q]);
       if constexpr (CENTRAL) {
         // the same operands (fp32: the values, four to a tile) are the agent's block of column (env) `col` of the
         // joint observation
@@ -686,6 +693,7 @@ next_row_block:
             ws.wait_oldest();
             if (t > 0) flush(t - 1, 0x1f);
           }
+          if constexpr (SPLIT_PER_NET) tri_operands_again(f, x[0]);
           int sn = 0;  // stage within the network
           auto prefetch_target = [&](int& next, int& nbuf) {
             next = net * spn + sn + Stream::AHEAD;
@@ -887,6 +895,7 @@ next_row_block:
             const int next = net * Stream::STAGES_PER_NET + s + Stream::AHEAD;
             return next >= Stream::STAGES_PER_STEP ? next - Stream::STAGES_PER_STEP : next;
           };
+          if constexpr (SPLIT_PER_NET) tri_operands_again(f, x[0]);
           if constexpr (L1S) {
             const int next = stage_ahead(0), nbuf = (gs + Stream::AHEAD) % NBUF;
             Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });

@@ -136,6 +136,13 @@ __device__ __forceinline__ void tri_operands(const f32x8 (&f)[N], Tri (&x)[N]) {
       }
   }
 }
+// the same anew for another network (the compiler would keep the first pieces instead)
+template <int N>
+__device__ __forceinline__ void tri_operands_again(f32x8 (&f)[N], Tri (&x)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) asm volatile("" : "+v"(f[k]));
+  tri_operands(f, x);
+}
 __device__ __forceinline__ f32x16 mma_piece(const u32x4& w, const u32x4& x, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
 }
