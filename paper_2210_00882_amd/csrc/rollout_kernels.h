@@ -138,8 +138,18 @@ enum : int { CLK_START = 0, CLK_OBS = 1, CLK_P_L1 = 2, CLK_P_STAGE = 3, CLK_V_L1
              CLK_WAIT = 20 };  // slot 20: cycles of the step spent in the waits at the stage barriers
 
 // ------------------------------------------------------------------ particle env
+// Most waves of a kernel that a SIMD may hold (the registers it asks for are raised to that).  One for the fp32 actor
+// fragment with a centralised critic of 64 units, which is written for one wave per SIMD: with 2 and 3 agents its
+// registers would let two in, and the two waves of a compute unit's second workgroup then go to SIMDs that have one while
+// others have none (8192 envs x 3: 13.4 -> 10.3 us; with 4 agents and more the registers see to it).
+constexpr int most_waves_per_simd(int H, bool bf16, int phase) {
+  return !bf16 && H == 64 && phase == PHASE_ACT_CENTRAL ? 1 : 8;
+}
+
 template <int N, int H, bool BF16, int NB, int WAVES, int PHASE = PHASE_ALL>
-__global__ __launch_bounds__(64 * WAVES) void particle_rollout_kernel(RolloutArgs a) {
+__global__ __launch_bounds__(64 * WAVES)
+__attribute__((amdgpu_waves_per_eu((WAVES + 3) / 4, most_waves_per_simd(H, BF16, PHASE))))
+void particle_rollout_kernel(RolloutArgs a) {
   constexpr int ROWS = 32 * NB;
   constexpr int EPW = ROWS / N;  // envs per wave
   constexpr int VR = EPW * N;    // rows in use
