@@ -114,6 +114,27 @@ def test_split_calls_reproduce_the_fused_rollout(which):
     assert (g_s == T).all()
 
 
+@pytest.mark.parametrize("N", range(1, 11))
+@pytest.mark.parametrize("H,dtype", [(64, synth.F32), (128, synth.BF16), (256, synth.BF16)])
+def test_env_step_rows_are_those_of_the_fused_rollout(N, H, dtype):
+    # (the env step's kernel deals a row's features out to the two lanes of the row in a way that depends on N)
+    import torch
+    cfg = synth.particle("rows", 37, N, H, 3, 2, dtype)
+    params = synth.make_params(cfg, bias_std=0.1)
+    with GpuRollout(cfg, params, 9) as fused, GpuRollout(cfg, params, 9) as steps:
+        want = fused.run(cfg.T)
+        obs = torch.full((cfg.M, cfg.obs_dim), -77.0, device="cuda")
+        rewards, dones = torch.empty(cfg.M, device="cuda"), torch.empty(cfg.M, dtype=torch.uint8, device="cuda")
+        steps.B.msrl_observe(steps.state, obs)
+        np.testing.assert_array_equal(obs.cpu().numpy(), want["obs"][0])
+        for t in range(cfg.T):
+            obs.fill_(-77.0)
+            steps.B.msrl_env_step(steps.state, fused.dev["actions"][t], rewards, dones, obs)
+            np.testing.assert_array_equal(obs.cpu().numpy(), want["obs"][t + 1], err_msg=f"t {t}")
+            np.testing.assert_array_equal(rewards.cpu().numpy(), want["rewards"][t])
+            np.testing.assert_array_equal(dones.cpu().numpy(), want["dones"][t])
+
+
 @pytest.mark.parametrize("which", ["n1_h64_f32", "n10_h256_bf16"])
 def test_actor_fragment_over_more_row_blocks_than_compute_units(which):
     # the plain actor kernel is persistent: with more row blocks than the device has compute units a workgroup
