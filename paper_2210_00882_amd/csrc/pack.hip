@@ -39,24 +39,32 @@ __device__ __forceinline__ float load_src(const void* src, int bf16, int idx) {
   return ((const float*)src)[idx];
 }
 
-// the NE source values (times the job's scale) of lane (m, h) in k tile kt of chunk uc
+// The NE source values (times the job's scale) of lane (m, h) in k tile kt of chunk uc.  The kernel is a wait for its loads:
+// every value has one, from somewhere in the buffer if it is not used, so that they are all in flight together.
 template <int NE>
 __device__ __forceinline__ void tile_values(const PackJob& j, int uc, int kt, int m, int h, float (&v)[NE]) {
   const int o = out_index(j.out_map, j.gauss_k, 32 * uc + m, j.n_out);
+  const void* from[NE];
+  int at[NE];
+  bool used[NE];
+#pragma unroll
   for (int e = 0; e < NE; ++e) {
     const int i = in_index(j, NE == 8, kt, h, e);
-    v[e] = 0.0f;
     bool weight = i < j.n_in;
     int li = i;
     if (j.in_block > 0) {
       weight = weight && i % j.in_block < j.in_block_used;
       li = (i / j.in_block) * j.in_block_stride + i % j.in_block;
     }
-    if (o >= 0 && weight)
-      v[e] = load_src(j.src, j.src_bf16, j.src_out_major ? o * j.n_in + li : li * j.n_out + o) * j.scale;
-    else if (o >= 0 && j.bias && i == j.bias_index)
-      v[e] = load_src(j.bias, j.src_bf16, o) * j.scale;
+    const bool bias = !weight && j.bias && i == j.bias_index;
+    used[e] = o >= 0 && (weight || bias);
+    from[e] = bias ? j.bias : j.src;
+    at[e] = !used[e] ? 0 : bias ? o : j.src_out_major ? o * j.n_in + li : li * j.n_out + o;
   }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) v[e] = load_src(from[e], j.src_bf16, at[e]);
+#pragma unroll
+  for (int e = 0; e < NE; ++e) v[e] = used[e] ? v[e] * j.scale : 0.0f;
 }
 
 // grid: (blocks over work items, job); one thread per (tile, lane) or per bias slot.
