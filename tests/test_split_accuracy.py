@@ -1,0 +1,123 @@
+"""Accuracy of the fp32 networks on the bf16 matrix pipe (three bf16 pieces per operand, six products per product).
+
+The error of a network's outputs against float64, 2-norm over 2-norm, has to stay below SPLIT_BOUND: twice what fp32
+networks with serially rounded sums show (up to 4.1e-7 over the shapes below, computed here), and below what is left
+of the accuracy when any one of the six products, or the last piece of a bias, is missing in any one layer (1.2e-6
+and more, computed here as well).
+"""
+import numpy as np
+import pytest
+
+from paper_2210_00882_amd import synth
+
+SPLIT_BOUND = 9e-7
+PRODUCTS = ((2, 0), (1, 0), (1, 1), (0, 0), (0, 1), (0, 2))   # (piece of the weight, piece of the input)
+SHAPES = [(64, 2, False), (64, 4, False), (128, 2, False), (128, 3, False), (256, 2, False), (256, 2, True), (256, 3, True)]
+
+
+def case(hidden, layers, gauss):
+    cfg = synth.lingauss("acc", 256, 17, 6, 256, 1, 1000) if gauss else synth.particle("acc", 64, 4, hidden, 1, 25, synth.F32)
+    cfg = cfg.with_(hidden_layers=layers)
+    params = synth.make_params(cfg, bias_std=0.15).astype(np.float32)
+    rng = np.random.default_rng(5)
+    # biases of the hidden layers behind the first: values whose last pieces are the largest (a layer has few biases, a
+    # last piece of the usual size would not show)
+    some = rng.uniform(0.2, 0.3, 40 * hidden).astype(np.float32)
+    some = some[np.argsort(-pieces(some)[2])[:hidden]]
+    at = 0
+    for out in (cfg.out_dim, 1):
+        dims = [cfg.obs_dim] + [hidden] * layers + [out]
+        for k, (i, o) in enumerate(zip(dims[:-1], dims[1:])):
+            if 0 < k < layers:
+                params[at + i * o:at + i * o + o] = rng.permutation(some) * rng.choice([-1.0, 1.0], o)
+            at += i * o + o
+    rows = rng.standard_normal((cfg.M, cfg.obs_dim)).astype(np.float32)
+    if not gauss:
+        rows[:, -2 * (cfg.num_agents - 1):] = 0.0     # the silent slots are not read
+    return cfg, params, rows
+
+
+def forward(cfg, params, rows, layer, value=False):
+    """layer(k, x, w, b) -> pre-activations of layer k; float64 or float32 as it returns them."""
+    nets = [[cfg.obs_dim] + [cfg.hidden] * cfg.hidden_layers + [o] for o in (cfg.out_dim, 1)]
+    at = sum(i * o + o for i, o in zip(nets[0][:-1], nets[0][1:])) if value else 0
+    x, dims = rows, nets[value]
+    for k, (i, o) in enumerate(zip(dims[:-1], dims[1:])):
+        x = layer(k, x, params[at:at + i * o].reshape(i, o), params[at + i * o:at + i * o + o])
+        at += i * o + o
+        if k < len(dims) - 2:
+            x = np.tanh(x.astype(np.float64)).astype(x.dtype)
+    return x
+
+
+def exact(cfg, params, rows, value=False):
+    return forward(cfg, params, rows.astype(np.float64), lambda k, x, w, b: x @ w.astype(np.float64) + b, value)
+
+
+def error(got, want):
+    return np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want)
+
+
+def pieces(v):
+    import torch
+    out = []
+    for _ in range(3):
+        p = torch.from_numpy(np.ascontiguousarray(v, dtype=np.float32)).to(torch.bfloat16).to(torch.float32).numpy()
+        out.append(p)
+        v = v - p
+    return out
+
+
+def split_layer(missing=None, at=None, bias_pieces=3):
+    def f(k, x, w, b):
+        px, pw, pb = pieces(x), pieces(w), pieces(b)
+        here = at is None or k == at
+        y = sum(px[j].astype(np.float64) @ pw[i] for i, j in PRODUCTS if not (here and (i, j) == missing))
+        return (y + sum(pb[:bias_pieces if here else 3])).astype(np.float32)
+    return f
+
+
+@pytest.mark.parametrize("hidden,layers,gauss", SHAPES)
+def test_the_bound_tells_a_missing_piece(hidden, layers, gauss):
+    cfg, params, rows = case(hidden, layers, gauss)
+    want = exact(cfg, params, rows)
+
+    def serial(k, x, w, b):
+        y = np.zeros((x.shape[0], w.shape[1]), np.float32)
+        for j in range(w.shape[0]):
+            y = y + x[:, j, None] * w[None, j]
+        return y + b
+
+    fp32 = error(forward(cfg, params, rows, serial), want)
+    assert 2.0 * fp32 < SPLIT_BOUND
+    assert error(forward(cfg, params, rows, split_layer()), want) < 0.25 * SPLIT_BOUND
+    for k in range(layers + 1):
+        for missing in PRODUCTS:
+            e = error(forward(cfg, params, rows, split_layer(missing, k)), want)
+            assert e > 1.25 * SPLIT_BOUND, (k, missing, e)
+    for k in range(1, layers):   # (layer 1's bias is one more input, the output layer's stays in fp32)
+        e = error(forward(cfg, params, rows, split_layer(at=k, bias_pieces=2)), want)
+        assert e > 1.25 * SPLIT_BOUND, ("bias", k, e)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hidden,layers,gauss", SHAPES)
+def test_fp32_networks_against_float64(hidden, layers, gauss):
+    import torch
+    from helpers import GpuRollout, oracle_setup
+    cfg, params, rows = case(hidden, layers, gauss)
+    dyn = oracle_setup(cfg)[3]
+    with GpuRollout(cfg, params, 11, dyn=dyn) as gpu:
+        B = gpu.B
+        a = torch.empty((cfg.M, cfg.act_dim) if gauss else (cfg.M,), dtype=torch.float32 if gauss else torch.int32, device="cuda")
+        lp, v = torch.empty(cfg.M, device="cuda"), torch.empty(cfg.M, device="cuda")
+        lg = torch.empty((cfg.M, cfg.out_dim), device="cuda")
+        B.msrl_act(gpu.state, gpu.params, torch.from_numpy(rows).cuda(), a, lp, v, lg)
+        tr = gpu.run(1, gae=False)      # the full rollout's kernel, on its own observations
+    for what, got, want in (("actor, outputs", lg.cpu().numpy(), exact(cfg, params, rows)),
+                            ("actor, values", v.cpu().numpy()[:, None], exact(cfg, params, rows, True)),
+                            ("rollout, outputs", tr["logits"][0], exact(cfg, params, tr["obs"][0])),
+                            ("rollout, values", tr["values"][0][:, None], exact(cfg, params, tr["obs"][0], True))):
+        e = error(got, want)
+        print(f"{what}: {e:.2e}")
+        assert e < SPLIT_BOUND, (what, e)
