@@ -47,7 +47,6 @@ __device__ __forceinline__ bf16x8 load_frag(const __bf16* p, int k0, int h, bf16
 }
 __device__ __forceinline__ bf16x8 load_frag(const float* p, int k0, int h, bf16x8*) {
   const f32x4 a = *(const f32x4*)(p + k0 + 8 * h), b = *(const f32x4*)(p + k0 + 8 * h + 4);
-  typedef float f32x8 __attribute__((ext_vector_type(8)));
   const f32x8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   return __builtin_convertvector(v, bf16x8);  // round to nearest even
 }
@@ -94,7 +93,6 @@ __device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
   *(f32x4*)(p + 4) = f32x4{v[4], v[5], v[6], v[7]};
 }
 __device__ __forceinline__ void store8(__bf16* p, const float (&v)[8]) {
-  typedef float f32x8 __attribute__((ext_vector_type(8)));
   const f32x8 f = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]};
   *(bf16x8*)p = __builtin_convertvector(f, bf16x8);
 }

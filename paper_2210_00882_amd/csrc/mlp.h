@@ -18,8 +18,6 @@
 
 namespace msrl {
 
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-
 __device__ __forceinline__ f32x16 mma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -56,19 +54,6 @@ __device__ __forceinline__ void mma_tile(const u32x4& raw, const typename Operan
     const f32x4 a = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc = mma(a[j], b[j], acc);
-  }
-}
-
-// the same for the first NM of the tile's MFMAs (fp32 tiles are four MFMAs of two inputs each: a layer-1 tile
-// whose last inputs do not exist needs fewer; the products left out are zero weight times zero input)
-template <bool BF16, int NM>
-__device__ __forceinline__ void mma_tile_first(const u32x4& raw, const typename Operand<BF16>::T* b, f32x16& acc) {
-  if constexpr (BF16) {
-    mma_tile<BF16>(raw, b, acc);
-  } else {
-    const f32x4 a = __builtin_bit_cast(f32x4, raw);
-#pragma unroll
-    for (int j = 0; j < NM; ++j) acc = mma(a[j], b[j], acc);
   }
 }
 
@@ -190,11 +175,9 @@ __device__ __forceinline__ void to_operands(const float (&t)[16], typename Opera
 // Software pipeline inside a wave: while the MFMAs of chunk c run, the VALU applies tanh to the
 // accumulators of chunk c-1, so both pipes are busy from one instruction stream.  In a layer-2
 // stage the layer-3 MFMAs of chunk c-1 follow.
-// L1_LAST: fp32 only, the MFMAs of the last layer-1 tile that meet an existing input (0: all four); which inputs
-// an MFMA of a tile multiplies depends on the operand layout of the kernel's observation
-// H1_ACC: fp32 only, the layer-1 outputs are parked in accumulation registers (a kernel with one wave per SIMD
-// has 256 of them beside its 256 vector registers, and an MFMA takes its B operand from either file)
-template <int H, bool BF16, int NB, int KT1, int L1_LAST = 0, bool H1_ACC = false>
+// fp32 (BF16 false): layer 1 only (pursuit env), and the sizes and tiles the kernels with loops of their own share; the other
+// fp32 networks run on the bf16 pipe (mlp_tri.h).
+template <int H, bool BF16, int NB, int KT1>
 struct Mlp {
   typedef typename Operand<BF16>::T Op;
   static constexpr int PT = Operand<BF16>::PER_TILE;
@@ -207,84 +190,13 @@ struct Mlp {
                                                          // tile, layer-3 tiles of chunk c-1, of chunk c
   static constexpr int L3_PREV = KT2 + 1, L3_OWN = KT2 + 1 + TPC;
   static constexpr int G = 4;  // LDS reads run G tiles ahead of the MFMAs that consume them
-  // bf16: one MFMA per tile and (with 256 units) one activation per tile, so the tanh chains are taken two
-  // tiles at a time (see tanh_stage1); fp32 tiles are four MFMAs long and hide a chain each as they are
-  static constexpr bool PAIRED = BF16 && KT2 % 2 == 0;
-  // fp32 networks: the output layer runs on the VALU.  Its few outputs (5 logits, 1 value, 2 K Gaussian
-  // parameters) would fill 32 rows of an MFMA that takes 64 cycles per 2 inputs - a sixth of the matrix
-  // work of a 128-unit network - while the VALU of these kernels is mostly idle.  Each lane multiplies the
-  // activations it holds (16 per chunk) with their weights as the tanh slices complete, between the MFMAs of
-  // the next chunk; `out` then holds the lane's partial sum of output o in register o, and out_finish adds the
-  // two lanes of a row and the bias and puts the result where the MFMA would have (the accumulator layout).
-  // bf16 networks keep the MFMA (2 instructions of 32 cycles per chunk; their VALU is the busy unit), and so do
-  // output layers with more than 6 outputs - more than one for 256-unit networks whose layer-1 outputs are not
-  // parked in accumulation registers (H1_ACC): those kernels have few registers to spare.
-  // OUTS: bit o set <-> output o exists.
-  template <uint32_t OUTS>
-  static constexpr bool l3v() {
-    return !BF16 && __builtin_popcount(OUTS) <= (H <= 128 || H1_ACC ? 6 : 1);
-  }
-  // layer-3 tiles of a chunk that pass through the ring of LDS reads
-  template <uint32_t OUTS>
-  static constexpr int l3s() { return l3v<OUTS>() ? 0 : TPC; }
 
-  __device__ static __forceinline__ int lane_id() {
-    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  }
-  // start value of the output accumulators: the bias (MFMA path), or zero (the bias comes in out_finish)
+  // Output layer: on the MFMA (2 instructions of 32 cycles per chunk; the VALU is the busy unit of the bf16 kernels).
+  // OUTS (here and below): outputs in use, for networks whose code depends on them (MlpTri).
   template <uint32_t OUTS>
-  __device__ static __forceinline__ f32x16 out_init(const float* lds_bias, int h) {
-    if constexpr (l3v<OUTS>()) return zero16();
-    else return bias_init(lds_bias, h);
-  }
-  // out[o] += sum over registers r in [r0, r1) of t[r] * W3[unit of (r, h)][o] for the outputs o whose bit is set
-  // in OUTS and that are below nout (a network with fewer outputs than the kernel's mask: a constant where the
-  // caller's loop over the networks is unrolled).  w3h: the layer-3 tiles
-  // of the chunk as floats, at the slot of lane 32 h: register r = 4 i + j meets component j of slot o + 32 h of
-  // tile i (the A operand of the MFMA that would multiply it), the same address for every lane of a half-wave.
+  __device__ static __forceinline__ f32x16 out_init(const float* lds_bias, int h) { return bias_init(lds_bias, h); }
   template <uint32_t OUTS>
-  __device__ static __forceinline__ void l3_slice(const float* w3h, const float (&t)[16], f32x16& out, int r0, int r1,
-                                                  int nout, f32x4 (&wg)[16]) {
-    static_assert(OUTS != 0 && OUTS < 65536u, "one register per output");
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (r >= r0 && r < r1) {
-        if (r % 4 == 0) {
-          // the weights of registers r .. r+3, 16 bytes per output, fetched as the group starts (as single
-          // words the compiler fetches them far ahead and the 128-unit kernel spills 29 registers)
-#pragma unroll
-          for (int o = 0; o < 16; ++o)
-            if (((OUTS >> o) & 1u) && o < nout) wg[o] = *(const f32x4*)(w3h + ((r / 4) * 64 + o) * 4);
-        }
-#pragma unroll
-        for (int o = 0; o < 16; ++o)
-          if (((OUTS >> o) & 1u) && o < nout) out[o] = __builtin_fmaf(t[r], wg[o][r % 4], out[o]);
-      }
-  }
-  // this half-wave's view of layer-3 tile `first` of the chunk block whose lane slots start at `tiles`
-  __device__ static __forceinline__ const float* l3_weights(const u32x4* tiles, int first, int h) {
-    return (const float*)(tiles + first * 64 - lane_id() + 32 * h);
-  }
-  // after the last chunk: (VALU path) partial sums of the two lanes of a row + bias, into the accumulator layout
-  template <uint32_t OUTS>
-  __device__ static __forceinline__ void out_finish(f32x16 (&out)[NB], const float* lds_bias, int h) {
-    if constexpr (l3v<OUTS>()) {
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        float tot[16];
-#pragma unroll
-        for (int o = 0; o < 16; ++o)
-          tot[o] = (OUTS >> o) & 1u ? out[q][o] + __shfl_xor(out[q][o], 32) + lds_bias[o] : 0.0f;
-        f32x16 res;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int u0 = 8 * (r / 4) + r % 4, u1 = u0 + 4;  // the register's output on the lanes h = 0 / h = 1
-          res[r] = h ? (u1 < 16 ? tot[u1 < 16 ? u1 : 0] : 0.0f) : (u0 < 16 ? tot[u0 < 16 ? u0 : 0] : 0.0f);
-        }
-        out[q] = res;
-      }
-    }
-  }
+  __device__ static __forceinline__ void out_finish(f32x16 (&)[NB], const float*, int) {}
 
   // tanh of the previous chunk, spread over the NT tiles of the current one
   template <int NT>
@@ -315,29 +227,14 @@ struct Mlp {
           u32x4 raw = ring[idx % G];
           if (idx + G < L1_TILES) ring[idx % G] = tiles[(idx + G) * 64];
           if (uc > 0) pin(raw);
-          constexpr int LAST = BF16 || L1_LAST == 0 ? PT : L1_LAST;
-          static_assert(LAST >= 1 && LAST <= PT, "one to four MFMAs");
 #pragma unroll
-          for (int q = 0; q < NB; ++q) {
-            if (kt == KT1 - 1)
-              mma_tile_first<BF16, LAST>(raw, &x[q][kt * PT], acc[q]);
-            else
-              mma_tile<BF16>(raw, &x[q][kt * PT], acc[q]);
-          }
+          for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw, &x[q][kt * PT], acc[q]);
         }
         if (uc > 0) tanh_slice<KT1>(prev, t, kt);
       }
       if (uc > 0) {
 #pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          if constexpr (H1_ACC && !BF16) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(h1[q][(uc - 1) * PC + r]) : "v"(t[q][r]));
-          } else {
-            to_operands<BF16>(t[q], &h1[q][(uc - 1) * PC]);
-          }
-        }
+        for (int q = 0; q < NB; ++q) to_operands<BF16>(t[q], &h1[q][(uc - 1) * PC]);
       }
 #pragma unroll
       for (int q = 0; q < NB; ++q) prev[q] = acc[q];
@@ -352,10 +249,6 @@ struct Mlp {
   __device__ static __forceinline__ void layer2_chunk(const u32x4* tiles, const Op (&h1)[NB][KT2 * PT],
                                                       f32x16 (&acc)[NB], f32x16 (&out)[NB], int h, int nout,
                                                       Tick&& tick) {
-    constexpr bool L3V = l3v<OUTS>();
-    constexpr int L3S = l3s<OUTS>();
-    const float* w3h = L3V ? l3_weights(tiles, L3_PREV, h) : nullptr;
-    f32x4 wg[16];
     u32x4 ring[G];
 #pragma unroll
     for (int i = 0; i < G; ++i) ring[i] = tiles[i * 64];
@@ -366,7 +259,7 @@ struct Mlp {
       prev[q] = acc[q];
       acc[q] = zero16();
     }
-    if constexpr (PIPE && PAIRED) {
+    if constexpr (PIPE) {
       // two tiles per round: the tanh chains of both tiles' share of the chunk before run side by side,
       // the second tile's MFMAs sit between their first and second stage
       float w[NB][16];
@@ -374,14 +267,14 @@ struct Mlp {
       for (int kt = 0; kt < KT2; kt += 2) {
         const int r0 = kt * 16 / KT2, r1 = (kt + 2) * 16 / KT2;
         u32x4 raw = ring[kt % G];
-        if (kt + G < L3_PREV + L3S) ring[kt % G] = tiles[(kt + G) * 64];
+        if (kt + G < L3_PREV + TPC) ring[kt % G] = tiles[(kt + G) * 64];
         pin(raw);
 #pragma unroll
         for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw, &h1[q][kt * PT], acc[q]);
 #pragma unroll
         for (int q = 0; q < NB; ++q) tanh_stage1(prev[q], w[q], r0, r1);
         u32x4 raw2 = ring[(kt + 1) % G];
-        if (kt + 1 + G < L3_PREV + L3S) ring[(kt + 1) % G] = tiles[(kt + 1 + G) * 64];
+        if (kt + 1 + G < L3_PREV + TPC) ring[(kt + 1) % G] = tiles[(kt + 1 + G) * 64];
         pin(raw2);
 #pragma unroll
         for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw2, &h1[q][(kt + 1) * PT], acc[q]);
@@ -395,30 +288,22 @@ struct Mlp {
       }
     } else {
 #pragma unroll
-    for (int kt = 0; kt < KT2; ++kt) {
-      u32x4 raw = ring[kt % G];
-      if (kt + G < L3_PREV + L3S) ring[kt % G] = tiles[(kt + G) * 64];
-      if (PIPE) pin(raw);
+      for (int kt = 0; kt < KT2; ++kt) {
+        const u32x4 raw = ring[kt % G];
+        if (kt + G < L3_PREV + TPC) ring[kt % G] = tiles[(kt + G) * 64];
 #pragma unroll
-      for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw, &h1[q][kt * PT], acc[q]);
-      if (PIPE) {
-        tanh_slice<KT2>(prev, t, kt);
-        if constexpr (l3v<OUTS>()) {
-#pragma unroll
-          for (int q = 0; q < NB; ++q) l3_slice<OUTS>(w3h, t[q], out[q], kt * 16 / KT2, (kt + 1) * 16 / KT2, nout, wg);
-        }
+        for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw, &h1[q][kt * PT], acc[q]);
+        tick(kt);
       }
-      tick(kt);
-    }
     }
     {
       const Op one = Operand<BF16>::one(h);
       const u32x4 raw = ring[KT2 % G];
-      if (KT2 + G < L3_PREV + L3S) ring[KT2 % G] = tiles[(KT2 + G) * 64];
+      if (KT2 + G < L3_PREV + TPC) ring[KT2 % G] = tiles[(KT2 + G) * 64];
 #pragma unroll
       for (int q = 0; q < NB; ++q) mma_bias_tile<BF16>(raw, one, acc[q]);
     }
-    if (PIPE && !L3V) {
+    if (PIPE) {
       Op h2[NB][PC];
 #pragma unroll
       for (int q = 0; q < NB; ++q) to_operands<BF16>(t[q], h2[q]);
@@ -441,10 +326,7 @@ struct Mlp {
                                                        Tick&& tick) {
     // tiles a chunk consumes, in order: its KT2 layer-2 tiles, its bias tile and, if piped, the TPC
     // layer-3 tiles fed by the chunk before it; they are consecutive inside the chunk block
-    // (the layer-3 tiles only where the MFMA multiplies them)
-    constexpr bool L3V = l3v<OUTS>();
-    constexpr int L3S = l3s<OUTS>();
-    constexpr int PER0 = KT2 + 1 + (PIPE0 ? L3S : 0), PERN = KT2 + 1 + L3S;
+    constexpr int PER0 = KT2 + 1 + (PIPE0 ? TPC : 0), PERN = KT2 + 1 + TPC;
     constexpr int TOTAL = PER0 + (CPS - 1) * PERN;
     auto tile_at = [](int p) -> int {  // position in the stream -> tile index in the buffer
       if (p < PER0) return p;
@@ -464,8 +346,6 @@ struct Mlp {
     for (int c = 0; c < CPS; ++c) {
       const bool pipe = PIPE0 || c > 0;
       const int p0 = c == 0 ? 0 : PER0 + (c - 1) * PERN;  // position of the chunk's first tile
-      const float* w3h = L3V ? l3_weights(tiles, c * CHUNK_TILES + L3_PREV, h) : nullptr;
-      f32x4 wg[16];
       f32x16 prev[NB];
       float t[NB][16];
 #pragma unroll
@@ -473,7 +353,7 @@ struct Mlp {
         prev[q] = acc[q];
         acc[q] = zero16();
       }
-      if (pipe && PAIRED) {
+      if (pipe) {
         // two tiles per round: the tanh chains of both tiles' share of the chunk before run side by
         // side, the second tile's MFMAs sit between their first and second stage
         float w[NB][16];
@@ -501,17 +381,9 @@ struct Mlp {
       } else {
 #pragma unroll
         for (int kt = 0; kt < KT2; ++kt) {
-          u32x4 raw = pop(p0 + kt);
-          if (pipe) pin(raw);
+          const u32x4 raw = pop(p0 + kt);
 #pragma unroll
           for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw, &h1[q][kt * PT], acc[q]);
-          if (pipe) {
-            tanh_slice<KT2>(prev, t, kt);
-            if constexpr (l3v<OUTS>()) {
-#pragma unroll
-              for (int q = 0; q < NB; ++q) l3_slice<OUTS>(w3h, t[q], out[q], kt * 16 / KT2, (kt + 1) * 16 / KT2, nout, wg);
-            }
-          }
           tick(c, kt);
         }
       }
@@ -521,7 +393,7 @@ struct Mlp {
 #pragma unroll
         for (int q = 0; q < NB; ++q) mma_bias_tile<BF16>(raw, one, acc[q]);
       }
-      if (pipe && !L3V) {
+      if (pipe) {
         Op h2[NB][PC];
 #pragma unroll
         for (int q = 0; q < NB; ++q) to_operands<BF16>(t[q], h2[q]);
@@ -552,7 +424,7 @@ struct Mlp {
       prev[q] = acc[q];
       acc[q] = zero16();
     }
-    if constexpr (PIPE && PAIRED) {
+    if constexpr (PIPE) {
       // two tiles per round, the tanh chains of both side by side (as in layer2_chunk)
       float w[NB][16];
 #pragma unroll
@@ -581,12 +453,10 @@ struct Mlp {
     } else {
 #pragma unroll
       for (int kt = 0; kt < KT2; ++kt) {
-        u32x4 raw = ring[kt % G];
+        const u32x4 raw = ring[kt % G];
         if (kt + G < KT2 + 1) ring[kt % G] = tiles[(kt + G) * 64];
-        if (PIPE) pin(raw);
 #pragma unroll
         for (int q = 0; q < NB; ++q) mma_tile<BF16>(raw, &hin[q][kt * PT], acc[q]);
-        if (PIPE) tanh_slice<KT2>(prev, t, kt);
         tick(kt);
       }
     }
@@ -615,17 +485,6 @@ struct Mlp {
   template <uint32_t OUTS>
   __device__ static __forceinline__ void layer2_drain(const u32x4* tiles, const f32x16 (&acc)[NB],
                                                       f32x16 (&out)[NB], int h, int nout) {
-    if constexpr (l3v<OUTS>()) {
-      const float* w3h = l3_weights(tiles, L3_OWN, h);
-      f32x4 wg[16];
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        float t[16];
-        tanh_range<!BF16>(acc[q], t, 0, 16, false);
-        l3_slice<OUTS>(w3h, t, out[q], 0, 16, nout, wg);
-      }
-      return;
-    }
     u32x4 w3[TPC];
 #pragma unroll
     for (int i = 0; i < TPC; ++i) w3[i] = tiles[(L3_OWN + i) * 64];
@@ -672,8 +531,8 @@ __device__ __forceinline__ void stage_priority(int stage, int wave, int waves) {
 // their own.
 // ADDR_IN_VCC: where the copies' addresses are formed.  In VCC they take no scalar registers from the kernel (the fp32
 // kernels spilled up to 132 of them), but no lane mask can live across a copy.  The particle env's bf16 kernels, short of
-// vector registers, are better off with a register pair per copy: the deep one of 256 units spills 51 vector registers
-// instead of 81, 8191 envs x 10 agents with six hidden layers 9.6 instead of 9.85 ms.
+// vector registers, are better off with a register pair per copy: the deep one of 256 units and 10 agents spills 51 vector
+// registers instead of 81.
 template <class Net, int WAVES, int NBUF, int CPS, bool L1S = false, bool ADDR_IN_VCC = true>
 struct WeightStream {
   // a stage = CPS consecutive chunk blocks of one network

@@ -397,8 +397,7 @@ next_row_block:
 
 
   // Outputs of a network as a bit mask (5 logits; the value network uses the first).  Only the fp32 output
-  // layer's code depends on it: few outputs run on the VALU (Mlp::l3v).  All 16 bits keep the output layer on
-  // the MFMA (bf16 kernels).
+  // layer's code depends on it: up to 8 outputs run on the VALU (MlpTri).
   constexpr uint32_t OUTS = BF16 ? 0xFFFFu : 0x1Fu;
 
   // Centralised critic (PHASE_CENTRAL).  The joint observations of the workgroup's envs are the
@@ -1283,9 +1282,8 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
             for (int j = 0; j < Net::KT2; ++j) h1[0][j] = hb[0][j];
           }
         }
-        // Output layer: the policy's 2 K outputs on the MFMA (all 16 bits), the one value on the VALU (`net` is a
-        // constant once the loop over the networks is unrolled).  Measured at the benchmark's shape: both on the
-        // MFMA 21.64 ms, the value on the VALU 21.27, both on the VALU 21.62 (12 sums per activation are too many).
+        // Output layer: the policy's 2 K outputs on the MFMA (all 16 bits; 12 sums per activation are too many for the
+        // VALU), the one value on the VALU (`net` is a constant once the loop over the networks is unrolled).
         constexpr uint32_t OUTS_P = 0xFFFFu, OUTS_V = 0x1u;
         out[0] = net == 0 ? Net::template out_init<OUTS_P>(s_b3[net], h) : Net::template out_init<OUTS_V>(s_b3[net], h);
 #pragma unroll 1

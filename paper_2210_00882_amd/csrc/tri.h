@@ -24,8 +24,6 @@
 
 namespace msrl {
 
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-
 // one operand: 8 values of a row as three bf16 pieces
 struct Tri {
   u32x4 p[3];
