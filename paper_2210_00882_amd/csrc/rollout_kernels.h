@@ -206,8 +206,8 @@ void particle_rollout_kernel(RolloutArgs a) {
   // in row layout, then the wave stores the same bytes as consecutive 16-byte (8-byte when D is
   // not a multiple of 4) pieces, so that one store instruction covers whole cache lines instead
   // of 64 separate rows.  SE envs (SR rows) are staged per pass: all of the wave's when they take at most
-  // STG_ALL bytes, else as many as fit STG_SOME (networks of 256 units fill the LDS with their resident
-  // layer-1 tiles and the window, fp32 ones the more, so their staging areas are smaller).
+  // STG_ALL bytes, else as many as fit STG_SOME (bf16 networks of 256 units and fp32 ones of
+  // 128 fill the LDS with their resident layer-1 tiles and the window, so their staging areas are smaller).
   constexpr bool TIGHT = SPLIT && H >= 128;  // (all weights resident: little LDS left)
   constexpr int STG_ALL = (!BF16 && H >= 256) || TIGHT ? 2048 : 4608;
   constexpr int STG_SOME = H >= 256 ? (BF16 ? 2560 : 2048) : (TIGHT ? 2048 : !BF16 && H >= 128 ? 2560 : 3072);
