@@ -417,6 +417,36 @@ def test_infinities_behave_as_in_fp32_arithmetic(hidden, gauss, layers, where):
     assert_close(got[fin], want[fin], TOL_F32, "finite outputs")
 
 
+@pytest.mark.parametrize("hidden,gauss,layers,central,roles", [
+    (64, False, 2, False, 1), (64, False, 2, False, 2), (64, False, 2, True, 0), (64, False, 3, False, 0),
+    (128, False, 2, False, 0), (128, False, 2, True, 0), (256, False, 2, False, 0), (256, False, 3, False, 0),
+    (256, True, 2, False, 0), (256, True, 3, False, 0)])
+def test_rollouts_of_large_and_infinite_states_in_fp32(hidden, gauss, layers, central, roles):
+    # every fp32 rollout kernel on states beyond the ordinary: its own observations through IEEE arithmetic
+    cfg = synth.lingauss("big", 40, 17, 6, 256, 4, 1000) if gauss else synth.particle("big", 40, 4, hidden, 4, 25, synth.F32)
+    cfg = cfg.with_(hidden_layers=layers, central_critic=central)
+    params, dyn = synth.make_params(cfg, bias_std=0.1).astype(np.float32), synth.make_dynamics(cfg) if gauss else None
+    D, H = cfg.obs_dim, cfg.hidden
+    with GpuRollout(cfg, params, 11, dyn=dyn, wave_roles=roles) as gpu:
+        es, _ = gpu.get_state()
+        for k, v in enumerate((7e4, 65536.0, -1e6, 1e20, -3.4e38, np.inf, -np.inf, np.nan)):
+            es[3 * k, 3] = v                 # (particle env: a velocity, which enters one agent's row alone)
+        if not gauss:
+            es[30, 0] = 1e10                 # a position, which enters every row of its env
+        gpu.set_state(es)
+        tr = gpu.run(1, gae=False)
+    rows = tr["obs"][0].astype(np.float64)
+    pol, at = ieee_net(params.astype(np.float64), [D] + [H] * layers + [cfg.out_dim], 0, rows)
+    val, _ = ieee_net(params.astype(np.float64), [cfg.value_in_dim] + [H] * layers + [1], at,
+                      rows.reshape(cfg.num_envs, -1) if central else rows)
+    val = np.repeat(val[:, 0], cfg.num_agents) if central else val[:, 0]
+    assert np.isinf(rows).any() and np.isnan(pol).any()
+    for what, got, want in (("logits", tr["logits"][0].astype(np.float64), pol), ("values", tr["values"][0].astype(np.float64), val)):
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want), err_msg=what)
+        ok = ~np.isnan(want)
+        assert_close(got[ok], want[ok], TOL_F32, what)
+
+
 @pytest.mark.parametrize("which", sorted(ACT_CASES))
 def test_observe_against_the_oracle(which):
     """msrl_observe == the oracle's observation of the state msrl_state_get returns, at the initial
