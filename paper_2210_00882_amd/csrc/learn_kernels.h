@@ -538,21 +538,27 @@ __global__ void fill_kernel(float* p, int64_t n, float v) {
 }
 
 // out[slice][u] = sum_{r in slice} src[u][r], r < rows (src unit-major).  blockIdx.x = unit, blockIdx.y =
-// slice of `per_slice` rows, whose sums lie slice_stride floats apart.
+// slice of `per_slice` rows, whose sums lie slice_stride floats apart.  Units from `units` on are those of a second
+// array, src2 -> out2.
 template <typename S>
 __global__ __launch_bounds__(256) void rowsum_kernel(const S* src, int64_t units, int64_t rows, int64_t lds_,
-                                                     int64_t per_slice, float* out, int64_t slice_stride) {
+                                                     int64_t per_slice, float* out, int64_t slice_stride,
+                                                     const S* src2 = nullptr, float* out2 = nullptr) {
   __shared__ float part[4];
-  const int64_t u = blockIdx.x;
+  int64_t u = blockIdx.x;
+  if (src2 && u >= units) {
+    u -= units;
+    src = src2;
+    out = out2;
+  }
   const int64_t r_begin = (int64_t)blockIdx.y * per_slice, r_end = min(rows, r_begin + per_slice);
   float s = 0.0f;
-  if (u < units)
-    for (int64_t r = r_begin + threadIdx.x; r < r_end; r += 256) s += load_elem(src + u * lds_ + r);
+  for (int64_t r = r_begin + threadIdx.x; r < r_end; r += 256) s += load_elem(src + u * lds_ + r);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0 && u < units)
+  if (threadIdx.x == 0)
     out[(int64_t)blockIdx.y * slice_stride + u] = part[0] + part[1] + part[2] + part[3];
 }
 
@@ -601,7 +607,10 @@ struct ReduceJobs {
   int32_t count[REDUCE_MAX_JOBS];
   int32_t slices[REDUCE_MAX_JOBS];
   int32_t first_block[REDUCE_MAX_JOBS + 1];  // prefix sums of ceil(count / REDUCE_ELEMS): block -> job
+  int32_t group_offset[REDUCE_MAX_JOBS];  // >= 0: column of group_sum the tensor starts at
   int32_t jobs;
+  const float* group_sum;  // [groups][group_stride]
+  int32_t groups, group_stride;
 };
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* part, int64_t slice_stride, ReduceJobs j,
                                                               float* grad, AdamArgs adam, float* stats) {
@@ -618,7 +627,25 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* part,
   const int n = j.slices[q];
   const int s_begin = wave * n / 4, s_end = (wave + 1) * n / 4;
   float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-  if (live) {
+  if (live && j.group_offset[q] >= 0) {
+    const float* p = j.group_sum + j.group_offset[q] + i;
+    auto slice_sum = [&](int s) {
+      float g[8], v = 0.0f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) g[w] = 8 * s + w < j.groups ? p[(int64_t)(8 * s + w) * j.group_stride] : 0.0f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v += g[w];
+      return v;
+    };
+    int s = s_begin;
+    for (; s + 4 <= s_end; s += 4) {
+      s0 += slice_sum(s);
+      s1 += slice_sum(s + 1);
+      s2 += slice_sum(s + 2);
+      s3 += slice_sum(s + 3);
+    }
+    for (; s < s_end; ++s) s0 += slice_sum(s);
+  } else if (live) {
     const float* p = part + j.offset[q] + i;
     int s = s_begin;
     for (; s + 4 <= s_end; s += 4) {

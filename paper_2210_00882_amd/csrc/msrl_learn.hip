@@ -13,6 +13,7 @@
 #include "api_common.h"
 #include "learn_kernels.h"
 #include "learn_fused_aux.h"
+#include "learn_block.h"
 
 using namespace msrl;
 
@@ -66,6 +67,11 @@ struct msrl_learner {
   NetLayout fly;         // layout of one image of the packed weights
   uint8_t* fpacked;      // per network: forward image, backward image
   int cus;               // compute units of the device
+  // fp32 gradient pass in one kernel (learn_block.h)
+  bool block;            // ... for both networks
+  bool block_policy;     // ... for the policy network only (centralised critic)
+  f32x4* bpacked;        // operand tiles of the networks it handles
+  float* bsum;           // [BSUM_MAX_ROWS / 32 at most][4 H] bias-gradient sums over 32 rows (Gaussian policies)
 };
 
 namespace {
@@ -77,6 +83,16 @@ namespace {
       return fail(e_ == hipErrorOutOfMemory ? MSRL_ENOMEM : MSRL_EDEVICE, "%s failed: %s",  \
                   #expr, hipGetErrorString(e_));                                            \
   } while (0)
+
+// most rows of a minibatch whose bias gradients are added up over 32 rows at a time (256 slices of 256 rows: the order
+// of the layer kernels, bit for bit); above, each slice keeps one running sum
+constexpr int64_t BSUM_MAX_ROWS = 65536;
+
+// 16-byte tiles of a network's packed weights (learn_block.h)
+size_t block_tiles(int in, int H, int out) {
+  const size_t T = (size_t)H / 32, KH = (size_t)H / 8;
+  return T * ((in + 7) / 8) + 2 * T * KH + (size_t)((out + 15) / 16) * (H / 16) + T * ((out + 7) / 8);
+}
 
 size_t net_count(int in, int H, int out, int layers = 2) {
   return (size_t)in * H + H + (size_t)(layers - 1) * ((size_t)H * H + H) + (size_t)H * out + out;
@@ -187,10 +203,11 @@ struct Reducer {
   ReduceJobs j;
   int blocks;
   Reducer() : blocks(0) { memset(&j, 0, sizeof(j)); }
-  void add(size_t offset, size_t count, int slices) {
+  void add(size_t offset, size_t count, int slices, int group_offset = -1) {
     j.offset[j.jobs] = (int32_t)offset;
     j.count[j.jobs] = (int32_t)count;
     j.slices[j.jobs] = slices;
+    j.group_offset[j.jobs] = group_offset;
     j.first_block[j.jobs] = blocks;
     blocks += (int)((count + REDUCE_ELEMS - 1) / REDUCE_ELEMS);
     j.first_block[++j.jobs] = blocks;
@@ -521,6 +538,97 @@ int fused_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSe
   return MSRL_OK;
 }
 
+// The same gradient for fp32 networks of two hidden layers: one kernel for both networks, a workgroup per network and
+// slice of the rows, with the weights packed in front and the slices' copies added up behind it.
+int block_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel, const float* obs,
+                    const void* actions, const float* logp_old, const float* adv, const float* ret,
+                    const msrl_ppo_cfg* c, float* grad, hipStream_t s, const AdamArgs* adam, int nets = 3,
+                    bool finish = true) {
+  const int D = L->pol.in_dim, H = L->pol.hidden;
+  const int64_t Rk = round_up(R, 16);
+  // Slices: as many as fill the chip once, of whole tiles of rows (5000 rows of 256 units: 0.11 ms in 64-row slices, 0.42
+  // in 256-row ones).  Gaussian policies keep the layer kernels' slices
+  // (at least 256 rows) and, up to 256 of those, their order of the bias sums: a few Adam steps on stale rows amplify
+  // a rounding of such a policy's update (ratios of e^30) until the two would differ in the third digit.
+  const bool gauss = L->pol.dist == MSRL_DIAG_GAUSSIAN, ordered = gauss && R <= BSUM_MAX_ROWS;
+  const int64_t tile = gauss ? 32 : 32 * block_row_tiles(H);
+  int64_t slices = gauss ? (Rk / 256 < 1 ? 1 : Rk / 256) : (int64_t)L->cus * block_per_cu(H) / (nets == 3 ? 2 : 1);
+  if (slices > L->part_slices) slices = L->part_slices;
+  BlockArgs a;
+  memset(&a, 0, sizeof(a));
+  a.rows_per_slice = round_up((Rk + slices - 1) / slices, tile);
+  slices = (Rk + a.rows_per_slice - 1) / a.rows_per_slice;
+  if ((slices - 1) * a.rows_per_slice >= R) --slices;  // (the last one holds padding only)
+  a.obs = obs; a.actions = actions; a.logp_old = logp_old; a.adv = adv; a.ret = ret; a.sel = sel; a.R = R; a.ldt = L->Rp;
+  a.D = D; a.dist = L->pol.dist;
+  a.clip = c->clip; a.vf_coef = c->vf_coef; a.ent_coef = c->ent_coef; a.inv_R = 1.0f / (float)R;
+  a.part = L->part; a.part_stride = L->part_stride; a.stats = L->stats; a.stat_bins = STAT_BINS;
+  a.bsum = ordered ? L->bsum : nullptr;
+  a.bsum_stride = 4 * H;
+  Reducer red;
+  red.j.group_sum = L->bsum;
+  red.j.groups = (int32_t)((R + 31) / 32);
+  red.j.group_stride = a.bsum_stride;
+  BlockPackJobs jobs;
+  memset(&jobs, 0, sizeof(jobs));
+  jobs.clear = L->stats;
+  jobs.n_clear = 8 + 5 * STAT_BINS;
+  int max_items = jobs.n_clear, used = 0;
+  size_t off = 0;
+  f32x4* dst = L->bpacked;
+  int64_t per_slice = 2048;  // rows per slice of the output layer's bias gradient
+  if ((R + per_slice - 1) / per_slice > L->part_slices) per_slice = (R + L->part_slices - 1) / L->part_slices;
+  const unsigned bias_slices = (unsigned)((R + per_slice - 1) / per_slice);
+  size_t ob3s[2] = {0, 0};
+  for (int n = 0; n < 2; ++n) {
+    const int O = n == 0 ? L->pol.out_dim : 1;
+    const size_t oW1 = off, ob1 = oW1 + (size_t)D * H, oW2 = ob1 + H, ob2 = oW2 + (size_t)H * H, oW3 = ob2 + H,
+                 ob3 = oW3 + (size_t)H * O;
+    off += net_count(D, H, O);
+    if (!((nets >> n) & 1)) continue;
+    BlockNet& b = a.net[used];
+    auto pack = [&](size_t src, int sk, int sn, int nk, int nn, int tiles, int kt, int form) -> const f32x4* {
+      BlockPackJob& j = jobs.job[jobs.n++];
+      j.src = params + src; j.dst = dst; j.sk = sk; j.sn = sn; j.nk = nk; j.nn = nn; j.tiles = tiles; j.kt = kt; j.form = form;
+      if (tiles * kt * 64 > max_items) max_items = tiles * kt * 64;
+      const f32x4* at = dst;
+      dst += (size_t)tiles * kt * 64;
+      return at;
+    };
+    b.w1 = pack(oW1, H, 1, D, H, H / 32, (D + 7) / 8, 0);
+    b.w2 = pack(oW2, H, 1, H, H, H / 32, H / 8, 0);
+    b.w3 = pack(oW3, O, 1, H, O, (O + 15) / 16, H / 16, 1);
+    b.w3t = pack(oW3, 1, O, O, H, H / 32, (O + 7) / 8, 0);
+    b.w2t = pack(oW2, 1, H, H, H, H / 32, H / 8, 0);
+    b.b1 = params + ob1; b.b2 = params + ob2; b.b3 = params + ob3;
+    b.dyt = (float*)L->net[n].dyt;
+    b.oW1 = (int32_t)oW1; b.ob1 = (int32_t)ob1; b.oW2 = (int32_t)oW2; b.ob2 = (int32_t)ob2; b.oW3 = (int32_t)oW3;
+    b.ob3 = (int32_t)ob3;
+    b.out = O;
+    b.policy = n == 0;
+    b.bsum = used * 2 * H;
+    red.add(oW1, (size_t)D * H, (int)slices);
+    red.add(oW2, (size_t)H * H, (int)slices);
+    red.add(oW3, (size_t)H * O, (int)slices);
+    const int tiles = (int)((R + 255) / 256);
+    red.add(ob1, H, ordered ? tiles : (int)slices, ordered ? b.bsum : -1);
+    red.add(ob2, H, ordered ? tiles : (int)slices, ordered ? b.bsum + H : -1);
+    red.add(ob3, O, ordered ? (int)bias_slices : (int)slices);
+    ob3s[used++] = ob3;
+  }
+  LTRY(launch_block_pack(jobs, max_items, s));
+  LTRY(launch_ppo_block(H, D, L->pol.out_dim, a, (unsigned)slices, (unsigned)used, s));
+  if (ordered) {
+    const unsigned units = (unsigned)(a.net[0].out + (used > 1 ? a.net[1].out : 0));
+    hipLaunchKernelGGL((rowsum_kernel<float>), dim3(units, bias_slices), dim3(256), 0, s, (const float*)a.net[0].dyt,
+                       (int64_t)a.net[0].out, R, L->Rp, per_slice, L->part + ob3s[0], L->part_stride,
+                       used > 1 ? (const float*)a.net[1].dyt : nullptr, used > 1 ? L->part + ob3s[1] : nullptr);
+    LTRY(hipGetLastError());
+  }
+  LTRY(red.launch(L, grad, adam, finish ? L->stats : nullptr, s));
+  return MSRL_OK;
+}
+
 int check_learner_args(const char* who, msrl_learner* L, const void* params, int64_t R, const void* obs,
                        const void* actions, const void* logp_old, const void* adv, const void* ret,
                        const msrl_row_select* rows, const msrl_ppo_cfg* c) {
@@ -562,6 +670,12 @@ int grad_rows(msrl_learner* L, const float* params, int64_t R, int64_t row0, con
               const float* obs, const void* actions, const float* logp_old, const float* adv, const float* ret,
               const msrl_ppo_cfg* cfg, float* grad, hipStream_t s, const AdamArgs* adam = nullptr) {
   const RowSel sel = selection(rows, row0);
+  if (L->block) return block_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam);
+  if (L->block_policy) {
+    int rc = block_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam, 1, false);
+    if (rc == MSRL_OK) rc = grad_pass<false>(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam, 2, true);
+    return rc;
+  }
   if (L->fused) return fused_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam);
   if (L->fused_policy) {
     // Centralised critic: the policy network on chip, then the value network (one row per group, a wide
@@ -625,6 +739,10 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
                     (policy->hidden == 64 || policy->hidden == 128 || policy->hidden == 256) && L->layers == 2 &&
                     path != MSRL_LEARNER_PATH_DEVICE_MEMORY;
   L->fused = L->fused_policy && L->G == 1;
+  L->block_policy = !L->bf16 && policy->in_dim <= 64 &&
+                    (policy->hidden == 64 || policy->hidden == 128 || policy->hidden == 256) && L->layers == 2 &&
+                    path != MSRL_LEARNER_PATH_DEVICE_MEMORY;
+  L->block = L->block_policy && L->G == 1;
   L->fly = net_layout(16 * L->kt1 - 1, policy->hidden, true);
   int rc = MSRL_OK;
   {
@@ -636,8 +754,13 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
     L->cus = cus;
   }
   auto A = [&](void** p, size_t bytes) { if (rc == MSRL_OK) rc = dev_alloc((uint8_t**)p, bytes); };
-  A(&L->xc, Rp * Dp * e);
-  A(&L->xt, (L->fused_policy && (size_t)(16 * L->kt1) > Dp ? (size_t)(16 * L->kt1) : Dp) * Rp * e);
+  if (L->block_policy) {
+    A((void**)&L->bpacked, (block_tiles(policy->in_dim, policy->hidden, policy->out_dim) +
+                            (L->block ? block_tiles(policy->in_dim, policy->hidden, 1) : 0)) * 64 * sizeof(f32x4));
+    if (policy->dist == MSRL_DIAG_GAUSSIAN) A((void**)&L->bsum, (size_t)((L->Rp < BSUM_MAX_ROWS ? L->Rp : BSUM_MAX_ROWS) / 32) * 4 * H * sizeof(float));
+  }
+  if (!L->block_policy) A(&L->xc, Rp * Dp * e);
+  if (!L->block_policy) A(&L->xt, (L->fused_policy && (size_t)(16 * L->kt1) > Dp ? (size_t)(16 * L->kt1) : Dp) * Rp * e);
   if (L->fused_policy) A((void**)&L->fpacked, 4 * L->fly.bytes);
   if (L->G > 1) {
     A(&L->xcv, (Rp / L->G + 128) * (size_t)L->Dvp * e);
@@ -645,6 +768,10 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
   }
   for (int n = 0; n < 2; ++n) {
     NetBufs& b = L->net[n];
+    if (L->block || (L->block_policy && n == 0)) {  // (the block kernel keeps everything else on chip)
+      if (policy->dist == MSRL_DIAG_GAUSSIAN) A(&b.dyt, 32 * Rp * e);
+      continue;
+    }
     for (int l = 0; l < L->layers; ++l) {
       A(&b.wt[l], H * (l == 0 ? (n == 1 && L->G > 1 ? (size_t)L->Dvp : Dp) : H) * e);
       if (l >= 1) A(&b.wn[l], H * H * e);
@@ -661,8 +788,13 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
     A(&b.dyt, 32 * Rp * e);
   }
   A((void**)&L->grad, L->n_params * sizeof(float));
-  // a contraction over the rows is split into at most this many slices (never more than one per 128 rows)
-  L->part_slices = (int)(L->Rp / 128 + 1 < 256 ? L->Rp / 128 + 1 : 256);
+  // a contraction over the rows is split into at most this many slices (the block kernel's of narrow networks, several
+  // workgroups to a compute unit, are smaller)
+  {
+    const bool narrow = L->block_policy && policy->hidden <= 64;
+    const int64_t most = narrow ? 512 : 256, by_rows = L->block_policy ? L->Rp / 32 : L->Rp / 128 + 1;
+    L->part_slices = (int)(by_rows < most ? by_rows : most);
+  }
   L->part_stride = round_up((int64_t)L->n_params, 64);
   A((void**)&L->part, (size_t)L->part_slices * (size_t)L->part_stride * sizeof(float));
   A((void**)&L->stats, (8 + 5 * STAT_BINS) * sizeof(float));
@@ -676,7 +808,7 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
 
 void msrl_learner_destroy(msrl_learner* L) {
   if (!L) return;
-  void* ptrs[] = {L->xc, L->xt, L->xcv, L->xtv, L->grad, L->part, L->stats, L->fpacked};
+  void* ptrs[] = {L->xc, L->xt, L->xcv, L->xtv, L->grad, L->part, L->stats, L->fpacked, L->bpacked, L->bsum};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int n = 0; n < 2; ++n) {
