@@ -406,10 +406,9 @@ typedef struct {
 } msrl_ppo_cfg;
 
 /* Allocates the workspaces.  EINVAL unless hidden is a multiple of 32 and out_dim <= 32.
- * bfloat16 networks with two hidden layers of 64, 128 or 256 units, a categorical policy of at most
- * 16 actions and at most 62 inputs take the path that keeps the activations on chip (with a
- * centralised critic: the policy network only), float32 networks with two hidden layers of 64, 128 or
- * 256 units and at most 64 inputs a single kernel (likewise); everything else the path through device memory.
+ * Networks with two hidden layers of 64, 128 or 256 units and at most 64 inputs (bfloat16: 62 inputs, and a
+ * categorical policy of at most 16 actions) take a single kernel that keeps the activations on chip (with
+ * a centralised critic: the policy network only); everything else the path through device memory.
  * Both compute the same gradient (the same rounding points in bfloat16 mode). */
 int msrl_learner_init(const msrl_policy_cfg* policy, int64_t max_rows, msrl_learner** out);
 /* The same with the choice of path made by the caller (tests and measurements: it keeps the

@@ -1,0 +1,6 @@
+// bf16 gradient kernel of the learner for hidden size 128
+#include "learn_block_bf16.h"
+
+namespace msrl {
+MSRL_BLOCK_BF16_LAUNCHER(128)
+}  // namespace msrl

@@ -1,0 +1,631 @@
+// Learner's gradient pass for bf16 networks of two hidden layers and a categorical policy of up to 16 actions: the
+// one-kernel form of learn_block.h (a team of waves, one per 32 hidden units, takes 64 rows at a time and keeps the
+// weight gradients of its rows in registers), on the bf16 matrix pipe.
+//
+// Layers are computed transposed (units x rows): weights are the A operand, the rows' activations the B operand, read
+// from LDS row by row, 8 units per lane.  A result has one row per lane and, for each 16 units, 8 of them in registers:
+// exactly what the lane of the next layer's operand needs, so they go back to LDS as 16 bytes and the units keep that
+// order there ("chained", packed.h).  The weight gradients contract over the rows: their operands (8 rows of a unit)
+// come from the same LDS rows through the transposing read (ds_read_b64_tr_b16), so nothing is stored twice.
+//
+// What bounds it: the six barriers of a tile and what waits between them.  Of the 27 k cycles of a 64-row tile of 256
+// units the matrix pipe is busy for 7.7 k, the vector ALU for 11 k, the LDS for 8 k (activations are read once by each
+// of the eight waves in either layer product, 2 k cycles each, as long as their MFMAs take).  Writing the activations
+// and their gradients out for contractions of their own (4 KiB per row and network) was bound by that traffic.
+// Gradient of 524,288 rows before and now: 256 units 1.39 -> 0.84 ms, 128 0.77 -> 0.43, 64 0.28 -> 0.19 (pursuit env 0.22
+// -> 0.16); of 8192 rows 128 -> 56, 79 -> 35, 61 -> 33 us (three launches where there were six).
+//
+// The sums keep their order from one version of the learner to the next: which rows an accumulator takes, in which
+// order, and which 16 products an MFMA adds at once.  A bf16 policy acts on the rounded parameters, so that a gradient
+// off by one rounding takes the next rollout of a training run another way.
+//
+// Rounding (the oracle's): weights, observations, h1, h2, dL/dy, dL/dz2 and dL/dz1 to bf16; biases as a high and a low
+// bf16 part, two more inputs of their layer that meet the constant 1; sums and the loss in fp32.
+#pragma once
+#include <type_traits>
+
+#include "mlp.h"
+#include "row_sel.h"
+
+namespace msrl {
+
+struct BlockNetB {
+  // operand tiles of 64 lanes x 8 inputs, [unit tile][k tile], lane (i, h): unit 32 t + i, inputs 16 kt + 8 h + s (w1)
+  // or 16 kt + 8 (s / 4) + 4 h + s % 4 (the others, chained); w1, w2 with the two parts of the bias behind the inputs
+  const u32x4 *w1, *w2, *w3;
+  const u32x4 *w3t, *w2t;     // the transposes, for the backward pass
+  const float* b3;            // output bias (fp32 master)
+  int32_t oW1, ob1, oW2, ob2, oW3, ob3;  // offsets in the gradient vector
+  int out;                    // outputs in use
+  int policy;                 // 1: policy network, 0: value network
+};
+struct BlockArgsB {
+  BlockNetB net[2];           // blockIdx.y picks one
+  const float* obs;           // [., D]
+  const int32_t* actions;
+  const float *logp_old, *adv, *ret;
+  RowSel sel;
+  int64_t R;
+  int64_t rows_per_slice;     // teams of a whole workgroup: rows of slice blockIdx.x, a multiple of 64
+  int D;
+  float clip, vf_coef, ent_coef, inv_R;
+  float* part;                // [workgroup][part_stride] copies of the gradient
+  int64_t part_stride;
+  float* stats;               // bins as in LossArgs
+  int stat_bins;
+};
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// An array of rows in LDS, CH pieces of 16 bytes (8 elements) each, without padding: piece c of row r lies at
+// c ^ swizzle(r), so that the 16 rows one cycle of a 16-byte access covers lie in different banks, and so do the four
+// rows and four pieces half a transposing read covers.  (With padded rows one of the two had two- and four-way
+// conflicts: 56 % of the LDS cycles of the 256-unit kernel.)
+template <int CH> struct LdsRows {
+  static_assert(CH == 2 || CH == 4 || CH == 8 || CH == 16 || CH == 32, "16-byte pieces per row");
+  static __device__ __forceinline__ int swizzle(int r) {
+    return CH >= 16 ? ((r & 3) << 2 | (r >> 2 & 3)) : CH == 8 ? ((r >> 1 & 1) << 2 | (r >> 2 & 3)) : CH == 4 ? (r >> 2 & 3) : (r >> 3 & 1);
+  }
+  static constexpr int ROW = 8 * CH;  // elements
+  // A lane's place: row r, low bits p of the piece's index, e elements into the piece.  at(place, c): element offset for
+  // piece c + p (c and p without a common bit).  The lane's part is hidden from the compiler: a place is cheap to form
+  // where it is used, and offsets kept over the phases of a tile would be spilled.
+  struct Place { int base, x; };
+  static __device__ __forceinline__ Place place(int r, int p, int e = 0) {
+    Place q = {r * ROW + e, p ^ swizzle(r)};
+    asm volatile("" : "+v"(q.base), "+v"(q.x));
+    return q;
+  }
+  static __device__ __forceinline__ int at(const Place& q, int c) {
+    constexpr int M = CH < 16 ? CH - 1 : 15;
+    return q.base + (((c & M) ^ q.x) + (c & ~M)) * 8;
+  }
+  // 8 rows of one column as an operand (rows r0 + 8 a .. + 7, a the lane's part of the contraction): lo, hi: places of
+  // the first and second four of its rows, at piece and half piece of the lane's four columns; s: at row r0, a multiple
+  // of 16
+  struct Columns { Place lo, hi; };
+  static __device__ __forceinline__ Columns columns(int r, int p, int half) { return {place(r, p, 4 * half), place(r + 4, p, 4 * half)}; }
+  static __device__ __forceinline__ bf16x8 read(const __bf16* s, const Columns& q, int c) {
+    typedef __attribute__((address_space(3))) s16x4* Lds;
+    struct { s16x4 lo, hi; } v;
+    v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Lds)(s + at(q.lo, c)));
+    v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((Lds)(s + at(q.hi, c)));
+    return __builtin_bit_cast(bf16x8, v);
+  }
+};
+// unit of position j of 32 in the chained order
+__device__ __forceinline__ int chained(int j) { return (j & 16) | (j & 4) << 1 | (j & 8) >> 1 | (j & 3); }
+
+// XT: 32-input tiles of the padded observation, 1 or 2
+template <int H, int XT> struct BlockShapeB {
+  static constexpr int NWU = H / 32;              // groups of 32 units
+  // 128 units: two waves per group of units, a 32-row tile each (eight waves for the compute unit, whose share of a
+  // minibatch is one workgroup)
+  static constexpr int RS = H == 128 ? 2 : 1;
+  static constexpr int NW = NWU * RS;             // waves of a team
+  // 64 units: four teams, who share the weights in LDS; the team takes every fourth 32-row tile, and the teams' sums are
+  // joined at the end
+  static constexpr int TEAMS = H == 64 ? 4 : 1;
+  static constexpr int TEAM_THREADS = 64 * NW, THREADS = TEAM_THREADS * TEAMS;
+  static constexpr int ROWS = 64, RT = ROWS / 32 / RS;  // rows of a team's tile; 32-row tiles of a wave
+  static constexpr int KH = H / 16, KX = 2 * XT;
+  typedef LdsRows<H / 8> Rh;    // activations
+  typedef LdsRows<4 * XT> Rx;   // observations
+  typedef LdsRows<2> Ry;        // dL/dy
+  // weights of the two layer products: in registers up to 128 units (KH + 1 and KH tiles of 4 each), else streamed from
+  // memory
+  static constexpr bool RESIDENT = H <= 128;
+  static constexpr int WD = 4;  // tiles fetched ahead of their product when streamed
+  static constexpr bool G3_LDS = H > 128;  // dL/dW3 waits in LDS between the tiles (the registers are full)
+  static constexpr int XBUF = H <= 64 ? 1 : 2;   // (64 units: four teams' rows leave no room for a second buffer)
+  static constexpr bool OWN_DZ = RS > 1;  // dL/dz in arrays of their own: two waves share a column of h1, h2
+  // dL/dW2: waves in a grid of MG groups of 32 MT units of layer 1 by NW / MG groups of 32 NT units of layer 2 (NT <= MG)
+  static constexpr int MT = H == 256 ? 2 : 1, MG = NWU / MT, NT = NWU * MG / NW;
+  static constexpr int CW = 16 * XT;              // threads per row in the copy of the observations, two columns each
+  static constexpr int RSTEP = TEAM_THREADS / CW; // rows per round
+  static constexpr int XN = ROWS / RSTEP;
+};
+
+// VEC2: observations come in pairs (D is even, the array 8-byte aligned); one dword per lane and load takes the address
+// unit twice as long
+template <int H, int XT, bool VEC2>
+__global__ __launch_bounds__((BlockShapeB<H, XT>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
+void ppo_block_bf16_kernel(BlockArgsB a) {
+  typedef BlockShapeB<H, XT> S;
+  constexpr int NW = S::NW, NWU = S::NWU, RS = S::RS, TEAMS = S::TEAMS, RT = S::RT, ROWS = S::ROWS, KH = S::KH, KX = S::KX;
+  typedef typename S::Rh Rh;
+  typedef typename S::Rx Rx;
+  typedef typename S::Ry Ry;
+  constexpr int MT = S::MT, MG = S::MG, NT = S::NT;
+  static_assert(MT * NT * NW == NWU * NWU && NT <= MG && (RS == 1 || TEAMS == 1), "the waves' tiles of dL/dW2 cover it");
+  constexpr int G1 = (XT + RS - 1) / RS;  // tiles of dL/dW1 per wave: t = RS g + rg
+  struct Team {
+    __attribute__((aligned(16))) __bf16 h1[ROWS * Rh::ROW], h2[ROWS * Rh::ROW];
+    __attribute__((aligned(16))) __bf16 dz[2][S::OWN_DZ ? ROWS * Rh::ROW : 1];  // else dL/dz1, dL/dz2 take the place of h1, h2
+    __attribute__((aligned(16))) __bf16 x[S::XBUF][ROWS * Rx::ROW];  // this tile's and, with two, the next one's
+    __attribute__((aligned(16))) __bf16 dy[ROWS * Ry::ROW];
+    __attribute__((aligned(16))) f32x4 st[ROWS];     // the rows' statistics, over the tiles
+    int64_t row[ROWS], obs[ROWS];                    // where the rows of a tile lie in the caller's arrays (-1: beyond the
+  };                                                 // end): row, first observation
+  __shared__ Team s_team[TEAMS];
+  __shared__ __attribute__((aligned(16))) float s_b3[32];
+  __shared__ __attribute__((aligned(16))) f32x4 s_g3[S::G3_LDS ? 2 * S::THREADS : 1];
+  __shared__ __attribute__((aligned(16))) u32x4 s_w1[NWU * KX * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 s_w3[KH * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 s_w3t[NWU * 64];
+  __shared__ float s_red[TEAMS > 1 ? (TEAMS - 1) * NW * 16 * 64 : 1];  // the other teams' copy of one gradient tile
+  const BlockNetB& nt = a.net[blockIdx.y];
+  const int gwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = gwave / NW, wave = gwave % NW;
+  Team& s = s_team[team];
+  int lane = threadIdx.x & 63;
+  const int O = nt.out, kx = (a.D + 2 + 15) / 16;
+  const int uw = wave % NWU, rg = wave / NWU, u0 = 32 * uw, ro = 32 * RT * rg;  // this wave's units and first row
+  __bf16 *const dz1 = S::OWN_DZ ? s.dz[0] : s.h1, *const dz2 = S::OWN_DZ ? s.dz[1] : s.h2;
+  const bool policy = nt.policy != 0;
+  const int mg = wave % MG, ng = wave / MG;  // this wave's part of dL/dW2
+
+  // rows: one team: the 64-row tiles of slice blockIdx.x; several: team t takes the 32-row tiles TEAMS g + t of the
+  // groups g = blockIdx.x, blockIdx.x + gridDim.x, ..., two at a time
+  const int64_t n_tiles = (a.R + 31) / 32, groups = (n_tiles + TEAMS - 1) / TEAMS;
+  const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_slice;
+  const int steps = TEAMS > 1 ? (int)(((groups - blockIdx.x + gridDim.x - 1) / gridDim.x + 1) / 2)
+                              : (int)((min(a.R - r_begin, a.rows_per_slice) + ROWS - 1) / ROWS);
+  // (the lanes of the team's last wave fill the table of step `st`)
+  auto fill_rows = [&](int st) {
+    if (wave != NW - 1) return;
+    int64_t r;
+    bool ok;
+    if constexpr (TEAMS > 1) {
+      const int64_t g = blockIdx.x + (int64_t)(2 * st + (lane >> 5)) * gridDim.x;
+      r = (g * TEAMS + team) * 32 + (lane & 31);
+      ok = g < groups && r < a.R;
+    } else {
+      r = r_begin + (int64_t)st * ROWS + lane;
+      ok = r < a.R && st < steps;  // (slices are whole tiles)
+    }
+    const int64_t p = ok ? a.sel.at(r) : 0;
+    s.row[lane] = ok ? p : -1;
+    s.obs[lane] = p * a.D;
+  };
+
+  for (int k = threadIdx.x; k < NWU * kx * 64; k += S::THREADS) s_w1[k] = nt.w1[k];
+  for (int k = threadIdx.x; k < KH * 64; k += S::THREADS) s_w3[k] = nt.w3[k];
+  for (int k = threadIdx.x; k < NWU * 64; k += S::THREADS) s_w3t[k] = nt.w3t[k];
+  if (threadIdx.x < 32) s_b3[threadIdx.x] = (int)threadIdx.x < O ? nt.b3[threadIdx.x] : 0.0f;
+  if (wave == 0) s.st[lane] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const u32x4 *w2 = nt.w2 + (size_t)uw * (KH + 1) * 64, *w2t = nt.w2t + (size_t)uw * KH * 64;
+  u32x4 rw2[S::RESIDENT ? KH + 1 : 1], rw2t[S::RESIDENT ? KH : 1];
+  if constexpr (S::RESIDENT) {
+#pragma unroll
+    for (int k = 0; k <= KH; ++k) rw2[k] = w2[k * 64 + lane];
+#pragma unroll
+    for (int k = 0; k < KH; ++k) rw2t[k] = w2t[k * 64 + lane];
+  }
+
+  f32x16 gW1[G1], gW2[MT][NT];
+  f32x4 gW3[2];  // outputs x the wave's units; the other half of the accumulator's registers stays zero
+#pragma unroll
+  for (int t = 0; t < G1; ++t) gW1[t] = zero16();
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) gW2[m][n] = zero16();
+  gW3[0] = gW3[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // (this thread's tiles; a place of its own)
+  auto g3_load = [&] {
+    if constexpr (S::G3_LDS)
+      for (int m = 0; m < 2; ++m) gW3[m] = s_g3[m * S::THREADS + 64 * gwave + lane];
+  };
+  auto g3_store = [&] {
+    if constexpr (S::G3_LDS)
+      for (int m = 0; m < 2; ++m) s_g3[m * S::THREADS + 64 * gwave + lane] = gW3[m];
+  };
+  g3_store();
+  float run2 = 0.0f, run3 = 0.0f;  // sums of dL/dz2 (this lane's unit of column tile mg) and, in the last wave, of dL/dy
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  // run + the sum over the rows of NF operands: every row of a product with ones is the column sum, so one register holds
+  // the accumulator between the tiles
+  auto add_rows = [&](float run, auto count, auto&& frag) {
+    f32x16 c;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) c[r] = run;
+#pragma unroll
+    for (int k = 0; k < count(); ++k) c = mma(ones, frag(k), c);
+    return c[0];
+  };
+
+  // observations: two columns per thread, RSTEP rows at a time; a row beyond the end reads as zero; columns D and D + 1
+  // are the constant 1 that the two parts of the bias meet
+  const int ttid = threadIdx.x % S::TEAM_THREADS;
+  int xc = 2 * (ttid % S::CW), xr = ttid / S::CW;
+  f32x2 xv[S::XN];
+  auto fetch_x = [&]() {  // (the row table holds the tile; always some row, so no branch around the loads)
+    const float *src = a.obs + (xc < a.D ? xc : 0), *src1 = a.obs + (xc + 1 < a.D ? xc + 1 : 0);
+#pragma unroll
+    for (int q = 0; q < S::XN; ++q) {
+      const int64_t at = s.obs[xr + S::RSTEP * q];
+      if constexpr (VEC2) xv[q] = *(const f32x2*)(src + at);
+      else xv[q] = f32x2{src[at], src1[at]};
+    }
+  };
+  auto store_x = [&](__bf16* to) {
+#pragma unroll
+    for (int q = 0; q < S::XN; ++q) {
+      const int t = xr + S::RSTEP * q;
+      const bool ok = s.row[t] >= 0;
+      f32x2 v;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) v[e] = xc + e < a.D ? (ok ? xv[q][e] : 0.0f) : xc + e < a.D + 2 ? 1.0f : 0.0f;
+      *(bf16x2*)(to + t * Rx::ROW + ((xc / 8) ^ Rx::swizzle(t)) * 8 + xc % 8) = __builtin_convertvector(v, bf16x2);
+    }
+  };
+  // acc[rt] += W act^T: weights from `tile(k)`, activations from LDS rows
+  auto product = [&](auto rows_of, auto most, f32x16 (&acc)[RT], const __bf16* act, int kn, auto&& tile) {
+    typedef decltype(rows_of) R;
+    const typename R::Place q = R::place(lane & 31, lane >> 5);
+#pragma unroll
+    for (int k = 0; k < most(); ++k) {
+      if (k >= kn) break;  // uniform
+      const bf16x8 w = __builtin_bit_cast(bf16x8, tile(k));
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = mma(w, *(const bf16x8*)(act + (ro + 32 * rt) * R::ROW + R::at(q, 2 * k)), acc[rt]);
+    }
+  };
+  auto clear = [&](f32x16 (&acc)[RT]) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[rt] = zero16();
+  };
+  // acc[rt] += bias tile * 1
+  auto add_bias = [&](f32x16 (&acc)[RT], const u32x4& w) {
+    bf16x8 one = {0, 0, 0, 0, 0, 0, 0, 0};  // the two parts of the bias sit at k slots 0 and 1 of h = 0
+    one[0] = (__bf16)(lane < 32 ? 1.0f : 0.0f);
+    one[1] = one[0];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[rt] = mma(__builtin_bit_cast(bf16x8, w), one, acc[rt]);
+  };
+  // streamed weights: a ring of WD tiles, filled ahead of the barrier in front of the product
+  u32x4 ring[S::RESIDENT ? 1 : S::WD];
+  auto ring_fill = [&](const u32x4* w) {
+    if constexpr (!S::RESIDENT) {
+#pragma unroll
+      for (int k = 0; k < S::WD; ++k) ring[k] = (w + k * 64)[(unsigned)lane];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // (n tiles: KH, or one more with the bias tile)
+  auto ring_product = [&](f32x16 (&acc)[RT], const __bf16* act, const u32x4* w, auto n) {
+    if constexpr (!S::RESIDENT) {
+      const typename Rh::Place q = Rh::place(lane & 31, lane >> 5);
+#pragma unroll
+      for (int k = 0; k < KH; ++k) {
+        const bf16x8 wk = __builtin_bit_cast(bf16x8, ring[k % S::WD]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = mma(wk, *(const bf16x8*)(act + (ro + 32 * rt) * Rh::ROW + Rh::at(q, 2 * k)), acc[rt]);
+        if (k + S::WD < n()) ring[k % S::WD] = (w + (k + S::WD) * 64)[(unsigned)lane];
+      }
+      if constexpr (n() > KH) add_bias(acc, ring[KH % S::WD]);
+    }
+  };
+  // registers 8 g .. 8 g + 7 of an accumulator: row lane % 32 of its tile, the lane's 8 units of the wave's 16-unit group
+  // g (chained order): piece u0 / 8 + 2 g + h of the row
+  auto activate = [&](const f32x16 (&acc)[RT], __bf16* to) {
+    const typename Rh::Place at = Rh::place(lane & 31, lane >> 5);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        f32x8 v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = fast_tanh(acc[rt][8 * g + e]);
+        *(bf16x8*)(to + (ro + 32 * rt) * Rh::ROW + Rh::at(at, u0 / 8 + 2 * g)) = __builtin_convertvector(v, bf16x8);
+      }
+  };
+  // to <- acc (1 - from^2)
+  auto derive = [&](const f32x16 (&acc)[RT], const __bf16* from, __bf16* to) {
+    const typename Rh::Place at = Rh::place(lane & 31, lane >> 5);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int o = (ro + 32 * rt) * Rh::ROW + Rh::at(at, u0 / 8 + 2 * g);
+        const bf16x8 hv = *(const bf16x8*)(from + o);
+        f32x8 v;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float f = (float)hv[e];
+          v[e] = acc[rt][8 * g + e] * (1.0f - f * f);
+        }
+        *(bf16x8*)(to + o) = __builtin_convertvector(v, bf16x8);
+      }
+  };
+  fill_rows(0);
+  __syncthreads();
+  fetch_x();
+  store_x(s.x[0]);
+
+  int buf = 0;
+#pragma unroll 1
+  for (int step = 0; step < steps; ++step) {
+    // (hidden from the compiler once per tile: the LDS addresses formed from them are cheap, and kept across tiles
+    // they would be spilled)
+    asm volatile("" : "+v"(lane), "+v"(xc), "+v"(xr));
+    const int i = lane & 31, h = lane >> 5, p16 = lane & 15, g16 = lane >> 4;
+    // the lane's part of the transposing reads: rows 8 h .., columns lane % 32
+    const int tr_row = 8 * h + p16 / 4, tr_piece = 2 * (g16 & 1) + (lane >> 1 & 1), tr_half = lane & 1;
+    const __bf16* s_x = s.x[buf];
+    __syncthreads();  // the observations are in
+    f32x16 acc[RT];
+    clear(acc);
+    product(Rx(), std::integral_constant<int, KX>(), acc, s_x, kx, [&](int k) { return s_w1[(uw * kx + k) * 64 + lane]; });
+    ring_fill(w2);
+    activate(acc, s.h1);
+    __syncthreads();
+    // what the loss reads: the first two waves take 32 rows each
+    int act = 0;
+    float lpo = 0.0f, adv = 0.0f, ret = 0.0f;
+    bool valid = false;
+    if (wave < ROWS / 32) {
+      const int64_t p = s.row[32 * wave + i];
+      valid = p >= 0;
+      if (valid && policy) {
+        act = a.actions[p];
+        lpo = a.logp_old[p];
+        adv = a.adv[p];
+      } else if (valid) {
+        ret = a.ret[p];
+      }
+    }
+    clear(acc);
+    if constexpr (S::RESIDENT) {
+      product(Rh(), std::integral_constant<int, KH>(), acc, s.h1, KH, [&](int k) { return rw2[k]; });
+      add_bias(acc, rw2[KH]);
+    } else {
+      // (of the two waves that share a SIMD one goes first, so that its tanh meets the other one's MFMAs)
+      if (wave < 4) __builtin_amdgcn_s_setprio(1);
+      ring_product(acc, s.h1, w2, std::integral_constant<int, KH + 1>());
+    }
+    activate(acc, s.h2);
+    if (!S::RESIDENT && wave < 4) __builtin_amdgcn_s_setprio(0);
+    __syncthreads();
+    // output layer and loss: register r of lane (i, h) <-> output 8 (r / 4) + 4 h + r % 4 of row i
+    if (wave < ROWS / 32) {
+      f32x16 out = bias_init(s_b3, h);
+      const typename Rh::Place at = Rh::place(i, h);
+#pragma unroll
+      for (int k = 0; k < KH; ++k)
+        out = mma(__builtin_bit_cast(bf16x8, s_w3[k * 64 + lane]), *(const bf16x8*)(s.h2 + 32 * wave * Rh::ROW + Rh::at(at, 2 * k)), out);
+      f32x8 dy = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+      f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (policy) {
+        float l[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const int r = 4 * (k >> 3) + (k & 3);
+          const float own = out[r], oth = __shfl_xor(own, 32);
+          l[k] = (((k >> 2) & 1) == h) ? own : oth;
+        }
+        float mx = l[0];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) mx = k < O ? fmaxf(mx, l[k]) : mx;
+        float z = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) z += k < O ? __expf(l[k] - mx) : 0.0f;
+        const float lse = mx + __logf(z);
+        float ent = 0.0f, logp = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const float lp = l[k] - lse;
+          ent -= k < O ? __expf(lp) * lp : 0.0f;
+          if (k == act) logp = lp;
+        }
+        const float rho = __expf(logp - lpo);
+        const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
+        const float un = rho * adv, cl = rc * adv;
+        const bool clipped = cl < un;
+        const float gl = clipped ? 0.0f : -adv * rho;
+        // each lane differentiates with respect to its own eight outputs
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const int k = 8 * (r / 4) + 4 * h + r % 4;
+          const float lp = out[r] - lse, pk = __expf(lp);
+          const float dlp = (k == act ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
+          dy[r] = (valid && k < O) ? (gl * dlp - a.ent_coef * dH) * a.inv_R : 0.0f;
+        }
+        st = f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo - logp};
+      } else if (h == 0) {
+        const float err = out[0] - ret;
+        dy[0] = valid ? a.vf_coef * 2.0f * err * a.inv_R : 0.0f;
+        st[0] = err * err;
+      }
+      *(bf16x8*)(s.dy + 32 * wave * Ry::ROW + Ry::at(Ry::place(i, h), 0)) = __builtin_convertvector(dy, bf16x8);
+      if (valid && h == 0) s.st[32 * wave + i] += st;
+    }
+    __syncthreads();
+    // dL/dW3 += dL/dy^T h2 (the wave's own units), dL/dz2
+    if (rg == 0 || wave == NW - 1) {
+      g3_load();
+      f32x16 c = zero16();
+#pragma unroll
+      for (int r = 0; r < 8; ++r) c[r] = gW3[r / 4][r % 4];
+      const typename Ry::Columns cy = Ry::columns(tr_row, tr_piece & 1, tr_half);
+      const typename Rh::Columns ch = Rh::columns(tr_row, tr_piece, tr_half);
+      const bf16x8 none = {0, 0, 0, 0, 0, 0, 0, 0};
+      bf16x8 fy[ROWS / 16];
+#pragma unroll
+      for (int k = 0; k < ROWS / 16; ++k) {
+        fy[k] = Ry::read(s.dy + 16 * k * Ry::ROW, cy, 0);
+        if (i >= 16) fy[k] = none;  // (a row holds 16 outputs)
+        if (rg == 0) c = mma(fy[k], Rh::read(s.h2 + 16 * k * Rh::ROW, ch, u0 / 8), c);
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) gW3[r / 4][r % 4] = c[r];
+      g3_store();
+      if (wave == NW - 1) run3 = add_rows(run3, std::integral_constant<int, ROWS / 16>(), [&](int k) { return fy[k]; });
+    }
+    {
+      const bf16x8 w = __builtin_bit_cast(bf16x8, s_w3t[uw * 64 + lane]);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = mma(w, *(const bf16x8*)(s.dy + (ro + 32 * rt) * Ry::ROW + Ry::at(Ry::place(i, h), 0)), zero16());
+    }
+    derive(acc, s.h2, dz2);
+    fill_rows(step + 1);
+    ring_fill(w2t);
+    __syncthreads();
+    // dL/dW2 += h1^T dL/dz2, and the bias sums of one of the wave's column tiles (each tile has one wave: ng, mg = t < NT)
+    {
+      const typename Rh::Columns cols = Rh::columns(tr_row, tr_piece, tr_half);
+#pragma unroll
+      for (int k = 0; k < ROWS / 16; ++k) {
+        const __bf16 *a1 = s.h1 + 16 * k * Rh::ROW, *a2 = dz2 + 16 * k * Rh::ROW;
+        bf16x8 fa[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) fa[m] = Rh::read(a1, cols, 4 * (MT * mg + m));
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+          const bf16x8 fb = Rh::read(a2, cols, 4 * (NT * ng + n));
+#pragma unroll
+          for (int m = 0; m < MT; ++m) gW2[m][n] = mma(fa[m], fb, gW2[m][n]);
+        }
+      }
+      if (mg < NT)
+        run2 = add_rows(run2, std::integral_constant<int, ROWS / 16>(),
+                        [&](int k) { return Rh::read(dz2 + 16 * k * Rh::ROW, cols, 4 * (NT * ng + mg)); });
+    }
+    // dL/dz1 = dL/dz2 W2^T times the derivative
+    clear(acc);
+    if constexpr (S::RESIDENT) {
+      product(Rh(), std::integral_constant<int, KH>(), acc, dz2, KH, [&](int k) { return rw2t[k]; });
+    } else {
+      ring_product(acc, dz2, w2t, std::integral_constant<int, KH>());
+    }
+    fetch_x();  // (behind the last of the weights: nothing waits for these loads before the end of the tile)
+    if constexpr (!S::OWN_DZ) __syncthreads();  // every wave is done with h1
+    derive(acc, s.h1, dz1);
+    if constexpr (RS > 1) __syncthreads();  // two waves hold the rows of a unit
+    else wave_lds_sync();
+    // dL/dW1 += x^T dL/dz1 (the wave's own units; input D is the constant 1: the bias gradient)
+    {
+      const typename Rh::Columns cols = Rh::columns(tr_row, tr_piece, tr_half);
+      const typename Rx::Columns colx = Rx::columns(tr_row, tr_piece, tr_half);
+#pragma unroll
+      for (int k = 0; k < ROWS / 16; ++k) {
+        const bf16x8 fb = Rh::read(dz1 + 16 * k * Rh::ROW, cols, u0 / 8);
+#pragma unroll
+        for (int g = 0; g < G1; ++g)
+          if (RS * g + rg < XT) gW1[g] = mma(Rx::read(s_x + 16 * k * Rx::ROW, colx, 4 * (RS * g + rg)), fb, gW1[g]);
+      }
+    }
+    if constexpr (S::XBUF == 1) __syncthreads();  // every wave is done with the observations
+    else buf ^= 1;
+    store_x(s.x[buf]);
+  }
+
+  // the teams' tiles are added in team order
+  auto join = [&](auto& g, auto n) {
+    if constexpr (TEAMS > 1) {
+      __syncthreads();  // the tile before has been read
+      if (team > 0) {
+#pragma unroll
+        for (int r = 0; r < n(); ++r) s_red[(((team - 1) * NW + wave) * 16 + r) * 64 + lane] = g[r];
+      }
+      __syncthreads();
+      if (team == 0) {
+#pragma unroll
+        for (int t = 0; t < TEAMS - 1; ++t)
+#pragma unroll
+          for (int r = 0; r < n(); ++r) g[r] += s_red[((t * NW + wave) * 16 + r) * 64 + lane];
+      }
+    }
+  };
+  constexpr std::integral_constant<int, 16> whole;
+  // this workgroup's copy of the gradient: register r of lane (i, h) <-> row 8 (r / 4) + 4 h + r % 4 of a tile, column i,
+  // where units are in the chained order
+  const int i = lane & 31, h = lane >> 5, ci = chained(i);
+  float* part = a.part + (int64_t)blockIdx.x * a.part_stride;
+#pragma unroll
+  for (int g = 0; g < G1; ++g) {
+    join(gW1[g], whole);
+    if (RS * g + rg >= XT) continue;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = 32 * (RS * g + rg) + 8 * (r / 4) + 4 * h + r % 4;
+      if (team == 0 && m < a.D) part[nt.oW1 + m * H + u0 + ci] = gW1[g][r];
+      if (team == 0 && m == a.D) part[nt.ob1 + u0 + ci] = gW1[g][r];
+    }
+  }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      join(gW2[mt][n], whole);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (team == 0)
+          part[nt.oW2 + (32 * (MT * mg + mt) + chained(8 * (r / 4) + 4 * h + r % 4)) * H + 32 * (NT * ng + n) + ci] = gW2[mt][n][r];
+    }
+  g3_load();
+  float last[10];  // dL/dW3, and the sums of dL/dz2 and dL/dy
+#pragma unroll
+  for (int r = 0; r < 8; ++r) last[r] = gW3[r / 4][r % 4];
+  last[8] = run2;
+  last[9] = run3;
+  join(last, std::integral_constant<int, 10>());
+  if (team == 0) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int o = chained(8 * (r / 4) + 4 * h + r % 4);
+      if (rg == 0 && o < O) part[nt.oW3 + (u0 + ci) * O + o] = last[r];
+    }
+    if (h == 0 && mg < NT) part[nt.ob2 + 32 * (NT * ng + mg) + ci] = last[8];
+    if (wave == NW - 1 && h == 0 && i < 16 && ci < O) part[nt.ob3 + ci] = last[9];
+  }
+  if (wave == 0) {  // (the last loss is behind a barrier)
+    f32x4 st = s.st[lane];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) st[q] += __shfl_xor(st[q], o);
+    const int bin = (blockIdx.x * TEAMS + team) % a.stat_bins;
+    if (lane == 0 && policy) {
+      atomicAdd(a.stats + 8 + bin, st[0]);
+#pragma unroll
+      for (int q = 1; q < 4; ++q) atomicAdd(a.stats + 8 + (q + 1) * a.stat_bins + bin, st[q]);
+    } else if (lane == 0) {
+      atomicAdd(a.stats + 8 + a.stat_bins + bin, st[0]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------- packing
+// dst[t][kt][lane] <- src[k * sk + n * sn] as bf16 (zero from nk, nn on), n = 32 t + lane % 32, k = 16 kt + 8 h + s
+// (linear) or 16 kt + 8 (s / 4) + 4 h + s % 4; with `bias`, k = nk and nk + 1 are its high and low part
+struct BlockPackJobB {
+  const float *src, *bias;
+  u32x4* dst;
+  int sk, sn, nk, nn;
+  int tiles, kt, linear;
+};
+struct BlockPackJobsB {
+  BlockPackJobB job[10];
+  int n;
+  float* clear;  // floats [0, n_clear) are set to zero (the statistics bins of the pass)
+  int n_clear;
+};
+hipError_t launch_block_pack_bf16(const BlockPackJobsB& jobs, int max_items, hipStream_t s);
+hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, unsigned slices, unsigned nets, hipStream_t s);
+
+#define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                              \
+  hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) {             \
+    const bool vec2 = in_dim % 2 == 0 && (uintptr_t)a.obs % 8 == 0;                                                \
+    const dim3 threads(BlockShapeB<HID, 1>::THREADS);                                                              \
+    if (in_dim <= 32 && vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, true>), grid, threads, 0, s, a);   \
+    else if (in_dim <= 32) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, false>), grid, threads, 0, s, a);     \
+    else if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, true>), grid, threads, 0, s, a);              \
+    else hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, false>), grid, threads, 0, s, a);                       \
+    return hipGetLastError();                                                                                      \
+  }
+
+}  // namespace msrl

@@ -12,8 +12,8 @@
 #include "../../include/msrl.h"
 #include "api_common.h"
 #include "learn_kernels.h"
-#include "learn_fused_aux.h"
 #include "learn_block.h"
+#include "learn_block_bf16.h"
 
 using namespace msrl;
 
@@ -30,7 +30,7 @@ struct NetBufs {
   void *wt3, *wn3;        // output layer: [32, H] and [H, 32]
   float* b3;              // output bias padded to 32
   void* h[MAX_LAYERS];    // activations [Rp, H]
-  void* ht[MAX_LAYERS];   // ... unit-major [H, Rp] (in the on-chip path: the tiled layout)
+  void* ht[MAX_LAYERS];   // ... unit-major [H, Rp]
   void* dz[MAX_LAYERS];   // dL/d pre-activation [Rp, H] (l >= 1; layer 0 is only needed unit-major)
   void* dzt[MAX_LAYERS];  // ... unit-major
   float* y;               // [Rp, 32]
@@ -60,17 +60,11 @@ struct msrl_learner {
   int64_t part_stride;   // n_params rounded up to 64 floats
   float* stats;          // [8 + 5 * STAT_BINS]: results, then the bins the loss kernel adds into
   size_t n_params;
-  // on-chip gradient pass (learn_fused.h): bf16 networks with a categorical policy of at most 16 actions
-  bool fused;            // ... for both networks
-  bool fused_policy;     // ... for the policy network only (centralised critic: its value network takes path (2))
-  int kt1;               // layer-1 tiles of the row kernel: inputs, plus the two bias parts, in tiles of 16
-  NetLayout fly;         // layout of one image of the packed weights
-  uint8_t* fpacked;      // per network: forward image, backward image
   int cus;               // compute units of the device
-  // fp32 gradient pass in one kernel (learn_block.h)
+  // gradient pass in one kernel (learn_block.h, learn_block_bf16.h)
   bool block;            // ... for both networks
   bool block_policy;     // ... for the policy network only (centralised critic)
-  f32x4* bpacked;        // operand tiles of the networks it handles
+  u32x4* bpacked;        // operand tiles of the networks it handles
   float* bsum;           // [BSUM_MAX_ROWS / 32 at most][4 H] bias-gradient sums over 32 rows (Gaussian policies)
 };
 
@@ -88,9 +82,10 @@ namespace {
 // of the layer kernels, bit for bit); above, each slice keeps one running sum
 constexpr int64_t BSUM_MAX_ROWS = 65536;
 
-// 16-byte tiles of a network's packed weights (learn_block.h)
-size_t block_tiles(int in, int H, int out) {
-  const size_t T = (size_t)H / 32, KH = (size_t)H / 8;
+// tiles (64 x 16 bytes) of a network's packed weights (learn_block.h, learn_block_bf16.h)
+size_t block_tiles(bool bf16, int in, int H, int out) {
+  const size_t T = (size_t)H / 32, KH = (size_t)H / (bf16 ? 16 : 8);
+  if (bf16) return T * ((in + 2 + 15) / 16) + T * (KH + 1) + KH + T + T * KH;
   return T * ((in + 7) / 8) + 2 * T * KH + (size_t)((out + 15) / 16) * (H / 16) + T * ((out + 7) / 8);
 }
 
@@ -391,153 +386,6 @@ int grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel
   return MSRL_OK;
 }
 
-static_assert(ROWS_STAT_BINS == STAT_BINS, "the row kernel and the loss kernel share the bins");
-
-// The same gradient with the activations kept on chip: weights packed into MFMA tiles, one row
-// kernel launch per network (forward, loss, backward through the activations; writes the tiled
-// unit-major operands), then the weight and bias gradients from those.
-int fused_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel, const float* obs,
-                    const void* actions, const float* logp_old, const float* adv, const float* ret,
-                    const msrl_ppo_cfg* c, float* grad, hipStream_t s, const AdamArgs* adam, int nets = 3,
-                    bool clear = true, bool finish = true) {
-  // nets: bit n set = network n is handled here (1: the policy network only; the value network's pass
-  // through device memory writes its own part of grad and adds to the same statistics bins).  clear /
-  // finish: zero the bins first / add the bins up at the end
-  const int D = L->pol.in_dim, H = L->pol.hidden, kt1 = L->kt1;
-  const NetLayout& ly = L->fly;
-  const float* b3p[2];
-  {
-    LearnPackJobs jobs;
-    memset(&jobs, 0, sizeof(jobs));
-    if (clear) {  // the statistics bins are zeroed on the way
-      jobs.clear = L->stats;
-      jobs.n_clear = 8 + 5 * STAT_BINS;
-    }
-    const float* P = params;
-    int max_items = 0;
-    for (int n = 0; n < 2; ++n) {
-      if (!((nets >> n) & 1)) continue;  // (only ever the value network, the last one: P needs no advance)
-      const int O = n == 0 ? L->pol.out_dim : 1;
-      const float* W1 = P;
-      const float* b1 = W1 + (size_t)D * H;
-      const float* W2 = b1 + H;
-      const float* b2 = W2 + (size_t)H * H;
-      const float* W3 = b2 + H;
-      b3p[n] = W3 + (size_t)H * O;
-      uint8_t* fwd = L->fpacked + (size_t)n * 2 * ly.bytes;
-      uint8_t* bwd = fwd + ly.bytes;
-      auto job = [&](const float* src, const float* bias, uint8_t* dst, int n_in, int n_out, int64_t s_in,
-                     int64_t s_out, int bias_index, int nuc, int kt, int group, int stride, int slot, int linear) {
-        LearnPackJob& j = jobs.job[jobs.n++];
-        j.src = src; j.bias = bias; j.dst = (u32x4*)dst; j.n_in = n_in; j.n_out = n_out; j.s_in = s_in; j.s_out = s_out;
-        j.bias_index = bias_index; j.nuc = nuc; j.kt = kt; j.group = group; j.chunk_stride = stride; j.slot_base = slot;
-        j.linear = linear;
-        if (nuc * kt * 64 > max_items) max_items = nuc * kt * 64;
-      };
-      // forward image: layer 1 (bias parts at inputs D, D + 1), chunk blocks of layer 2 (+ bias tile), layer 3
-      // next to the chunk it consumes and once more in the block after it
-      job(W1, b1, fwd + ly.w1, D, H, H, 1, D, ly.nuc, ly.kt1, ly.kt1, ly.kt1, 0, 1);
-      job(W2, b2, fwd + ly.chunks, H, H, H, 1, H, ly.nuc, ly.kt2 + 1, ly.kt2 + 1, ly.chunk_tiles, 0, 0);
-      job(W3, nullptr, fwd + ly.chunks, H, O, O, 1, 0, 1, ly.kt2, ly.tpc, ly.chunk_tiles, ly.kt2 + 1 + ly.tpc, 0);
-      if (ly.nuc > 1)
-        job(W3, nullptr, fwd + ly.chunks + ly.chunk_bytes, H, O, O, 1, 0, 1, ly.kt2 - ly.tpc, ly.tpc, ly.chunk_tiles,
-            ly.kt2 + 1, 0);
-      // backward image: W3 with the layer-2 units as tile rows (in the layer-1 area), W2 with the layer-1
-      // units as tile rows (chunk blocks)
-      job(W3, nullptr, bwd + ly.w1, O, H, 1, O, 0, ly.nuc, 1, 1, 1, 0, 0);
-      job(W2, nullptr, bwd + ly.chunks, H, H, 1, H, 0, ly.nuc, ly.kt2, ly.kt2, ly.chunk_tiles, 0, 0);
-      P = b3p[n] + O;
-    }
-    hipLaunchKernelGGL(learn_pack_kernel, dim3((unsigned)((max_items + 255) / 256), (unsigned)jobs.n), dim3(256), 0, s,
-                       jobs);
-    LTRY(hipGetLastError());
-  }
-  const int64_t n_tiles = (R + 31) / 32;
-  const int64_t groups = (n_tiles + rows_waves(H) - 1) / rows_waves(H);
-  const int64_t resident = (int64_t)L->cus * rows_workgroups_per_cu(H);
-  unsigned grid = (unsigned)(groups < resident ? groups : resident);
-  if (H <= 64 && grid > (unsigned)L->part_slices) grid = (unsigned)L->part_slices;  // one copy of the gradient per workgroup
-  // 64-unit networks: the row kernel forms the weight gradients itself, one copy per workgroup
-  const bool small = H <= 64;
-  Reducer red;
-  size_t off = 0;
-  for (int n = 0; n < 2; ++n) {
-    const int O = n == 0 ? L->pol.out_dim : 1;
-    const size_t oW1 = off, ob1 = oW1 + (size_t)D * H, oW2 = ob1 + H, ob2 = oW2 + (size_t)H * H, oW3 = ob2 + H,
-                 ob3 = oW3 + (size_t)H * O;
-    off += net_count(D, H, O);
-    if (!((nets >> n) & 1)) continue;
-    NetBufs& b = L->net[n];
-    RowsArgs a;
-    memset(&a, 0, sizeof(a));
-    if (small) {
-      a.part = L->part; a.part_stride = L->part_stride;
-      a.oW1 = (int32_t)oW1; a.ob1 = (int32_t)ob1; a.oW2 = (int32_t)oW2; a.ob2 = (int32_t)ob2; a.oW3 = (int32_t)oW3;
-      a.ob3 = (int32_t)ob3;
-      const size_t offs[6] = {oW1, ob1, oW2, ob2, oW3, ob3};
-      const size_t counts[6] = {(size_t)D * H, (size_t)H, (size_t)H * H, (size_t)H, (size_t)H * O, (size_t)O};
-      for (int q = 0; q < 6; ++q) red.add(offs[q], counts[q], (int)grid);
-    }
-    a.packed = L->fpacked + (size_t)n * 2 * ly.bytes;
-    a.b3 = b3p[n];
-    a.obs = obs; a.actions = actions; a.logp_old = logp_old; a.adv = adv; a.ret = ret;
-    a.R = R; a.n_tiles = n_tiles; a.D = D; a.out_dim = L->pol.out_dim;
-    a.obs_vec4 = (D % 4 == 0 && ((uintptr_t)obs & 15) == 0) ? 1 : 0;
-    a.sel = sel;
-    a.clip = c->clip; a.vf_coef = c->vf_coef; a.ent_coef = c->ent_coef; a.inv_R = 1.0f / (float)R;
-    a.xt = (__bf16*)L->xt; a.h1t = (__bf16*)b.ht[0]; a.h2t = (__bf16*)b.ht[1]; a.dz2t = (__bf16*)b.dzt[1];
-    a.dz1t = (__bf16*)b.dzt[0]; a.dyt = (__bf16*)b.dyt;
-    a.stats = L->stats;
-    hipError_t e = H == 64 ? launch_ppo_rows_h64(kt1, n, a, grid, s)
-                 : H == 128 ? launch_ppo_rows_h128(kt1, n, a, grid, s)
-                            : launch_ppo_rows_h256(kt1, n, a, grid, s);
-    LTRY(e);
-  }
-  LTRY(hipGetLastError());
-  if (small) {
-    LTRY(red.launch(L, grad, adam, finish ? L->stats : nullptr, s));
-    return MSRL_OK;
-  }
-  off = 0;
-  // Slices of row tiles: two compute units' share per slice, i.e. half as many workgroups per contraction as
-  // compute units (the six contractions of a pass run two launches deep, so the chip stays busy).  Every
-  // slice stores a copy of its result; the copies are added up in slice order afterwards.
-  int tps = (int)((n_tiles + L->cus - 1) / L->cus);
-  tps = (tps + 1) / 2 * 2 * 2;
-  while ((n_tiles + tps - 1) / tps > L->part_slices) tps *= 2;
-  const unsigned slices = (unsigned)((n_tiles + tps - 1) / tps);
-  // the contractions of both networks in two launches: the four with a hidden layer's width of columns,
-  // and the two of the output layers
-  WgradTJobs wide, narrow;
-  wide.n = narrow.n = 0;
-  for (int n = 0; n < 2; ++n) {
-    if (!((nets >> n) & 1)) continue;  // (the value network, behind the policy network's gradient)
-    NetBufs& b = L->net[n];
-    const int O = n == 0 ? L->pol.out_dim : 1;
-    const size_t oW1 = off, ob1 = oW1 + (size_t)D * H, oW2 = ob1 + H, ob2 = oW2 + (size_t)H * H, oW3 = ob2 + H,
-                 ob3 = oW3 + (size_t)H * O;
-    auto wg = [&](const void* A, int UA, int M, const void* B, int UB, int N, size_t oC, int64_t ldc, size_t obias) {
-      WgradTArgs& g = N <= 32 ? narrow.job[narrow.n++] : wide.job[wide.n++];
-      memset(&g, 0, sizeof(g));
-      g.A = (const __bf16*)A; g.B = (const __bf16*)B; g.UA = UA; g.UB = UB; g.M = M; g.N = N; g.m_out = M;
-      g.n_tiles = n_tiles; g.tiles_per_slice = tps; g.C = L->part + oC; g.ldc = ldc; g.bias = L->part + obias;
-      g.slice_stride = L->part_stride;
-      red.add(oC, (size_t)M * ldc, (int)slices);
-      red.add(obias, (size_t)N, (int)slices);
-    };
-    wg(b.ht[1], H, H, b.dyt, 16, O, oW3, O, ob3);
-    wg(b.ht[0], H, H, b.dzt[1], H, H, oW2, H, ob2);
-    wg(L->xt, 16 * kt1, D, b.dzt[0], H, H, oW1, H, ob1);
-    off += net_count(D, H, O);
-  }
-  if (wide.n)
-    hipLaunchKernelGGL((wgrad_tiled_kernel<8, 2>), dim3(slices, (unsigned)wide.n), dim3(512), 0, s, wide);
-  if (narrow.n) hipLaunchKernelGGL((wgrad_tiled_kernel<1, 4>), dim3(slices, (unsigned)narrow.n), dim3(512), 0, s, narrow);
-  LTRY(hipGetLastError());
-  LTRY(red.launch(L, grad, adam, finish ? L->stats : nullptr, s));  // (the bins are complete: the row kernels ran)
-  return MSRL_OK;
-}
-
 // The same gradient for fp32 networks of two hidden layers: one kernel for both networks, a workgroup per network and
 // slice of the rows, with the weights packed in front and the slices' copies added up behind it.
 int block_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel, const float* obs,
@@ -575,7 +423,7 @@ int block_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSe
   jobs.n_clear = 8 + 5 * STAT_BINS;
   int max_items = jobs.n_clear, used = 0;
   size_t off = 0;
-  f32x4* dst = L->bpacked;
+  f32x4* dst = (f32x4*)L->bpacked;
   int64_t per_slice = 2048;  // rows per slice of the output layer's bias gradient
   if ((R + per_slice - 1) / per_slice > L->part_slices) per_slice = (R + L->part_slices - 1) / L->part_slices;
   const unsigned bias_slices = (unsigned)((R + per_slice - 1) / per_slice);
@@ -629,6 +477,75 @@ int block_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSe
   return MSRL_OK;
 }
 
+// ... and for bf16 networks with a categorical policy
+int block_bf16_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel, const float* obs,
+                         const void* actions, const float* logp_old, const float* adv, const float* ret,
+                         const msrl_ppo_cfg* c, float* grad, hipStream_t s, const AdamArgs* adam, int nets = 3,
+                         bool finish = true) {
+  const int D = L->pol.in_dim, H = L->pol.hidden;
+  // 64 units: up to a workgroup per compute unit, each over every fourth row tile for each of its four teams.  Wider:
+  // slices of whole 128 rows, half as many as compute units for large minibatches (two networks side by side).
+  const int64_t n_tiles = (R + 31) / 32;
+  int64_t slices;
+  BlockArgsB a;
+  memset(&a, 0, sizeof(a));
+  if (H == 64) {
+    slices = (n_tiles + 3) / 4;
+    if (slices > L->cus) slices = L->cus;
+    if (slices > L->part_slices) slices = L->part_slices;
+  } else {
+    int64_t tiles = (n_tiles + L->cus - 1) / L->cus;
+    tiles = (tiles + 1) / 2 * 4;
+    while ((n_tiles + tiles - 1) / tiles > L->part_slices) tiles *= 2;
+    slices = (n_tiles + tiles - 1) / tiles;
+    a.rows_per_slice = 32 * tiles;
+  }
+  a.obs = obs; a.actions = (const int32_t*)actions; a.logp_old = logp_old; a.adv = adv; a.ret = ret; a.sel = sel; a.R = R;
+  a.D = D;
+  a.clip = c->clip; a.vf_coef = c->vf_coef; a.ent_coef = c->ent_coef; a.inv_R = 1.0f / (float)R;
+  a.part = L->part; a.part_stride = L->part_stride; a.stats = L->stats; a.stat_bins = STAT_BINS;
+  Reducer red;
+  BlockPackJobsB jobs;
+  memset(&jobs, 0, sizeof(jobs));
+  jobs.clear = L->stats;
+  jobs.n_clear = 8 + 5 * STAT_BINS;
+  int max_items = jobs.n_clear, used = 0;
+  size_t off = 0;
+  u32x4* dst = (u32x4*)L->bpacked;
+  for (int n = 0; n < 2; ++n) {
+    const int O = n == 0 ? L->pol.out_dim : 1;
+    const size_t oW1 = off, ob1 = oW1 + (size_t)D * H, oW2 = ob1 + H, ob2 = oW2 + (size_t)H * H, oW3 = ob2 + H,
+                 ob3 = oW3 + (size_t)H * O;
+    off += net_count(D, H, O);
+    if (!((nets >> n) & 1)) continue;
+    BlockNetB& b = a.net[used++];
+    auto pack = [&](size_t src, int sk, int sn, int nk, int nn, int tiles, int kt, int linear, const float* bias) -> const u32x4* {
+      BlockPackJobB& j = jobs.job[jobs.n++];
+      j.src = params + src; j.bias = bias; j.dst = dst; j.sk = sk; j.sn = sn; j.nk = nk; j.nn = nn; j.tiles = tiles; j.kt = kt;
+      j.linear = linear;
+      if (tiles * kt * 64 > max_items) max_items = tiles * kt * 64;
+      const u32x4* at = dst;
+      dst += (size_t)tiles * kt * 64;
+      return at;
+    };
+    b.w1 = pack(oW1, H, 1, D, H, H / 32, (D + 2 + 15) / 16, 1, params + ob1);
+    b.w2 = pack(oW2, H, 1, H, H, H / 32, H / 16 + 1, 0, params + ob2);
+    b.w3 = pack(oW3, O, 1, H, O, 1, H / 16, 0, nullptr);
+    b.w3t = pack(oW3, 1, O, O, H, H / 32, 1, 0, nullptr);
+    b.w2t = pack(oW2, 1, H, H, H, H / 32, H / 16, 0, nullptr);
+    b.b3 = params + ob3;
+    b.oW1 = (int32_t)oW1; b.ob1 = (int32_t)ob1; b.oW2 = (int32_t)oW2; b.ob2 = (int32_t)ob2; b.oW3 = (int32_t)oW3;
+    b.ob3 = (int32_t)ob3;
+    b.out = O;
+    b.policy = n == 0;
+    red.add(oW1, off - oW1, (int)slices);  // (every tensor has the same slices: one job)
+  }
+  LTRY(launch_block_pack_bf16(jobs, max_items, s));
+  LTRY(launch_ppo_block_bf16(H, D, a, (unsigned)slices, (unsigned)used, s));
+  LTRY(red.launch(L, grad, adam, finish ? L->stats : nullptr, s));
+  return MSRL_OK;
+}
+
 int check_learner_args(const char* who, msrl_learner* L, const void* params, int64_t R, const void* obs,
                        const void* actions, const void* logp_old, const void* adv, const void* ret,
                        const msrl_row_select* rows, const msrl_ppo_cfg* c) {
@@ -670,22 +587,16 @@ int grad_rows(msrl_learner* L, const float* params, int64_t R, int64_t row0, con
               const float* obs, const void* actions, const float* logp_old, const float* adv, const float* ret,
               const msrl_ppo_cfg* cfg, float* grad, hipStream_t s, const AdamArgs* adam = nullptr) {
   const RowSel sel = selection(rows, row0);
-  if (L->block) return block_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam);
   if (L->block_policy) {
-    int rc = block_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam, 1, false);
-    if (rc == MSRL_OK) rc = grad_pass<false>(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam, 2, true);
-    return rc;
-  }
-  if (L->fused) return fused_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam);
-  if (L->fused_policy) {
-    // Centralised critic: the policy network on chip, then the value network (one row per group, a wide
-    // first layer) through device memory; it adds its part of grad and of the statistics.  (Running the
-    // second pass on a stream of its own beside the first was measured: no gain, the row kernel's
-    // workgroups leave no LDS for the value network's kernels to start beside them.)
-    // (With an Adam step folded in, each pass steps its own network's parameters: the value network's pass reads
-    // none of the policy network's.)
-    int rc = fused_grad_pass(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam, 1, true, false);
-    if (rc == MSRL_OK) rc = grad_pass<true>(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam, 2, true);
+    // (Centralised critic: the policy network in one kernel, then the value network (one row per group, a wide first
+    // layer) through device memory; it adds its part of grad and of the statistics.  With an Adam step folded in, each
+    // pass steps its own network's parameters: the value network's pass reads none of the policy network's.)
+    const int mine = L->block ? 3 : 1;
+    int rc = (L->bf16 ? block_bf16_grad_pass : block_grad_pass)(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad,
+                                                                s, adam, mine, L->block);
+    if (rc == MSRL_OK && !L->block)
+      rc = (L->bf16 ? grad_pass<true> : grad_pass<false>)(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s,
+                                                          adam, 2, true);
     return rc;
   }
   return L->bf16 ? grad_pass<true>(L, params, R, sel, obs, actions, logp_old, adv, ret, cfg, grad, s, adam)
@@ -734,16 +645,11 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
   L->n_params = net_count(policy->in_dim, policy->hidden, policy->out_dim, L->layers) +
                 net_count(L->G * policy->in_dim, policy->hidden, 1, L->layers);
   const size_t H = (size_t)policy->hidden, Rp = (size_t)L->Rp, Dp = (size_t)L->Dp, e = L->esz;
-  L->kt1 = policy->in_dim + 2 <= 32 ? 2 : 4;
-  L->fused_policy = L->bf16 && policy->dist == MSRL_CATEGORICAL && policy->out_dim <= 16 && policy->in_dim + 2 <= 64 &&
-                    (policy->hidden == 64 || policy->hidden == 128 || policy->hidden == 256) && L->layers == 2 &&
-                    path != MSRL_LEARNER_PATH_DEVICE_MEMORY;
-  L->fused = L->fused_policy && L->G == 1;
-  L->block_policy = !L->bf16 && policy->in_dim <= 64 &&
-                    (policy->hidden == 64 || policy->hidden == 128 || policy->hidden == 256) && L->layers == 2 &&
-                    path != MSRL_LEARNER_PATH_DEVICE_MEMORY;
+  L->block_policy = (policy->hidden == 64 || policy->hidden == 128 || policy->hidden == 256) && L->layers == 2 &&
+                    path != MSRL_LEARNER_PATH_DEVICE_MEMORY &&
+                    (L->bf16 ? policy->in_dim <= 62 && policy->dist == MSRL_CATEGORICAL && policy->out_dim <= 16
+                             : policy->in_dim <= 64);
   L->block = L->block_policy && L->G == 1;
-  L->fly = net_layout(16 * L->kt1 - 1, policy->hidden, true);
   int rc = MSRL_OK;
   {
     int dev = 0, cus = 0;
@@ -755,13 +661,14 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
   }
   auto A = [&](void** p, size_t bytes) { if (rc == MSRL_OK) rc = dev_alloc((uint8_t**)p, bytes); };
   if (L->block_policy) {
-    A((void**)&L->bpacked, (block_tiles(policy->in_dim, policy->hidden, policy->out_dim) +
-                            (L->block ? block_tiles(policy->in_dim, policy->hidden, 1) : 0)) * 64 * sizeof(f32x4));
+    A((void**)&L->bpacked, (block_tiles(L->bf16, policy->in_dim, policy->hidden, policy->out_dim) +
+                            (L->block ? block_tiles(L->bf16, policy->in_dim, policy->hidden, 1) : 0)) * 64 * sizeof(f32x4));
     if (policy->dist == MSRL_DIAG_GAUSSIAN) A((void**)&L->bsum, (size_t)((L->Rp < BSUM_MAX_ROWS ? L->Rp : BSUM_MAX_ROWS) / 32) * 4 * H * sizeof(float));
   }
-  if (!L->block_policy) A(&L->xc, Rp * Dp * e);
-  if (!L->block_policy) A(&L->xt, (L->fused_policy && (size_t)(16 * L->kt1) > Dp ? (size_t)(16 * L->kt1) : Dp) * Rp * e);
-  if (L->fused_policy) A((void**)&L->fpacked, 4 * L->fly.bytes);
+  if (!L->block_policy) {
+    A(&L->xc, Rp * Dp * e);
+    A(&L->xt, Dp * Rp * e);
+  }
   if (L->G > 1) {
     A(&L->xcv, (Rp / L->G + 128) * (size_t)L->Dvp * e);
     A(&L->xtv, (size_t)L->Dvp * Rp * e);
@@ -791,8 +698,8 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
   // a contraction over the rows is split into at most this many slices (the block kernel's of narrow networks, several
   // workgroups to a compute unit, are smaller)
   {
-    const bool narrow = L->block_policy && policy->hidden <= 64;
-    const int64_t most = narrow ? 512 : 256, by_rows = L->block_policy ? L->Rp / 32 : L->Rp / 128 + 1;
+    const bool block_f32 = L->block_policy && !L->bf16, narrow = block_f32 && policy->hidden <= 64;
+    const int64_t most = narrow ? 512 : 256, by_rows = block_f32 ? L->Rp / 32 : L->Rp / 128 + 1;
     L->part_slices = (int)(by_rows < most ? by_rows : most);
   }
   L->part_stride = round_up((int64_t)L->n_params, 64);
@@ -808,7 +715,7 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
 
 void msrl_learner_destroy(msrl_learner* L) {
   if (!L) return;
-  void* ptrs[] = {L->xc, L->xt, L->xcv, L->xtv, L->grad, L->part, L->stats, L->fpacked, L->bpacked, L->bsum};
+  void* ptrs[] = {L->xc, L->xt, L->xcv, L->xtv, L->grad, L->part, L->stats, L->bpacked, L->bsum};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int n = 0; n < 2; ++n) {
