@@ -527,8 +527,37 @@ next_row_block:
   };
   float checksum[NB] = {};      // PHASE_MLP only
 
+  // Waves whose rows hold no env (few envs for the chip: ceil(E / CUs) per workgroup).  Where two waves share a SIMD
+  // such a wave would take half the issue slots of one that has rows, so it only does its part of what the workgroup
+  // does together: the waits, its copies of the weights, its arrays of the collected outputs; the same barriers in the
+  // same order as in the steps below, 2 stages_per_net of them per evaluation of the networks.  A workgroup with at
+  // most four waves at work then has one per SIMD: 32 steps of 10 agents with bf16 networks of 256 units take 526 us with
+  // one wave at work, 632 with four, 838 with five and 934 with eight.  8191 envs, six hidden layers, 50 steps (six of
+  // eight waves): 9.67 -> 8.58 ms.  (Kernels of up to four waves have one per SIMD as they are; PHASE_ACT_DEEP would spill.)
+  constexpr bool IDLE_LOOP = WAVES > 4 && (PHASE == PHASE_ALL || PHASE == PHASE_DEEP || PHASE == PHASE_ACT);
+  static_assert(!IDLE_LOOP || Stream::STAGES_PER_NET > 1, "a network of one stage has one more barrier");
+  if constexpr (IDLE_LOOP) {
+    if (live_rows == 0) {
+      const int stages = 2 * ws.stages_per_net;
+#pragma unroll 1
+      for (int t = 0; t <= (ACT ? 0 : a.T); ++t) {
+#pragma unroll 1
+        for (int s = 0; s < stages; ++s) {
+          ws.wait_oldest();
+          if (FULL && t > 0 && s == ws.stages_per_net) flush(t - 1, 0x1f);
+          const int next = s + Stream::AHEAD;
+          ws.issue(next >= stages ? next - stages : next, (gs + Stream::AHEAD) % NBUF);
+          ++gs;
+        }
+      }
+    }
+  }
+  // with a centralised critic a wave without rows computes its chunk of the critic and nothing else (2037 envs x 10, 50
+  // steps, three of eight waves: 970 -> 819 us)
+  const bool idle = CENTRAL && WAVES > 4 && live_rows == 0;
+
   long long clk0 = 0;
-  for (int t = 0; t <= a.T; ++t) {
+  for (int t = IDLE_LOOP && live_rows == 0 ? a.T + 1 : 0; t <= a.T; ++t) {
     const int par = SPLIT ? (t & 1) : 0;
     auto stamp = [&](int i) {
       if constexpr (PHASE == PHASE_CLOCKS) {
@@ -580,7 +609,7 @@ next_row_block:
     // ---------------- observation rows: build, store (through the staging area), convert to MFMA operands
     Op x[NB][KT1 * Net::PT];
     f32x8 f[KT1];
-    {
+    if (!idle) {
       constexpr int q = 0;
       auto pair_value = [&](int gp) -> float2 {
         // pair 0: v, 1: p, [2, 2+L): landmark - p, [2+L, 1+L+N): other agent - p, rest 0
@@ -828,7 +857,7 @@ next_row_block:
         for (int q = 0; q < NB; ++q) out_p[q] = out_v[q] = out[q];
       } else if constexpr (CENTRAL) {
         // ---------------- policy network through the window, the critic riding on its stages
-        Net::layer1(&s_l1[0][0] + lane, x, h1);
+        if (!idle) Net::layer1(&s_l1[0][0] + lane, x, h1);
         f32x16 acc[NB];
         {
           const f32x16 b = Net::template out_init<OUTS>(s_b3[0], h);
@@ -877,11 +906,15 @@ next_row_block:
           const int nbuf = (gs + Stream::AHEAD) % NBUF;
           const u32x4* tiles = ws.tiles(gs % NBUF, 0);
           auto tick = [&](int kt) { ws.spread(next, nbuf, kt, Net::KT2); };
-          if (sc == 0)
-            Net::template layer2_chunk<false, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
-          else
-            Net::template layer2_chunk<true, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
-          if (sc == SPN - 1) Net::template layer2_drain<OUTS>(tiles, acc, out_p, h, 16);
+          if (idle) {
+            ws.issue(next, nbuf);
+          } else {
+            if (sc == 0)
+              Net::template layer2_chunk<false, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
+            else
+              Net::template layer2_chunk<true, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
+            if (sc == SPN - 1) Net::template layer2_drain<OUTS>(tiles, acc, out_p, h, 16);
+          }
           ++gs;
         }
         Net::template out_finish<OUTS>(out_p, s_b3[0], h);
@@ -964,6 +997,10 @@ next_row_block:
         if (h == 0 && valid[q] && (!SPLIT || role == 1)) s_out[par][0][wrow0 + row[q]] = out_v[q][0];
     }
     if (!ACT && t == a.T) break;
+    if (idle) {
+      if constexpr (ACT) break;
+      continue;
+    }
 
     // ---------------- sampling, physics
     float rew_term[NB];
