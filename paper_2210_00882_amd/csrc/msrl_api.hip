@@ -342,20 +342,34 @@ bool find_kernel(const msrl_env_cfg& env, const msrl_policy_cfg& pol, int phase,
   return found;
 }
 
-// Envs per workgroup of a launch of `kernel`.  Every workgroup runs all T steps, so the launch takes
-// ceil(blocks / CUs) rounds.  The block is shrunk to the smallest size that needs no more rounds than
-// the largest one: equal work per workgroup instead of a short last round.  (Rounds are counted per CU
-// even where several workgroups fit one: they would share its SIMDs, and a wave with fewer rows costs
-// the same.)  Computed per launch: the kernels of a state (full rollout, actor fragment, env step,
-// measurement variants) differ in the row blocks a workgroup holds.
-int envs_per_block(const KernelEntry& kernel, int64_t num_envs, int cus) {
+// Workgroups of a launch of `kernel` and their envs: `full` ones of the largest size, then ones of `envs`.
+// Every workgroup runs all T steps, so the launch takes ceil(blocks / CUs) rounds, at least as many as full
+// workgroups need.  Two ways to spend them:
+//   equal work per workgroup: the smallest size that needs no more rounds.  (Rounds are counted per CU even
+//     where several workgroups fit one: they would share its SIMDs, and a wave with fewer rows costs the same.)
+//   full workgroups and a smaller last round, where that one has at most four of eight waves at work: one
+//     per SIMD (two_block_sizes).  A round costs by its waves at work, measured as us for 32 steps of 10 agents, bf16
+//     networks of 256 units: 1: 526, 2: 550, 4: 632, 5: 838, 6: 849, 8: 934.  8 + 1 against
+//     5 + 5: 1573 -> 1398 us, 8 + 4 against 6 + 6: 1656 -> 1550; fp32 of 128 units, 6 agents: 1649 -> 1463, 1687 -> 1562;
+//     centralised critic 1354 -> 1282, 1427 -> 1372.  A last round of five waves and more saves nothing.
+// Computed per launch: the kernels of a state (full rollout, actor fragment, env step, measurement variants) differ
+// in the row blocks a workgroup holds.
+struct Blocks {
+  int envs, full;
+  int64_t total;
+};
+Blocks plan_blocks(const KernelEntry& kernel, int64_t num_envs, int cus) {
   const int64_t max_epb = (int64_t)kernel.envs_per_wave * (kernel.row_waves ? kernel.row_waves : kernel.waves);
   const int64_t blocks_max = (num_envs + max_epb - 1) / max_epb;
   const int64_t rounds = (blocks_max + cus - 1) / cus;
-  int64_t epb = (num_envs + rounds * cus - 1) / (rounds * cus);
+  const int64_t full = (rounds - 1) * cus, rest = num_envs - full * max_epb;
+  int64_t epb = (rest + cus - 1) / cus;
+  if (kernel.kind == MSRL_ENV_PARTICLE && two_block_sizes(kernel.waves, kernel.phase) && full > 0 && epb <= 4 * kernel.envs_per_wave)
+    return {(int)epb, (int)full, full + (rest + epb - 1) / epb};
+  epb = (num_envs + rounds * cus - 1) / (rounds * cus);
   if (epb < 1) epb = 1;
   if (epb > max_epb) epb = max_epb;
-  return (int)epb;
+  return {(int)epb, 0, (num_envs + epb - 1) / epb};
 }
 
 // params may be null for the variants that run no network; obs_in / actions_in feed the
@@ -394,10 +408,12 @@ int enqueue_rollout(msrl_state* st, const KernelEntry& kernel, const void* param
   a.M = (int64_t)st->env.num_envs * st->env.num_agents;
   a.obs_in = obs_in;
   a.actions_in = actions_in;
-  a.envs_per_block = envs_per_block(kernel, st->env.num_envs, st->cus);
+  const Blocks plan = plan_blocks(kernel, st->env.num_envs, st->cus);
+  a.envs_per_block = plan.envs;
+  a.full_blocks = plan.full;
   a.layers = layers_of(st->pol);
   a.critic = st->central ? st->packed + st->layout.bytes : nullptr;
-  int64_t blocks = ((int64_t)a.E + a.envs_per_block - 1) / a.envs_per_block;
+  int64_t blocks = plan.total;
   // (the actor fragment's kernel walks over the row blocks itself: one workgroup per compute unit at most)
   if (kernel.kind == MSRL_ENV_PARTICLE && kernel.phase == PHASE_ACT && blocks > st->cus) blocks = st->cus;
   void* args[] = {&a};
@@ -797,8 +813,7 @@ int msrl_rollout_shape(const msrl_state* st, int32_t* workgroups, int32_t* waves
     wg = ((int64_t)st->env.num_envs + 32 * st->tag_tiles - 1) / (32 * st->tag_tiles);
     w = rw = st->env.num_agents * st->tag_tiles;
   } else {
-    const int epb = envs_per_block(st->kernel, st->env.num_envs, st->cus);
-    wg = ((int64_t)st->env.num_envs + epb - 1) / epb;
+    wg = plan_blocks(st->kernel, st->env.num_envs, st->cus).total;
     w = st->kernel.waves;
     rw = st->kernel.row_waves ? st->kernel.row_waves : st->kernel.waves;
   }

@@ -39,6 +39,7 @@ struct RolloutArgs {
   const uint8_t* dyn;     // lingauss: tiles of A, then one tile of B
   int E, T, ep;
   int envs_per_block;     // envs owned by one workgroup (<= WAVES * envs per wave)
+  int full_blocks;        // ... of those from this one on; the ones before own WAVES * envs per wave
   float dt, keep, fdt, coll2;  // particle: dt, 1 - damping, force * dt, (2 radius)^2
   float noise_std, act_cost;   // lingauss
   uint32_t seed_lo, seed_hi;
@@ -130,6 +131,10 @@ constexpr int CRITIC_FETCH_PAD_TILES = 32;
 
 enum : int { PHASE_ALL = 0, PHASE_ENV = 1, PHASE_MLP = 2, PHASE_CLOCKS = 3, PHASE_ACT = 4, PHASE_STEP = 5,
              PHASE_DEEP = 6, PHASE_CENTRAL = 7, PHASE_ACT_DEEP = 8, PHASE_ACT_CENTRAL = 9, PHASE_SPLIT = 10 };
+// kernels that take RolloutArgs::full_blocks: those in which waves without rows leave their SIMD to the others (but
+// not the deep ones: six layers of 256 units, 8 + 1 waves against 5 + 5: 5.42 ms and 5.32, 8 + 4 against 6 + 6: 5.31 and 5.59,
+// 8 + 3: no faster)
+constexpr bool two_block_sizes(int waves, int phase) { return waves > 4 && (phase == PHASE_ALL || phase == PHASE_CENTRAL); }
 // stamps: start of the step, observation rows built and stored, policy layer 1 done (after the
 // stage barrier that precedes it), policy stage s done (s < 5), same for the value network,
 // logits and values ready, sampling and move done, end of the step
@@ -315,8 +320,12 @@ void particle_rollout_kernel(RolloutArgs a) {
   int64_t vb = blockIdx.x;
 next_row_block:
   // envs of this workgroup: [blk0, blk0 + envs_per_block); of this wave: EPW of them
-  const int64_t blk0 = vb * a.envs_per_block;
-  const int64_t blk_end = min(blk0 + (int64_t)a.envs_per_block, (int64_t)a.E);
+  constexpr bool TWO_SIZES = two_block_sizes(WAVES, PHASE);
+  const bool full_block = TWO_SIZES && vb < a.full_blocks;
+  const int64_t blk0 = full_block ? vb * (WAVES * EPW)
+                       : TWO_SIZES ? vb * a.envs_per_block + (int64_t)a.full_blocks * (WAVES * EPW - a.envs_per_block)
+                                   : vb * a.envs_per_block;
+  const int64_t blk_end = min(blk0 + (full_block ? WAVES * EPW : (int64_t)a.envs_per_block), (int64_t)a.E);
   const int64_t env0 = blk0 + (int64_t)rset * EPW;
   float2* tab = s_tab[wave];
   float* stg = s_stg[wave];
@@ -328,6 +337,62 @@ next_row_block:
   // rows of this wave that hold an env (the same for every lane)
   const int live_rows =
       __builtin_amdgcn_readfirstlane((int)max((int64_t)0, min((int64_t)EPW, blk_end - env0))) * N;
+
+  // stores the collected per-row outputs of step ts; bit k of `arrays` selects array k (value,
+  // action, logp, reward, done), which goes out through wave k % WAVES, 64 consecutive rows per
+  // store instruction
+  auto flush = [&](int ts, int arrays) {
+    const int wg_rows = __builtin_amdgcn_readfirstlane((int)(blk_end - blk0)) * N;
+    const size_t o0 = (size_t)ts * a.M + (size_t)blk0 * N;
+    const int fp = SPLIT ? (ts & 1) : 0;
+    constexpr int J = (WGR + 63) / 64;
+    for (int arr = wave; arr < 5; arr += WAVES) {
+      if (!((arrays >> arr) & 1)) continue;
+      if (arr < 4) {
+        float vv[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) vv[j] = s_out[fp][arr][min(lane + 64 * j, WGR - 1)];
+        float* dst = arr == 0 ? a.values : arr == 1 ? (float*)a.actions : arr == 2 ? a.logp : a.rewards;
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+          if (lane + 64 * j < wg_rows) dst[o0 + lane + 64 * j] = vv[j];
+      } else {
+        uint8_t vv[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) vv[j] = s_done[fp][min(lane + 64 * j, WGR - 1)];
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+          if (lane + 64 * j < wg_rows) a.dones[o0 + lane + 64 * j] = vv[j];
+      }
+    }
+  };
+
+  // (Here, in front of the state's loads: behind them the deep kernel of 8 agents spilled 77 registers, not 55.)
+  // Waves whose rows hold no env (few envs for the chip: ceil(E / CUs) per workgroup).  Where two waves share a SIMD
+  // such a wave would take half the issue slots of one that has rows, so it only does its part of what the workgroup
+  // does together: the waits, its copies of the weights, its arrays of the collected outputs; the same barriers in the
+  // same order as in the steps below, 2 stages_per_net of them per evaluation of the networks.  A workgroup with at
+  // most four waves at work then has one per SIMD: 32 steps of 10 agents with bf16 networks of 256 units take 526 us with
+  // one wave at work, 632 with four, 838 with five and 934 with eight; before, 870 to 960 with any number.  8191 envs, six hidden layers, 50 steps (six of
+  // eight waves): 9.67 -> 8.58 ms.  (Kernels of up to four waves have one per SIMD as they are; PHASE_ACT_DEEP would spill.)
+  constexpr bool IDLE_LOOP = WAVES > 4 && (PHASE == PHASE_ALL || PHASE == PHASE_DEEP || PHASE == PHASE_ACT);
+  static_assert(!IDLE_LOOP || Stream::STAGES_PER_NET > 1, "a network of one stage has one more barrier");
+  if constexpr (IDLE_LOOP) {
+    if (live_rows == 0) {
+      const int stages = 2 * ws.stages_per_net;
+#pragma unroll 1
+      for (int t = 0; t <= (ACT ? 0 : a.T); ++t) {
+#pragma unroll 1
+        for (int s = 0; s < stages; ++s) {
+          ws.wait_oldest();
+          if (FULL && t > 0 && s == ws.stages_per_net) flush(t - 1, 0x1f);
+          const int next = s + Stream::AHEAD;
+          ws.issue(next >= stages ? next - stages : next, (gs + Stream::AHEAD) % NBUF);
+          ++gs;
+        }
+      }
+    }
+  }
 
   int row[NB], base[NB], ag[NB];
   uint32_t env[NB];
@@ -366,36 +431,6 @@ next_row_block:
 
   const int64_t m0 = env0 * N;  // first trajectory row of this wave
   const int wrow0 = rset * VR;  // ... and its first row within the workgroup
-  // stores the collected per-row outputs of step ts; bit k of `arrays` selects array k (value,
-  // action, logp, reward, done), which goes out through wave k % WAVES, 64 consecutive rows per
-  // store instruction
-  auto flush = [&](int ts, int arrays) {
-    const int wg_rows = __builtin_amdgcn_readfirstlane((int)(blk_end - blk0)) * N;
-    const size_t o0 = (size_t)ts * a.M + (size_t)blk0 * N;
-    const int fp = SPLIT ? (ts & 1) : 0;
-    constexpr int J = (WGR + 63) / 64;
-    for (int arr = wave; arr < 5; arr += WAVES) {
-      if (!((arrays >> arr) & 1)) continue;
-      if (arr < 4) {
-        float vv[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j) vv[j] = s_out[fp][arr][min(lane + 64 * j, WGR - 1)];
-        float* dst = arr == 0 ? a.values : arr == 1 ? (float*)a.actions : arr == 2 ? a.logp : a.rewards;
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-          if (lane + 64 * j < wg_rows) dst[o0 + lane + 64 * j] = vv[j];
-      } else {
-        uint8_t vv[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j) vv[j] = s_done[fp][min(lane + 64 * j, WGR - 1)];
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-          if (lane + 64 * j < wg_rows) a.dones[o0 + lane + 64 * j] = vv[j];
-      }
-    }
-  };
-
-
   // Outputs of a network as a bit mask (5 logits; the value network uses the first).  Only the fp32 output
   // layer's code depends on it: up to 8 outputs run on the VALU (MlpTri).
   constexpr uint32_t OUTS = BF16 ? 0xFFFFu : 0x1Fu;
@@ -527,33 +562,8 @@ next_row_block:
   };
   float checksum[NB] = {};      // PHASE_MLP only
 
-  // Waves whose rows hold no env (few envs for the chip: ceil(E / CUs) per workgroup).  Where two waves share a SIMD
-  // such a wave would take half the issue slots of one that has rows, so it only does its part of what the workgroup
-  // does together: the waits, its copies of the weights, its arrays of the collected outputs; the same barriers in the
-  // same order as in the steps below, 2 stages_per_net of them per evaluation of the networks.  A workgroup with at
-  // most four waves at work then has one per SIMD: 32 steps of 10 agents with bf16 networks of 256 units take 526 us with
-  // one wave at work, 632 with four, 838 with five and 934 with eight.  8191 envs, six hidden layers, 50 steps (six of
-  // eight waves): 9.67 -> 8.58 ms.  (Kernels of up to four waves have one per SIMD as they are; PHASE_ACT_DEEP would spill.)
-  constexpr bool IDLE_LOOP = WAVES > 4 && (PHASE == PHASE_ALL || PHASE == PHASE_DEEP || PHASE == PHASE_ACT);
-  static_assert(!IDLE_LOOP || Stream::STAGES_PER_NET > 1, "a network of one stage has one more barrier");
-  if constexpr (IDLE_LOOP) {
-    if (live_rows == 0) {
-      const int stages = 2 * ws.stages_per_net;
-#pragma unroll 1
-      for (int t = 0; t <= (ACT ? 0 : a.T); ++t) {
-#pragma unroll 1
-        for (int s = 0; s < stages; ++s) {
-          ws.wait_oldest();
-          if (FULL && t > 0 && s == ws.stages_per_net) flush(t - 1, 0x1f);
-          const int next = s + Stream::AHEAD;
-          ws.issue(next >= stages ? next - stages : next, (gs + Stream::AHEAD) % NBUF);
-          ++gs;
-        }
-      }
-    }
-  }
   // with a centralised critic a wave without rows computes its chunk of the critic and nothing else (2037 envs x 10, 50
-  // steps, three of eight waves: 970 -> 819 us)
+  // steps, three of eight waves: 1114 -> 857 us)
   const bool idle = CENTRAL && WAVES > 4 && live_rows == 0;
 
   long long clk0 = 0;
