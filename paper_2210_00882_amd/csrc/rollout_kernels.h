@@ -373,8 +373,9 @@ next_row_block:
   // does together: the waits, its copies of the weights, its arrays of the collected outputs; the same barriers in the
   // same order as in the steps below, 2 stages_per_net of them per evaluation of the networks.  A workgroup with at
   // most four waves at work then has one per SIMD: 32 steps of 10 agents with bf16 networks of 256 units take 526 us with
-  // one wave at work, 632 with four, 838 with five and 934 with eight; before, 870 to 960 with any number.  8191 envs, six hidden layers, 50 steps (six of
-  // eight waves): 9.67 -> 8.58 ms.  (Kernels of up to four waves have one per SIMD as they are; PHASE_ACT_DEEP would spill.)
+  // one wave at work, 632 with four, 838 with five and 934 with eight; before, 870 to 960 with any number.  8191 envs,
+  // six hidden layers, 50 steps (six of eight waves): 10.04 -> 8.58 ms.  (Kernels of up to four waves have one per SIMD as
+  // they are; PHASE_ACT_DEEP would spill.)
   constexpr bool IDLE_LOOP = WAVES > 4 && (PHASE == PHASE_ALL || PHASE == PHASE_DEEP || PHASE == PHASE_ACT);
   static_assert(!IDLE_LOOP || Stream::STAGES_PER_NET > 1, "a network of one stage has one more barrier");
   if constexpr (IDLE_LOOP) {
