@@ -97,7 +97,18 @@ template <int CH> struct LdsRows {
 // unit of position j of 32 in the chained order
 __device__ __forceinline__ int chained(int j) { return (j & 16) | (j & 4) << 1 | (j & 8) >> 1 | (j & 3); }
 
-// XT: 32-input tiles of the padded observation, 1 or 2
+// A row of observations is followed by two constant inputs, for the two parts of the bias: layer-1 operand tiles of 16
+// inputs, and the 32-input tiles of a row in LDS (XT).  There are instances of one and two.
+constexpr int block_bf16_k_tiles(int in_dim) { return (in_dim + 2 + 15) / 16; }
+constexpr int block_bf16_x_tiles(int in_dim) { return (in_dim + 2 + 31) / 32; }
+constexpr int BLOCK_BF16_MAX_IN = 2 * 32 - 2;
+constexpr bool block_bf16_widths_fit() {
+  for (int d = 1; d <= BLOCK_BF16_MAX_IN; ++d)
+    if (block_bf16_x_tiles(d) > 2 || block_bf16_k_tiles(d) > 2 * block_bf16_x_tiles(d)) return false;
+  return block_bf16_x_tiles(BLOCK_BF16_MAX_IN + 1) > 2;
+}
+static_assert(block_bf16_widths_fit(), "every width the learner takes has an instance that holds its inputs and its bias");
+
 template <int H, int XT> struct BlockShapeB {
   static constexpr int NWU = H / 32;              // groups of 32 units
   // 128 units: two waves per group of units, a 32-row tile each (eight waves for the compute unit, whose share of a
@@ -159,7 +170,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   const int gwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = gwave / NW, wave = gwave % NW;
   Team& s = s_team[team];
   int lane = threadIdx.x & 63;
-  const int O = nt.out, kx = (a.D + 2 + 15) / 16;
+  const int O = nt.out, kx = block_bf16_k_tiles(a.D);  // (<= KX: the launcher's choice of XT)
   const int uw = wave % NWU, rg = wave / NWU, u0 = 32 * uw, ro = 32 * RT * rg;  // this wave's units and first row
   __bf16 *const dz1 = S::OWN_DZ ? s.dz[0] : s.h1, *const dz2 = S::OWN_DZ ? s.dz[1] : s.h2;
   const bool policy = nt.policy != 0;
@@ -617,15 +628,17 @@ struct BlockPackJobsB {
 hipError_t launch_block_pack_bf16(const BlockPackJobsB& jobs, int max_items, hipStream_t s);
 hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, unsigned slices, unsigned nets, hipStream_t s);
 
-#define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                              \
-  hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) {             \
-    const bool vec2 = in_dim % 2 == 0 && (uintptr_t)a.obs % 8 == 0;                                                \
-    const dim3 threads(BlockShapeB<HID, 1>::THREADS);                                                              \
-    if (in_dim <= 32 && vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, true>), grid, threads, 0, s, a);   \
-    else if (in_dim <= 32) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, false>), grid, threads, 0, s, a);     \
-    else if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, true>), grid, threads, 0, s, a);              \
-    else hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, false>), grid, threads, 0, s, a);                       \
-    return hipGetLastError();                                                                                      \
+#define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                       \
+  hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) {      \
+    const bool vec2 = in_dim % 2 == 0 && (uintptr_t)a.obs % 8 == 0;                                         \
+    const int xt = block_bf16_x_tiles(in_dim);                                                              \
+    const dim3 threads(BlockShapeB<HID, 1>::THREADS);                                                       \
+    if (in_dim < 1 || xt > 2) return hipErrorInvalidValue; /* (no LDS for more inputs) */                   \
+    if (xt == 1 && vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, true>), grid, threads, 0, s, a); \
+    else if (xt == 1) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, false>), grid, threads, 0, s, a);   \
+    else if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, true>), grid, threads, 0, s, a);       \
+    else hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, false>), grid, threads, 0, s, a);                \
+    return hipGetLastError();                                                                               \
   }
 
 }  // namespace msrl

@@ -85,7 +85,7 @@ constexpr int64_t BSUM_MAX_ROWS = 65536;
 // tiles (64 x 16 bytes) of a network's packed weights (learn_block.h, learn_block_bf16.h)
 size_t block_tiles(bool bf16, int in, int H, int out) {
   const size_t T = (size_t)H / 32, KH = (size_t)H / (bf16 ? 16 : 8);
-  if (bf16) return T * ((in + 2 + 15) / 16) + T * (KH + 1) + KH + T + T * KH;
+  if (bf16) return T * block_bf16_k_tiles(in) + T * (KH + 1) + KH + T + T * KH;
   return T * ((in + 7) / 8) + 2 * T * KH + (size_t)((out + 15) / 16) * (H / 16) + T * ((out + 7) / 8);
 }
 
@@ -533,7 +533,7 @@ int block_bf16_grad_pass(msrl_learner* L, const float* params, int64_t R, const 
       dst += (size_t)tiles * kt * 64;
       return at;
     };
-    b.w1 = pack(oW1, H, 1, D, H, H / 32, (D + 2 + 15) / 16, 1, params + ob1);
+    b.w1 = pack(oW1, H, 1, D, H, H / 32, block_bf16_k_tiles(D), 1, params + ob1);
     b.w2 = pack(oW2, H, 1, H, H, H / 32, H / 16 + 1, 0, params + ob2);
     b.w3 = pack(oW3, O, 1, H, O, 1, H / 16, 0, nullptr);
     b.w3t = pack(oW3, 1, O, O, H, H / 32, 1, 0, nullptr);
@@ -652,7 +652,7 @@ int msrl_learner_init_path(const msrl_policy_cfg* policy, int64_t max_rows, int3
   const size_t H = (size_t)policy->hidden, Rp = (size_t)L->Rp, Dp = (size_t)L->Dp, e = L->esz;
   L->block_policy = (policy->hidden == 64 || policy->hidden == 128 || policy->hidden == 256) && L->layers == 2 &&
                     path != MSRL_LEARNER_PATH_DEVICE_MEMORY &&
-                    (L->bf16 ? policy->in_dim <= 62 && policy->dist == MSRL_CATEGORICAL && policy->out_dim <= 16
+                    (L->bf16 ? policy->in_dim <= BLOCK_BF16_MAX_IN && policy->dist == MSRL_CATEGORICAL && policy->out_dim <= 16
                              : policy->in_dim <= 64);
   L->block = L->block_policy && L->G == 1;
   int rc = MSRL_OK;

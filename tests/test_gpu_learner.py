@@ -72,6 +72,9 @@ CASES = {
     # 64 units with more than 30 inputs: the on-chip weight gradients with two tiles of observation inputs
     "p6_bf16_h64": (synth.particle("p6c", 8, 6, 64, 4, 4, synth.BF16, 14), 32 * 9 + 5),
     "p10_bf16_h64": (synth.particle("p10c", 8, 10, 64, 4, 4, synth.BF16, 15), 217),
+    # the pursuit task's learner with 32 inputs (5 chasers, 3 runners, no landmark): the two parts of the bias need a second
+    # tile of inputs
+    "tag_5_3_bf16": (synth.tag("t8", 8, 5, 3, 0, 64, 4, 4, synth.BF16, 16).with_(kind=synth.PARTICLE), 32 * 7 + 9),
     # the same bf16 networks through the kernels that keep the activations in device memory
     "p3_bf16_unfused": (synth.particle("p3b", 8, 3, 64, 4, 4, synth.BF16, 12), 300),
     "cfg5_bf16_unfused": (synth.CONFIGS[5], 259),
