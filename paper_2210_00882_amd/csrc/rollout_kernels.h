@@ -38,8 +38,7 @@ struct RolloutArgs {
   const uint8_t* packed;  // policy network, then value network (packed.h)
   const uint8_t* dyn;     // lingauss: tiles of A, then one tile of B
   int E, T, ep;
-  int envs_per_block;     // envs owned by one workgroup (<= WAVES * envs per wave)
-  int full_blocks;        // ... of those from this one on; the ones before own WAVES * envs per wave
+  int envs_per_block;     // envs owned by one workgroup (<= WAVES * envs per wave), but see full_blocks
   float dt, keep, fdt, coll2;  // particle: dt, 1 - damping, force * dt, (2 radius)^2
   float noise_std, act_cost;   // lingauss
   uint32_t seed_lo, seed_hi;
@@ -54,6 +53,7 @@ struct RolloutArgs {
   const float* obs_in;     // PHASE_ACT: observation rows [M, D] to act on
   const void* actions_in;  // PHASE_STEP: actions [M] to apply
   int layers;              // hidden layers of both networks (>= 2; kernels other than PHASE_DEEP take 2)
+  int full_blocks;         // two_block_sizes: workgroups in front of those of envs_per_block, which own WAVES * envs per wave
   const uint8_t* critic;   // PHASE_CENTRAL: packed value network on the joint observation (NetLayout of N * NZ inputs)
 };
 
