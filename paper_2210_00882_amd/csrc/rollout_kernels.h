@@ -392,6 +392,14 @@ next_row_block:
           ++gs;
         }
       }
+      // (bf16 networks of 128 units: an end of its own in place of the one behind the steps, which are then known to begin with
+      // t = 0 and gs = 0; full workgroups of 9 agents, 16 steps, 210 -> 207 us.  The others are as fast or slower with it, fp32
+      // by 1 %.)
+      if constexpr (PHASE == PHASE_ALL && BF16 && H == 128) {
+        ws.wait_all();
+        flush(a.T, 0x01);
+        return;
+      }
     }
   }
 
@@ -511,7 +519,7 @@ next_row_block:
     }
   };
   // tanh of the chunk's layer-2 sums and the output layer: the chunk's share of the value of column lane % 32
-  auto critic_l3 = [&](const f32x16& c) {
+  auto critic_l3 = [&](const f32x16& c) __attribute__((always_inline)) {
     float tt[16];
     tanh_range<!BF16>(c, tt, 0, 16, false);
     if constexpr (BF16) {
@@ -534,7 +542,7 @@ next_row_block:
     }
   };
   // tanh of the chunk's layer-1 sums; outputs (as the next layer's operand tiles) to s_hc
-  auto critic_l1_publish = [&](const f32x16& c) {
+  auto critic_l1_publish = [&](const f32x16& c) __attribute__((always_inline)) {
     float tt[16];
     COp hc[Critic::PC];
     tanh_range<!BF16>(c, tt, 0, 16, false);
@@ -563,12 +571,58 @@ next_row_block:
   };
   float checksum[NB] = {};      // PHASE_MLP only
 
-  // with a centralised critic a wave without rows computes its chunk of the critic and nothing else (2037 envs x 10, 50
-  // steps, three of eight waves: 1114 -> 857 us)
-  const bool idle = CENTRAL && WAVES > 4 && live_rows == 0;
-
   long long clk0 = 0;
-  for (int t = IDLE_LOOP && live_rows == 0 ? a.T + 1 : 0; t <= a.T; ++t) {
+  // With a centralised critic a wave without rows computes its chunk of the critic and nothing else (2037 envs x 10, 50
+  // steps, three of eight waves: 1114 -> 857 us): the critic's part of the steps below, with their barriers.  (Said again
+  // here because as branches inside the steps it costs the waves that have rows 1 to 3 %: 16 steps of 8192 envs x 7, full
+  // workgroups, 339 -> 350 us; and as a lambda for both places the kernels of 128 units 1 to 3 %.)
+  if constexpr (CENTRAL && WAVES > 4) {
+    if (live_rows == 0) {
+#pragma unroll 1
+      for (int t = 0; t <= (ACT ? 0 : a.T); ++t) {
+#pragma unroll 1
+        for (int sc = 0; sc < SPN; ++sc) {
+          ws.wait_oldest();
+          if (FULL && sc == 1 && t > 0) {
+            flush(t - 1, 0x1e);
+            if (t > 1) flush(t - 2, 0x01);
+          }
+          if (sc < S2) {
+            if (t > 0) {
+#pragma unroll
+              for (int i = 0; i < RING; ++i)
+                if (sc * RING + i < L2T) critic_l2_tile(cring[i], sc * RING + i, cacc);
+            }
+          } else {
+            if (sc == S2) {
+              if (t > 0) critic_l3(cacc);
+              cacc = zero16();
+            }
+#pragma unroll
+            for (int i = 0; i < RING; ++i) {
+              const int kt = (sc - S2) * RING + i;
+              if (kt < KT1C) {
+                COp b[Critic::PT];
+                lds_operands(s_j[kt * 64 + lane], b);
+                mma_tile<BF16>(cring[i], b, cacc);
+              }
+            }
+          }
+          const uint8_t* nb = sc + 1 < S2 ? t2 + (size_t)(sc + 1) * RING * 1024
+                              : sc + 1 < SPN ? t1 + (size_t)(sc + 1 - S2) * RING * 1024 : t2;
+          fetch_tiles(nb, std::integral_constant<int, RING>{}, cring);
+          const int next = sc + Stream::AHEAD;
+          ws.issue(next >= SPN ? next - SPN : next, (gs + Stream::AHEAD) % NBUF);
+          ++gs;
+        }
+        critic_l1_publish(cacc);
+        cacc = zero16();
+      }
+      if constexpr (ACT) goto behind_steps;  // (past its one step; else the loop below ends at once, with fewer spills)
+    }
+  }
+
+  for (int t = (IDLE_LOOP || (CENTRAL && WAVES > 4 && !ACT)) && live_rows == 0 ? a.T + 1 : 0; t <= a.T; ++t) {
     const int par = SPLIT ? (t & 1) : 0;
     auto stamp = [&](int i) {
       if constexpr (PHASE == PHASE_CLOCKS) {
@@ -620,7 +674,7 @@ next_row_block:
     // ---------------- observation rows: build, store (through the staging area), convert to MFMA operands
     Op x[NB][KT1 * Net::PT];
     f32x8 f[KT1];
-    if (!idle) {
+    {
       constexpr int q = 0;
       auto pair_value = [&](int gp) -> float2 {
         // pair 0: v, 1: p, [2, 2+L): landmark - p, [2+L, 1+L+N): other agent - p, rest 0
@@ -868,7 +922,7 @@ next_row_block:
         for (int q = 0; q < NB; ++q) out_p[q] = out_v[q] = out[q];
       } else if constexpr (CENTRAL) {
         // ---------------- policy network through the window, the critic riding on its stages
-        if (!idle) Net::layer1(&s_l1[0][0] + lane, x, h1);
+        Net::layer1(&s_l1[0][0] + lane, x, h1);
         f32x16 acc[NB];
         {
           const f32x16 b = Net::template out_init<OUTS>(s_b3[0], h);
@@ -917,15 +971,11 @@ next_row_block:
           const int nbuf = (gs + Stream::AHEAD) % NBUF;
           const u32x4* tiles = ws.tiles(gs % NBUF, 0);
           auto tick = [&](int kt) { ws.spread(next, nbuf, kt, Net::KT2); };
-          if (idle) {
-            ws.issue(next, nbuf);
-          } else {
-            if (sc == 0)
-              Net::template layer2_chunk<false, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
-            else
-              Net::template layer2_chunk<true, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
-            if (sc == SPN - 1) Net::template layer2_drain<OUTS>(tiles, acc, out_p, h, 16);
-          }
+          if (sc == 0)
+            Net::template layer2_chunk<false, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
+          else
+            Net::template layer2_chunk<true, OUTS>(tiles, h1, acc, out_p, h, 16, tick);
+          if (sc == SPN - 1) Net::template layer2_drain<OUTS>(tiles, acc, out_p, h, 16);
           ++gs;
         }
         Net::template out_finish<OUTS>(out_p, s_b3[0], h);
@@ -1008,10 +1058,6 @@ next_row_block:
         if (h == 0 && valid[q] && (!SPLIT || role == 1)) s_out[par][0][wrow0 + row[q]] = out_v[q][0];
     }
     if (!ACT && t == a.T) break;
-    if (idle) {
-      if constexpr (ACT) break;
-      continue;
-    }
 
     // ---------------- sampling, physics
     float rew_term[NB];
@@ -1116,6 +1162,7 @@ next_row_block:
     }
   }
 
+behind_steps: __attribute__((unused));
   if constexpr (PERSIST) {
     __syncthreads();  // every wave's outputs of this row block are in s_out
     flush(0, 0x07);   // values, actions, logp (the next block writes s_out behind several stage barriers)
