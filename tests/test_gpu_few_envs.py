@@ -1,7 +1,7 @@
 """Waves of a rollout workgroup that own no rows skip the networks: few envs for the chip, or a last round of smaller
 workgroups behind full ones.  An env's trajectory
 depends on the seed, its index and the parameters only, so it is the same bits whether the other waves of its workgroup
-have rows or not; the run of equal workgroups without such a wave is the reference (checked against the oracle in
+have rows or not; the reference is a run of full workgroups, where every wave has rows (checked against the oracle in
 test_gpu_parity.py, like the shapes here at 50 envs)."""
 import numpy as np
 import pytest
@@ -42,7 +42,7 @@ def test_waves_without_rows_leave_the_others_bits(N, H, dtype, layers, central):
         c = synth.particle("few", E, N, H, T, 3, dtype=dtype, idx=33)
         return c.with_(hidden_layers=layers, central_critic=central)
 
-    full, es, g = _run(cfg(CUS * 21 * epw), T)  # three rounds of seven waves
+    full, es, g = _run(cfg(CUS * 24 * epw), T)  # three rounds of full workgroups, of up to eight waves
     # one env in all; one per workgroup; one full wave and one env; three waves, the last workgroup with fewer envs;
     # seven waves and one env in the eighth; one full round and five envs; two and one of three waves
     for E in (1, CUS + 1, CUS * (epw + 1), CUS * (2 * epw + 1) - 3, CUS * (7 * epw + 1), CUS * 8 * epw + 5, CUS * (18 * epw + 1) - 3):
