@@ -462,6 +462,7 @@ next_row_block:
   // The last step's layers 2 and 3 run behind the loop.
   constexpr int SPN = Stream::STAGES_PER_NET;
   static_assert(!CENTRAL || SPN >= 2, "the critic rides on the policy stages");
+  constexpr bool FLUSH_EARLY = CENTRAL && !ACT && SPN == 2;
   constexpr int L2T = Critic::KT2 + 1;  // layer-2 tiles of a chunk, the bias tile included
   constexpr int S2_ = (SPN * L2T + (L2T + KT1C) / 2) / (L2T + KT1C);  // stages in proportion to the tiles
   constexpr int S2 = S2_ < 1 ? 1 : (S2_ > SPN - 1 ? SPN - 1 : S2_);
@@ -668,6 +669,9 @@ next_row_block:
       // the wave still has in flight, so it must not sit behind the observation stores below.
       stage_wait();
       if constexpr (CENTRAL) {
+        // (64 units: stage 1 is the last one, so this store must come a barrier earlier than the others' for one to lie
+        // between its reads of s_out and the writes of this step)
+        if (FLUSH_EARLY && t > 0) flush(t - 1, 0x1e);
         if (t > 1) collect_values();  // of step t - 2
       }
     }
@@ -934,7 +938,7 @@ next_row_block:
           if (sc != 0) {
             ws.wait_oldest();
             if (sc == 1 && t > 0) {
-              flush(t - 1, 0x1e);
+              if (!FLUSH_EARLY) flush(t - 1, 0x1e);
               if (t > 1) flush(t - 2, 0x01);
             }
           }
