@@ -12,13 +12,16 @@
 // past resident activations nothing else comes near it: per 64 rows and wave of 256 units some 900 MFMAs = 57 k
 // cycles stand against 66 KiB of weights and 340 KiB of LDS reads.  Kept apart as one kernel per layer, the same
 // work wrote and read back 7 KiB per row and ran at a fifth of the matrix rate.  One gradient of 32,768 rows, 256 units:
-// 1.06 ms by layers (35 launches), 0.34-0.36 ms here (3 or 4; a 64-row tile takes 157 k cycles, of which the MFMAs of
-// its two waves per SIMD need 112 k and tanhf 15 k); 64 units 0.38 -> 0.07 ms, 1000 rows of 64 units 0.38 -> 0.04 ms.
+// 1.03 ms by layers (35 launches), 0.30-0.32 ms here (3 or 4; counters: 171 k cycles per 64-row tile, the store of the
+// gradient included, of which the MFMAs of its two waves per SIMD take 111 k and the VALU, tanhf above all, 32 k); 64 units
+// 0.37 -> 0.06 ms, 1000 rows of 64 units 0.35 -> 0.025 ms.  256 units with more than 32 inputs or 16 outputs spill 18 to 46
+// registers.
 //
-// The products of a sum are added in the order of the layer kernels (learn_kernels.h): inputs and rows ascending in
-// one accumulator each (an fp32 MFMA adds its products one after the other, rounded each time, whatever its shape).
-// With BlockArgs::bsum the bias gradients are summed in those kernels' order too, and given their slices the whole
-// gradient is theirs bit for bit.
+// The products of a layer and, inside a slice, of a weight gradient are added in the order of the layer kernels
+// (learn_kernels.h): inputs and rows ascending in one accumulator each (an fp32 MFMA adds its products one after the other,
+// rounded each time, whatever its shape).  With BlockArgs::bsum the bias gradients are summed in those kernels' order
+// too, and given their slices the whole gradient is theirs bit for bit; without, a bias gradient is one running sum
+// over the slice's rows.
 #pragma once
 #include "dev_common.h"
 #include "row_sel.h"

@@ -8,16 +8,18 @@
 // order there ("chained", packed.h).  The weight gradients contract over the rows: their operands (8 rows of a unit)
 // come from the same LDS rows through the transposing read (ds_read_b64_tr_b16), so nothing is stored twice.
 //
-// What bounds it: the six barriers of a tile and what waits between them.  Of the 27 k cycles of a 64-row tile of 256
-// units the matrix pipe is busy for 7.7 k, the vector ALU for 11 k, the LDS for 8 k (activations are read once by each
-// of the eight waves in either layer product, 2 k cycles each, as long as their MFMAs take).  Writing the activations
+// What bounds it: the six barriers of a tile and what waits between them.  Of the 26.8 k cycles of a 64-row tile of 256
+// units the matrix pipe is busy for 8.2 k, the vector ALU for 11.2 k, the LDS for 7.2 k (counters; activations are read
+// once by each of the eight waves in either layer product); the waves wait for 48 % of theirs.  Writing the activations
 // and their gradients out for contractions of their own (4 KiB per row and network) was bound by that traffic.
-// Gradient of 524,288 rows before and now: 256 units 1.39 -> 0.84 ms, 128 0.77 -> 0.43, 64 0.28 -> 0.19 (pursuit env 0.22
-// -> 0.16); of 8192 rows 128 -> 56, 79 -> 35, 61 -> 33 us (three launches where there were six).
+// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.78 ms, 128 (36) 0.71 -> 0.39, 64 (18) 0.22 ->
+// 0.15 (the pursuit env's 20 inputs alike); of 8192 rows 126 -> 57, 76 -> 32, 45 -> 28 us (three launches where there were
+// six).
 //
-// The sums keep their order from one version of the learner to the next: which rows an accumulator takes, in which
-// order, and which 16 products an MFMA adds at once.  A bf16 policy acts on the rounded parameters, so that a gradient
-// off by one rounding takes the next rollout of a training run another way.
+// Inside a slice of the rows the sums keep their order from one version of the learner to the next: a 64-row tile behind the
+// other, and which 16 products an MFMA adds at once.  Where the slices begin follows the number of compute units.  A bf16
+// policy acts on the rounded parameters, so that a gradient off by one rounding takes the next rollout of a training run
+// another way.
 //
 // Rounding (the oracle's): weights, observations, h1, h2, dL/dy, dL/dz2 and dL/dz1 to bf16; biases as a high and a low
 // bf16 part, two more inputs of their layer that meet the constant 1; sums and the loss in fp32.

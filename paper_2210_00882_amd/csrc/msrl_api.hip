@@ -351,7 +351,8 @@ bool find_kernel(const msrl_env_cfg& env, const msrl_policy_cfg& pol, int phase,
 //     per SIMD (two_block_sizes).  A round costs by its waves at work, measured as us for 32 steps of 10 agents, bf16
 //     networks of 256 units: 1: 526, 2: 550, 4: 632, 5: 838, 6: 849, 8: 934.  8 + 1 against
 //     5 + 5: 1573 -> 1398 us, 8 + 4 against 6 + 6: 1656 -> 1550; fp32 of 128 units, 6 agents: 1649 -> 1463, 1687 -> 1562;
-//     centralised critic 1354 -> 1282, 1427 -> 1372.  A last round of five waves and more saves nothing.
+//     centralised critic 1354 -> 1282, 1427 -> 1372 (1145 and 1227 since its waves without rows have a loop of their
+//     own).  A last round of five waves and more saves nothing.
 // Computed per launch: the kernels of a state (full rollout, actor fragment, env step, measurement variants) differ
 // in the row blocks a workgroup holds.
 struct Blocks {
