@@ -20,8 +20,8 @@
 // The products of a layer and, inside a slice, of a weight gradient are added in the order of the layer kernels
 // (learn_kernels.h): inputs and rows ascending in one accumulator each (an fp32 MFMA adds its products one after the other,
 // rounded each time, whatever its shape).  With BlockArgs::bsum the bias gradients are summed in those kernels' order
-// too, and given their slices the whole gradient is theirs bit for bit; without, a bias gradient is one running sum
-// over the slice's rows.
+// too, and given their slices the whole gradient is theirs bit for bit; without, the sums over 32 rows are added up in a
+// register.
 #pragma once
 #include "dev_common.h"
 #include "row_sel.h"
@@ -410,18 +410,20 @@ __global__ __launch_bounds__(2 * H) void ppo_block_kernel(BlockArgs a) {
     }
     if (!a.bsum && wave == NW - 1) {
       const float* col = s_y + h * (ROWS / 2) * YP + block_pos(i);
+      float v = 0.0f;
 #pragma unroll 8
-      for (int r = 0; r < ROWS / 2; ++r) run3 += col[r * YP];
+      for (int r = 0; r < ROWS / 2; ++r) v += col[r * YP];
+      run3 += v;
     }
     block_layer<RT, 2>(acc, s_y + i * YP + 4 * h, YP, w3t, lane, ky);
     derive(acc, s_h2);
     // sums over 32 rows, in row order: lane (i, h) takes row group h
     auto column_sum = [&](const float* s, float& run, int at, int32_t ob) {
       const float* col = s + (RT > 1 ? h * 32 * HP : 0) + cu;
-      float v = a.bsum ? 0.0f : run;
+      float v = 0.0f;
 #pragma unroll 8
       for (int r = 0; r < 32; ++r) v += col[r * HP];
-      run = v;
+      run += v;  // (a chain over all of the slice's rows would be two to four times as far from the exact sum)
       const int g0 = t0 + (RT > 1 ? 32 * h : 0);
       if (a.bsum && g0 < n_rows && (RT > 1 || h == 0))
         a.bsum[((r_begin + g0) / 32) * a.bsum_stride + nt.bsum + at + u0 + i] = v;
