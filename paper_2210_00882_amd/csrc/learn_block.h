@@ -15,7 +15,7 @@
 // 1.03 ms by layers (35 launches), 0.30-0.32 ms here (3 or 4; counters: 171 k cycles per 64-row tile, the store of the
 // gradient included, of which the MFMAs of its two waves per SIMD take 111 k and the VALU, tanhf above all, 32 k); 64 units
 // 0.37 -> 0.06 ms, 1000 rows of 64 units 0.35 -> 0.025 ms.  256 units with more than 32 inputs or 16 outputs spill 18 to 46
-// registers.
+// registers (2 otherwise, with two copies to a slice).
 //
 // The products of a layer and, inside a slice, of a weight gradient are added in the order of the layer kernels
 // (learn_kernels.h): inputs and rows ascending in one accumulator each (an fp32 MFMA adds its products one after the other,
@@ -51,7 +51,8 @@ struct BlockArgs {
   int64_t rows_per_slice;      // a multiple of 32
   int D, dist;
   float clip, vf_coef, ent_coef, inv_R;
-  float* part;                 // [slice][part_stride] copies of the gradient
+  float* part;                 // [slice][part_stride] copies of the gradient, or (split > 0, 256 units) two to a slice, of its
+  int split;                   //   rows before and from row `split`, a multiple of the rows taken at a time
   int64_t part_stride;
   float* bsum;                 // [R / 32][bsum_stride] sums of dL/dz2 and dL/dz1 over 32 rows each; null: the bias
   int bsum_stride;             //   gradients of a slice go to `part` like the others
@@ -222,7 +223,8 @@ __device__ __forceinline__ f32x4 block_loss_row(const BlockArgs& a, int O, bool 
   return st;
 }
 
-template <int H, int RT, int XT, int OT>
+// HALVES: with BlockArgs::split (an instance of its own: in one with the others it costs small minibatches 1 to 2 %)
+template <int H, int RT, int XT, int OT, bool HALVES = false>
 __global__ __launch_bounds__(2 * H) void ppo_block_kernel(BlockArgs a) {
   typedef BlockShape<H, RT, XT> S;
   constexpr int NW = S::NW, ROWS = S::ROWS, HP = S::HP, XP = S::XP, YP = S::YP, AP = S::AP, KH = H / 8;
@@ -246,17 +248,8 @@ __global__ __launch_bounds__(2 * H) void ppo_block_kernel(BlockArgs a) {
 
   f32x16 gW1[XT], gW2[NW];
   f32x4 gW3[2][OT];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-#pragma unroll
-    for (int t = 0; t < XT; ++t) gW1[t][r] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < NW; ++t) gW2[t][r] = 0.0f;
-  }
-#pragma unroll
-  for (int c = 0; c < OT; ++c) gW3[0][c] = gW3[1][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   // bsum == null: sums of dL/dz1, dL/dz2 of this lane's unit over its half of the rows; in the last wave, of dL/dy
-  float run1 = 0.0f, run2 = 0.0f, run3 = 0.0f;
+  float run1, run2, run3;
 
   // observations: thread -> row tx / TPR, inputs tx % TPR + TPR q; a row beyond the slice reads as zero
   int xr = threadIdx.x / S::TPR, xc = threadIdx.x % S::TPR;
@@ -306,8 +299,61 @@ __global__ __launch_bounds__(2 * H) void ppo_block_kernel(BlockArgs a) {
       }
   };
 
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+#pragma unroll
+      for (int t = 0; t < XT; ++t) gW1[t][r] = 0.0f;
+#pragma unroll
+      for (int t = 0; t < NW; ++t) gW2[t][r] = 0.0f;
+    }
+#pragma unroll
+    for (int c = 0; c < OT; ++c) gW3[0][c] = gW3[1][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    run1 = run2 = run3 = 0.0f;
+  };
+  // a copy of the gradient: register r of lane (i, h) <-> row 8 (r / 4) + 4 h + r % 4 of a tile, column i
+  auto store = [&](float* part) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = 8 * (r / 4) + 4 * h + r % 4;
+#pragma unroll
+      for (int t = 0; t < XT; ++t)
+        if (32 * t + m < a.D) part[nt.oW1 + (32 * t + m) * H + u0 + i] = gW1[t][r];
+#pragma unroll
+      for (int t = 0; t < NW; ++t) part[nt.oW2 + (u0 + m) * H + 32 * t + i] = gW2[t][r];
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int c = 0; c < OT; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {  // register r of lane l <-> row 4 (l / 16) + r, column l % 16
+          const int o = 16 * c + (lane & 15);
+          if (o < O) part[nt.oW3 + (u0 + 16 * m + 4 * (lane >> 4) + r) * O + o] = gW3[m][c][r];
+        }
+    if (!a.bsum) {
+      if (RT > 1) {
+        run1 += __shfl_xor(run1, 32);
+        run2 += __shfl_xor(run2, 32);
+      }
+      if (h == 0) {
+        part[nt.ob1 + u0 + i] = run1;
+        part[nt.ob2 + u0 + i] = run2;
+      }
+      run3 += __shfl_xor(run3, 32);
+      if (wave == NW - 1 && h == 0 && i < O) part[nt.ob3 + i] = run3;
+    }
+  };
+  float* part = a.part + (int64_t)(HALVES ? 2 * blockIdx.x : blockIdx.x) * a.part_stride;
+  clear();
+
 #pragma unroll 1
   for (int t0 = 0; t0 < n_rows; t0 += ROWS) {
+    if (HALVES && t0 == a.split) {
+      store(part);
+      part += a.part_stride;
+      clear();
+    }
     const int live = min(ROWS, n_rows - t0);
     // (hidden from the compiler once per tile: the LDS addresses formed from them are cheap, and kept across tiles
     // they would be spilled)
@@ -462,37 +508,10 @@ __global__ __launch_bounds__(2 * H) void ppo_block_kernel(BlockArgs a) {
       atomicAdd(a.stats + 8 + a.stat_bins + bin, st[0]);
     }
   }
-  // this slice's copy of the gradient: register r of lane (i, h) <-> row 8 (r / 4) + 4 h + r % 4 of a tile, column i
-  float* part = a.part + (int64_t)blockIdx.x * a.part_stride;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = 8 * (r / 4) + 4 * h + r % 4;
-#pragma unroll
-    for (int t = 0; t < XT; ++t)
-      if (32 * t + m < a.D) part[nt.oW1 + (32 * t + m) * H + u0 + i] = gW1[t][r];
-#pragma unroll
-    for (int t = 0; t < NW; ++t) part[nt.oW2 + (u0 + m) * H + 32 * t + i] = gW2[t][r];
-  }
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int c = 0; c < OT; ++c)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {  // register r of lane l <-> row 4 (l / 16) + r, column l % 16
-        const int o = 16 * c + (lane & 15);
-        if (o < O) part[nt.oW3 + (u0 + 16 * m + 4 * (lane >> 4) + r) * O + o] = gW3[m][c][r];
-      }
-  if (!a.bsum) {
-    if (RT > 1) {
-      run1 += __shfl_xor(run1, 32);
-      run2 += __shfl_xor(run2, 32);
-    }
-    if (h == 0) {
-      part[nt.ob1 + u0 + i] = run1;
-      part[nt.ob2 + u0 + i] = run2;
-    }
-    run3 += __shfl_xor(run3, 32);
-    if (wave == NW - 1 && h == 0 && i < O) part[nt.ob3 + i] = run3;
+  store(part);
+  if (HALVES && n_rows <= a.split) {  // (the last slice: no second half)
+    part += a.part_stride;
+    for (int k = threadIdx.x; k < nt.ob3 + O - nt.oW1; k += S::THREADS) part[nt.oW1 + k] = 0.0f;
   }
 }
 
@@ -517,16 +536,24 @@ hipError_t launch_ppo_block(int hidden, int in_dim, int out_dim, const BlockArgs
 // 32-row tiles a workgroup takes at a time, and workgroups that share a compute unit (by their LDS and registers)
 constexpr int block_row_tiles(int H) { return H <= 128 ? 1 : 2; }
 constexpr int block_per_cu(int H) { return H <= 64 ? 4 : H <= 128 ? 2 : 1; }
+constexpr bool block_halves(int H) { return H > 128; }  // two copies to a slice (narrower networks have slices enough)
 
-#define MSRL_BLOCK_LAUNCHER(HID)                                                                                  \
-  hipError_t launch_ppo_block_h##HID(int in_dim, int out_dim, const BlockArgs& a, dim3 grid, hipStream_t s) {     \
-    constexpr int RT = block_row_tiles(HID);                                                                      \
-    const dim3 threads(2 * HID);                                                                                  \
-    if (in_dim <= 32 && out_dim <= 16) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 1, 1>), grid, threads, 0, s, a); \
-    else if (in_dim <= 32) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 1, 2>), grid, threads, 0, s, a);         \
-    else if (out_dim <= 16) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 2, 1>), grid, threads, 0, s, a);        \
-    else hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 2, 2>), grid, threads, 0, s, a);                           \
-    return hipGetLastError();                                                                                     \
+#define MSRL_BLOCK_LAUNCHER(HID)                                                                                          \
+  hipError_t launch_ppo_block_h##HID(int in_dim, int out_dim, const BlockArgs& a, dim3 grid, hipStream_t s) {             \
+    constexpr int RT = block_row_tiles(HID);                                                                              \
+    constexpr bool HALVES = block_halves(HID);                                                                            \
+    const dim3 threads(2 * HID);                                                                                          \
+    const int one = in_dim <= 32, few = out_dim <= 16;                                                                    \
+    if (a.split > 0 && !HALVES) return hipErrorInvalidValue;                                                              \
+    if (a.split > 0 && one && few) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 1, 1, HALVES>), grid, threads, 0, s, a); \
+    else if (a.split > 0 && one) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 1, 2, HALVES>), grid, threads, 0, s, a);   \
+    else if (a.split > 0 && few) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 2, 1, HALVES>), grid, threads, 0, s, a);   \
+    else if (a.split > 0) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 2, 2, HALVES>), grid, threads, 0, s, a);          \
+    else if (one && few) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 1, 1>), grid, threads, 0, s, a);                   \
+    else if (one) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 1, 2>), grid, threads, 0, s, a);                          \
+    else if (few) hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 2, 1>), grid, threads, 0, s, a);                          \
+    else hipLaunchKernelGGL((ppo_block_kernel<HID, RT, 2, 2>), grid, threads, 0, s, a);                                   \
+    return hipGetLastError();                                                                                             \
   }
 
 }  // namespace msrl

@@ -46,14 +46,13 @@ def action_logp(pol, params, obs, actions):
     return torch.log_softmax(x, 1).gather(1, actions.long().view(-1, 1)).view(-1)
 
 
-def gradients(pol, R, path, rows=None, seed=3, bias=0.1):
-    """Gradient and statistics of R rows (of a larger array, if `rows` selects them); the same inputs for both paths."""
+def batch_of(pol, M, seed, bias):
+    """Parameters and M stored rows."""
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
     d, h, o = pol.in_dim, pol.hidden, pol.out_dim
     params = torch.cat([weights(d, h, o, g, bias), weights(d, h, 1, g, bias)])
     assert params.numel() == B.msrl_param_count(pol)
-    M = R if rows is None else R // rows.count * rows.group
     f = lambda *s: torch.randn(s, device="cuda", generator=g)
     if pol.dist == synth.DIAG_GAUSSIAN:
         obs, actions = None, f(M, o // 2)
@@ -65,7 +64,12 @@ def gradients(pol, R, path, rows=None, seed=3, bias=0.1):
         obs = f(M, d)
         shift = torch.tensor([-0.5, -0.1, 0.0, 0.1, 0.5], device="cuda")
         logp = action_logp(pol, params, obs, actions) - shift[torch.randint(0, 5, (M,), device="cuda", generator=g)]
-    batch = [f(M, d) if obs is None else obs, actions, logp, f(M), f(M)]
+    return params, [f(M, d) if obs is None else obs, actions, logp, f(M), f(M)]
+
+
+def gradients(pol, R, path, rows=None, seed=3, bias=0.1):
+    """Gradient and statistics of R rows (of a larger array, if `rows` selects them); the same inputs for both paths."""
+    params, batch = batch_of(pol, R if rows is None else R // rows.count * rows.group, seed, bias)
     L = B.msrl_learner_init_path(pol, R, path)
     grad, stats = torch.full_like(params, float("nan")), torch.empty(5, device="cuda")
     try:
@@ -95,6 +99,29 @@ def test_block_kernel_equals_the_layer_kernels(d, h, o, gauss, R):
         # of the terms' size; that is a few times the sum's own where the terms cancel
         assert_tensors_close(pol, g, g_ref, 4e-6)
     assert torch.allclose(st, st_ref, rtol=1e-4, atol=1e-4 * R ** 0.5)
+
+
+# 256 units, more than 512 rows to a slice: two copies of the gradient each.  One row more than that; a last slice of 200 rows
+# (of 640, split at 320), of exactly 320, and all of them full
+@pytest.mark.parametrize("d,o", [(30, 5), (60, 17)])
+@pytest.mark.parametrize("R", [65537, 74440, 74560, 131072])
+def test_slices_with_two_copies(d, o, R):
+    pol = policy(d, 256, o, False)
+    params, batch = batch_of(pol, R, 5, 0.1)
+    more = 131072 + 256
+    got = []
+    for path in (0, 0, 1):
+        L = B.msrl_learner_init_path(pol, more, path)
+        got.append(torch.full_like(params, float("nan")))
+        try:
+            if len(got) == 2:   # a larger call before leaves every copy of the workspace filled
+                B.msrl_ppo_grad(L, params, *[torch.cat([x, x, x])[:more].contiguous() for x in batch], B.make_ppo_cfg(), got[-1])
+            B.msrl_ppo_grad(L, params, *batch, B.make_ppo_cfg(), got[-1])
+            torch.cuda.synchronize()
+        finally:
+            B.msrl_learner_destroy(L)
+    assert torch.equal(got[0], got[1])
+    assert_tensors_close(pol, got[0], got[2], 2.0 ** -24 * R ** 0.5)   # (as above)
 
 
 def bf16_tolerance(R):
