@@ -5,128 +5,150 @@
 // issued as one batch, and the batch after it is already in flight while the
 // dependent recurrence consumes this one, which keeps enough bytes in flight
 // without any cross-lane communication.
+//
+// Four columns per lane need no alignment: rows of an odd length put every row at another offset, and a 16-byte access
+// at a multiple of 4 bytes (the dones' 4 bytes at any address) is one instruction as an aligned one is.  200 steps of
+// 655,357 columns: 4-byte accesses 560 us, 16-byte ones 495 (4.5 TB/s); of 400,001 columns 360 and 310, of 200,003 183
+// and 140.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace msrl {
 
 template <int VEC> struct VecT;
-template <> struct VecT<1> { typedef float F; typedef uint8_t B; };
-template <> struct VecT<4> { typedef float4 F; typedef uchar4 B; };
+template <> struct VecT<1> {
+  typedef float F;
+  typedef uint8_t B;
+  static __device__ __forceinline__ float at(const float& v, int) { return v; }
+  static __device__ __forceinline__ void set(float& v, int, float x) { v = x; }
+};
+template <> struct VecT<4> {
+  typedef float F __attribute__((ext_vector_type(4), aligned(4)));
+  typedef uint32_t B __attribute__((aligned(1)));
+  static __device__ __forceinline__ float at(const F& v, int i) { return v[i]; }
+  static __device__ __forceinline__ void set(F& v, int i, float x) { v[i] = x; }
+};
 
-__device__ __forceinline__ float comp(const float& v, int) { return v; }
-__device__ __forceinline__ float comp(const float4& v, int i) { return (&v.x)[i]; }
-__device__ __forceinline__ float compb(const uint8_t& v, int) { return (float)v; }
-__device__ __forceinline__ float compb(const uchar4& v, int i) { return (float)(&v.x)[i]; }
-__device__ __forceinline__ float& comp_ref(float& v, int) { return v; }
-__device__ __forceinline__ float& comp_ref(float4& v, int i) { return (&v.x)[i]; }
+struct GaeArgs {
+  const float *rewards, *values;
+  const uint8_t* dones;
+  int T;
+  int64_t M;
+  float gamma, gl;
+  float *adv, *ret;
+};
 
-template <int VEC, int UNROLL>
-__global__ __launch_bounds__(256) void gae_kernel(const float* __restrict__ rewards,
-                                                  const float* __restrict__ values,
-                                                  const uint8_t* __restrict__ dones, int T,
-                                                  int64_t M, float gamma, float gl,
-                                                  float* __restrict__ adv,
-                                                  float* __restrict__ ret) {
-  typedef typename VecT<VEC>::F F;
-  typedef typename VecT<VEC>::B B;
-  const int64_t col = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC;
-  if (col >= M) return;
-  const F* r = (const F*)(rewards + col);
-  const F* v = (const F*)(values + col);
-  const B* d = (const B*)(dones + col);
-  F* a = (F*)(adv + col);
-  F* q = (F*)(ret + col);
-  const int64_t stride = M / VEC;  // rows are M elements apart
-
+// the scan of columns col .. col + VEC - 1
+template <int VEC, int UNROLL, bool STREAM>
+__device__ __forceinline__ void gae_columns(const GaeArgs& a, int64_t col) {
+  typedef VecT<VEC> V;
+  typedef typename V::F F;
+  typedef typename V::B B;
+  auto get = [](const auto* p) {
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+  };
+  auto put = [](auto* p, const F& v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
   float next_adv[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) next_adv[i] = 0.0f;
-  F v_next = v[(int64_t)T * stride];
+  F v_next = get((const F*)(a.values + (int64_t)a.T * a.M + col));
 
+  auto load = [&](int t, F& r, F& v, uint32_t& d) {
+    const int64_t o = (int64_t)t * a.M + col;
+    r = get((const F*)(a.rewards + o));
+    v = get((const F*)(a.values + o));
+    d = get((const B*)(a.dones + o));
+  };
+  auto step = [&](int t, const F& r, const F& v, uint32_t d) {
+    F oa, oq;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      const float nd = 1.0f - (float)(d >> (8 * i) & 0xFFu);
+      const float vt = V::at(v, i);
+      const float delta = V::at(r, i) + a.gamma * nd * V::at(v_next, i) - vt;
+      next_adv[i] = delta + a.gl * nd * next_adv[i];
+      V::set(oa, i, next_adv[i]);
+      V::set(oq, i, next_adv[i] + vt);
+    }
+    const int64_t o = (int64_t)t * a.M + col;
+    put((F*)(a.adv + o), oa);
+    put((F*)(a.ret + o), oq);
+    v_next = v;
+  };
   // UNROLL time steps per batch; the loads of the next batch are in flight while this one runs
-  auto load = [&](int tt, F (&rr)[UNROLL], F (&vv)[UNROLL], B (&dd)[UNROLL]) {
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const int64_t o = (int64_t)(tt - u) * stride;
-      rr[u] = r[o];
-      vv[u] = v[o];
-      dd[u] = d[o];
-    }
+  struct Batch {
+    F r[UNROLL], v[UNROLL];
+    uint32_t d[UNROLL];
   };
-  auto scan = [&](int tt, const F (&rr)[UNROLL], const F (&vv)[UNROLL], const B (&dd)[UNROLL]) {
+  auto load_batch = [&](int t, Batch& b) {
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      F oa, oq;
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) {
-        const float nd = 1.0f - compb(dd[u], i);
-        const float vt = comp(vv[u], i);
-        const float delta = comp(rr[u], i) + gamma * nd * comp(v_next, i) - vt;
-        next_adv[i] = delta + gl * nd * next_adv[i];
-        comp_ref(oa, i) = next_adv[i];
-        comp_ref(oq, i) = next_adv[i] + vt;
-      }
-      const int64_t o = (int64_t)(tt - u) * stride;
-      a[o] = oa;
-      q[o] = oq;
-      v_next = vv[u];
-    }
+    for (int u = 0; u < UNROLL; ++u) load(t - u, b.r[u], b.v[u], b.d[u]);
   };
-  int t = T - 1;
+  auto scan = [&](int t, const Batch& b) {
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) step(t - u, b.r[u], b.v[u], b.d[u]);
+  };
+  int t = a.T - 1;
   if (t >= UNROLL - 1) {
-    F ra[UNROLL], va[UNROLL], rb[UNROLL], vb[UNROLL];
-    B da[UNROLL], db[UNROLL];
-    load(t, ra, va, da);
+    Batch b0, b1;
+    load_batch(t, b0);
     while (true) {
       bool more = t - UNROLL >= UNROLL - 1;  // a whole batch is left below this one
-      if (more) load(t - UNROLL, rb, vb, db);
-      scan(t, ra, va, da);
+      if (more) load_batch(t - UNROLL, b1);
+      scan(t, b0);
       t -= UNROLL;
       if (!more) break;
       more = t - UNROLL >= UNROLL - 1;
-      if (more) load(t - UNROLL, ra, va, da);
-      scan(t, rb, vb, db);
+      if (more) load_batch(t - UNROLL, b0);
+      scan(t, b1);
       t -= UNROLL;
       if (!more) break;
     }
   }
   for (; t >= 0; --t) {
-    const int64_t o = (int64_t)t * stride;
-    const F rr = r[o], vv = v[o];
-    const B dd = d[o];
-    F oa, oq;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-      const float nd = 1.0f - compb(dd, i);
-      const float vt = comp(vv, i);
-      const float delta = comp(rr, i) + gamma * nd * comp(v_next, i) - vt;
-      next_adv[i] = delta + gl * nd * next_adv[i];
-      comp_ref(oa, i) = next_adv[i];
-      comp_ref(oq, i) = next_adv[i] + vt;
-    }
-    a[o] = oa;
-    q[o] = oq;
-    v_next = vv;
+    F r, v;
+    uint32_t d;
+    load(t, r, v, d);
+    step(t, r, v, d);
   }
+}
+
+// lanes 0 .. M / VEC - 1 take VEC columns each, the M % VEC lanes behind them one of the last columns each
+template <int VEC, bool STREAM, int THREADS>
+__global__ __launch_bounds__(THREADS) void gae_kernel(GaeArgs a) {
+  const int64_t k = (int64_t)blockIdx.x * THREADS + threadIdx.x, whole = a.M / VEC;
+  if (k < whole) gae_columns<VEC, 8, STREAM>(a, k * VEC);
+  else if (VEC > 1 && k < whole + a.M % VEC) gae_columns<1, 8, STREAM>(a, k + whole * (VEC - 1));
+  // (column of lane k >= whole: whole * VEC + (k - whole))
+}
+
+template <int VEC, bool STREAM, int THREADS>
+static void launch(const GaeArgs& a, hipStream_t stream) {
+  const int64_t lanes = a.M / VEC + a.M % VEC;
+  hipLaunchKernelGGL((gae_kernel<VEC, STREAM, THREADS>), dim3((unsigned)((lanes + THREADS - 1) / THREADS)), dim3(THREADS), 0,
+                     stream, a);
 }
 
 hipError_t launch_gae(const float* rewards, const float* values, const uint8_t* dones, int T,
                       int64_t M, float gamma, float lambda, float* adv, float* ret,
                       hipStream_t stream) {
   if (T <= 0 || M <= 0) return hipSuccess;
-  const float gl = gamma * lambda;
+  const GaeArgs a = {rewards, values, dones, T, M, gamma, gamma * lambda, adv, ret};
   const uintptr_t align = (uintptr_t)rewards | (uintptr_t)values | (uintptr_t)adv | (uintptr_t)ret;
-  const bool vec4 = (M % 4 == 0) && (align % 16 == 0) && ((uintptr_t)dones % 4 == 0) &&
-                    (M / 4 >= 64 * 1024);
-  if (vec4) {
-    const int64_t threads = M / 4;
-    hipLaunchKernelGGL((gae_kernel<4, 8>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0,
-                       stream, rewards, values, dones, T, M, gamma, gl, adv, ret);
-  } else {
-    hipLaunchKernelGGL((gae_kernel<1, 8>), dim3((unsigned)((M + 255) / 256)), dim3(256), 0, stream,
-                       rewards, values, dones, T, M, gamma, gl, adv, ret);
-  }
+  // One column per lane while four would leave too few waves to keep the memory busy: 200 steps of 131,071 columns 104 us
+  // (four: 112), of 65,537 35 (45), of 200,003 183 (140).
+  const bool vec4 = M >= 160 * 1000;
+  // Rows of whole aligned 16-byte pieces that do not fit the 256 MB cache behind the L2s go past the caches, in
+  // workgroups of one wave: 200 steps of 655,360 columns 441 -> 410 us (5.5 TB/s).  Unaligned rows share cache lines
+  // between waves, which then must meet in L2: 495 us and 515 with it.
+  const bool stream_past = vec4 && M % 4 == 0 && align % 16 == 0 && (uintptr_t)dones % 4 == 0 && 17.0 * T * M > 512e6;
+  if (stream_past) launch<4, true, 64>(a, stream);
+  else if (vec4) launch<4, false, 256>(a, stream);
+  else launch<1, false, 256>(a, stream);
   return hipGetLastError();
 }
 

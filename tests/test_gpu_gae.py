@@ -34,6 +34,29 @@ def test_gae_matches_oracle(T, M, ep):
     assert_close(ret, orr, TOL_F32, "ret")
 
 
+@pytest.mark.parametrize("T,M,off", [
+    (9, 159999, 1),                                                                 # the last width of one column per lane
+    (9, 160000, 0), (8, 160001, 1), (17, 160002, 2), (7, 160003, 3),                # four, and one lane per column left over
+    (188, 160000, 0), (189, 160000, 0), (189, 160000, 1), (189, 160001, 0),         # around the sizes that go past the caches
+])
+def test_gae_at_any_alignment(T, M, off):
+    """Arrays that start `off` elements into a buffer: every column against the oracle, and nothing around them written."""
+    import torch
+    from paper_2210_00882_amd import binding as B
+    r, v, d = synth.make_gae_inputs(T, M, 7, seed=T + M)
+    put = lambda x: torch.from_numpy(np.concatenate([np.zeros(off, x.dtype), x.reshape(-1)])).cuda()[off:].view(x.shape)
+    rt, vt, dt = put(r), put(v), put(d)
+    whole = [torch.full((off + T * M + 8,), -77.0, device="cuda") for _ in range(2)]
+    adv, ret = (w[off:off + T * M].view(T, M) for w in whole)
+    B.msrl_gae(rt, vt, dt, 0.99, 0.95, adv, ret)
+    torch.cuda.synchronize()
+    oa, orr = ref.gae(r, v, d, 0.99, 0.95)
+    assert_close(adv.cpu().numpy(), oa, TOL_F32, "adv")
+    assert_close(ret.cpu().numpy(), orr, TOL_F32, "ret")
+    for w in whole:
+        assert bool((w[:off] == -77.0).all()) and bool((w[off + T * M:] == -77.0).all())
+
+
 def test_gae_other_discounts_and_all_done():
     T, M = 40, 777
     r, v, d = synth.make_gae_inputs(T, M, 9, seed=5)
