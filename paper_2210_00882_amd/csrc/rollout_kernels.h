@@ -68,6 +68,20 @@ __device__ __forceinline__ void load_resident(u32x4* l1, float* b3, const uint8_
   }
 }
 
+// Calls part(first chunk, one behind the last) for the stages in which layer 1 comes through the weight window.
+template <class Net, class Part>
+__device__ __forceinline__ void layer1_parts(Part&& part) {
+  constexpr std::integral_constant<int, 0> begin;
+  constexpr std::integral_constant<int, Net::NUC / 2> half;
+  constexpr std::integral_constant<int, Net::NUC> end;
+  if constexpr (Net::L1_STAGES == 2) {
+    part(begin, half);
+    part(half, end);
+  } else {
+    part(begin, end);
+  }
+}
+
 // Categorical draw by inverse CDF in fp32, in index order; logp = z_a - log(sum exp z).
 __device__ __forceinline__ void sample_categorical5(const float (&l)[5], float u, int& action,
                                                     float& logp) {
@@ -796,7 +810,8 @@ next_row_block:
 #pragma unroll
       for (int q = 0; q < NB; ++q) out_p[q] = out_v[q] = zero16();
     } else {
-      Op h1[NB][Net::KT2 * Net::PT];
+      typedef typename Net::Act Act;
+      Act h1[NB][Net::KT2 * Net::PT];
       if constexpr (DEEP) {
         const int spn = ws.stages_per_net;
 #pragma unroll 1
@@ -814,11 +829,17 @@ next_row_block:
             nbuf = (gs + Stream::AHEAD) % NBUF;
           };
           if constexpr (L1S) {
-            int next, nbuf;
-            prefetch_target(next, nbuf);
-            Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });
-            ++gs;
-            ++sn;
+            f32x16 a1;
+            auto part = [&](auto u0, auto u1) __attribute__((always_inline)) {
+              if (u0() > 0) ws.wait_oldest();
+              int next, nbuf;
+              prefetch_target(next, nbuf);
+              Net::template layer1_part<u0(), u1()>(ws.tiles(gs % NBUF, 0), x, h1, a1,
+                                                    [&](int i) { ws.spread(next, nbuf, i, (u1() - u0()) * KT1); });
+              ++gs;
+              ++sn;
+            };
+            layer1_parts<Net>(part);
           } else {
             Net::layer1(&s_l1[net][0] + lane, x, h1);
           }
@@ -826,13 +847,13 @@ next_row_block:
           // hidden layers 2 .. layers-1: h1 <- tanh(W h1 + b), one 32-unit chunk per block
 #pragma unroll 1
           for (int layer = 2; layer < layers; ++layer) {
-            Op hb[NB][Net::KT2 * Net::PT];
+            Act hb[NB][Net::KT2 * Net::PT];
 #pragma unroll 1
             for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
               if (sn != 0) ws.wait_oldest();
               int next, nbuf;
               prefetch_target(next, nbuf);
-              Op hn[CPS][NB][Net::PC];
+              Act hn[CPS][NB][Net::PC];
 #pragma unroll
               for (int c = 0; c < CPS; ++c) {
                 const u32x4* tiles = ws.tiles(gs % NBUF, c);
@@ -861,8 +882,8 @@ next_row_block:
               ++sn;
             }
             {
-              Op hl[NB][Net::PC];
-              Net::hidden_drain(acc, hl);
+              Act hl[NB][Net::PC];
+              Net::hidden_drain(ws.tiles((gs + NBUF - 1) % NBUF, CPS - 1), acc, hl, h);  // (the last stage's buffer)
 #pragma unroll
               for (int q = 0; q < NB; ++q)
 #pragma unroll
@@ -1010,9 +1031,15 @@ next_row_block:
           };
           if constexpr (SPLIT_PER_NET) tri_operands_again(f, x[0]);
           if constexpr (L1S) {
-            const int next = stage_ahead(0), nbuf = (gs + Stream::AHEAD) % NBUF;
-            Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });
-            ++gs;
+            f32x16 a1;
+            auto part = [&](auto u0, auto u1) __attribute__((always_inline)) {
+              if (u0() > 0) stage_wait();
+              const int next = stage_ahead(u0() > 0 ? 1 : 0), nbuf = (gs + Stream::AHEAD) % NBUF;
+              Net::template layer1_part<u0(), u1()>(ws.tiles(gs % NBUF, 0), x, h1, a1,
+                                                    [&](int i) { ws.spread(next, nbuf, i, (u1() - u0()) * KT1); });
+              ++gs;
+            };
+            layer1_parts<Net>(part);
           } else {
             Net::layer1(&s_l1[net][0] + lane, x, h1);
           }
@@ -1318,7 +1345,7 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
     if constexpr (!HAS_NETS) {
       out_p[0] = out_v[0] = zero16();
     } else {
-      Tri h1[1][Net::KT2];
+      Duo h1[1][Net::KT2];
       Tri x[1][KT1];  // the state with the constant 1 at input D
       f32x8 f[KT1];
 #pragma unroll
@@ -1336,11 +1363,16 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
         const int spn = ws.stages_per_net;
         int sn = 0;  // stage within the network
         if constexpr (L1S) {
-          ws.wait_oldest();
-          const int next = net * spn + Stream::AHEAD, nbuf = (gs + Stream::AHEAD) % NBUF;
-          Net::layer1(ws.tiles(gs % NBUF, 0), x, h1, [&](int i) { ws.spread(next, nbuf, i, Net::NUC * KT1); });
-          ++gs;
-          ++sn;
+          f32x16 a1;
+          auto part = [&](auto u0, auto u1) __attribute__((always_inline)) {
+            ws.wait_oldest();
+            const int next = net * spn + sn + Stream::AHEAD, nbuf = (gs + Stream::AHEAD) % NBUF;
+            Net::template layer1_part<u0(), u1()>(ws.tiles(gs % NBUF, 0), x, h1, a1,
+                                                  [&](int i) { ws.spread(next, nbuf, i, (u1() - u0()) * KT1); });
+            ++gs;
+            ++sn;
+          };
+          layer1_parts<Net>(part);
         } else {
           Net::layer1(&s_l1[net][0] + lane, x, h1);
         }
@@ -1348,14 +1380,14 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
           // hidden layers 2 .. layers-1 (see the particle kernel): h1 <- tanh(W h1 + b)
 #pragma unroll 1
           for (int layer = 2; layer < layers; ++layer) {
-            Tri hb[1][Net::KT2];
+            Duo hb[1][Net::KT2];
 #pragma unroll 1
             for (int sc = 0; sc < Stream::CHUNK_STAGES; ++sc) {
               ws.wait_oldest();
               int next = net * spn + sn + Stream::AHEAD;
               if (next >= 2 * spn) next -= 2 * spn;
               const int nbuf = (gs + Stream::AHEAD) % NBUF;
-              Tri hn[1][Net::PC];
+              Duo hn[1][Net::PC];
               const u32x4* tiles = ws.tiles(gs % NBUF, 0);
               auto tick = [&](int kt) { ws.spread(next, nbuf, kt, Net::KT2); };
               if (sc == 0)
@@ -1372,8 +1404,8 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
               ++sn;
             }
             {
-              Tri hl[1][Net::PC];
-              Net::hidden_drain(acc, hl);
+              Duo hl[1][Net::PC];
+              Net::hidden_drain(ws.tiles((gs + NBUF - 1) % NBUF, 0), acc, hl, h);  // (the last stage's buffer)
 #pragma unroll
               for (int j = 0; j < Net::PC; ++j) hb[0][(Net::NUC - 1) * Net::PC + j] = hl[0][j];
             }

@@ -121,3 +121,65 @@ def test_fp32_networks_against_float64(hidden, layers, gauss):
         e = error(got, want)
         print(f"{what}: {e:.2e}")
         assert e < SPLIT_BOUND, (what, e)
+
+
+# ---- layers behind the first one: two fp16 pieces per operand, three products, each unit's weights times a power of two
+FP16_PRODUCTS = ((1, 0), (0, 1), (0, 0))   # (piece of the weight, piece of the input)
+
+
+def fp16_pieces(v):
+    a = v.astype(np.float16).astype(np.float32)
+    return a, (v - a).astype(np.float16).astype(np.float32)
+
+
+def fp16_layer(missing=None, at=None):
+    first = split_layer()
+
+    def f(k, x, w, b):
+        if k == 0:
+            return first(k, x, w, b)
+        power = np.exp2(14 - np.floor(np.log2(np.abs(w).max(0)))).astype(np.float32)
+        px, pw = fp16_pieces(x), fp16_pieces(w * power)
+        y = sum(px[j].astype(np.float64) @ pw[i] for i, j in FP16_PRODUCTS if not (k == at and (i, j) == missing))
+        return (y / power + b).astype(np.float32)
+    return f
+
+
+@pytest.mark.parametrize("hidden,layers,gauss", SHAPES)
+def test_the_bound_tells_a_missing_fp16_piece(hidden, layers, gauss):
+    cfg, params, rows = case(hidden, layers, gauss)
+    want = exact(cfg, params, rows)
+    # (the loss of two pieces, below the bound's share for a network with serially rounded sums)
+    assert error(forward(cfg, params, rows, fp16_layer()), want) < 0.25 * SPLIT_BOUND
+    for k in range(1, layers):
+        for missing in FP16_PRODUCTS:
+            e = error(forward(cfg, params, rows, fp16_layer(missing, k)), want)
+            assert e > 1.25 * SPLIT_BOUND, (k, missing, e)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hidden,layers,gauss", [(64, 2, False), (128, 3, False), (256, 2, False), (256, 3, True)])
+def test_units_with_weights_of_any_magnitude(hidden, layers, gauss):
+    """Hidden units whose weights and bias are 2^-140 to 2^110 times the usual ones: the power of two that a unit's weights
+    are stored with follows them."""
+    import torch
+    from helpers import GpuRollout, oracle_setup
+    cfg, params, rows = case(hidden, layers, gauss)
+    rng, at = np.random.default_rng(7), 0
+    for out in (cfg.out_dim, 1):
+        dims = [cfg.obs_dim] + [hidden] * layers + [out]
+        for k, (i, o) in enumerate(zip(dims[:-1], dims[1:])):
+            if 0 < k < layers:
+                power = np.exp2(rng.choice([-140, -90, -20, 0, 0, 0, 0, 2, 40, 110], o)).astype(np.float32)
+                params[at:at + i * o].reshape(i, o)[:] *= power
+                params[at + i * o:at + i * o + o] *= power
+            at += i * o + o
+    with GpuRollout(cfg, params, 11, dyn=oracle_setup(cfg)[3]) as gpu:
+        a = torch.empty((cfg.M, cfg.act_dim) if gauss else (cfg.M,), dtype=torch.float32 if gauss else torch.int32, device="cuda")
+        lp, v = torch.empty(cfg.M, device="cuda"), torch.empty(cfg.M, device="cuda")
+        lg = torch.empty((cfg.M, cfg.out_dim), device="cuda")
+        gpu.B.msrl_act(gpu.state, gpu.params, torch.from_numpy(rows).cuda(), a, lp, v, lg)
+    for what, got, value in (("outputs", lg.cpu().numpy(), False), ("values", v.cpu().numpy()[:, None], True)):
+        e = error(got, exact(cfg, params, rows, value))
+        print(f"{what}: {e:.2e}")
+        assert e < SPLIT_BOUND, (what, e)
