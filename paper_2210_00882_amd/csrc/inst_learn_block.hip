@@ -57,8 +57,7 @@ hipError_t launch_ppo_block_bf16_h64(int in_dim, const BlockArgsB& a, dim3 grid,
 hipError_t launch_ppo_block_bf16_h128(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s);
 hipError_t launch_ppo_block_bf16_h256(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s);
 
-hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, unsigned slices, unsigned nets, hipStream_t s) {
-  const dim3 grid(slices, nets);
+hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) {
   return hidden == 64 ? launch_ppo_block_bf16_h64(in_dim, a, grid, s)
        : hidden == 128 ? launch_ppo_block_bf16_h128(in_dim, a, grid, s) : launch_ppo_block_bf16_h256(in_dim, a, grid, s);
 }

@@ -1,5 +1,5 @@
-// Learner's gradient pass for bf16 networks of two hidden layers and a categorical policy of up to 16 actions: the
-// one-kernel form of learn_block.h (a team of waves, one per 32 hidden units, takes 64 rows at a time and keeps the
+// Learner's gradient pass for bf16 networks of two hidden layers of 128 or 256 units and a categorical policy of up to 16 actions: the
+// one-kernel form of learn_block.h (a workgroup's waves, one or two per 32 hidden units, take 64 rows at a time and keep the
 // weight gradients of its rows in registers), on the bf16 matrix pipe.
 //
 // Layers are computed transposed (units x rows): weights are the A operand, the rows' activations the B operand, read
@@ -12,9 +12,8 @@
 // units the matrix pipe is busy for 8.2 k, the vector ALU for 11.2 k, the LDS for 7.2 k (counters; activations are read
 // once by each of the eight waves in either layer product); the waves wait for 48 % of theirs.  Writing the activations
 // and their gradients out for contractions of their own (4 KiB per row and network) was bound by that traffic.
-// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.78 ms, 128 (36) 0.71 -> 0.39, 64 (18) 0.22 ->
-// 0.15 (the pursuit env's 20 inputs alike); of 8192 rows 126 -> 57, 76 -> 32, 45 -> 28 us (three launches where there were
-// six).
+// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.78 ms, 128 (36) 0.71 -> 0.39; of 8192 rows 126 ->
+// 57, 76 -> 32 us (three launches where there were six).  64 units: learn_wave_bf16.h.
 //
 // Inside a slice of the rows the sums keep their order from one version of the learner to the next: a 64-row tile behind the
 // other, and which 16 products an MFMA adds at once.  Where the slices begin follows the number of compute units.  A bf16
@@ -48,7 +47,8 @@ struct BlockArgsB {
   const float *logp_old, *adv, *ret;
   RowSel sel;
   int64_t R;
-  int64_t rows_per_slice;     // teams of a whole workgroup: rows of slice blockIdx.x, a multiple of 64
+  int64_t rows_per_slice;     // rows of slice blockIdx.x, a multiple of 64 (128 and 256 units)
+  int slices0;                // 64 units: workgroups of net[0], in front of those of net[1]
   int D;
   float clip, vf_coef, ent_coef, inv_R;
   float* part;                // [workgroup][part_stride] copies of the gradient
@@ -116,27 +116,23 @@ template <int H, int XT> struct BlockShapeB {
   // 128 units: two waves per group of units, a 32-row tile each (eight waves for the compute unit, whose share of a
   // minibatch is one workgroup)
   static constexpr int RS = H == 128 ? 2 : 1;
-  static constexpr int NW = NWU * RS;             // waves of a team
-  // 64 units: four teams, who share the weights in LDS; the team takes every fourth 32-row tile, and the teams' sums are
-  // joined at the end
-  static constexpr int TEAMS = H == 64 ? 4 : 1;
-  static constexpr int TEAM_THREADS = 64 * NW, THREADS = TEAM_THREADS * TEAMS;
-  static constexpr int ROWS = 64, RT = ROWS / 32 / RS;  // rows of a team's tile; 32-row tiles of a wave
+  static constexpr int NW = NWU * RS;             // waves
+  static constexpr int THREADS = 64 * NW;
+  static constexpr int ROWS = 64, RT = ROWS / 32 / RS;  // rows of a tile; 32-row tiles of a wave
   static constexpr int KH = H / 16, KX = 2 * XT;
   typedef LdsRows<H / 8> Rh;    // activations
   typedef LdsRows<4 * XT> Rx;   // observations
   typedef LdsRows<2> Ry;        // dL/dy
-  // weights of the two layer products: in registers up to 128 units (KH + 1 and KH tiles of 4 each), else streamed from
+  // weights of the two layer products: in registers for 128 units (KH + 1 and KH tiles of 4 each), else streamed from
   // memory
   static constexpr bool RESIDENT = H <= 128;
   static constexpr int WD = 4;  // tiles fetched ahead of their product when streamed
   static constexpr bool G3_LDS = H > 128;  // dL/dW3 waits in LDS between the tiles (the registers are full)
-  static constexpr int XBUF = H <= 64 ? 1 : 2;   // (64 units: four teams' rows leave no room for a second buffer)
   static constexpr bool OWN_DZ = RS > 1;  // dL/dz in arrays of their own: two waves share a column of h1, h2
   // dL/dW2: waves in a grid of MG groups of 32 MT units of layer 1 by NW / MG groups of 32 NT units of layer 2 (NT <= MG)
   static constexpr int MT = H == 256 ? 2 : 1, MG = NWU / MT, NT = NWU * MG / NW;
   static constexpr int CW = 16 * XT;              // threads per row in the copy of the observations, two columns each
-  static constexpr int RSTEP = TEAM_THREADS / CW; // rows per round
+  static constexpr int RSTEP = THREADS / CW;      // rows per round
   static constexpr int XN = ROWS / RSTEP;
 };
 
@@ -146,31 +142,29 @@ template <int H, int XT, bool VEC2>
 __global__ __launch_bounds__((BlockShapeB<H, XT>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
 void ppo_block_bf16_kernel(BlockArgsB a) {
   typedef BlockShapeB<H, XT> S;
-  constexpr int NW = S::NW, NWU = S::NWU, RS = S::RS, TEAMS = S::TEAMS, RT = S::RT, ROWS = S::ROWS, KH = S::KH, KX = S::KX;
+  constexpr int NW = S::NW, NWU = S::NWU, RS = S::RS, RT = S::RT, ROWS = S::ROWS, KH = S::KH, KX = S::KX;
   typedef typename S::Rh Rh;
   typedef typename S::Rx Rx;
   typedef typename S::Ry Ry;
   constexpr int MT = S::MT, MG = S::MG, NT = S::NT;
-  static_assert(MT * NT * NW == NWU * NWU && NT <= MG && (RS == 1 || TEAMS == 1), "the waves' tiles of dL/dW2 cover it");
+  static_assert(MT * NT * NW == NWU * NWU && NT <= MG, "the waves' tiles of dL/dW2 cover it");
   constexpr int G1 = (XT + RS - 1) / RS;  // tiles of dL/dW1 per wave: t = RS g + rg
-  struct Team {
+  struct Rows {
     __attribute__((aligned(16))) __bf16 h1[ROWS * Rh::ROW], h2[ROWS * Rh::ROW];
     __attribute__((aligned(16))) __bf16 dz[2][S::OWN_DZ ? ROWS * Rh::ROW : 1];  // else dL/dz1, dL/dz2 take the place of h1, h2
-    __attribute__((aligned(16))) __bf16 x[S::XBUF][ROWS * Rx::ROW];  // this tile's and, with two, the next one's
+    __attribute__((aligned(16))) __bf16 x[2][ROWS * Rx::ROW];  // this tile's and the next one's
     __attribute__((aligned(16))) __bf16 dy[ROWS * Ry::ROW];
     __attribute__((aligned(16))) f32x4 st[ROWS];     // the rows' statistics, over the tiles
     int64_t row[ROWS], obs[ROWS];                    // where the rows of a tile lie in the caller's arrays (-1: beyond the
   };                                                 // end): row, first observation
-  __shared__ Team s_team[TEAMS];
+  __shared__ Rows s;
   __shared__ __attribute__((aligned(16))) float s_b3[32];
   __shared__ __attribute__((aligned(16))) f32x4 s_g3[S::G3_LDS ? 2 * S::THREADS : 1];
   __shared__ __attribute__((aligned(16))) u32x4 s_w1[NWU * KX * 64];
   __shared__ __attribute__((aligned(16))) u32x4 s_w3[KH * 64];
   __shared__ __attribute__((aligned(16))) u32x4 s_w3t[NWU * 64];
-  __shared__ float s_red[TEAMS > 1 ? (TEAMS - 1) * NW * 16 * 64 : 1];  // the other teams' copy of one gradient tile
   const BlockNetB& nt = a.net[blockIdx.y];
-  const int gwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), team = gwave / NW, wave = gwave % NW;
-  Team& s = s_team[team];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int lane = threadIdx.x & 63;
   const int O = nt.out, kx = block_bf16_k_tiles(a.D);  // (<= KX: the launcher's choice of XT)
   const int uw = wave % NWU, rg = wave / NWU, u0 = 32 * uw, ro = 32 * RT * rg;  // this wave's units and first row
@@ -178,25 +172,14 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   const bool policy = nt.policy != 0;
   const int mg = wave % MG, ng = wave / MG;  // this wave's part of dL/dW2
 
-  // rows: one team: the 64-row tiles of slice blockIdx.x; several: team t takes the 32-row tiles TEAMS g + t of the
-  // groups g = blockIdx.x, blockIdx.x + gridDim.x, ..., two at a time
-  const int64_t n_tiles = (a.R + 31) / 32, groups = (n_tiles + TEAMS - 1) / TEAMS;
+  // rows: the 64-row tiles of slice blockIdx.x
   const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_slice;
-  const int steps = TEAMS > 1 ? (int)(((groups - blockIdx.x + gridDim.x - 1) / gridDim.x + 1) / 2)
-                              : (int)((min(a.R - r_begin, a.rows_per_slice) + ROWS - 1) / ROWS);
-  // (the lanes of the team's last wave fill the table of step `st`)
+  const int steps = (int)((min(a.R - r_begin, a.rows_per_slice) + ROWS - 1) / ROWS);
+  // (the lanes of the last wave fill the table of step `st`)
   auto fill_rows = [&](int st) {
     if (wave != NW - 1) return;
-    int64_t r;
-    bool ok;
-    if constexpr (TEAMS > 1) {
-      const int64_t g = blockIdx.x + (int64_t)(2 * st + (lane >> 5)) * gridDim.x;
-      r = (g * TEAMS + team) * 32 + (lane & 31);
-      ok = g < groups && r < a.R;
-    } else {
-      r = r_begin + (int64_t)st * ROWS + lane;
-      ok = r < a.R && st < steps;  // (slices are whole tiles)
-    }
+    const int64_t r = r_begin + (int64_t)st * ROWS + lane;
+    const bool ok = r < a.R && st < steps;  // (slices are whole tiles)
     const int64_t p = ok ? a.sel.at(r) : 0;
     s.row[lane] = ok ? p : -1;
     s.obs[lane] = p * a.D;
@@ -228,11 +211,11 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   // (this thread's tiles; a place of its own)
   auto g3_load = [&] {
     if constexpr (S::G3_LDS)
-      for (int m = 0; m < 2; ++m) gW3[m] = s_g3[m * S::THREADS + 64 * gwave + lane];
+      for (int m = 0; m < 2; ++m) gW3[m] = s_g3[m * S::THREADS + 64 * wave + lane];
   };
   auto g3_store = [&] {
     if constexpr (S::G3_LDS)
-      for (int m = 0; m < 2; ++m) s_g3[m * S::THREADS + 64 * gwave + lane] = gW3[m];
+      for (int m = 0; m < 2; ++m) s_g3[m * S::THREADS + 64 * wave + lane] = gW3[m];
   };
   g3_store();
   float run2 = 0.0f, run3 = 0.0f;  // sums of dL/dz2 (this lane's unit of column tile mg) and, in the last wave, of dL/dy
@@ -252,8 +235,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
 
   // observations: two columns per thread, RSTEP rows at a time; a row beyond the end reads as zero; columns D and D + 1
   // are the constant 1 that the two parts of the bias meet
-  const int ttid = threadIdx.x % S::TEAM_THREADS;
-  int xc = 2 * (ttid % S::CW), xr = ttid / S::CW;
+  int xc = 2 * (threadIdx.x % S::CW), xr = threadIdx.x / S::CW;
   f32x2 xv[S::XN];
   auto fetch_x = [&]() {  // (the row table holds the tile; always some row, so no branch around the loads)
     const float *src = a.obs + (xc < a.D ? xc : 0), *src1 = a.obs + (xc + 1 < a.D ? xc + 1 : 0);
@@ -531,77 +513,47 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
           if (RS * g + rg < XT) gW1[g] = mma(Rx::read(s_x + 16 * k * Rx::ROW, colx, 4 * (RS * g + rg)), fb, gW1[g]);
       }
     }
-    if constexpr (S::XBUF == 1) __syncthreads();  // every wave is done with the observations
-    else buf ^= 1;
+    buf ^= 1;
     store_x(s.x[buf]);
   }
 
-  // the teams' tiles are added in team order
-  auto join = [&](auto& g, auto n) {
-    if constexpr (TEAMS > 1) {
-      __syncthreads();  // the tile before has been read
-      if (team > 0) {
-#pragma unroll
-        for (int r = 0; r < n(); ++r) s_red[(((team - 1) * NW + wave) * 16 + r) * 64 + lane] = g[r];
-      }
-      __syncthreads();
-      if (team == 0) {
-#pragma unroll
-        for (int t = 0; t < TEAMS - 1; ++t)
-#pragma unroll
-          for (int r = 0; r < n(); ++r) g[r] += s_red[((t * NW + wave) * 16 + r) * 64 + lane];
-      }
-    }
-  };
-  constexpr std::integral_constant<int, 16> whole;
   // this workgroup's copy of the gradient: register r of lane (i, h) <-> row 8 (r / 4) + 4 h + r % 4 of a tile, column i,
   // where units are in the chained order
   const int i = lane & 31, h = lane >> 5, ci = chained(i);
   float* part = a.part + (int64_t)blockIdx.x * a.part_stride;
 #pragma unroll
   for (int g = 0; g < G1; ++g) {
-    join(gW1[g], whole);
     if (RS * g + rg >= XT) continue;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int m = 32 * (RS * g + rg) + 8 * (r / 4) + 4 * h + r % 4;
-      if (team == 0 && m < a.D) part[nt.oW1 + m * H + u0 + ci] = gW1[g][r];
-      if (team == 0 && m == a.D) part[nt.ob1 + u0 + ci] = gW1[g][r];
+      if (m < a.D) part[nt.oW1 + m * H + u0 + ci] = gW1[g][r];
+      if (m == a.D) part[nt.ob1 + u0 + ci] = gW1[g][r];
     }
   }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      join(gW2[mt][n], whole);
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (team == 0)
-          part[nt.oW2 + (32 * (MT * mg + mt) + chained(8 * (r / 4) + 4 * h + r % 4)) * H + 32 * (NT * ng + n) + ci] = gW2[mt][n][r];
+        part[nt.oW2 + (32 * (MT * mg + mt) + chained(8 * (r / 4) + 4 * h + r % 4)) * H + 32 * (NT * ng + n) + ci] = gW2[mt][n][r];
     }
   g3_load();
-  float last[10];  // dL/dW3, and the sums of dL/dz2 and dL/dy
 #pragma unroll
-  for (int r = 0; r < 8; ++r) last[r] = gW3[r / 4][r % 4];
-  last[8] = run2;
-  last[9] = run3;
-  join(last, std::integral_constant<int, 10>());
-  if (team == 0) {
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int o = chained(8 * (r / 4) + 4 * h + r % 4);
-      if (rg == 0 && o < O) part[nt.oW3 + (u0 + ci) * O + o] = last[r];
-    }
-    if (h == 0 && mg < NT) part[nt.ob2 + 32 * (NT * ng + mg) + ci] = last[8];
-    if (wave == NW - 1 && h == 0 && i < 16 && ci < O) part[nt.ob3 + ci] = last[9];
+  for (int r = 0; r < 8; ++r) {
+    const int o = chained(8 * (r / 4) + 4 * h + r % 4);
+    if (rg == 0 && o < O) part[nt.oW3 + (u0 + ci) * O + o] = gW3[r / 4][r % 4];
   }
+  if (h == 0 && mg < NT) part[nt.ob2 + 32 * (NT * ng + mg) + ci] = run2;
+  if (wave == NW - 1 && h == 0 && i < 16 && ci < O) part[nt.ob3 + ci] = run3;
   if (wave == 0) {  // (the last loss is behind a barrier)
     f32x4 st = s.st[lane];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
       for (int q = 0; q < 4; ++q) st[q] += __shfl_xor(st[q], o);
-    const int bin = (blockIdx.x * TEAMS + team) % a.stat_bins;
+    const int bin = blockIdx.x % a.stat_bins;
     if (lane == 0 && policy) {
       atomicAdd(a.stats + 8 + bin, st[0]);
 #pragma unroll
@@ -628,7 +580,7 @@ struct BlockPackJobsB {
   int n_clear;
 };
 hipError_t launch_block_pack_bf16(const BlockPackJobsB& jobs, int max_items, hipStream_t s);
-hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, unsigned slices, unsigned nets, hipStream_t s);
+hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s);
 
 #define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                       \
   hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) {      \

@@ -1,0 +1,450 @@
+// Learner's gradient pass for bf16 networks of two hidden layers of 64 units and a categorical policy of up to 16 actions: a
+// wave takes 32 rows of one network through the forward pass, the loss and the backward pass by itself.
+//
+// A network of 64 units is small enough for that: a layer is two accumulators, what a layer gives is the next one's
+// operand (lane = row; "chained", packed.h) and stays in registers, forward and backward, and so do all the weight gradients
+// (120 registers).  The workgroup's eight waves share the weights in LDS and meet again only at the end, when their gradients
+// are added up in wave order.  LDS turns rows into columns: the weight gradients contract over the rows, and their
+// operands come from the wave's own copy of its rows through the transposing read (LdsRows).
+//
+// What bounds it: one tile's chain (a tile of 32 rows takes a wave 5.3 us, of which its vector instructions are about 3) and that
+// two waves to a SIMD do not cover it: the VALU is active for 60 % of the cycles, the matrix pipe for 18 %.  Before (teams of two
+// waves on 64 rows, the layers meeting in LDS behind six barriers a tile) 49 % and 13 %.  Gradient of 524,288, 131,072, 32,768
+// and 1000 rows with 20 inputs, before and now: 158 -> 111 us, 67 -> 46, 53 -> 29, 25 -> 22; with 48 inputs 176 -> 165,
+// 76 -> 66, 60 -> 42, 29 -> 28.  No faster: the vector work dealt out between the MFMAs by hand (117; it takes registers, or
+// LDS in their place), the policy's waves on more of the compute units than the value network's (54 %: 115).
+//
+// Rounding as in learn_block_bf16.h.
+#pragma once
+#include "learn_block_bf16.h"
+
+namespace msrl {
+
+template <int XT> struct WaveShapeB {
+  // (above 30 inputs dL/dW1 takes 32 registers more, and one wave to a SIMD is faster than two that spill: 165 us, not 233)
+  static constexpr int WAVES = XT == 1 ? 8 : 4, THREADS = 64 * WAVES;
+  static constexpr int KX = 2 * XT;
+  typedef LdsRows<8> Rh;        // activations
+  typedef LdsRows<4 * XT> Rx;   // observations
+  typedef LdsRows<2> Ry;        // dL/dy
+  // a lane's gradient registers: dL/dW1, dL/dW2, dL/dW3, and of dL/db2 and dL/db3 one each
+  static constexpr int Q1 = XT * 2 * 16, Q2 = 64, Q3 = 16, QB = 2, Q = Q1 + Q2 + Q3 + QB;
+};
+
+// 16 x 16 (x 32): lane (j = lane % 16, g = lane / 16): operands hold row / column j, contraction index 8 g .. 8 g + 7; register r
+// of the result is row 4 g + r, column j
+__device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// the values of lane % 32 and of lane % 32 + 32, on both
+__device__ __forceinline__ void both_halves(float v, float& lo, float& hi) {
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  lo = __uint_as_float(q[0]);
+  hi = __uint_as_float(q[1]);
+}
+
+// OT: outputs there is room for, 8 or 16 (two lanes share a row's: lane (i, h) has outputs 8 (r / 4) + 4 h + r % 4, r < OT / 2)
+template <int XT, int OT, bool VEC2>
+__global__ __launch_bounds__((WaveShapeB<XT>::THREADS)) __attribute__((amdgpu_waves_per_eu(WaveShapeB<XT>::WAVES / 4)))
+void ppo_wave_bf16_kernel(BlockArgsB a) {
+  typedef WaveShapeB<XT> S;
+  typedef typename S::Rh Rh;
+  typedef typename S::Rx Rx;
+  typedef typename S::Ry Ry;
+  constexpr int H = 64, KH = H / 16, KX = S::KX, WAVES = S::WAVES, OR = OT / 2;
+  struct Wave {
+    __attribute__((aligned(16))) __bf16 h1[32 * Rh::ROW], h2[32 * Rh::ROW];  // dL/dz1, dL/dz2 take their places
+    __attribute__((aligned(16))) __bf16 x[32 * Rx::ROW];
+    __attribute__((aligned(16))) __bf16 dy[32 * Ry::ROW];
+  };
+  constexpr int JOIN = (int)(sizeof(Wave) / 256);  // gradient registers of a wave that fit its place
+  __shared__ Wave s_wave[WAVES];
+  // weight tiles in the order in which they are used
+  constexpr int T1 = 2 * KX, T2 = 2 * (KH + 1), T3 = KH, T3T = 2, T2T = 2 * KH, TILES = T1 + T2 + T3 + T3T + T2T;
+  __shared__ __attribute__((aligned(16))) u32x4 s_w[TILES * 64];
+  __shared__ __attribute__((aligned(16))) float s_b3[32];
+  __shared__ __attribute__((aligned(16))) u32x4 s_real[2];  // pairs of a lane's outputs: which are outputs
+  __shared__ __attribute__((aligned(16))) u32x4 s_keep[KX][2], s_one[KX][2];  // pairs of inputs: which are observations, which the constant 1
+  const int net = blockIdx.x < (unsigned)a.slices0 ? 0 : 1;
+  const BlockNetB& nt = a.net[net];
+  const int slice = net == 0 ? (int)blockIdx.x : (int)blockIdx.x - a.slices0;
+  const int slices = net == 0 ? a.slices0 : (int)gridDim.x - a.slices0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Wave& s = s_wave[wave];
+  int lane = threadIdx.x & 63;
+  const int O = nt.out, D = a.D, kx = block_bf16_k_tiles(D);  // (<= KX: the launcher's choice of XT)
+  const bool policy = nt.policy != 0;
+  const int64_t n_tiles = (a.R + 31) / 32;
+
+  for (int k = threadIdx.x; k < TILES * 64; k += S::THREADS) {
+    const int l = k & 63;
+    int t = k >> 6;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (t < T1) {
+      if (t % KX < kx) v = nt.w1[(t / KX * kx + t % KX) * 64 + l];
+    } else if ((t -= T1) < T2) {
+      // k tiles 0 and 1 of both unit tiles, then 2, 3 and the bias of the first and of the second
+      const int c = t < 4 ? t / 2 : t < 7 ? 0 : 1, q = t < 4 ? t % 2 : t < 7 ? t - 2 : t - 5;
+      v = nt.w2[(c * (KH + 1) + q) * 64 + l];
+    } else if ((t -= T2) < T3) {
+      v = nt.w3[t * 64 + l];
+    } else if ((t -= T3) < T3T) {
+      v = nt.w3t[t * 64 + l];
+    } else {
+      v = nt.w2t[(t - T3T) * 64 + l];
+    }
+    s_w[k] = v;
+  }
+  // (an output that is none has a logit of -1e38: no share in the sums over the actions)
+  if (threadIdx.x < 32) s_b3[threadIdx.x] = (int)threadIdx.x < O ? nt.b3[threadIdx.x] : -1.0e38f;
+  if (threadIdx.x < 8) {
+    uint32_t real = 0;
+    for (int e = 0; e < 2; ++e) real |= chained(2 * threadIdx.x + e) < O ? 0xFFFFu << 16 * e : 0u;
+    ((uint32_t*)s_real)[threadIdx.x] = real;
+  }
+  if (threadIdx.x < KX * 8) {  // columns D and D + 1 are the constant 1 that the two parts of the bias meet
+    uint32_t keep = 0, one = 0;
+    for (int e = 0; e < 2; ++e) {
+      const int c = 2 * threadIdx.x + e;
+      keep |= c < D ? 0xFFFFu << 16 * e : 0u;
+      one |= c >= D && c < D + 2 ? 0x3F80u << 16 * e : 0u;
+    }
+    ((uint32_t*)s_keep)[threadIdx.x] = keep;
+    ((uint32_t*)s_one)[threadIdx.x] = one;
+  }
+
+  f32x16 gW1[XT][2], gW2[2][2];
+  f32x4 gW3[4], gb = {0.0f, 0.0f, 0.0f, 0.0f}, st = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int t = 0; t < XT; ++t) gW1[t][0] = gW1[t][1] = zero16();
+#pragma unroll
+  for (int m = 0; m < 2; ++m) gW2[m][0] = gW2[m][1] = zero16();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) gW3[u] = gb;
+  auto ones_in = [](bool row) {  // an operand of ones in some rows
+    const uint32_t w = row ? 0x3F803F80u : 0u;
+    return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
+  };
+
+  // Tiles of this wave: (8 k + wave) slices + slice, k = 0, 1, ...: few tiles go to different compute units.  Row r of the
+  // minibatch is array row q group + first + rem with r = q count + rem: one division here, then steps of a fixed number of rows.
+  int64_t tile = (int64_t)wave * slices + slice;
+  const int64_t tile_step = (int64_t)WAVES * slices;
+  const int count = a.sel.count == 0 ? 1 : a.sel.count, group = a.sel.count == 0 ? 1 : a.sel.group;
+  int64_t p = a.sel.at(tile * 32 + (lane & 31));
+  int rem = (int)((a.sel.row0 + tile * 32 + (lane & 31)) % count);
+  const int64_t p_step = (tile_step * 32) / count * group + (tile_step * 32) % count;
+  const int rem_step = (int)((tile_step * 32) % count);
+
+  // this row's inputs 16 kt + 8 h .. + 7 and what the loss reads; a row beyond the end reads row 0 of the arrays
+  f32x2 xv[KX][4];
+  int act = 0;
+  float lpo = 0.0f, target = 0.0f;
+  bool valid = false;
+  const float* targets = policy ? a.adv : a.ret;  // advantage or return
+  auto fetch = [&]() {
+    const int h = lane >> 5;
+    valid = tile * 32 + (lane & 31) < a.R;
+    const int64_t at = valid ? p : 0;
+    const float* src = a.obs + at * D;
+#pragma unroll
+    for (int kt = 0; kt < KX; ++kt) {
+      if (kt >= kx) break;  // uniform
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 16 * kt + 8 * h + 2 * e;
+        if constexpr (VEC2) xv[kt][e] = *(const f32x2*)(src + min(c, D - 2));
+        else xv[kt][e] = f32x2{src[min(c, D - 1)], src[min(c + 1, D - 1)]};
+      }
+    }
+    act = a.actions[at];
+    lpo = a.logp_old[at];
+    target = targets[at];
+  };
+  if (tile < n_tiles) fetch();
+  __syncthreads();  // the weights are in
+  // the tiles of s_w one behind the other and round again: LDS reads run a ring ahead (two waves to a SIMD have no registers
+  // for more than two tiles)
+  constexpr int RING = WAVES == 8 ? 2 : 4;
+  static_assert(TILES % RING == 0, "the ring goes round with the tiles");
+  u32x4 ring[RING];
+#pragma unroll
+  for (int k = 0; k < RING; ++k) ring[k] = s_w[k * 64 + lane];
+
+#pragma unroll 1
+  for (; tile < n_tiles;) {
+    // (hidden from the compiler once per tile: the LDS addresses formed from it are cheap, and kept across tiles they
+    // would be spilled)
+    asm volatile("" : "+v"(lane));
+    const int i = lane & 31, h = lane >> 5, p16 = lane & 15;
+    const typename Rh::Place rows = Rh::place(i, h);
+    // the lane's part of the transposing reads for products of 32 x 32 (rows 8 h .., columns lane % 32) and of 16 x 16 (rows
+    // 8 (lane / 16) .., columns lane % 16)
+    const int tr_row = 8 * h + p16 / 4, tr_piece = 2 * (lane >> 4 & 1) + (lane >> 1 & 1), tr_half = lane & 1;
+    const int tr_row16 = 8 * (lane >> 4) + p16 / 4, tr_piece16 = lane >> 1 & 1;
+    const bool row_ok = valid, whole = (tile + 1) * 32 <= a.R;
+    // ---- layer 1
+    bf16x8 xo[KX];
+    if (!whole) {
+#pragma unroll
+      for (int kt = 0; kt < KX; ++kt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xv[kt][e] = row_ok ? xv[kt][e] : f32x2{0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int kt = 0; kt < KX; ++kt) {
+      const u32x4 keep = s_keep[kt][h], one = s_one[kt][h];
+      u32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(xv[kt][e], bf16x2)) & keep[e] | one[e];
+      xo[kt] = __builtin_bit_cast(bf16x8, v);
+      *(bf16x8*)(s.x + Rx::at(Rx::place(i, h), 2 * kt)) = xo[kt];
+    }
+    const int act_ = act;
+    const float lpo_ = lpo, target_ = target;
+    auto pop = [&](int t) -> bf16x8 {  // (t is a constant)
+      const bf16x8 w = __builtin_bit_cast(bf16x8, ring[t % RING]);
+      ring[t % RING] = s_w[(t + RING) % TILES * 64 + lane];
+      return w;
+    };
+    auto operand = [&](const u32x4& v) { return __builtin_bit_cast(bf16x8, v); };
+    // values 4 q .. 4 q + 3 of unit tile c, as two pairs of an operand: tanh; times the derivative of the activation
+    auto activate = [&](const f32x16& acc, u32x4 (&to)[KH], int c, int q) {
+#pragma unroll
+      for (int e = 4 * q; e < 4 * q + 4; e += 2)
+        to[2 * c + q / 2][e % 8 / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{fast_tanh(acc[e]), fast_tanh(acc[e + 1])}), bf16x2));
+    };
+    auto derive = [&](const f32x16& acc, const u32x4 (&from)[KH], u32x4 (&to)[KH], int c, int q) {
+#pragma unroll
+      for (int e = 4 * q; e < 4 * q + 4; e += 2) {
+        const uint32_t w = from[2 * c + q / 2][e % 8 / 2];
+        const float f0 = __uint_as_float(w << 16), f1 = __uint_as_float(w & 0xFFFF0000u);
+        to[2 * c + q / 2][e % 8 / 2] =
+            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{acc[e] * (1.0f - f0 * f0), acc[e + 1] * (1.0f - f1 * f1)}), bf16x2));
+      }
+    };
+    u32x4 h1[KH], h2[KH], dz[KH];
+    f32x16 acc[2], acc2[2];
+#pragma unroll
+    for (int t = 0; t < T1; ++t) acc[t / KX] = mma(pop(t), xo[t % KX], t % KX == 0 ? zero16() : acc[t / KX]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) activate(acc[0], h1, 0, q);
+    // ---- layer 2
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      acc2[m / 2] = mma(pop(T1 + m), operand(h1[m % 2]), m % 2 == 0 ? zero16() : acc2[m / 2]);
+      activate(acc[1], h1, 1, m);
+    }
+#pragma unroll
+    for (int k = 0; k < KH; ++k) *(u32x4*)(s.h1 + Rh::at(rows, 2 * k)) = h1[k];
+    {
+      // the two parts of the bias sit at k slots 0 and 1 of h = 0
+      const u32x4 one = {lane < 32 ? 0x3F803F80u : 0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int m = 0; m < 3; ++m) acc2[0] = mma(pop(T1 + 4 + m), operand(m < 2 ? h1[2 + m] : one), acc2[0]);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) acc2[1] = mma(pop(T1 + 7 + m), operand(m < 2 ? h1[2 + m] : one), acc2[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) activate(acc2[0], h2, 0, q);
+    // ---- output layer and loss: register r of lane (i, h) <-> output 8 (r / 4) + 4 h + r % 4 of row i
+    f32x8 dy = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    {
+      f32x16 out = bias_init(s_b3, h);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) activate(acc2[1], h2, 1, q);
+#pragma unroll
+      for (int k = 0; k < KH; ++k) out = mma(pop(T1 + T2 + k), operand(h2[k]), out);
+#pragma unroll
+      for (int k = 0; k < KH; ++k) *(u32x4*)(s.h2 + Rh::at(rows, 2 * k)) = h2[k];
+      if (policy) {
+        // in powers of two: u = log2 of the unnormalised probability
+        constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
+        float own[OR], u[OT], e[OT];
+#pragma unroll
+        for (int r = 0; r < OR; ++r) {
+          own[r] = out[r] * LOG2E;
+          both_halves(own[r], u[8 * (r / 4) + r % 4], u[8 * (r / 4) + 4 + r % 4]);
+        }
+        float mx = u[0];
+#pragma unroll
+        for (int k = 1; k < OT; ++k) mx = fmaxf(mx, u[k]);
+        float z = 0.0f, zu = 0.0f, ua = 0.0f;
+#pragma unroll
+        for (int k = 0; k < OT; ++k) {
+          u[k] -= mx;
+          e[k] = __builtin_amdgcn_exp2f(u[k]);
+          z += e[k];
+          zu = __builtin_fmaf(e[k], u[k], zu);
+          ua = k == act_ ? u[k] : ua;
+        }
+        const float lz = __builtin_amdgcn_logf(z), rz = __builtin_amdgcn_rcpf(z);
+        const float ent = LN2 * (lz - zu * rz), logp = LN2 * (ua - lz);
+        const float rho = __expf(logp - lpo_);
+        const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
+        const float un = rho * target_, cl = rc * target_;
+        const bool clipped = cl < un;
+        const float gl = clipped ? 0.0f : -target_ * rho;
+        // each lane differentiates with respect to its own outputs
+#pragma unroll
+        for (int r = 0; r < OR; ++r) {
+          const int k = 8 * (r / 4) + 4 * h + r % 4;
+          const float pk = (h ? e[8 * (r / 4) + 4 + r % 4] : e[8 * (r / 4) + r % 4]) * rz, lp = LN2 * (own[r] - mx - lz);
+          const float dlp = (k == act_ ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
+          dy[r] = (gl * dlp - a.ent_coef * dH) * a.inv_R;
+        }
+        if (!whole) {
+#pragma unroll
+          for (int r = 0; r < OR; ++r) dy[r] = row_ok ? dy[r] : 0.0f;
+        }
+        if (row_ok) st += f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo_ - logp};
+      } else if (row_ok && h == 0) {
+        const float err = out[0] - target_;
+        dy[0] = a.vf_coef * 2.0f * err * a.inv_R;
+        st[0] += err * err;
+      }
+    }
+    const bf16x8 dyo = operand(__builtin_bit_cast(u32x4, __builtin_convertvector(dy, bf16x8)) & s_real[h]);
+    *(bf16x8*)(s.dy + Ry::at(Ry::place(i, h), 0)) = dyo;
+    wave_lds_sync();
+    // ---- dL/dW3 += dL/dy^T h2, dL/db3, dL/dz2 (h1 and h2 are read back where they are used: they would be in the way before)
+    const typename Rh::Columns ch = Rh::columns(tr_row16, tr_piece16, tr_half);
+    {
+      const bf16x8 fy = Ry::read(s.dy, Ry::columns(tr_row16, tr_piece16, tr_half), 0);
+      bf16x8 fh[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) fh[u] = Rh::read(s.h2, ch, 2 * u);
+      u32x4 hr[KH];
+#pragma unroll
+      for (int k = 0; k < KH; ++k) hr[k] = *(const u32x4*)(s.h2 + Rh::at(rows, 2 * k));
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[c] = mma(pop(T1 + T2 + T3 + c), dyo, zero16());
+#pragma unroll
+      for (int u = 0; u < 4; ++u) gW3[u] = mma16(fy, fh[u], gW3[u]);
+      gb = mma16(ones_in(p16 % 4 == 1), fy, gb);
+#pragma unroll
+      for (int v = 0; v < 8; ++v) derive(acc[v / 4], hr, dz, v / 4, v % 4);
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < KH; ++k) *(u32x4*)(s.h2 + Rh::at(rows, 2 * k)) = dz[k];
+    wave_lds_sync();
+    // ---- dL/dz1 = dL/dz2 W2^T times the derivative; dL/dW2 += h1^T dL/dz2 and the sums of dL/dz2 (ones in row 4 u only
+    // put those of units 16 u .. there: one register; those of dL/dy went to rows 1, 5, 9 and 13)
+    const typename Rh::Columns cols = Rh::columns(tr_row, tr_piece, tr_half);
+    {
+      bf16x8 fa[2], fb[2], fu[4];
+      auto frags = [&](int k) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          fa[m] = Rh::read(s.h1 + 16 * k * Rh::ROW, cols, 4 * m);
+          fb[m] = Rh::read(s.h2 + 16 * k * Rh::ROW, cols, 4 * m);
+        }
+      };
+#pragma unroll
+      for (int u = 0; u < 4; ++u) fu[u] = Rh::read(s.h2, ch, 2 * u);
+      u32x4 hr[KH];
+#pragma unroll
+      for (int k = 0; k < KH; ++k) hr[k] = *(const u32x4*)(s.h1 + Rh::at(rows, 2 * k));
+#pragma unroll
+      for (int m = 0; m < T2T; ++m)
+        acc[m / KH] = mma(pop(T1 + T2 + T3 + T3T + m), operand(dz[m % KH]), m % KH == 0 ? zero16() : acc[m / KH]);
+      frags(0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) gb = mma16(ones_in(p16 == 4 * u), fu[u], gb);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        if (m == 4) frags(1);
+        gW2[m % 2][m / 2 % 2] = mma(fa[m % 2], fb[m / 2 % 2], gW2[m % 2][m / 2 % 2]);
+        derive(acc[m / 4], hr, dz, m / 4, m % 4);
+      }
+    }
+    // (the next tile's rows: nothing waits for these loads before the end of this one)
+    tile += tile_step;
+    p += p_step;
+    rem += rem_step;
+    if (rem >= count) {
+      rem -= count;
+      p += group - count;
+    }
+    if (tile < n_tiles) fetch();
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < KH; ++k) *(u32x4*)(s.h1 + Rh::at(rows, 2 * k)) = dz[k];
+    wave_lds_sync();
+    // ---- dL/dW1 += x^T dL/dz1 (input D is the constant 1: the bias gradient)
+    const typename Rx::Columns colx = Rx::columns(tr_row, tr_piece, tr_half);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const bf16x8 fb = Rh::read(s.h1 + 16 * k * Rh::ROW, cols, 4 * c);
+#pragma unroll
+        for (int t = 0; t < XT; ++t) gW1[t][c] = mma(Rx::read(s.x + 16 * k * Rx::ROW, colx, 4 * t), fb, gW1[t][c]);
+      }
+    wave_lds_sync();
+  }
+
+  // ---- statistics: sums over the lanes (both lanes of a row hold the policy's)
+  if (policy && lane >= 32) st = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) st[q] += __shfl_xor(st[q], o);
+  const int bin = (slice * WAVES + wave) % a.stat_bins;
+  if ((int64_t)wave * slices + slice < n_tiles && lane == 0) {
+    if (policy) {
+      atomicAdd(a.stats + 8 + bin, st[0]);
+#pragma unroll
+      for (int q = 1; q < 4; ++q) atomicAdd(a.stats + 8 + (q + 1) * a.stat_bins + bin, st[q]);
+    } else {
+      atomicAdd(a.stats + 8 + a.stat_bins + bin, st[0]);
+    }
+  }
+
+  // ---- the waves' gradients, added in wave order; this workgroup's copy
+  float* part = a.part + (int64_t)slice * a.part_stride;
+  // place in the gradient of register q of lane l, or -1
+  auto place = [&](int q, int l) -> int {
+    const int i = l & 31, h = l >> 5, r = q & 15, row = 8 * (r >> 2) + 4 * h + (r & 3);
+    if (q < S::Q1) {
+      const int m = 32 * (q >> 5) + row, u = 32 * (q >> 4 & 1) + chained(i);
+      return m < D ? nt.oW1 + m * H + u : m == D ? nt.ob1 + u : -1;
+    }
+    q -= S::Q1;
+    if (q < S::Q2) return nt.oW2 + (32 * (q >> 5) + chained(row)) * H + 32 * (q >> 4 & 1) + chained(i);
+    q -= S::Q2;
+    const int o = chained(4 * (l >> 4) + (q & 3));
+    if (q < S::Q3) return o < O ? nt.oW3 + (32 * (q >> 3) + chained(16 * (q >> 2 & 1) + (l & 15))) * O + o : -1;
+    q -= S::Q3;
+    if (q == 0) return nt.ob2 + 32 * (l >> 5) + chained(l & 31);
+    return l < 16 && chained(l) < O ? nt.ob3 + chained(l) : -1;
+  };
+  auto reg = [&](int q) -> float {  // (q is a constant)
+    if (q < S::Q1) return gW1[q / 32][q / 16 % 2][q % 16];
+    q -= S::Q1;
+    if (q < S::Q2) return gW2[q / 32][q / 16 % 2][q % 16];
+    q -= S::Q2;
+    if (q < S::Q3) return gW3[q / 4][q % 4];
+    q -= S::Q3;
+    return gb[q % 2];
+  };
+  const int with_tiles = (int)min((int64_t)WAVES, (n_tiles - slice + slices - 1) / slices);  // waves that had a tile
+  float* s_join = (float*)s_wave;
+#pragma unroll
+  for (int q0 = 0; q0 < S::Q; q0 += JOIN) {
+    __syncthreads();
+    if (wave < with_tiles) {
+#pragma unroll
+      for (int q = q0; q < q0 + JOIN && q < S::Q; ++q) s_join[(wave * JOIN + q - q0) * 64 + lane] = reg(q);
+    }
+    __syncthreads();
+    for (int q = q0 + wave; q < q0 + JOIN && q < S::Q; q += WAVES) {
+      const int at = place(q, lane);
+      float v = 0.0f;
+      for (int w = 0; w < with_tiles; ++w) v += s_join[(w * JOIN + q - q0) * 64 + lane];
+      if (at >= 0) part[at] = v;
+    }
+  }
+}
+
+}  // namespace msrl

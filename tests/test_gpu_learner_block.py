@@ -151,6 +151,22 @@ def test_bf16_block_kernel_equals_the_layer_kernels(d, h, o, R):
     assert torch.allclose(st, st_ref, rtol=1e-2, atol=1e-2 * R ** 0.5)
 
 
+# 64 units: a wave to a tile of 32 rows; one tile more than there are workgroups (128 of a network on 256 compute units), one
+# row more than a tile for each of their waves (8 up to 30 inputs, 4 above), and tiles of selected rows that lie in three groups
+# of rows
+@pytest.mark.parametrize("d,o", [(1, 2), (20, 5), (24, 16), (30, 9), (48, 5)])
+@pytest.mark.parametrize("R,count", [(32, 0), (4097, 0), (16385, 0), (32769, 0), (70001, 0), (33000, 3), (5001, 1)])
+def test_bf16_tiles_of_64_units(d, o, R, count):
+    pol = policy(d, 64, o, False, synth.BF16)
+    sel = B.msrl_row_select(4, 1, count) if count else None
+    R = R // count * count if count else R
+    g, st = gradients(pol, R, 0, rows=sel, bias=1.0)
+    g_ref, st_ref = gradients(pol, R, 1, rows=sel, bias=1.0)
+    assert torch.isfinite(g).all()
+    assert_tensors_close(pol, g, g_ref, bf16_tolerance(R))
+    assert torch.allclose(st, st_ref, rtol=1e-2, atol=1e-2 * R ** 0.5)
+
+
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
 @pytest.mark.parametrize("first,count", [(0, 3), (3, 1), (1, 2)])
 def test_block_kernel_reads_selected_rows(first, count, dtype):
