@@ -463,14 +463,22 @@ int block_grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSe
     b.out = O;
     b.policy = n == 0;
     b.bsum = used * 2 * H;
-    red.add(oW1, (size_t)D * H, (int)copies);
-    red.add(oW2, (size_t)H * H, (int)copies);
-    red.add(oW3, (size_t)H * O, (int)copies);
-    const int tiles = (int)((R + 255) / 256);
-    red.add(ob1, H, ordered ? tiles : (int)copies, ordered ? b.bsum : -1);
-    red.add(ob2, H, ordered ? tiles : (int)copies, ordered ? b.bsum + H : -1);
-    red.add(ob3, O, ordered ? (int)bias_slices : (int)copies);
     ob3s[used++] = ob3;
+  }
+  // (sums over 32 rows first: few elements, whose chains are longer than the others' and would be left over at the end)
+  for (int n = 0; n < used && ordered; ++n) {
+    const int tiles = (int)((R + 255) / 256);
+    red.add(a.net[n].ob1, H, tiles, a.net[n].bsum);
+    red.add(a.net[n].ob2, H, tiles, a.net[n].bsum + H);
+  }
+  for (int n = 0; n < used; ++n) {
+    const BlockNet& b = a.net[n];
+    red.add(b.oW1, (size_t)D * H, (int)copies);
+    red.add(b.oW2, (size_t)H * H, (int)copies);
+    red.add(b.oW3, (size_t)H * b.out, (int)copies);
+    if (!ordered) red.add(b.ob1, H, (int)copies);
+    if (!ordered) red.add(b.ob2, H, (int)copies);
+    red.add(b.ob3, b.out, ordered ? (int)bias_slices : (int)copies);
   }
   LTRY(launch_block_pack(jobs, max_items, s));
   LTRY(launch_ppo_block(H, D, L->pol.out_dim, a, (unsigned)slices, (unsigned)used, s));
