@@ -96,6 +96,21 @@ template <int CH> struct LdsRows {
     return __builtin_bit_cast(bf16x8, v);
   }
 };
+// the largest and the sum of eight lanes' values, on each of them
+template <int CTRL> __device__ __forceinline__ float lane_moved(float v) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int LANE_XOR1 = 0xB1, LANE_XOR2 = 0x4E, LANE_REV8 = 0x141;  // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror
+__device__ __forceinline__ float max_of_8(float v) {
+  v = fmaxf(v, lane_moved<LANE_XOR1>(v));
+  v = fmaxf(v, lane_moved<LANE_XOR2>(v));
+  return fmaxf(v, lane_moved<LANE_REV8>(v));
+}
+__device__ __forceinline__ float sum_of_8(float v) {
+  v += lane_moved<LANE_XOR1>(v);
+  v += lane_moved<LANE_XOR2>(v);
+  return v + lane_moved<LANE_REV8>(v);
+}
 // unit of position j of 32 in the chained order
 __device__ __forceinline__ int chained(int j) { return (j & 16) | (j & 4) << 1 | (j & 8) >> 1 | (j & 3); }
 
@@ -111,7 +126,8 @@ constexpr bool block_bf16_widths_fit() {
 }
 static_assert(block_bf16_widths_fit(), "every width the learner takes has an instance that holds its inputs and its bias");
 
-template <int H, int XT> struct BlockShapeB {
+// OT: outputs there is room for
+template <int H, int XT, int OT> struct BlockShapeB {
   static constexpr int NWU = H / 32;              // groups of 32 units
   // 128 units: two waves per group of units, a 32-row tile each (eight waves for the compute unit, whose share of a
   // minibatch is one workgroup)
@@ -127,6 +143,9 @@ template <int H, int XT> struct BlockShapeB {
   // memory
   static constexpr bool RESIDENT = H <= 128;
   static constexpr int WD = 4;  // tiles fetched ahead of their product when streamed
+  // Up to 8 outputs every wave takes its units through the output layer while it has them in registers, and the loss of eight
+  // rows, a lane to an output (else the first two waves do that of 32 rows each: no LDS for the waves' shares)
+  static constexpr bool SPREAD = OT <= 8;
   static constexpr bool G3_LDS = H > 128;  // dL/dW3 waits in LDS between the tiles (the registers are full)
   static constexpr bool OWN_DZ = RS > 1;  // dL/dz in arrays of their own: two waves share a column of h1, h2
   // dL/dW2: waves in a grid of MG groups of 32 MT units of layer 1 by NW / MG groups of 32 NT units of layer 2 (NT <= MG)
@@ -138,10 +157,10 @@ template <int H, int XT> struct BlockShapeB {
 
 // VEC2: observations come in pairs (D is even, the array 8-byte aligned); one dword per lane and load takes the address
 // unit twice as long
-template <int H, int XT, bool VEC2>
-__global__ __launch_bounds__((BlockShapeB<H, XT>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
+template <int H, int XT, int OT, bool VEC2>
+__global__ __launch_bounds__((BlockShapeB<H, XT, OT>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
 void ppo_block_bf16_kernel(BlockArgsB a) {
-  typedef BlockShapeB<H, XT> S;
+  typedef BlockShapeB<H, XT, OT> S;
   constexpr int NW = S::NW, NWU = S::NWU, RS = S::RS, RT = S::RT, ROWS = S::ROWS, KH = S::KH, KX = S::KX;
   typedef typename S::Rh Rh;
   typedef typename S::Rx Rx;
@@ -161,7 +180,8 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   __shared__ __attribute__((aligned(16))) float s_b3[32];
   __shared__ __attribute__((aligned(16))) f32x4 s_g3[S::G3_LDS ? 2 * S::THREADS : 1];
   __shared__ __attribute__((aligned(16))) u32x4 s_w1[NWU * KX * 64];
-  __shared__ __attribute__((aligned(16))) u32x4 s_w3[KH * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 s_w3[S::SPREAD ? 1 : KH * 64];
+  __shared__ __attribute__((aligned(16))) float s_out[S::SPREAD ? NWU : 1][ROWS][8];  // the unit groups' shares of the outputs
   __shared__ __attribute__((aligned(16))) u32x4 s_w3t[NWU * 64];
   const BlockNetB& nt = a.net[blockIdx.y];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -170,6 +190,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   const int uw = wave % NWU, rg = wave / NWU, u0 = 32 * uw, ro = 32 * RT * rg;  // this wave's units and first row
   __bf16 *const dz1 = S::OWN_DZ ? s.dz[0] : s.h1, *const dz2 = S::OWN_DZ ? s.dz[1] : s.h2;
   const bool policy = nt.policy != 0;
+  const float* targets = policy ? a.adv : a.ret;  // advantage or return
   const int mg = wave % MG, ng = wave / MG;  // this wave's part of dL/dW2
 
   // rows: the 64-row tiles of slice blockIdx.x
@@ -186,7 +207,11 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   };
 
   for (int k = threadIdx.x; k < NWU * kx * 64; k += S::THREADS) s_w1[k] = nt.w1[k];
-  for (int k = threadIdx.x; k < KH * 64; k += S::THREADS) s_w3[k] = nt.w3[k];
+  if constexpr (S::SPREAD) {
+    for (int k = threadIdx.x; k < ROWS * Ry::ROW / 8; k += S::THREADS) ((u32x4*)s.dy)[k] = u32x4{0u, 0u, 0u, 0u};  // (outputs that are none)
+  } else {
+    for (int k = threadIdx.x; k < KH * 64; k += S::THREADS) s_w3[k] = nt.w3[k];
+  }
   for (int k = threadIdx.x; k < NWU * 64; k += S::THREADS) s_w3t[k] = nt.w3t[k];
   if (threadIdx.x < 32) s_b3[threadIdx.x] = (int)threadIdx.x < O ? nt.b3[threadIdx.x] : 0.0f;
   if (wave == 0) s.st[lane] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -306,7 +331,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   };
   // registers 8 g .. 8 g + 7 of an accumulator: row lane % 32 of its tile, the lane's 8 units of the wave's 16-unit group
   // g (chained order): piece u0 / 8 + 2 g + h of the row
-  auto activate = [&](const f32x16 (&acc)[RT], __bf16* to) {
+  auto activate = [&](const f32x16 (&acc)[RT], __bf16* to, auto&& also) {
     const typename Rh::Place at = Rh::place(lane & 31, lane >> 5);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -315,7 +340,9 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
         f32x8 v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = fast_tanh(acc[rt][8 * g + e]);
-        *(bf16x8*)(to + (ro + 32 * rt) * Rh::ROW + Rh::at(at, u0 / 8 + 2 * g)) = __builtin_convertvector(v, bf16x8);
+        const bf16x8 a8 = __builtin_convertvector(v, bf16x8);
+        *(bf16x8*)(to + (ro + 32 * rt) * Rh::ROW + Rh::at(at, u0 / 8 + 2 * g)) = a8;
+        also(rt, g, a8);
       }
   };
   // to <- acc (1 - from^2)
@@ -356,22 +383,25 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
     clear(acc);
     product(Rx(), std::integral_constant<int, KX>(), acc, s_x, kx, [&](int k) { return s_w1[(uw * kx + k) * 64 + lane]; });
     ring_fill(w2);
-    activate(acc, s.h1);
+    activate(acc, s.h1, [](int, int, const bf16x8&) {});
     __syncthreads();
-    // what the loss reads: the first two waves take 32 rows each
+    // what the loss reads: eight rows to a wave, or 32 to each of the first two
     int act = 0;
-    float lpo = 0.0f, adv = 0.0f, ret = 0.0f;
+    float lpo = 0.0f, target = 0.0f;
     bool valid = false;
-    if (wave < ROWS / 32) {
-      const int64_t p = s.row[32 * wave + i];
+    u32x4 w3[S::SPREAD ? 2 : 1];
+    if constexpr (S::SPREAD) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) w3[k] = nt.w3[(2 * uw + k) * 64 + lane];
+    }
+    static_assert(!S::SPREAD || 8 * NW == ROWS, "a wave to eight rows");
+    if (S::SPREAD || wave < ROWS / 32) {
+      const int64_t p = s.row[S::SPREAD ? 8 * wave + (lane >> 3) : 32 * wave + i];
       valid = p >= 0;
-      if (valid && policy) {
-        act = a.actions[p];
-        lpo = a.logp_old[p];
-        adv = a.adv[p];
-      } else if (valid) {
-        ret = a.ret[p];
-      }
+      const int64_t at = valid ? p : 0;
+      act = a.actions[at];
+      lpo = a.logp_old[at];
+      target = targets[at];
     }
     clear(acc);
     if constexpr (S::RESIDENT) {
@@ -382,11 +412,51 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
       if (wave < 4) __builtin_amdgcn_s_setprio(1);
       ring_product(acc, s.h1, w2, std::integral_constant<int, KH + 1>());
     }
-    activate(acc, s.h2);
+    if constexpr (S::SPREAD) {
+      // register r of lane (i, h) <-> output 4 h + r of row i, r < 4
+      f32x16 out;
+      activate(acc, s.h2, [&](int rt, int g, const bf16x8& h2) {
+        out = mma(__builtin_bit_cast(bf16x8, w3[g]), h2, g == 0 ? zero16() : out);
+        if (g == 1) *(f32x4*)&s_out[uw][ro + 32 * rt + i][4 * h] = f32x4{out[0], out[1], out[2], out[3]};
+      });
+    } else {
+      activate(acc, s.h2, [](int, int, const bf16x8&) {});
+    }
     if (!S::RESIDENT && wave < 4) __builtin_amdgcn_s_setprio(0);
     __syncthreads();
-    // output layer and loss: register r of lane (i, h) <-> output 8 (r / 4) + 4 h + r % 4 of row i
-    if (wave < ROWS / 32) {
+    if constexpr (S::SPREAD) {
+      // loss of row 8 wave + lane / 8, output lane % 8; sums over the outputs of a row go round its eight lanes
+      const int row = 8 * wave + (lane >> 3), o = lane & 7;
+      float y = s_b3[o];
+#pragma unroll
+      for (int w = 0; w < NWU; ++w) y += s_out[w][row][o];
+      float dy = 0.0f;
+      f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (policy) {
+        // in powers of two: u = log2 of the unnormalised probability
+        constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
+        const float x = o < O ? y * LOG2E : -1.0e38f, u = x - max_of_8(x), e = __builtin_amdgcn_exp2f(u);
+        const float z = sum_of_8(e), zu = sum_of_8(e * u), ua = sum_of_8(o == act ? u : 0.0f);
+        const float lz = __builtin_amdgcn_logf(z), pk = e * __builtin_amdgcn_rcpf(z), lp = LN2 * (u - lz);
+        const float ent = LN2 * (lz - zu * __builtin_amdgcn_rcpf(z)), logp = LN2 * (ua - lz);
+        const float rho = __expf(logp - lpo);
+        const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
+        const float un = rho * target, cl = rc * target;
+        const bool clipped = cl < un;
+        const float gl = clipped ? 0.0f : -target * rho;
+        const float dlp = (o == act ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
+        dy = (gl * dlp - a.ent_coef * dH) * a.inv_R;
+        st = f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo - logp};
+      } else {
+        const float err = y - target;
+        dy = a.vf_coef * 2.0f * err * a.inv_R;
+        st[0] = err * err;
+      }
+      const int at = chained(o);
+      s.dy[row * Ry::ROW + ((at / 8) ^ Ry::swizzle(row)) * 8 + at % 8] = (__bf16)(valid && o < O ? dy : 0.0f);
+      if (valid && o == 0) s.st[row] += st;
+    } else if (wave < ROWS / 32) {
+      // output layer and loss: register r of lane (i, h) <-> output 8 (r / 4) + 4 h + r % 4 of row i
       f32x16 out = bias_init(s_b3, h);
       const typename Rh::Place at = Rh::place(i, h);
 #pragma unroll
@@ -418,9 +488,9 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
         }
         const float rho = __expf(logp - lpo);
         const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
-        const float un = rho * adv, cl = rc * adv;
+        const float un = rho * target, cl = rc * target;
         const bool clipped = cl < un;
-        const float gl = clipped ? 0.0f : -adv * rho;
+        const float gl = clipped ? 0.0f : -target * rho;
         // each lane differentiates with respect to its own eight outputs
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
@@ -431,7 +501,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
         }
         st = f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo - logp};
       } else if (h == 0) {
-        const float err = out[0] - ret;
+        const float err = out[0] - target;
         dy[0] = valid ? a.vf_coef * 2.0f * err * a.inv_R : 0.0f;
         st[0] = err * err;
       }
@@ -582,17 +652,23 @@ struct BlockPackJobsB {
 hipError_t launch_block_pack_bf16(const BlockPackJobsB& jobs, int max_items, hipStream_t s);
 hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s);
 
-#define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                       \
-  hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) {      \
-    const bool vec2 = in_dim % 2 == 0 && (uintptr_t)a.obs % 8 == 0;                                         \
-    const int xt = block_bf16_x_tiles(in_dim);                                                              \
-    const dim3 threads(BlockShapeB<HID, 1>::THREADS);                                                       \
-    if (in_dim < 1 || xt > 2) return hipErrorInvalidValue; /* (no LDS for more inputs) */                   \
-    if (xt == 1 && vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, true>), grid, threads, 0, s, a); \
-    else if (xt == 1) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 1, false>), grid, threads, 0, s, a);   \
-    else if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, true>), grid, threads, 0, s, a);       \
-    else hipLaunchKernelGGL((ppo_block_bf16_kernel<HID, 2, false>), grid, threads, 0, s, a);                \
-    return hipGetLastError();                                                                               \
+template <int H, int XT, int OT>
+void launch_block_bf16(bool vec2, const BlockArgsB& a, dim3 grid, hipStream_t s) {
+  const dim3 threads(BlockShapeB<H, XT, OT>::THREADS);
+  if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<H, XT, OT, true>), grid, threads, 0, s, a);
+  else hipLaunchKernelGGL((ppo_block_bf16_kernel<H, XT, OT, false>), grid, threads, 0, s, a);
+}
+#define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                  \
+  hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) { \
+    const bool vec2 = in_dim % 2 == 0 && (uintptr_t)a.obs % 8 == 0;                                    \
+    const bool wide = a.net[0].out > 8 || a.net[1].out > 8;                                            \
+    const int xt = block_bf16_x_tiles(in_dim);                                                         \
+    if (in_dim < 1 || xt > 2) return hipErrorInvalidValue; /* (no LDS for more inputs) */              \
+    if (xt == 1 && !wide) launch_block_bf16<HID, 1, 8>(vec2, a, grid, s);                              \
+    else if (xt == 1) launch_block_bf16<HID, 1, 16>(vec2, a, grid, s);                                 \
+    else if (!wide) launch_block_bf16<HID, 2, 8>(vec2, a, grid, s);                                    \
+    else launch_block_bf16<HID, 2, 16>(vec2, a, grid, s);                                              \
+    return hipGetLastError();                                                                          \
   }
 
 }  // namespace msrl
