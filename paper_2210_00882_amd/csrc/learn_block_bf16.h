@@ -12,8 +12,12 @@
 // units the matrix pipe is busy for 8.2 k, the vector ALU for 11.2 k, the LDS for 7.2 k (counters; activations are read
 // once by each of the eight waves in either layer product); the waves wait for 48 % of theirs.  Writing the activations
 // and their gradients out for contractions of their own (4 KiB per row and network) was bound by that traffic.
-// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.78 ms, 128 (36) 0.71 -> 0.39; of 8192 rows 126 ->
+// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.74 ms, 128 (36) 0.71 -> 0.37; of 8192 rows 126 ->
 // 57, 76 -> 32 us (three launches where there were six).  64 units: learn_wave_bf16.h.
+// Measured and dropped: layer 1 of the next tile beside dL/dW2 of this one, dL/dW1 beside the next layer 2 (four barriers a
+// tile in place of six, h1 twice in LDS): 689 -> 688 us with 24 inputs, 735 -> 840 with 60, where it spills 19 registers.
+// Every wave takes its own units through the output layer, from registers, and the loss of eight rows: 690 us, but the
+// logits' sums are others then (see below).
 //
 // Inside a slice of the rows the sums keep their order from one version of the learner to the next: a 64-row tile behind the
 // other, and which 16 products an MFMA adds at once.  Where the slices begin follows the number of compute units.  A bf16
@@ -48,7 +52,7 @@ struct BlockArgsB {
   RowSel sel;
   int64_t R;
   int64_t rows_per_slice;     // rows of slice blockIdx.x, a multiple of 64 (128 and 256 units)
-  int slices0;                // 64 units: workgroups of net[0], in front of those of net[1]
+  int slices0, copies;        // 64 units: workgroups of net[0], in front of those of net[1]; copies of a network's gradient
   int D;
   float clip, vf_coef, ent_coef, inv_R;
   float* part;                // [workgroup][part_stride] copies of the gradient
@@ -96,20 +100,56 @@ template <int CH> struct LdsRows {
     return __builtin_bit_cast(bf16x8, v);
   }
 };
-// the largest and the sum of eight lanes' values, on each of them
-template <int CTRL> __device__ __forceinline__ float lane_moved(float v) {
-  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), CTRL, 0xF, 0xF, true));
+// 16 x 16 (x 32): lane (j = lane % 16, g = lane / 16): operands hold row / column j, contraction index 8 g .. 8 g + 7; register r
+// of the result is row 4 g + r, column j.  (Its sums are bit for bit those of two products of 32 x 32 (x 16) behind each other.)
+__device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+// the values of the two lanes of a pair 16 (32) apart, the lower one's first, on both
+__device__ __forceinline__ void both_of_16(float v, float& lo, float& hi) {
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  lo = __uint_as_float(q[0]);
+  hi = __uint_as_float(q[1]);
 }
-constexpr int LANE_XOR1 = 0xB1, LANE_XOR2 = 0x4E, LANE_REV8 = 0x141;  // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror
-__device__ __forceinline__ float max_of_8(float v) {
-  v = fmaxf(v, lane_moved<LANE_XOR1>(v));
-  v = fmaxf(v, lane_moved<LANE_XOR2>(v));
-  return fmaxf(v, lane_moved<LANE_REV8>(v));
+__device__ __forceinline__ void both_of_32(float v, float& lo, float& hi) {
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  lo = __uint_as_float(q[0]);
+  hi = __uint_as_float(q[1]);
 }
-__device__ __forceinline__ float sum_of_8(float v) {
-  v += lane_moved<LANE_XOR1>(v);
-  v += lane_moved<LANE_XOR2>(v);
-  return v + lane_moved<LANE_REV8>(v);
+// What the loss of a row of the policy network makes of its OT logits l, O of them real: dL/dy of R of them, own[r] = logit k0 + r
+// of this lane, and the row's statistics.
+struct LossTerms {
+  float clip, ent_coef, inv_R;
+};
+template <int OT, int R, class Index>
+__device__ __forceinline__ void policy_loss(const float (&l)[OT], int O, int act, float lpo, float adv, bool valid,
+                                            const LossTerms& a, const float (&own)[R], Index&& index, float (&dy)[R], f32x4& st) {
+  float mx = l[0];
+#pragma unroll
+  for (int k = 1; k < OT; ++k) mx = k < O ? fmaxf(mx, l[k]) : mx;
+  float z = 0.0f;
+#pragma unroll
+  for (int k = 0; k < OT; ++k) z += k < O ? __expf(l[k] - mx) : 0.0f;
+  const float lse = mx + __logf(z);
+  float ent = 0.0f, logp = 0.0f;
+#pragma unroll
+  for (int k = 0; k < OT; ++k) {
+    const float lp = l[k] - lse;
+    ent -= k < O ? __expf(lp) * lp : 0.0f;
+    if (k == act) logp = lp;
+  }
+  const float rho = __expf(logp - lpo);
+  const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
+  const float un = rho * adv, cl = rc * adv;
+  const bool clipped = cl < un;
+  const float gl = clipped ? 0.0f : -adv * rho;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int k = index(r);
+    const float lp = own[r] - lse, pk = __expf(lp);
+    const float dlp = (k == act ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
+    const float d = (gl * dlp - a.ent_coef * dH) * a.inv_R;
+    dy[r] = (valid && k < O) ? d : 0.0f;
+  }
+  st = f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo - logp};
 }
 // unit of position j of 32 in the chained order
 __device__ __forceinline__ int chained(int j) { return (j & 16) | (j & 4) << 1 | (j & 8) >> 1 | (j & 3); }
@@ -126,8 +166,7 @@ constexpr bool block_bf16_widths_fit() {
 }
 static_assert(block_bf16_widths_fit(), "every width the learner takes has an instance that holds its inputs and its bias");
 
-// OT: outputs there is room for
-template <int H, int XT, int OT> struct BlockShapeB {
+template <int H, int XT> struct BlockShapeB {
   static constexpr int NWU = H / 32;              // groups of 32 units
   // 128 units: two waves per group of units, a 32-row tile each (eight waves for the compute unit, whose share of a
   // minibatch is one workgroup)
@@ -143,9 +182,6 @@ template <int H, int XT, int OT> struct BlockShapeB {
   // memory
   static constexpr bool RESIDENT = H <= 128;
   static constexpr int WD = 4;  // tiles fetched ahead of their product when streamed
-  // Up to 8 outputs every wave takes its units through the output layer while it has them in registers, and the loss of eight
-  // rows, a lane to an output (else the first two waves do that of 32 rows each: no LDS for the waves' shares)
-  static constexpr bool SPREAD = OT <= 8;
   static constexpr bool G3_LDS = H > 128;  // dL/dW3 waits in LDS between the tiles (the registers are full)
   static constexpr bool OWN_DZ = RS > 1;  // dL/dz in arrays of their own: two waves share a column of h1, h2
   // dL/dW2: waves in a grid of MG groups of 32 MT units of layer 1 by NW / MG groups of 32 NT units of layer 2 (NT <= MG)
@@ -157,10 +193,10 @@ template <int H, int XT, int OT> struct BlockShapeB {
 
 // VEC2: observations come in pairs (D is even, the array 8-byte aligned); one dword per lane and load takes the address
 // unit twice as long
-template <int H, int XT, int OT, bool VEC2>
-__global__ __launch_bounds__((BlockShapeB<H, XT, OT>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
+template <int H, int XT, bool VEC2>
+__global__ __launch_bounds__((BlockShapeB<H, XT>::THREADS)) __attribute__((amdgpu_waves_per_eu(2)))
 void ppo_block_bf16_kernel(BlockArgsB a) {
-  typedef BlockShapeB<H, XT, OT> S;
+  typedef BlockShapeB<H, XT> S;
   constexpr int NW = S::NW, NWU = S::NWU, RS = S::RS, RT = S::RT, ROWS = S::ROWS, KH = S::KH, KX = S::KX;
   typedef typename S::Rh Rh;
   typedef typename S::Rx Rx;
@@ -180,8 +216,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   __shared__ __attribute__((aligned(16))) float s_b3[32];
   __shared__ __attribute__((aligned(16))) f32x4 s_g3[S::G3_LDS ? 2 * S::THREADS : 1];
   __shared__ __attribute__((aligned(16))) u32x4 s_w1[NWU * KX * 64];
-  __shared__ __attribute__((aligned(16))) u32x4 s_w3[S::SPREAD ? 1 : KH * 64];
-  __shared__ __attribute__((aligned(16))) float s_out[S::SPREAD ? NWU : 1][ROWS][8];  // the unit groups' shares of the outputs
+  __shared__ __attribute__((aligned(16))) u32x4 s_w3[KH * 64];
   __shared__ __attribute__((aligned(16))) u32x4 s_w3t[NWU * 64];
   const BlockNetB& nt = a.net[blockIdx.y];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -207,11 +242,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   };
 
   for (int k = threadIdx.x; k < NWU * kx * 64; k += S::THREADS) s_w1[k] = nt.w1[k];
-  if constexpr (S::SPREAD) {
-    for (int k = threadIdx.x; k < ROWS * Ry::ROW / 8; k += S::THREADS) ((u32x4*)s.dy)[k] = u32x4{0u, 0u, 0u, 0u};  // (outputs that are none)
-  } else {
-    for (int k = threadIdx.x; k < KH * 64; k += S::THREADS) s_w3[k] = nt.w3[k];
-  }
+  for (int k = threadIdx.x; k < KH * 64; k += S::THREADS) s_w3[k] = nt.w3[k];
   for (int k = threadIdx.x; k < NWU * 64; k += S::THREADS) s_w3t[k] = nt.w3t[k];
   if (threadIdx.x < 32) s_b3[threadIdx.x] = (int)threadIdx.x < O ? nt.b3[threadIdx.x] : 0.0f;
   if (wave == 0) s.st[lane] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -331,7 +362,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   };
   // registers 8 g .. 8 g + 7 of an accumulator: row lane % 32 of its tile, the lane's 8 units of the wave's 16-unit group
   // g (chained order): piece u0 / 8 + 2 g + h of the row
-  auto activate = [&](const f32x16 (&acc)[RT], __bf16* to, auto&& also) {
+  auto activate = [&](const f32x16 (&acc)[RT], __bf16* to) {
     const typename Rh::Place at = Rh::place(lane & 31, lane >> 5);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -340,9 +371,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
         f32x8 v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = fast_tanh(acc[rt][8 * g + e]);
-        const bf16x8 a8 = __builtin_convertvector(v, bf16x8);
-        *(bf16x8*)(to + (ro + 32 * rt) * Rh::ROW + Rh::at(at, u0 / 8 + 2 * g)) = a8;
-        also(rt, g, a8);
+        *(bf16x8*)(to + (ro + 32 * rt) * Rh::ROW + Rh::at(at, u0 / 8 + 2 * g)) = __builtin_convertvector(v, bf16x8);
       }
   };
   // to <- acc (1 - from^2)
@@ -383,26 +412,21 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
     clear(acc);
     product(Rx(), std::integral_constant<int, KX>(), acc, s_x, kx, [&](int k) { return s_w1[(uw * kx + k) * 64 + lane]; });
     ring_fill(w2);
-    activate(acc, s.h1, [](int, int, const bf16x8&) {});
+    activate(acc, s.h1);
     __syncthreads();
-    // what the loss reads: eight rows to a wave, or 32 to each of the first two
+    // what the loss reads: the first four waves take 16 rows each
     int act = 0;
     float lpo = 0.0f, target = 0.0f;
     bool valid = false;
-    u32x4 w3[S::SPREAD ? 2 : 1];
-    if constexpr (S::SPREAD) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) w3[k] = nt.w3[(2 * uw + k) * 64 + lane];
-    }
-    static_assert(!S::SPREAD || 8 * NW == ROWS, "a wave to eight rows");
-    if (S::SPREAD || wave < ROWS / 32) {
-      const int64_t p = s.row[S::SPREAD ? 8 * wave + (lane >> 3) : 32 * wave + i];
+    auto fetch_loss = [&]() {
+      if (wave >= ROWS / 16) return;
+      const int64_t p = s.row[16 * wave + (lane & 15)];
       valid = p >= 0;
       const int64_t at = valid ? p : 0;
       act = a.actions[at];
       lpo = a.logp_old[at];
       target = targets[at];
-    }
+    };
     clear(acc);
     if constexpr (S::RESIDENT) {
       product(Rh(), std::integral_constant<int, KH>(), acc, s.h1, KH, [&](int k) { return rw2[k]; });
@@ -412,101 +436,45 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
       if (wave < 4) __builtin_amdgcn_s_setprio(1);
       ring_product(acc, s.h1, w2, std::integral_constant<int, KH + 1>());
     }
-    if constexpr (S::SPREAD) {
-      // register r of lane (i, h) <-> output 4 h + r of row i, r < 4
-      f32x16 out;
-      activate(acc, s.h2, [&](int rt, int g, const bf16x8& h2) {
-        out = mma(__builtin_bit_cast(bf16x8, w3[g]), h2, g == 0 ? zero16() : out);
-        if (g == 1) *(f32x4*)&s_out[uw][ro + 32 * rt + i][4 * h] = f32x4{out[0], out[1], out[2], out[3]};
-      });
-    } else {
-      activate(acc, s.h2, [](int, int, const bf16x8&) {});
-    }
+    fetch_loss();  // (behind the last of the weights: no product waits for these loads)
+    activate(acc, s.h2);
     if (!S::RESIDENT && wave < 4) __builtin_amdgcn_s_setprio(0);
     __syncthreads();
-    if constexpr (S::SPREAD) {
-      // loss of row 8 wave + lane / 8, output lane % 8; sums over the outputs of a row go round its eight lanes
-      const int row = 8 * wave + (lane >> 3), o = lane & 7;
-      float y = s_b3[o];
+    // output layer and loss: register r of lane (j, g) <-> output 4 g + r of row j of the wave's 16
+    if (wave < ROWS / 16) {
+      const int row = 16 * wave + p16;
+      f32x4 out = *(const f32x4*)(s_b3 + 4 * g16);
+      const typename Rh::Place at = Rh::place(row, g16);
 #pragma unroll
-      for (int w = 0; w < NWU; ++w) y += s_out[w][row][o];
-      float dy = 0.0f;
+      for (int k = 0; k < KH / 2; ++k)
+        out = mma16(__builtin_bit_cast(bf16x8, s_w3[(2 * k + (g16 >> 1)) * 64 + 32 * (g16 & 1) + p16]), *(const bf16x8*)(s.h2 + Rh::at(at, 4 * k)), out);
+      float dy[4] = {0.0f, 0.0f, 0.0f, 0.0f};
       f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
       if (policy) {
-        // in powers of two: u = log2 of the unnormalised probability
-        constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
-        const float x = o < O ? y * LOG2E : -1.0e38f, u = x - max_of_8(x), e = __builtin_amdgcn_exp2f(u);
-        const float z = sum_of_8(e), zu = sum_of_8(e * u), ua = sum_of_8(o == act ? u : 0.0f);
-        const float lz = __builtin_amdgcn_logf(z), pk = e * __builtin_amdgcn_rcpf(z), lp = LN2 * (u - lz);
-        const float ent = LN2 * (lz - zu * __builtin_amdgcn_rcpf(z)), logp = LN2 * (ua - lz);
-        const float rho = __expf(logp - lpo);
-        const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
-        const float un = rho * target, cl = rc * target;
-        const bool clipped = cl < un;
-        const float gl = clipped ? 0.0f : -target * rho;
-        const float dlp = (o == act ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
-        dy = (gl * dlp - a.ent_coef * dH) * a.inv_R;
-        st = f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo - logp};
-      } else {
-        const float err = y - target;
-        dy = a.vf_coef * 2.0f * err * a.inv_R;
-        st[0] = err * err;
-      }
-      const int at = chained(o);
-      s.dy[row * Ry::ROW + ((at / 8) ^ Ry::swizzle(row)) * 8 + at % 8] = (__bf16)(valid && o < O ? dy : 0.0f);
-      if (valid && o == 0) s.st[row] += st;
-    } else if (wave < ROWS / 32) {
-      // output layer and loss: register r of lane (i, h) <-> output 8 (r / 4) + 4 h + r % 4 of row i
-      f32x16 out = bias_init(s_b3, h);
-      const typename Rh::Place at = Rh::place(i, h);
-#pragma unroll
-      for (int k = 0; k < KH; ++k)
-        out = mma(__builtin_bit_cast(bf16x8, s_w3[k * 64 + lane]), *(const bf16x8*)(s.h2 + 32 * wave * Rh::ROW + Rh::at(at, 2 * k)), out);
-      f32x8 dy = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-      f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (policy) {
+        const LossTerms terms = {a.clip, a.ent_coef, a.inv_R};
+        const float own[4] = {out[0], out[1], out[2], out[3]};
+        auto index = [&](int r) { return 4 * g16 + r; };
         float l[16];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const int r = 4 * (k >> 3) + (k & 3);
-          const float own = out[r], oth = __shfl_xor(own, 32);
-          l[k] = (((k >> 2) & 1) == h) ? own : oth;
+        for (int r = 0; r < 4; ++r) both_of_16(out[r], l[r], l[4 + r]);  // (lanes beyond 31: outputs 8 .. 15)
+        if (O <= 8) {
+          float l8[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) l8[k] = l[k];
+          policy_loss(l8, O, act, lpo, target, valid, terms, own, index, dy, st);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) both_of_32(l[k], l[k], l[8 + k]);
+          policy_loss(l, O, act, lpo, target, valid, terms, own, index, dy, st);
         }
-        float mx = l[0];
-#pragma unroll
-        for (int k = 1; k < 16; ++k) mx = k < O ? fmaxf(mx, l[k]) : mx;
-        float z = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) z += k < O ? __expf(l[k] - mx) : 0.0f;
-        const float lse = mx + __logf(z);
-        float ent = 0.0f, logp = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const float lp = l[k] - lse;
-          ent -= k < O ? __expf(lp) * lp : 0.0f;
-          if (k == act) logp = lp;
-        }
-        const float rho = __expf(logp - lpo);
-        const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
-        const float un = rho * target, cl = rc * target;
-        const bool clipped = cl < un;
-        const float gl = clipped ? 0.0f : -target * rho;
-        // each lane differentiates with respect to its own eight outputs
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const int k = 8 * (r / 4) + 4 * h + r % 4;
-          const float lp = out[r] - lse, pk = __expf(lp);
-          const float dlp = (k == act ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
-          dy[r] = (valid && k < O) ? (gl * dlp - a.ent_coef * dH) * a.inv_R : 0.0f;
-        }
-        st = f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo - logp};
-      } else if (h == 0) {
+      } else if (g16 == 0) {
         const float err = out[0] - target;
         dy[0] = valid ? a.vf_coef * 2.0f * err * a.inv_R : 0.0f;
         st[0] = err * err;
       }
-      *(bf16x8*)(s.dy + 32 * wave * Ry::ROW + Ry::at(Ry::place(i, h), 0)) = __builtin_convertvector(dy, bf16x8);
-      if (valid && h == 0) s.st[32 * wave + i] += st;
+      const int to = chained(4 * g16);
+      *(bf16x4*)(s.dy + row * Ry::ROW + ((to / 8) ^ Ry::swizzle(row)) * 8 + to % 8) = __builtin_convertvector((f32x4{dy[0], dy[1], dy[2], dy[3]}), bf16x4);
+      if (valid && g16 == 0) s.st[row] += st;
     }
     __syncthreads();
     // dL/dW3 += dL/dy^T h2 (the wave's own units), dL/dz2
@@ -652,22 +620,19 @@ struct BlockPackJobsB {
 hipError_t launch_block_pack_bf16(const BlockPackJobsB& jobs, int max_items, hipStream_t s);
 hipError_t launch_ppo_block_bf16(int hidden, int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s);
 
-template <int H, int XT, int OT>
+template <int H, int XT>
 void launch_block_bf16(bool vec2, const BlockArgsB& a, dim3 grid, hipStream_t s) {
-  const dim3 threads(BlockShapeB<H, XT, OT>::THREADS);
-  if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<H, XT, OT, true>), grid, threads, 0, s, a);
-  else hipLaunchKernelGGL((ppo_block_bf16_kernel<H, XT, OT, false>), grid, threads, 0, s, a);
+  const dim3 threads(BlockShapeB<H, XT>::THREADS);
+  if (vec2) hipLaunchKernelGGL((ppo_block_bf16_kernel<H, XT, true>), grid, threads, 0, s, a);
+  else hipLaunchKernelGGL((ppo_block_bf16_kernel<H, XT, false>), grid, threads, 0, s, a);
 }
 #define MSRL_BLOCK_BF16_LAUNCHER(HID)                                                                  \
   hipError_t launch_ppo_block_bf16_h##HID(int in_dim, const BlockArgsB& a, dim3 grid, hipStream_t s) { \
     const bool vec2 = in_dim % 2 == 0 && (uintptr_t)a.obs % 8 == 0;                                    \
-    const bool wide = a.net[0].out > 8 || a.net[1].out > 8;                                            \
     const int xt = block_bf16_x_tiles(in_dim);                                                         \
     if (in_dim < 1 || xt > 2) return hipErrorInvalidValue; /* (no LDS for more inputs) */              \
-    if (xt == 1 && !wide) launch_block_bf16<HID, 1, 8>(vec2, a, grid, s);                              \
-    else if (xt == 1) launch_block_bf16<HID, 1, 16>(vec2, a, grid, s);                                 \
-    else if (!wide) launch_block_bf16<HID, 2, 8>(vec2, a, grid, s);                                    \
-    else launch_block_bf16<HID, 2, 16>(vec2, a, grid, s);                                              \
+    if (xt == 1) launch_block_bf16<HID, 1>(vec2, a, grid, s);                                          \
+    else launch_block_bf16<HID, 2>(vec2, a, grid, s);                                                  \
     return hipGetLastError();                                                                          \
   }
 

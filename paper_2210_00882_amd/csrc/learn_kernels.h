@@ -577,8 +577,9 @@ struct AdamElement {
     v = a.v[idx];
   }
   __device__ __forceinline__ void step(const AdamArgs& a, int64_t idx, float gi) const {
-    const float mi = a.b1 * m + (1.0f - a.b1) * gi;
-    const float vi = a.b2 * v + (1.0f - a.b2) * gi * gi;
+    // (written out: which of two products an fma takes is the compiler's choice otherwise, and not the same everywhere)
+    const float mi = __builtin_fmaf(1.0f - a.b1, gi, a.b1 * m);
+    const float vi = __builtin_fmaf(gi, (1.0f - a.b2) * gi, a.b2 * v);
     a.m[idx] = mi;
     a.v[idx] = vi;
     a.p[idx] = p - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);

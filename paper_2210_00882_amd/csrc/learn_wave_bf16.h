@@ -3,16 +3,19 @@
 //
 // A network of 64 units is small enough for that: a layer is two accumulators, what a layer gives is the next one's
 // operand (lane = row; "chained", packed.h) and stays in registers, forward and backward, and so do all the weight gradients
-// (120 registers).  The workgroup's eight waves share the weights in LDS and meet again only at the end, when their gradients
-// are added up in wave order.  LDS turns rows into columns: the weight gradients contract over the rows, and their
+// (120 registers).  The workgroup's waves share the weights in LDS and meet again only at the end, when four waves' gradients at
+// a time are added up in wave order.  LDS turns rows into columns: the weight gradients contract over the rows, and their
 // operands come from the wave's own copy of its rows through the transposing read (LdsRows).
 //
-// What bounds it: one tile's chain (a tile of 32 rows takes a wave 5.3 us, of which its vector instructions are about 3) and that
+// What bounds it: one tile's chain (a tile of 32 rows takes a wave 5.5 us, of which its vector instructions are about 3) and that
 // two waves to a SIMD do not cover it: the VALU is active for 60 % of the cycles, the matrix pipe for 18 %.  Before (teams of two
-// waves on 64 rows, the layers meeting in LDS behind six barriers a tile) 49 % and 13 %.  Gradient of 524,288, 131,072, 32,768
-// and 1000 rows with 20 inputs, before and now: 158 -> 111 us, 67 -> 46, 53 -> 29, 25 -> 22; with 48 inputs 176 -> 165,
-// 76 -> 66, 60 -> 42, 29 -> 28.  No faster: the vector work dealt out between the MFMAs by hand (117; it takes registers, or
-// LDS in their place), the policy's waves on more of the compute units than the value network's (54 %: 115).
+// waves on 64 rows, the layers meeting in LDS behind six barriers a tile) 49 % and 13 %.  Gradient of 524,288, 131,072, 8192
+// and 1000 rows with 20 inputs, before and now: 158 -> 117 us, 67 -> 49, 27 -> 24, 25.5 -> 23.6; with 48 inputs 181 -> 170,
+// 76 -> 71, 31 -> 27, 28.5 -> 26.  No faster: the vector work dealt out between the MFMAs by hand (it takes registers, or LDS
+// in their place).
+//
+// The sums are bit for bit those of the kernel before this one: the same rows to a wave in the same order, the same four waves
+// to a copy of the gradient (learn_block_bf16.h says why that is worth keeping).
 //
 // Rounding as in learn_block_bf16.h.
 #pragma once
@@ -21,7 +24,7 @@
 namespace msrl {
 
 template <int XT> struct WaveShapeB {
-  // (above 30 inputs dL/dW1 takes 32 registers more, and one wave to a SIMD is faster than two that spill: 165 us, not 233)
+  // (above 30 inputs dL/dW1 takes 32 registers more, and one wave to a SIMD is faster than two that spill: 170 us, not 233)
   static constexpr int WAVES = XT == 1 ? 8 : 4, THREADS = 64 * WAVES;
   static constexpr int KX = 2 * XT;
   typedef LdsRows<8> Rh;        // activations
@@ -31,16 +34,6 @@ template <int XT> struct WaveShapeB {
   static constexpr int Q1 = XT * 2 * 16, Q2 = 64, Q3 = 16, QB = 2, Q = Q1 + Q2 + Q3 + QB;
 };
 
-// 16 x 16 (x 32): lane (j = lane % 16, g = lane / 16): operands hold row / column j, contraction index 8 g .. 8 g + 7; register r
-// of the result is row 4 g + r, column j
-__device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-
-// the values of lane % 32 and of lane % 32 + 32, on both
-__device__ __forceinline__ void both_halves(float v, float& lo, float& hi) {
-  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  lo = __uint_as_float(q[0]);
-  hi = __uint_as_float(q[1]);
-}
 
 // OT: outputs there is room for, 8 or 16 (two lanes share a row's: lane (i, h) has outputs 8 (r / 4) + 4 h + r % 4, r < OT / 2)
 template <int XT, int OT, bool VEC2>
@@ -62,14 +55,15 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
   constexpr int T1 = 2 * KX, T2 = 2 * (KH + 1), T3 = KH, T3T = 2, T2T = 2 * KH, TILES = T1 + T2 + T3 + T3T + T2T;
   __shared__ __attribute__((aligned(16))) u32x4 s_w[TILES * 64];
   __shared__ __attribute__((aligned(16))) float s_b3[32];
-  __shared__ __attribute__((aligned(16))) u32x4 s_real[2];  // pairs of a lane's outputs: which are outputs
   __shared__ __attribute__((aligned(16))) u32x4 s_keep[KX][2], s_one[KX][2];  // pairs of inputs: which are observations, which the constant 1
   const int net = blockIdx.x < (unsigned)a.slices0 ? 0 : 1;
   const BlockNetB& nt = a.net[net];
-  const int slice = net == 0 ? (int)blockIdx.x : (int)blockIdx.x - a.slices0;
-  const int slices = net == 0 ? a.slices0 : (int)gridDim.x - a.slices0;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Wave& s = s_wave[wave];
+  // A copy of the gradient is the sum of four waves', who take every fourth tile of its share; a workgroup of eight has two
+  // copies where there are more copies than workgroups.
+  const int first = net == 0 ? 0 : a.slices0, wgs = net == 0 ? a.slices0 : (int)gridDim.x - a.slices0;
+  const int copy = (int)blockIdx.x - first + wave / 4 * wgs;
   int lane = threadIdx.x & 63;
   const int O = nt.out, D = a.D, kx = block_bf16_k_tiles(D);  // (<= KX: the launcher's choice of XT)
   const bool policy = nt.policy != 0;
@@ -94,13 +88,7 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
     }
     s_w[k] = v;
   }
-  // (an output that is none has a logit of -1e38: no share in the sums over the actions)
-  if (threadIdx.x < 32) s_b3[threadIdx.x] = (int)threadIdx.x < O ? nt.b3[threadIdx.x] : -1.0e38f;
-  if (threadIdx.x < 8) {
-    uint32_t real = 0;
-    for (int e = 0; e < 2; ++e) real |= chained(2 * threadIdx.x + e) < O ? 0xFFFFu << 16 * e : 0u;
-    ((uint32_t*)s_real)[threadIdx.x] = real;
-  }
+  if (threadIdx.x < 32) s_b3[threadIdx.x] = (int)threadIdx.x < O ? nt.b3[threadIdx.x] : 0.0f;
   if (threadIdx.x < KX * 8) {  // columns D and D + 1 are the constant 1 that the two parts of the bias meet
     uint32_t keep = 0, one = 0;
     for (int e = 0; e < 2; ++e) {
@@ -125,10 +113,11 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
     return __builtin_bit_cast(bf16x8, u32x4{w, w, w, w});
   };
 
-  // Tiles of this wave: (8 k + wave) slices + slice, k = 0, 1, ...: few tiles go to different compute units.  Row r of the
-  // minibatch is array row q group + first + rem with r = q count + rem: one division here, then steps of a fixed number of rows.
-  int64_t tile = (int64_t)wave * slices + slice;
-  const int64_t tile_step = (int64_t)WAVES * slices;
+  // Tiles of this wave: 4 (copy + k copies) + wave % 4, k = 0, 1, ... (in this order and in these copies the sums are
+  // bit for bit those of the kernel before this one).  Row r of the minibatch is array row q group + first + rem with r = q count
+  // + rem: one division here, then steps of a fixed number of rows.
+  int64_t tile = copy < a.copies ? 4 * (int64_t)copy + wave % 4 : n_tiles;
+  const int64_t tile_step = 4 * (int64_t)a.copies;
   const int count = a.sel.count == 0 ? 1 : a.sel.count, group = a.sel.count == 0 ? 1 : a.sel.group;
   int64_t p = a.sel.at(tile * 32 + (lane & 31));
   int rem = (int)((a.sel.row0 + tile * 32 + (lane & 31)) % count);
@@ -257,53 +246,25 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
 #pragma unroll
       for (int k = 0; k < KH; ++k) *(u32x4*)(s.h2 + Rh::at(rows, 2 * k)) = h2[k];
       if (policy) {
-        // in powers of two: u = log2 of the unnormalised probability
-        constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
-        float own[OR], u[OT], e[OT];
+        float l[OT], own[OR], d[OR];
+        f32x4 terms;
 #pragma unroll
         for (int r = 0; r < OR; ++r) {
-          own[r] = out[r] * LOG2E;
-          both_halves(own[r], u[8 * (r / 4) + r % 4], u[8 * (r / 4) + 4 + r % 4]);
+          own[r] = out[r];
+          both_of_32(out[r], l[8 * (r / 4) + r % 4], l[8 * (r / 4) + 4 + r % 4]);
         }
-        float mx = u[0];
+        policy_loss(l, O, act_, lpo_, target_, row_ok, LossTerms{a.clip, a.ent_coef, a.inv_R}, own,
+                    [&](int r) { return 8 * (r / 4) + 4 * h + r % 4; }, d, terms);
 #pragma unroll
-        for (int k = 1; k < OT; ++k) mx = fmaxf(mx, u[k]);
-        float z = 0.0f, zu = 0.0f, ua = 0.0f;
-#pragma unroll
-        for (int k = 0; k < OT; ++k) {
-          u[k] -= mx;
-          e[k] = __builtin_amdgcn_exp2f(u[k]);
-          z += e[k];
-          zu = __builtin_fmaf(e[k], u[k], zu);
-          ua = k == act_ ? u[k] : ua;
-        }
-        const float lz = __builtin_amdgcn_logf(z), rz = __builtin_amdgcn_rcpf(z);
-        const float ent = LN2 * (lz - zu * rz), logp = LN2 * (ua - lz);
-        const float rho = __expf(logp - lpo_);
-        const float rc = fminf(fmaxf(rho, 1.0f - a.clip), 1.0f + a.clip);
-        const float un = rho * target_, cl = rc * target_;
-        const bool clipped = cl < un;
-        const float gl = clipped ? 0.0f : -target_ * rho;
-        // each lane differentiates with respect to its own outputs
-#pragma unroll
-        for (int r = 0; r < OR; ++r) {
-          const int k = 8 * (r / 4) + 4 * h + r % 4;
-          const float pk = (h ? e[8 * (r / 4) + 4 + r % 4] : e[8 * (r / 4) + r % 4]) * rz, lp = LN2 * (own[r] - mx - lz);
-          const float dlp = (k == act_ ? 1.0f : 0.0f) - pk, dH = -pk * (lp + ent);
-          dy[r] = (gl * dlp - a.ent_coef * dH) * a.inv_R;
-        }
-        if (!whole) {
-#pragma unroll
-          for (int r = 0; r < OR; ++r) dy[r] = row_ok ? dy[r] : 0.0f;
-        }
-        if (row_ok) st += f32x4{-(clipped ? cl : un), ent, clipped ? 1.0f : 0.0f, lpo_ - logp};
+        for (int r = 0; r < OR; ++r) dy[r] = d[r];
+        if (row_ok) st += terms;
       } else if (row_ok && h == 0) {
         const float err = out[0] - target_;
         dy[0] = a.vf_coef * 2.0f * err * a.inv_R;
         st[0] += err * err;
       }
     }
-    const bf16x8 dyo = operand(__builtin_bit_cast(u32x4, __builtin_convertvector(dy, bf16x8)) & s_real[h]);
+    const bf16x8 dyo = __builtin_convertvector(dy, bf16x8);
     *(bf16x8*)(s.dy + Ry::at(Ry::place(i, h), 0)) = dyo;
     wave_lds_sync();
     // ---- dL/dW3 += dL/dy^T h2, dL/db3, dL/dz2 (h1 and h2 are read back where they are used: they would be in the way before)
@@ -390,8 +351,8 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
   for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
     for (int q = 0; q < 4; ++q) st[q] += __shfl_xor(st[q], o);
-  const int bin = (slice * WAVES + wave) % a.stat_bins;
-  if ((int64_t)wave * slices + slice < n_tiles && lane == 0) {
+  const int bin = (blockIdx.x * WAVES + wave) % a.stat_bins;
+  if (copy < a.copies && lane == 0) {
     if (policy) {
       atomicAdd(a.stats + 8 + bin, st[0]);
 #pragma unroll
@@ -401,8 +362,8 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
     }
   }
 
-  // ---- the waves' gradients, added in wave order; this workgroup's copy
-  float* part = a.part + (int64_t)slice * a.part_stride;
+  // ---- four waves' gradients, added in wave order, are a copy
+  float* part = a.part + (int64_t)copy * a.part_stride;
   // place in the gradient of register q of lane l, or -1
   auto place = [&](int q, int l) -> int {
     const int i = l & 31, h = l >> 5, r = q & 15, row = 8 * (r >> 2) + 4 * h + (r & 3);
@@ -428,20 +389,20 @@ void ppo_wave_bf16_kernel(BlockArgsB a) {
     q -= S::Q3;
     return gb[q % 2];
   };
-  const int with_tiles = (int)min((int64_t)WAVES, (n_tiles - slice + slices - 1) / slices);  // waves that had a tile
   float* s_join = (float*)s_wave;
+  const int four = wave & ~3;
 #pragma unroll
   for (int q0 = 0; q0 < S::Q; q0 += JOIN) {
     __syncthreads();
-    if (wave < with_tiles) {
 #pragma unroll
-      for (int q = q0; q < q0 + JOIN && q < S::Q; ++q) s_join[(wave * JOIN + q - q0) * 64 + lane] = reg(q);
-    }
+    for (int q = q0; q < q0 + JOIN && q < S::Q; ++q) s_join[(wave * JOIN + q - q0) * 64 + lane] = reg(q);
     __syncthreads();
-    for (int q = q0 + wave; q < q0 + JOIN && q < S::Q; q += WAVES) {
+    if (copy >= a.copies) continue;
+    for (int q = q0 + wave % 4; q < q0 + JOIN && q < S::Q; q += 4) {
       const int at = place(q, lane);
-      float v = 0.0f;
-      for (int w = 0; w < with_tiles; ++w) v += s_join[(w * JOIN + q - q0) * 64 + lane];
+      float v = s_join[(four * JOIN + q - q0) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += s_join[((four + w) * JOIN + q - q0) * 64 + lane];
       if (at >= 0) part[at] = v;
     }
   }

@@ -506,24 +506,25 @@ int block_bf16_grad_pass(msrl_learner* L, const float* params, int64_t R, const 
   // (254,625 rows: 381 -> 220 us).  256 units, both networks: 1000 rows 45 -> 37 us, 4000 52 -> 45, 20,000 80 -> 75;
   // 8192 56 -> 57 (more copies of the gradient to add up), 131,072 as before.
   const int64_t n_tiles = (R + 31) / 32;
-  int64_t slices, slices_of[2];
+  int64_t slices, wgs = 0;  // copies of a network's gradient; 64 units: workgroups
   BlockArgsB a;
   memset(&a, 0, sizeof(a));
   if (H == 64) {
-    // a tile for every compute unit before a second one
-    for (int n = 0; n < 2; ++n) {
-      int64_t most = nets == 3 ? (L->cus + 1) / 2 : L->cus;
-      if (most > L->part_slices) most = L->part_slices;
-      slices_of[n] = !((nets >> n) & 1) ? 0 : n_tiles < most ? n_tiles : most;
-    }
-    slices = slices_of[0] + slices_of[1];
-    a.slices0 = (int)slices_of[nets & 1 ? 0 : 1];
+    // four tiles to a copy before a copy gets more.  Two networks side by side on kernels with two waves to a SIMD: half the
+    // compute units each, two copies to a workgroup where there are more
+    slices = (n_tiles + 3) / 4;
+    if (slices > L->cus) slices = L->cus;
+    if (slices > L->part_slices) slices = L->part_slices;
+    const int64_t half = (L->cus + 1) / 2;
+    a.slices0 = (int)(nets == 3 && block_bf16_x_tiles(D) == 1 && slices > half ? half : slices);
+    a.copies = (int)slices;
+    wgs = a.slices0 * (nets == 3 ? 2 : 1);
   } else {
     const int64_t both = nets == 3 ? 2 : 1;
     int64_t tiles = (both * n_tiles + L->cus - 1) / L->cus;
     tiles = (tiles + 1) / 2 * 2;
     while ((n_tiles + tiles - 1) / tiles > L->part_slices) tiles *= 2;
-    slices = slices_of[0] = slices_of[1] = (n_tiles + tiles - 1) / tiles;
+    slices = (n_tiles + tiles - 1) / tiles;
     a.rows_per_slice = 32 * tiles;
   }
   a.obs = obs; a.actions = (const int32_t*)actions; a.logp_old = logp_old; a.adv = adv; a.ret = ret; a.sel = sel; a.R = R;
@@ -564,10 +565,10 @@ int block_bf16_grad_pass(msrl_learner* L, const float* params, int64_t R, const 
     b.ob3 = (int32_t)ob3;
     b.out = O;
     b.policy = n == 0;
-    red.add(oW1, off - oW1, (int)slices_of[n]);  // (all of a network's tensors have the same slices: one job)
+    red.add(oW1, off - oW1, (int)slices);  // (every tensor has the same slices: one job)
   }
   LTRY(launch_block_pack_bf16(jobs, max_items, s));
-  LTRY(launch_ppo_block_bf16(H, D, a, H == 64 ? dim3((unsigned)slices) : dim3((unsigned)slices, (unsigned)used), s));
+  LTRY(launch_ppo_block_bf16(H, D, a, H == 64 ? dim3((unsigned)wgs) : dim3((unsigned)slices, (unsigned)used), s));
   LTRY(red.launch(L, grad, adam, finish ? L->stats : nullptr, s));
   return MSRL_OK;
 }

@@ -153,8 +153,9 @@ def test_bf16_block_kernel_equals_the_layer_kernels(d, h, o, R):
 
 # 64 units: a wave to a tile of 32 rows; one tile more than there are workgroups (128 of a network on 256 compute units), one
 # row more than a tile for each of their waves (8 up to 30 inputs, 4 above), and tiles of selected rows that lie in three groups
-# of rows
-@pytest.mark.parametrize("d,o", [(1, 2), (20, 5), (24, 16), (30, 9), (48, 5)])
+# of rows.  (Networks of few inputs are left to the sizes above: with one input and two outputs the 16,385 rows' shares of a
+# bias gradient cancel to a norm 2^9 below theirs, and the tolerance, which is of that norm, is no bound: 2.16e-3 for 2.01e-3.)
+@pytest.mark.parametrize("d,o", [(8, 3), (20, 5), (24, 16), (30, 9), (48, 5)])
 @pytest.mark.parametrize("R,count", [(32, 0), (4097, 0), (16385, 0), (32769, 0), (70001, 0), (33000, 3), (5001, 1)])
 def test_bf16_tiles_of_64_units(d, o, R, count):
     pol = policy(d, 64, o, False, synth.BF16)
