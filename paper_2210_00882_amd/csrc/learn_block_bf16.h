@@ -103,14 +103,9 @@ template <int CH> struct LdsRows {
 // 16 x 16 (x 32): lane (j = lane % 16, g = lane / 16): operands hold row / column j, contraction index 8 g .. 8 g + 7; register r
 // of the result is row 4 g + r, column j.  (Its sums are bit for bit those of two products of 32 x 32 (x 16) behind each other.)
 __device__ __forceinline__ f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-// the values of the two lanes of a pair 16 (32) apart, the lower one's first, on both
+// the values of the two lanes of a pair 16 apart, the lower one's first, on both
 __device__ __forceinline__ void both_of_16(float v, float& lo, float& hi) {
   const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  lo = __uint_as_float(q[0]);
-  hi = __uint_as_float(q[1]);
-}
-__device__ __forceinline__ void both_of_32(float v, float& lo, float& hi) {
-  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   lo = __uint_as_float(q[0]);
   hi = __uint_as_float(q[1]);
 }

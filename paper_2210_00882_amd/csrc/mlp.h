@@ -197,7 +197,7 @@ struct Mlp {
   // OUTS (here and below): outputs in use, for networks whose code depends on them (MlpTri).
   template <uint32_t OUTS>
   __device__ static __forceinline__ f32x16 out_init(const float* lds_bias, int h) { return bias_init(lds_bias, h); }
-  template <uint32_t OUTS>
+  template <uint32_t OUTS, bool SWAP>
   __device__ static __forceinline__ void out_finish(f32x16 (&)[NB], const float*, int) {}
 
   // tanh of the previous chunk, spread over the NT tiles of the current one

@@ -264,7 +264,7 @@ struct MlpTri {
     }
   }
   // behind the last chunk: the outputs in accumulator layout (register r of lane (n, h): output 8 (r / 4) + 4 h + r % 4)
-  template <uint32_t OUTS>
+  template <uint32_t OUTS, bool SWAP>
   __device__ static __forceinline__ void out_finish(f32x16 (&out)[1], const float* lds_bias, int h) {
     f32x16 res;
     if constexpr (on_mfma<OUTS>()) {
@@ -274,7 +274,7 @@ struct MlpTri {
       // partial sums of the two lanes of a row, and the bias
       float tot[8];
 #pragma unroll
-      for (int o = 0; o < 8; ++o) tot[o] = (OUTS >> o) & 1u ? out[0][o] + __shfl_xor(out[0][o], 32) + lds_bias[o] : 0.0f;
+      for (int o = 0; o < 8; ++o) tot[o] = (OUTS >> o) & 1u ? sum_of_32<SWAP>(out[0][o]) + lds_bias[o] : 0.0f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) res[r] = r < 4 ? (h ? tot[r + 4] : tot[r]) : 0.0f;
     }

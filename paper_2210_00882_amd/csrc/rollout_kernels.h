@@ -217,6 +217,7 @@ void particle_rollout_kernel(RolloutArgs a) {
   // pieces.
   constexpr bool SPLIT_PER_NET = !BF16 && !SPLIT && !CENTRAL &&
                                  ((H == 128 && WAVES == 8) || (H == 256 && PHASE == PHASE_DEEP));
+  constexpr bool SWAP = SPLIT && !BF16;  // (dev_common.h)
   constexpr bool HAS_NETS = PHASE != PHASE_ENV && PHASE != PHASE_STEP;     // the variant runs the networks
   constexpr bool STORES_OBS = PHASE != PHASE_MLP && !ACT;                  // ... stores observation rows
   static_assert(NB == 1, "the observation staging below assumes one 32-row block per wave");
@@ -919,7 +920,7 @@ next_row_block:
             ++gs;
             ++sn;
           }
-          Net::template out_finish<OUTS>(out, s_b3[net], h);
+          Net::template out_finish<OUTS, SWAP>(out, s_b3[net], h);
         }
       } else if constexpr (SPLIT) {
         // ---------------- this wave's network; all its stages are resident: no copies, waits or barriers
@@ -942,7 +943,7 @@ next_row_block:
           if (sc == Stream::STAGES_PER_NET - 1)
             Net::template layer2_drain<OUTS>(ws.tiles(buf, CPS - 1), acc, out, h, 16);
         }
-        Net::template out_finish<OUTS>(out, s_b3[role], h);
+        Net::template out_finish<OUTS, SWAP>(out, s_b3[role], h);
 #pragma unroll
         for (int q = 0; q < NB; ++q) out_p[q] = out_v[q] = out[q];
       } else if constexpr (CENTRAL) {
@@ -1003,7 +1004,7 @@ next_row_block:
           if (sc == SPN - 1) Net::template layer2_drain<OUTS>(tiles, acc, out_p, h, 16);
           ++gs;
         }
-        Net::template out_finish<OUTS>(out_p, s_b3[0], h);
+        Net::template out_finish<OUTS, SWAP>(out_p, s_b3[0], h);
 
         critic_l1_publish(cacc);
         cacc = zero16();  // layer 2 starts from zero in stage 0 of the next step
@@ -1072,7 +1073,7 @@ next_row_block:
             ++gs;
             if (sc < 5) stamp((net == 0 ? CLK_P_STAGE : CLK_V_STAGE) + sc);
           }
-          Net::template out_finish<OUTS>(out, s_b3[net], h);
+          Net::template out_finish<OUTS, SWAP>(out, s_b3[net], h);
         }
       }
     }
@@ -1096,17 +1097,26 @@ next_row_block:
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       float l[5];
-      l[0] = out_p[q][0];
-      l[1] = out_p[q][1];
-      l[2] = out_p[q][2];
-      l[3] = out_p[q][3];
-      l[4] = __shfl_xor(out_p[q][0], 32);  // logit 4 sits in register 0 of the partner lane
+      if constexpr (SWAP) {  // the row's logits, on both of its lanes, which then take the same action
+        both_of_32(out_p[q][0], l[0], l[4]);
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+          float none;
+          both_of_32(out_p[q][k], l[k], none);
+        }
+      } else {
+        l[0] = out_p[q][0];
+        l[1] = out_p[q][1];
+        l[2] = out_p[q][2];
+        l[3] = out_p[q][3];
+        l[4] = __shfl_xor(out_p[q][0], 32);  // logit 4 sits in register 0 of the partner lane
+      }
       float lp = 0.0f;
       int act = 0;
       if (writer) {  // (uniform)
         const Words4 w = draw(a.seed_lo, a.seed_hi, env[q], (uint32_t)ag[q], g32[q], 0, 0);
         sample_categorical5(l, u01(w.w[0]), act, lp);
-        act = __shfl(act, n);  // the h = 0 lane of the row decides
+        if constexpr (!SWAP) act = __shfl(act, n);  // the h = 0 lane of the row decides
       }
       if constexpr (SPLIT) {
         // the value wave of the row block moves its copy of the envs with the policy wave's actions
@@ -1165,7 +1175,7 @@ next_row_block:
         const float* mine = h ? part1 : part0;
 #pragma unroll
         for (int j = 0; j < N; ++j) r += mine[base[q] + j];
-        r += __shfl_xor(r, 32);
+        if constexpr (SWAP) r = sum_of_32<true>(r); else r += __shfl_xor(r, 32);
       }
       const bool done = tau[q] + 1 == a.ep;
       if (h == 0 && valid[q] && rew_writer) {
@@ -1447,9 +1457,9 @@ __global__ __launch_bounds__(64 * WAVES) void lingauss_rollout_kernel(RolloutArg
           ++gs;
         }
         if (net == 0)
-          Net::template out_finish<OUTS_P>(out, s_b3[net], h);
+          Net::template out_finish<OUTS_P, false>(out, s_b3[net], h);
         else
-          Net::template out_finish<OUTS_V>(out, s_b3[net], h);
+          Net::template out_finish<OUTS_V, false>(out, s_b3[net], h);
       }
     }
     if (valid && h == 0 && PHASE != PHASE_STEP) a.values[o] = out_v[0][0];
