@@ -391,8 +391,30 @@ __global__ __launch_bounds__(512) void rowgemm_kernel(RowGemmArgs ra) {
 // shared through LDS (loaded once per workgroup, by all threads, one chunk ahead in registers), the
 // A fragments are the wave's own and come straight from global memory.  Every slice writes its own
 // copy of C (slice_stride floats apart); reduce_partials_kernel adds the copies in slice order.
+// A network's contractions (weights of each layer, the joint observation's in panels of 256 inputs) run side by side, blockIdx.y
+// picks one: with at least 256 rows to a slice one of them alone leaves most of the chip idle.  Centralised critic of 256 units on
+// 600 inputs, 25,462 rows: five launches of 26 us before, one of 59 now.
+constexpr int WGRAD_MAX = 24;
+struct WGradJobs {
+  int n;
+  const void *A[WGRAD_MAX], *B[WGRAD_MAX];
+  float* C[WGRAD_MAX];
+  int32_t M[WGRAD_MAX], N[WGRAD_MAX], M_alloc[WGRAD_MAX], N_alloc[WGRAD_MAX], ldc[WGRAD_MAX];
+  int64_t ld;  // of A and B
+  int64_t K, k_per_slice, slice_stride;
+};
 template <bool BF16, typename S>
-__global__ __launch_bounds__(512) void wgrad_kernel(GemmArgs g) {
+__global__ __launch_bounds__(512) void wgrad_kernel(WGradJobs jobs) {
+  struct {
+    const void *A, *B;
+    float* C;
+    int64_t M, N, M_alloc, N_alloc, lda, ldb, ldc, K, k_per_slice, slice_stride;
+  } g;
+  const int q = blockIdx.y;
+  g.A = jobs.A[q]; g.B = jobs.B[q]; g.C = jobs.C[q];
+  g.M = jobs.M[q]; g.N = jobs.N[q]; g.M_alloc = jobs.M_alloc[q]; g.N_alloc = jobs.N_alloc[q];
+  g.lda = g.ldb = jobs.ld; g.ldc = jobs.ldc[q];
+  g.K = jobs.K; g.k_per_slice = jobs.k_per_slice; g.slice_stride = jobs.slice_stride;
   typedef typename Frag<BF16>::T F;
   constexpr int KT = Frag<BF16>::KT, KC = 4 * KT, NTW = 8, PER = NTW * 4 * 64 / 512;  // fragments per thread
   __shared__ __attribute__((aligned(16))) u32x4 s_b[NTW * 4 * 64];

@@ -153,27 +153,30 @@ hipError_t rowgemm(hipStream_t s, const void* A, int64_t M_alloc, int64_t lda, c
   return hipGetLastError();
 }
 
-// weight-gradient contraction: C[slice][M <= 256, N <= 256] = A B^T over the slice's part of K = rows; K is split
-// into at most `slices` parts, `*used` of them in the end, whose copies of C lie slice_stride floats apart
-template <bool BF16>
-hipError_t wgrad(hipStream_t s, const void* A, int64_t M_alloc, int64_t lda, const void* B, int64_t N_alloc,
-                 int64_t ldb, float* C, int64_t M, int64_t N, int64_t ldc, int64_t K, int slices, int64_t slice_stride,
-                 int* used_out) {
-  typedef typename CT<BF16>::T E;
-  if (M > 256 || N > 256) return hipErrorInvalidValue;
-  GemmArgs g;
-  memset(&g, 0, sizeof(g));
-  g.A = A; g.B = B; g.C = C;
-  g.M = M; g.N = N; g.M_alloc = M_alloc; g.N_alloc = N_alloc; g.K = K;
-  g.lda = lda; g.ldb = ldb; g.ldc = ldc;
-  const int64_t kc = 4 * Frag<BF16>::KT;
-  g.k_per_slice = round_up((K + slices - 1) / slices, kc);
-  g.slice_stride = slice_stride;
-  const int64_t used = (K + g.k_per_slice - 1) / g.k_per_slice;
-  *used_out = (int)used;
-  hipLaunchKernelGGL((wgrad_kernel<BF16, E>), dim3((unsigned)used), dim3(512), 0, s, g);
-  return hipGetLastError();
-}
+// weight-gradient contractions: C[slice][M <= 256, N <= 256] = A B^T over the slice's part of K = rows; K is split
+// into at most `slices` parts, `used()` of them in the end, whose copies of C lie slice_stride floats apart.  One launch for all
+// that are added (as many as its argument holds: launch() where that is full).
+struct WGrad {
+  WGradJobs j;
+  bool full() const { return j.n == WGRAD_MAX; }
+  WGrad(int64_t ld, int64_t K, int slices, int64_t slice_stride, int64_t k_chunk) {
+    memset(&j, 0, sizeof(j));
+    j.ld = ld; j.K = K; j.slice_stride = slice_stride;
+    j.k_per_slice = round_up((K + slices - 1) / slices, k_chunk);
+  }
+  int used() const { return (int)((j.K + j.k_per_slice - 1) / j.k_per_slice); }
+  void add(const void* A, int64_t M_alloc, const void* B, int64_t N_alloc, float* C, int64_t M, int64_t N) {
+    const int q = j.n++;
+    j.A[q] = A; j.B[q] = B; j.C[q] = C;
+    j.M[q] = (int32_t)M; j.N[q] = (int32_t)N; j.M_alloc[q] = (int32_t)M_alloc; j.N_alloc[q] = (int32_t)N_alloc;
+    j.ldc[q] = (int32_t)N;
+  }
+  template <bool BF16> hipError_t launch(hipStream_t s) {
+    hipLaunchKernelGGL((wgrad_kernel<BF16, typename CT<BF16>::T>), dim3((unsigned)used(), (unsigned)j.n), dim3(512), 0, s, j);
+    j.n = 0;
+    return hipGetLastError();
+  }
+};
 
 template <typename S, typename D>
 hipError_t transpose(hipStream_t s, const S* src, int64_t rows, int64_t cols, int64_t ld_src, D* dst, int64_t ldd,
@@ -347,19 +350,20 @@ int grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel
     int slices = (int)fmax(1.0, fmin(256.0, (double)(Rk / 256)));
     if (slices > L->part_slices) slices = L->part_slices;
     if (H <= 256) {
-      LTRY((wgrad<BF16>(s, b.ht[NL - 1], H, Rp, b.dyt, 32, Rp, part + oW3, H, O, O, Rk, slices, ps, &used)));
-      red.add(oW3, (size_t)H * O, used);
-      for (int l = NL - 1; l >= 1; --l) {
-        LTRY((wgrad<BF16>(s, b.ht[l - 1], H, Rp, b.dzt[l], H, Rp, part + oW(l), H, H, H, Rk, slices, ps, &used)));
-        red.add(oW(l), (size_t)H * H, used);
-      }
-      // (more input units than the kernel's panel holds - the joint observation - go in panels of 256: the same
-      // slices of the rows for each, so one reduce job covers the whole tensor)
+      WGrad wg(Rp, Rk, slices, ps, 4 * Frag<BF16>::KT);
+      used = wg.used();
+      // the largest first.  (More input units than the kernel's panel holds - the joint observation - go in panels of 256: the
+      // same slices of the rows for each, so one reduce job covers the whole tensor)
       for (int d0 = 0; d0 < D; d0 += 256) {
-        const int dm = D - d0 < 256 ? D - d0 : 256;
-        LTRY((wgrad<BF16>(s, (const E*)xtn[n] + (size_t)d0 * Rp, Dp - d0, Rp, b.dzt[0], H, Rp,
-                          part + oW(0) + (size_t)d0 * H, dm, H, H, Rk, slices, ps, &used)));
+        if (wg.full()) LTRY(wg.launch<BF16>(s));
+        wg.add((const E*)xtn[n] + (size_t)d0 * Rp, Dp - d0, b.dzt[0], H, part + oW(0) + (size_t)d0 * H, D - d0 < 256 ? D - d0 : 256, H);
       }
+      if (wg.j.n + NL > WGRAD_MAX) LTRY(wg.launch<BF16>(s));
+      for (int l = NL - 1; l >= 1; --l) wg.add(b.ht[l - 1], H, b.dzt[l], H, part + oW(l), H, H);
+      wg.add(b.ht[NL - 1], H, b.dyt, 32, part + oW3, H, O);
+      LTRY(wg.launch<BF16>(s));
+      red.add(oW3, (size_t)H * O, used);
+      for (int l = NL - 1; l >= 1; --l) red.add(oW(l), (size_t)H * H, used);
       red.add(oW(0), (size_t)D * H, used);
     } else {
       LTRY((gemm<BF16, float, EPI_PARTIAL>(s, b.ht[NL - 1], H, Rp, b.dyt, 32, Rp, part + oW3, H, O, O, Rk, nullptr, nullptr, 0, slices, ps, &used)));
