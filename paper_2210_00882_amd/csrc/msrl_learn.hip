@@ -195,6 +195,24 @@ hipError_t convert_pad(hipStream_t s, const S* src, int64_t rows, int64_t cols, 
   return hipGetLastError();
 }
 
+// The weights that a gradient pass reads in the compute type (weights_kernel)
+struct WeightPrep {
+  WeightJobs j;
+  WeightPrep() { memset(&j, 0, sizeof(j)); }
+  void add(const float* src, int rows, int cols, void* dst, int dst_rows, int ldd, bool transposed, bool fp32 = false) {
+    const int q = j.n++;
+    j.src[q] = src; j.rows[q] = rows; j.cols[q] = cols;
+    j.dst[q] = dst; j.dst_rows[q] = dst_rows; j.ldd[q] = ldd;
+    j.transposed[q] = transposed; j.fp32[q] = fp32;
+    j.first_block[q + 1] = j.first_block[q] + (dst_rows + 31) / 32 * ((ldd + 31) / 32);
+  }
+  template <typename E> hipError_t launch(hipStream_t s) {
+    hipLaunchKernelGGL((weights_kernel<E>), dim3((unsigned)j.first_block[j.n]), dim3(256), 0, s, j);
+    return hipGetLastError();
+  }
+};
+static_assert(WEIGHT_JOBS_MAX >= 2 * (2 * MAX_LAYERS + 2), "two forms of a weight tensor and a bias per network");
+
 // The parameter tensors of a gradient pass, each with the number of slices its contraction was split
 // into; launch() adds the slices' copies (in L->part) up into grad, in slice order.
 struct Reducer {
@@ -259,7 +277,27 @@ int grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel
   }
   const int NL = L->layers;
   const size_t mid = (size_t)H * H + H;
+  // weights in compute type: transposed for the forward pass, as stored for the backward pass
+  WeightPrep prep;
   const float* P = params;
+  for (int n = 0; n < 2; ++n) {
+    const NetBufs& b = L->net[n];
+    const int O = n == 0 ? L->pol.out_dim : 1, D = Dn[n];
+    const float *W1 = P, *W2 = W1 + (size_t)D * H + H, *W3 = W2 + (size_t)(NL - 1) * mid;
+    P = W3 + (size_t)H * O + O;
+    if (!((nets >> n) & 1)) continue;
+    prep.add(W1, D, H, b.wt[0], H, Dpn[n], true);
+    for (int l = 1; l < NL; ++l) {
+      const float* Wl = W2 + (size_t)(l - 1) * mid;
+      prep.add(Wl, H, H, b.wt[l], H, H, true);
+      prep.add(Wl, H, H, b.wn[l], H, H, false);
+    }
+    prep.add(W3, H, O, b.wt3, 32, H, true);
+    prep.add(W3, H, O, b.wn3, H, 32, false);
+    prep.add(W3 + (size_t)H * O, 1, O, b.b3, 1, 32, false, true);
+  }
+  LTRY(prep.launch<E>(s));
+  P = params;
   for (int n = 0; n < 2; ++n) {
     NetBufs& b = L->net[n];
     const int O = n == 0 ? L->pol.out_dim : 1;
@@ -272,16 +310,6 @@ int grad_pass(msrl_learner* L, const float* params, int64_t R, const RowSel& sel
       P = b3 + O;
       continue;
     }
-    // weights in compute type: transposed for the forward pass, as stored for the backward pass
-    LTRY(transpose(s, P, D, H, H, (E*)b.wt[0], Dp, Dp, H));
-    for (int l = 1; l < NL; ++l) {
-      const float* Wl = P + first + (size_t)(l - 1) * mid;
-      LTRY(transpose(s, Wl, H, H, H, (E*)b.wt[l], H, H, H));
-      LTRY(convert_pad(s, Wl, H, H, H, (E*)b.wn[l], H, H));
-    }
-    LTRY(transpose(s, W3, H, O, O, (E*)b.wt3, H, H, 32));
-    LTRY(convert_pad(s, W3, H, O, O, (E*)b.wn3, 32, H));
-    LTRY(convert_pad(s, b3, 1, O, O, b.b3, 32, 1));
     // forward (the activations also leave unit-major, for the weight gradients)
     if (Dp <= 256) {
       LTRY((rowgemm<BF16, E, EPI_BIAS_TANH>(s, xcn[n], Rp, Dp, b.wt[0], H, Dp, b.h[0], R, H, H, Dp, P + (size_t)D * H, nullptr, 0, b.ht[0], Rp, Rk)));
