@@ -12,7 +12,7 @@
 // units the matrix pipe is busy for 8.2 k, the vector ALU for 11.2 k, the LDS for 7.2 k (counters; activations are read
 // once by each of the eight waves in either layer product); the waves wait for 48 % of theirs.  Writing the activations
 // and their gradients out for contractions of their own (4 KiB per row and network) was bound by that traffic.
-// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.74 ms, 128 (36) 0.71 -> 0.37; of 8192 rows 126 ->
+// Gradient of 524,288 rows before and now: 256 units (60 inputs) 1.33 -> 0.73 ms, 128 (36) 0.71 -> 0.36; of 8192 rows 126 ->
 // 57, 76 -> 32 us (three launches where there were six).  64 units: learn_wave_bf16.h.
 // Measured and dropped: layer 1 of the next tile beside dL/dW2 of this one, dL/dW1 beside the next layer 2 (four barriers a
 // tile in place of six, h1 twice in LDS): 689 -> 688 us with 24 inputs, 735 -> 840 with 60, where it spills 19 registers.
@@ -178,6 +178,9 @@ template <int H, int XT> struct BlockShapeB {
   static constexpr bool RESIDENT = H <= 128;
   static constexpr int WD = 4;  // tiles fetched ahead of their product when streamed
   static constexpr bool G3_LDS = H > 128;  // dL/dW3 waits in LDS between the tiles (the registers are full)
+  // Rows of a wave in the loss.  128 units: 16, a lane to an output, four waves at work.  256 units: 32, two waves, with the loads in
+  // front of layer 2 (16 and 32 rows to a wave, 524,288 rows: 726 and 727 us, 8192 57.4 and 56.1, 1000 38.5 and 36.9).
+  static constexpr int LR = H == 128 ? 16 : 32;
   static constexpr bool OWN_DZ = RS > 1;  // dL/dz in arrays of their own: two waves share a column of h1, h2
   // dL/dW2: waves in a grid of MG groups of 32 MT units of layer 1 by NW / MG groups of 32 NT units of layer 2 (NT <= MG)
   static constexpr int MT = H == 256 ? 2 : 1, MG = NWU / MT, NT = NWU * MG / NW;
@@ -214,7 +217,7 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
   __shared__ __attribute__((aligned(16))) u32x4 s_w3[KH * 64];
   __shared__ __attribute__((aligned(16))) u32x4 s_w3t[NWU * 64];
   const BlockNetB& nt = a.net[blockIdx.y];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % NW;  // (its range is worth a register)
   int lane = threadIdx.x & 63;
   const int O = nt.out, kx = block_bf16_k_tiles(a.D);  // (<= KX: the launcher's choice of XT)
   const int uw = wave % NWU, rg = wave / NWU, u0 = 32 * uw, ro = 32 * RT * rg;  // this wave's units and first row
@@ -286,7 +289,8 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
 
   // observations: two columns per thread, RSTEP rows at a time; a row beyond the end reads as zero; columns D and D + 1
   // are the constant 1 that the two parts of the bias meet
-  int xc = 2 * (threadIdx.x % S::CW), xr = threadIdx.x / S::CW;
+  const int tid = threadIdx.x % S::THREADS;
+  int xc = 2 * (tid % S::CW), xr = tid / S::CW;
   f32x2 xv[S::XN];
   auto fetch_x = [&]() {  // (the row table holds the tile; always some row, so no branch around the loads)
     const float *src = a.obs + (xc < a.D ? xc : 0), *src1 = a.obs + (xc + 1 < a.D ? xc + 1 : 0);
@@ -409,19 +413,30 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
     ring_fill(w2);
     activate(acc, s.h1);
     __syncthreads();
-    // what the loss reads: the first four waves take 16 rows each
+    // what the loss reads: the first waves take LR rows each
     int act = 0;
     float lpo = 0.0f, target = 0.0f;
     bool valid = false;
     auto fetch_loss = [&]() {
-      if (wave >= ROWS / 16) return;
-      const int64_t p = s.row[16 * wave + (lane & 15)];
+      if (wave >= ROWS / S::LR) return;
+      const int64_t p = s.row[S::LR * wave + lane % S::LR];
       valid = p >= 0;
-      const int64_t at = valid ? p : 0;
-      act = a.actions[at];
-      lpo = a.logp_old[at];
-      target = targets[at];
+      if constexpr (S::LR == 32) {
+        if (valid && policy) {
+          act = a.actions[p];
+          lpo = a.logp_old[p];
+          target = a.adv[p];
+        } else if (valid) {
+          target = a.ret[p];
+        }
+      } else {  // (nothing waits for these loads)
+        const int64_t at = valid ? p : 0;
+        act = a.actions[at];
+        lpo = a.logp_old[at];
+        target = targets[at];
+      }
     };
+    if constexpr (S::LR == 32) fetch_loss();
     clear(acc);
     if constexpr (S::RESIDENT) {
       product(Rh(), std::integral_constant<int, KH>(), acc, s.h1, KH, [&](int k) { return rw2[k]; });
@@ -431,12 +446,14 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
       if (wave < 4) __builtin_amdgcn_s_setprio(1);
       ring_product(acc, s.h1, w2, std::integral_constant<int, KH + 1>());
     }
-    fetch_loss();  // (behind the last of the weights: no product waits for these loads)
+    if constexpr (S::LR == 16) fetch_loss();  // (behind the last of the weights: no product waits for these loads)
     activate(acc, s.h2);
     if (!S::RESIDENT && wave < 4) __builtin_amdgcn_s_setprio(0);
     __syncthreads();
-    // output layer and loss: register r of lane (j, g) <-> output 4 g + r of row j of the wave's 16
-    if (wave < ROWS / 16) {
+    // output layer and loss
+    const LossTerms terms = {a.clip, a.ent_coef, a.inv_R};
+    if (wave >= ROWS / S::LR) {
+    } else if constexpr (S::LR == 16) {  // register r of lane (j, g) <-> output 4 g + r of row j of the wave's 16
       const int row = 16 * wave + p16;
       f32x4 out = *(const f32x4*)(s_b3 + 4 * g16);
       const typename Rh::Place at = Rh::place(row, g16);
@@ -446,7 +463,6 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
       float dy[4] = {0.0f, 0.0f, 0.0f, 0.0f};
       f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
       if (policy) {
-        const LossTerms terms = {a.clip, a.ent_coef, a.inv_R};
         const float own[4] = {out[0], out[1], out[2], out[3]};
         auto index = [&](int r) { return 4 * g16 + r; };
         float l[16];
@@ -470,6 +486,32 @@ void ppo_block_bf16_kernel(BlockArgsB a) {
       const int to = chained(4 * g16);
       *(bf16x4*)(s.dy + row * Ry::ROW + ((to / 8) ^ Ry::swizzle(row)) * 8 + to % 8) = __builtin_convertvector((f32x4{dy[0], dy[1], dy[2], dy[3]}), bf16x4);
       if (valid && g16 == 0) s.st[row] += st;
+    } else {  // register r of lane (i, h) <-> output 8 (r / 4) + 4 h + r % 4 of row i
+      f32x16 out = bias_init(s_b3, h);
+      const typename Rh::Place at = Rh::place(i, h);
+#pragma unroll
+      for (int k = 0; k < KH; ++k)
+        out = mma(__builtin_bit_cast(bf16x8, s_w3[k * 64 + lane]), *(const bf16x8*)(s.h2 + 32 * wave * Rh::ROW + Rh::at(at, 2 * k)), out);
+      float dy[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+      f32x4 st = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (policy) {
+        float l[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const int r = 4 * (k >> 3) + (k & 3);
+          const float own = out[r], oth = __shfl_xor(own, 32);
+          l[k] = (((k >> 2) & 1) == h) ? own : oth;
+        }
+        const float own[8] = {out[0], out[1], out[2], out[3], out[4], out[5], out[6], out[7]};
+        policy_loss(l, O, act, lpo, target, valid, terms, own, [&](int r) { return 8 * (r / 4) + 4 * h + r % 4; }, dy, st);
+      } else if (h == 0) {
+        const float err = out[0] - target;
+        dy[0] = valid ? a.vf_coef * 2.0f * err * a.inv_R : 0.0f;
+        st[0] = err * err;
+      }
+      const f32x8 v = {dy[0], dy[1], dy[2], dy[3], dy[4], dy[5], dy[6], dy[7]};
+      *(bf16x8*)(s.dy + 32 * wave * Ry::ROW + Ry::at(Ry::place(i, h), 0)) = __builtin_convertvector(v, bf16x8);
+      if (valid && h == 0) s.st[32 * wave + i] += st;
     }
     __syncthreads();
     // dL/dW3 += dL/dy^T h2 (the wave's own units), dL/dz2
