@@ -176,7 +176,7 @@ __device__ __forceinline__ void to_operands(const float (&t)[16], typename Opera
 // accumulators of chunk c-1, so both pipes are busy from one instruction stream.  In a layer-2
 // stage the layer-3 MFMAs of chunk c-1 follow.
 // fp32 (BF16 false): layer 1 only (pursuit env), and the sizes and tiles the kernels with loops of their own share; the other
-// fp32 networks run on the bf16 pipe (mlp_tri.h).
+// fp32 networks run on the 16-bit matrix pipe (mlp_tri.h).
 template <int H, bool BF16, int NB, int KT1>
 struct Mlp {
   typedef typename Operand<BF16>::T Op;

@@ -580,8 +580,7 @@ int configure_state(msrl_state* st, const char* who, const msrl_env_cfg* env, co
 // allocate) in this array.  Every GPU holds its own copy at its own address; in host code the name
 // below is only a handle for hipGetSymbolAddress, never a device address.
 // What a configuration may take is counted in the networks' own type (own_type_bytes), so that it does not depend on the
-// form the kernels read; the largest image within that limit, fp32 networks of 128 units and six hidden layers, takes
-// 1,132,544 bytes in three bf16 pieces.
+// form the kernels read.
 constexpr size_t STATIC_ARRAY_BYTES = (size_t)MSRL_STATIC_SCRATCH_BYTES / 4 * 5;
 static __device__ __align__(256) uint8_t scratch[STATIC_ARRAY_BYTES];
 

@@ -536,7 +536,7 @@ int block_bf16_grad_pass(msrl_learner* L, const float* params, int64_t R, const 
                          const msrl_ppo_cfg* c, float* grad, hipStream_t s, const AdamArgs* adam, int nets = 3,
                          bool finish = true) {
   const int D = L->pol.in_dim, H = L->pol.hidden;
-  // 64 units: up to a workgroup per compute unit, each over every fourth row tile for each of its four teams.  Wider:
+  // 64 units: four tiles to a copy, as many copies as there are compute units (below).  Wider:
   // as many slices of whole 64 rows as give every compute unit one workgroup, of one network or of two side by side.
   // Bounded by a workgroup's tiles one behind the other: slices of whole 128 rows, sized for two networks whatever
   // their number, left half of the units idle for small minibatches and for the policy alone beside a centralised critic

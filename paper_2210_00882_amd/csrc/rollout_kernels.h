@@ -184,7 +184,7 @@ void particle_rollout_kernel(RolloutArgs a) {
   constexpr bool CENTRAL = PHASE == PHASE_CENTRAL || PHASE == PHASE_ACT_CENTRAL;
   // chunk blocks per stage (fewer barriers when they fit; the centralised critic needs the LDS)
   constexpr int CPS = BF16 && H >= 64 && !CENTRAL ? 2 : 1;
-  // fp32 networks run on the bf16 matrix pipe (mlp_tri.h)
+  // fp32 networks run on the 16-bit matrix pipe (mlp_tri.h)
   typedef std::conditional_t<BF16, Mlp<H, true, 1, KT1>, MlpTri<H, KT1>> Net;
   constexpr bool L1S = !BF16 && tri_streams_layer1(H);  // the layer-1 tiles come through the window
   typedef Mlp<H, BF16, 1, KT1> Critic;  // the centralised critic's layers 2 and 3: native tiles for both types
